@@ -2,6 +2,8 @@
 // import / export, the streaming-read probe; and their launch wrappers.
 #include "launch_common.hpp"
 
+#include <algorithm>
+
 namespace es {
 
 // ------------------------------------------------------------------------------------------
@@ -43,21 +45,31 @@ __global__ void accept_kernel(const int32_t* draft, const int32_t* target, int b
   bonus[b] = target[b * (gamma + 1) + m];
 }
 
-// user [L][Hkv][n][hd] <-> cache [L][B][Hkv][max_ctx][hd], 16-byte fragments
-__global__ void kv_copy_kernel(u32x4* cache, u32x4* user, int L, int B, int Hkv, int max_ctx, int n, int frag_per_row,
-                               int seq, int to_cache) {
-  const size_t total = (size_t)L * Hkv * n * frag_per_row;
-  const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= total) return;
-  const int f = (int)(i % frag_per_row);
-  size_t r = i / frag_per_row;
-  const int s = (int)(r % n);
-  r /= n;
-  const int h = (int)(r % Hkv);
-  const int l = (int)(r / Hkv);
-  const size_t ci = ((((size_t)l * B + seq) * Hkv + h) * max_ctx + s) * frag_per_row + f;
-  if (to_cache) cache[ci] = user[i];
-  else user[i] = cache[ci];
+// user [L][Hkv][n][hd] <-> cache [L][B][Hkv][max_ctx][hd], K and V in one launch.  The slots of a (layer, KV head)
+// are one contiguous run on both sides, so a workgroup moves a piece of one run: no division per element, and
+// kKvPieces 16-byte loads per thread are in flight before the first store.  Bound by memory (every byte read once
+// and written once): an import or export of 2048 slots of the 8B shape (268 MB each way, 537 MB of traffic).
+// grid = (pieces of a run, layer x KV head, K / V).
+constexpr int kKvThreads = 256, kKvPieces = 8;
+__global__ __launch_bounds__(kKvThreads) void kv_copy_kernel(u32x4* kc, u32x4* vc, u32x4* k_user, u32x4* v_user, size_t layer_pitch,
+                                                             size_t head_pitch, size_t seq_off, int Hkv, size_t run, int to_cache) {
+  const int lh = blockIdx.y, l = lh / Hkv, h = lh % Hkv;
+  u32x4* cache = (blockIdx.z ? vc : kc) + l * layer_pitch + seq_off + h * head_pitch;
+  u32x4* user = (blockIdx.z ? v_user : k_user) + (size_t)lh * run;
+  const u32x4* src = to_cache ? user : cache;
+  u32x4* dst = to_cache ? cache : user;
+  const size_t i0 = (size_t)blockIdx.x * (kKvThreads * kKvPieces) + threadIdx.x;
+  u32x4 v[kKvPieces];
+#pragma unroll
+  for (int j = 0; j < kKvPieces; ++j) {
+    const size_t i = i0 + (size_t)j * kKvThreads;
+    if (i < run) v[j] = __builtin_nontemporal_load(src + i);
+  }
+#pragma unroll
+  for (int j = 0; j < kKvPieces; ++j) {
+    const size_t i = i0 + (size_t)j * kKvThreads;
+    if (i < run) __builtin_nontemporal_store(v[j], dst + i);
+  }
 }
 
 void launch_repack(int dtype, const void* src, void* dst, int rows, int K, int R, int half, int row_add, hipStream_t st) {
@@ -110,13 +122,18 @@ void launch_accept(const int32_t* draft, const int32_t* target, int batch, int g
 void launch_kv_copy(const Shape& s, const Buffers& b, int seq, void* k_user, void* v_user, int n_slots, int to_cache,
                     hipStream_t st) {
   const int fpr = s.hd * (s.dtype == 1 ? 2 : 4) / 16;
-  const size_t total = (size_t)s.L * s.Hkv * n_slots * fpr;
-  if (total == 0) return;
-  const unsigned grid = (unsigned)((total + 255) / 256);
-  hipLaunchKernelGGL(kv_copy_kernel, dim3(grid), dim3(256), 0, st, (u32x4*)b.kc, (u32x4*)k_user, s.L, s.B, s.Hkv, s.max_ctx,
-                     n_slots, fpr, seq, to_cache);
-  hipLaunchKernelGGL(kv_copy_kernel, dim3(grid), dim3(256), 0, st, (u32x4*)b.vc, (u32x4*)v_user, s.L, s.B, s.Hkv, s.max_ctx,
-                     n_slots, fpr, seq, to_cache);
+  const size_t run = (size_t)n_slots * fpr, head_pitch = (size_t)s.max_ctx * fpr, seq_pitch = s.Hkv * head_pitch;
+  if (run == 0) return;
+  constexpr size_t per_wg = kKvThreads * kKvPieces;
+  // the grid's second extent is limited: whole layers at a time
+  const int layers_at_once = std::max(1, 65535 / s.Hkv);
+  for (int l0 = 0; l0 < s.L; l0 += layers_at_once) {
+    const int nl = std::min(layers_at_once, s.L - l0);
+    const size_t c0 = (size_t)l0 * s.B * seq_pitch, u0 = (size_t)l0 * s.Hkv * run;
+    hipLaunchKernelGGL(kv_copy_kernel, dim3((unsigned)((run + per_wg - 1) / per_wg), nl * s.Hkv, 2), dim3(kKvThreads), 0, st,
+                       (u32x4*)b.kc + c0, (u32x4*)b.vc + c0, (u32x4*)k_user + u0, (u32x4*)v_user + u0, s.B * seq_pitch, head_pitch,
+                       seq * seq_pitch, s.Hkv, run, to_cache);
+  }
 }
 
 }  // namespace es

@@ -555,39 +555,49 @@ __global__ __launch_bounds__(512) void attn_kernel(AttnArgs a, Cols c) {
 
 // ------------------------------------------------------------------------------------------
 // Attention on the matrix cores (bf16 caches).  The query rows that share one KV head — the G
-// heads of up to 16/G columns of one sequence (the tokens of a calibration, the nodes of a tree
-// level; a single column in a plain draft step) — are the 16 columns of MFMA tiles, so K and V
+// heads of up to 16 NW / G columns of one sequence (the tokens of a calibration, the nodes of a tree
+// level) — are the columns of NW MFMA tiles of 16, one tile per wave of the workgroup, so K and V
 // are read once per group of columns and the per-slot arithmetic leaves the vector ALUs:
 //   S^T[slot][row]  = K[slot][:] . Q[row][:]      A = K (rows = slots), B = Q^T, two-term bf16 q
 //   O^T[e][row]    += V^T[e][slot] P^T[slot][row]  A = V^T, B = P^T, two-term bf16 p
-// Each wave walks its own sub-chunk of the context in super tiles of 64 slots and leaves one
-// split-KV partial per query row (merged by attn_merge_kernel; written out directly if the
-// column's whole context is one sub-chunk).  The slots of a super tile are dealt to the four
-// S^T tiles so that lane (row r, quarter q) ends up with the 16 CONSECUTIVE slots q*16 .. q*16+15:
-// the accumulator layout of S^T is then the B-operand layout of the P.V instruction, and a
-// V^T fragment is 8 consecutive slots.  V is stored [slot][head_dim]; a wave transposes its
-// 64 x head_dim tile through its own piece of LDS (XOR-swizzled pieces, read back with the
-// transposing LDS read).  grid = (ceil(sub-chunks / waves), Hkv, k * groups), block = 64 * waves.
+// A workgroup walks its chunk of the context in super tiles of 64 slots: its waves load the K and V
+// rows of a tile together (coalesced) and put them into LDS (XOR-swizzled 16-byte pieces; V is read
+// back with the transposing LDS read), each wave then takes its own 16 query rows through scores,
+// softmax and P.V.  One split-KV partial per query row and chunk (merged by attn_merge_kernel;
+// written out directly if the column's whole context is one chunk).  The slots of a super tile are
+// dealt to the four S^T tiles so that lane (row r, quarter q) ends up with the 16 CONSECUTIVE slots
+// q*16 .. q*16+15: the accumulator layout of S^T is then the B-operand layout of the P.V
+// instruction, and a V^T fragment is 8 consecutive slots.
+// What bounds it is the dependent chain of one tile in a wave (loads, LDS, scores, softmax, P.V).
+// Sharing the tile between the waves reads K and V once for up to 64 query rows and leaves a wave
+// few enough registers (its share of the tile instead of all of it) that two or more run on a SIMD.
+// Before (every wave alone with up to 16 query rows and a tile of its own, one wave per SIMD) and now: prefill of
+// 16 tokens at context 8192 4495 -> 4143 us, calibration of 4 x 6 tokens at contexts 4096 .. 32768 7353 -> 6570 us,
+// tree levels of 4 and 12 nodes at context 2048 6092 -> 5946 us together.  Two row tiles per wave instead (one
+// chain for 32 rows): 4553, 7875 and 6171 us; the registers of a private 64-slot tile leave one wave per SIMD.
+// grid = (chunks, Hkv, k * groups), block = 64 * NW.
 // ------------------------------------------------------------------------------------------
 struct ColGroups {
   int32_t n;                // groups
   int32_t first[kMaxCols];  // first column of group i
-  int32_t count[kMaxCols];  // its columns (consecutive, same sequence); count * G <= 16
+  int32_t count[kMaxCols];  // its columns (consecutive, same sequence); count * G <= 16 NW
 };
-constexpr int kMfmaAttnWaves = 4;
 typedef short v4i16 __attribute__((ext_vector_type(4)));
+typedef short v8i16 __attribute__((ext_vector_type(8)));
 
-template <int HD, bool TREE>
-__global__ __launch_bounds__(64 * kMfmaAttnWaves) void attn_mfma_kernel(AttnArgs a, Cols c, ColGroups cg, int G) {
-  constexpr int KT = HD / 32, ET = HD / 16, PIECES = HD / 8;
-  extern __shared__ u32x4 dyn_v[];  // per wave: V tile [64 slots][PIECES] then K tile [16 slots][PIECES], 16-byte pieces, swizzled
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, NWV = blockDim.x >> 6;
-  const int chunk = blockIdx.x * NWV + wave, kvh = blockIdx.y;
+template <int HD, bool TREE, int NW>
+__global__ __launch_bounds__(64 * NW, NW == 1 ? 1 : 2) void attn_mfma_kernel(AttnArgs a, Cols c, ColGroups cg, int G) {
+  constexpr int KT = HD / 32, ET = HD / 16, PIECES = HD / 8, NL = PIECES / NW;
+  __shared__ u32x4 kt_lds[64 * PIECES], vt[64 * PIECES];  // [64 slots][PIECES] 16-byte pieces each, swizzled
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  const int chunk = blockIdx.x, kvh = blockIdx.y;
   const int li = blockIdx.z / cg.n, grp = blockIdx.z % cg.n;
   const int first = cg.first[grp], cnt = cg.count[grp];
   const int r = lane & 15, q4 = lane >> 4;  // query row (MFMA column) and quarter / k-group
-  const bool row_ok = r < cnt * G;
-  const int col = first + (row_ok ? r / G : 0), g = row_ok ? r % G : 0;
+  const int row = wave * 16 + r;
+  const bool active = wave * 16 < cnt * G;  // wave-uniform: a wave without query rows only helps to load the tiles
+  const bool row_ok = row < cnt * G;
+  const int col = first + (row_ok ? row / G : 0), g = row_ok ? row % G : 0;
   int n_max = 0;         // slots the longest column of the group attends to
   int n_all = INT_MAX;   // slots below this one are visible to every column of the group
   for (int i = 0; i < cnt; ++i) {
@@ -595,38 +605,30 @@ __global__ __launch_bounds__(64 * kMfmaAttnWaves) void attn_mfma_kernel(AttnArgs
     n_all = min(n_all, TREE ? min(c.pos[first + i] + 1, c.vis_base[first + i]) : c.pos[first + i] + 1);
   }
   const int ws0 = chunk * a.CH;
-  if (ws0 >= n_max) return;  // whole wave; nothing below synchronises across waves
+  if (ws0 >= n_max) return;  // whole workgroup
   const int ws1 = min(ws0 + a.CH, n_max);
   const int n_slots = c.pos[col] + 1;  // of this lane's row
   const int vbase = c.vis_base[col];
   const unsigned long long vmask = c.vis_mask[col];
   const int HQ = a.Hq * HD;
   const size_t rowbase = (((size_t)(a.layer0 + li) * a.B + c.seq[first]) * a.Hkv + kvh) * (size_t)a.max_ctx;
-  const bf16_t* kc = reinterpret_cast<const bf16_t*>(a.kc) + rowbase * HD;
+  const u32x4* kc = reinterpret_cast<const u32x4*>(reinterpret_cast<const bf16_t*>(a.kc) + rowbase * HD);
   const u32x4* vc = reinterpret_cast<const u32x4*>(reinterpret_cast<const bf16_t*>(a.vc) + rowbase * HD);
-  u32x4* vt = dyn_v + (size_t)wave * 80 * PIECES;
-  u32x4* kt_lds = vt + 64 * PIECES;
-  const u32x4* kc4 = reinterpret_cast<const u32x4*>(kc);
 
-  // K and V rows of a super tile as they lie in memory (coalesced): fragment f = it*64 + lane of its
-  // 64 x PIECES 16-byte pieces.  The registers are free again once their contents sit in LDS, so
-  // the next super tile is requested while the current one is still being worked on; the first
-  // one before the queries are fetched.
-  // Loads are unconditional: a slot past the sub-chunk's end (only the last sub-chunk of the longest
-  // column has any: sub-chunks are multiples of 64 slots) re-reads the last row; its scores are masked
-  // below for every query row, so its probabilities are exact zeros.
-  u32x4 kf[PIECES], vf[PIECES];
+  // This thread's pieces of a super tile: piece `piece` of slots sl0 + j * 64 NW / PIECES.  The registers are
+  // free again once their contents sit in LDS, so the next tile is requested while the current one is still
+  // being worked on; the first one before the queries are fetched.
+  // Loads are unconditional: a slot past the chunk's end (only the last chunk of the longest column has any:
+  // chunks are multiples of 64 slots) re-reads the last row; its scores are masked below for every query row,
+  // so its probabilities are exact zeros.
+  const int piece = tid % PIECES, sl0 = tid / PIECES;
+  constexpr int SL = 64 * NW / PIECES;  // slots one load of the workgroup covers
+  u32x4 kf[NL], vf[NL];
   auto request = [&](int base) {
 #pragma unroll
-    for (int it = 0; it < PIECES; ++it) {
-      const int f = it * 64 + lane, sl = min(base + f / PIECES, ws1 - 1), piece = f % PIECES;
-      kf[it] = __builtin_nontemporal_load(kc4 + (size_t)sl * PIECES + piece);
-    }
+    for (int j = 0; j < NL; ++j) kf[j] = __builtin_nontemporal_load(kc + (size_t)min(base + sl0 + j * SL, ws1 - 1) * PIECES + piece);
 #pragma unroll
-    for (int it = 0; it < PIECES; ++it) {
-      const int f = it * 64 + lane, sl = min(base + f / PIECES, ws1 - 1), piece = f % PIECES;
-      vf[it] = __builtin_nontemporal_load(vc + (size_t)sl * PIECES + piece);
-    }
+    for (int j = 0; j < NL; ++j) vf[j] = __builtin_nontemporal_load(vc + (size_t)min(base + sl0 + j * SL, ws1 - 1) * PIECES + piece);
   };
   request(ws0);
 
@@ -649,52 +651,56 @@ __global__ __launch_bounds__(64 * kMfmaAttnWaves) void attn_mfma_kernel(AttnArgs
   float m_run = -INFINITY, l_run = 0.f;  // l_run: this lane's 16 slots per super tile only
 
   for (int base = ws0; base < ws1; base += 64) {
-    // V tile into LDS, the 32-byte blocks of slot s XORed by s % 4: the transposing reads below take
-    // the same block of four consecutive slots at once, which then lie in different banks
+    if (base > ws0) __syncthreads();  // every wave has read the previous tile
+    // K rows as the four score tiles take them: slot sl is row m = (sl / 16) * 4 + sl % 4 of tile t = (sl / 4) % 4;
+    // piece p of row m is stored at p ^ m, so that the 16 rows of one piece hit 16 different banks.
+    // V rows in order, the 32-byte blocks of slot s XORed by s % 4: the transposing reads below take the same
+    // block of four consecutive slots at once, which then lie in different banks.
 #pragma unroll
-    for (int it = 0; it < PIECES; ++it) {
-      const int f = it * 64 + lane, sl = f / PIECES, piece = f % PIECES;
-      vt[sl * PIECES + (piece ^ ((sl & 3) << 1))] = vf[it];
+    for (int j = 0; j < NL; ++j) {
+      const int sl = sl0 + j * SL, t = (sl >> 2) & 3, m = (sl >> 4) * 4 + (sl & 3);
+      kt_lds[(t * 16 + m) * PIECES + (piece ^ (m & (PIECES - 1)))] = kf[j];
     }
-    // scores of this lane's row against its 16 slots base + q4*16 + t*4 + i.  S^T tile t takes
-    // the slots (m/4)*16 + t*4 + m%4, m = 0..15, as its A rows: their pieces go through LDS
-    // (piece p of A row m stored at p ^ m, so that the 16 rows of one piece hit 16 different banks)
+#pragma unroll
+    for (int j = 0; j < NL; ++j) {
+      const int sl = sl0 + j * SL;
+      vt[sl * PIECES + (piece ^ ((sl & 3) << 1))] = vf[j];
+    }
+    __syncthreads();
+    if (base + 64 < ws1) request(base + 64);
+    if (!active) continue;
+    // scores of this lane's row against its 16 slots base + q4*16 + t*4 + i
+    f32x4 st[4];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) st[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int kt = 0; kt < KT; ++kt) {
+      u32x4 ka[4];
+#pragma unroll
+      for (int t = 0; t < 4; ++t) ka[t] = kt_lds[(t * 16 + r) * PIECES + ((kt * 4 + q4) ^ (r & (PIECES - 1)))];
+#pragma unroll
+      for (int t = 0; t < 4; ++t) st[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, ka[t]), qh[kt], st[t], 0, 0, 0);
+#pragma unroll
+      for (int t = 0; t < 4; ++t) st[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, ka[t]), ql[kt], st[t], 0, 0, 0);
+    }
     float sc[4][4];
+    if (base + 64 <= n_all) {  // wave-uniform: a super tile that every query row sees whole needs no mask
 #pragma unroll
-    for (int t = 0; t < 4; ++t) {
+      for (int t = 0; t < 4; ++t)  // (padding rows get finite scores of a zero query; they are never stored)
 #pragma unroll
-      for (int it = 0; it < PIECES; ++it) {
-        const int f = it * 64 + lane, sl = f / PIECES, piece = f % PIECES;
-        // slot sl belongs to tile (sl / 4) % 4; with 16 pieces per row that is it % 4 for every lane
-        if (PIECES == 16 ? (it & 3) == t : ((sl >> 2) & 3) == t) {
-          const int m = (sl >> 4) * 4 + (sl & 3);
-          kt_lds[m * PIECES + (piece ^ (m & (PIECES - 1)))] = kf[it];
-        }
-      }
-      __builtin_amdgcn_wave_barrier();  // LDS operations of one wave execute in order: no wait is needed
-      f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+        for (int i = 0; i < 4; ++i) sc[t][i] = st[t][i] * a.scale;
+    } else {
 #pragma unroll
-      for (int kt = 0; kt < KT; ++kt) {
-        const u32x4 ka = kt_lds[r * PIECES + ((kt * 4 + q4) ^ (r & (PIECES - 1)))];
-        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, ka), qh[kt], acc, 0, 0, 0);
-        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, ka), ql[kt], acc, 0, 0, 0);
-      }
-      __builtin_amdgcn_wave_barrier();
+      for (int t = 0; t < 4; ++t)
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const float v = acc[i] * a.scale;
-        if (base + 64 <= n_all) {  // wave-uniform: a super tile that every query row sees whole needs no mask
-          sc[t][i] = v;            // (padding rows get finite scores of a zero query; they are never stored)
-        } else {
+        for (int i = 0; i < 4; ++i) {
           const int slot = base + q4 * 16 + t * 4 + i;
           // no short circuit: the shift amount is masked instead of guarded, so that this stays straight-line code
           const bool seen = !TREE || (int)(slot < vbase) | (int)((vmask >> ((slot - vbase) & 63)) & 1ull);
           const bool valid = (int)row_ok & (int)(slot < n_slots) & (int)seen;
-          sc[t][i] = valid ? v : -INFINITY;
+          sc[t][i] = valid ? st[t][i] * a.scale : -INFINITY;
         }
-      }
     }
-    if (base + 64 < ws1) request(base + 64);  // both register sets are in LDS / consumed by now
     float bm = -INFINITY;
 #pragma unroll
     for (int t = 0; t < 4; ++t)
@@ -723,7 +729,6 @@ __global__ __launch_bounds__(64 * kMfmaAttnWaves) void attn_mfma_kernel(AttnArgs
       }
       split_bf16x8(pv, ph[h], pl[h]);
     }
-    __builtin_amdgcn_wave_barrier();
     // A operands: V^T row e = et*16 + lane%16, the 8 slots q4*16 + h*8 + j, by the LDS transposing
     // read (ds_read_b64_tr_b16): in a group of 16 lanes, lane i offers the 8 bytes at its address
     // (4 elements of "row" i) and receives element i%4 of rows i/4, i/4 + 4, i/4 + 8, i/4 + 12.
@@ -737,23 +742,21 @@ __global__ __launch_bounds__(64 * kMfmaAttnWaves) void attn_mfma_kernel(AttnArgs
 #pragma unroll
         for (int t2 = 0; t2 < 2; ++t2) {
           const int slot = q4 * 16 + h * 8 + t2 * 4 + (r >> 2);  // this lane's row of the transposed block
-          const int piece = (et * 2 + ((r & 3) >> 1)) ^ ((slot & 3) << 1);
-          const char* src = reinterpret_cast<const char*>(vt) + slot * (HD * 2) + piece * 16 + (r & 1) * 8;
+          const int vp = (et * 2 + ((r & 3) >> 1)) ^ ((slot & 3) << 1);
+          const char* src = reinterpret_cast<const char*>(vt) + slot * (HD * 2) + vp * 16 + (r & 1) * 8;
           half[t2] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) v4i16*)(src));
         }
-        typedef short v8i16 __attribute__((ext_vector_type(8)));
         const v8i16 both = {half[0][0], half[0][1], half[0][2], half[0][3], half[1][0], half[1][1], half[1][2], half[1][3]};
         const bf16x8 va = __builtin_bit_cast(bf16x8, both);
         o[et] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va, ph[h], o[et], 0, 0, 0);
         o[et] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va, pl[h], o[et], 0, 0, 0);
       }
     }
-    __builtin_amdgcn_wave_barrier();  // the gathers are issued before the next tile's stores into the same piece of LDS
   }
 
   l_run += __shfl_xor(l_run, 16, 64);
   l_run += __shfl_xor(l_run, 32, 64);
-  if (!row_ok || ws0 >= n_slots) return;  // padding rows; columns that end before this sub-chunk
+  if (!row_ok || ws0 >= n_slots) return;  // padding rows; columns that end before this chunk
   const int nch = (n_slots + a.CH - 1) / a.CH;
   const int head = kvh * G + g;
   if (nch == 1) {
@@ -764,13 +767,13 @@ __global__ __launch_bounds__(64 * kMfmaAttnWaves) void attn_mfma_kernel(AttnArgs
       store_act4<bf16_t>(dst, (size_t)kMaxCols * HQ, o[et][0] / l_run, o[et][1] / l_run, o[et][2] / l_run, o[et][3] / l_run);
     }
   } else {
-    const size_t row = ((size_t)li * kMaxCols + col) * a.Hq + head;
+    const size_t prow = ((size_t)li * kMaxCols + col) * a.Hq + head;
 #pragma unroll
     for (int et = 0; et < ET; ++et)
-      *reinterpret_cast<f32x4*>(a.PO + (row * kMaxChunks + chunk) * HD + et * 16 + q4 * 4) = o[et];
+      *reinterpret_cast<f32x4*>(a.PO + (prow * kMaxChunks + chunk) * HD + et * 16 + q4 * 4) = o[et];
     if (q4 == 0) {
-      a.PM[row * kMaxChunks + chunk] = m_run;
-      a.PL[row * kMaxChunks + chunk] = l_run;
+      a.PM[prow * kMaxChunks + chunk] = m_run;
+      a.PL[prow * kMaxChunks + chunk] = l_run;
     }
   }
 }
@@ -871,10 +874,24 @@ static bool attn_use_mfma(const Shape& s, const Cols& c, int n_set) {
   return shared && (long)n_set * c.n * max_len >= min_work && (n_set > 1 || c.n >= 5);
 }
 
+// Waves per workgroup of the matrix-core kernel = tiles of 16 query rows that share K and V: as many as the
+// longest run of columns of one sequence fills (1, 2 or 4).
+static int row_tiles(const Cols& c, int G) {
+  const int forced = env_int("EASYSPEC_ATTN_ROW_TILES", 0);  // tests: read at every call
+  if (forced == 1 || forced == 2 || forced == 4) return forced;
+  int longest = 1;
+  for (int i = 1, run = 1; i < c.n; ++i) {
+    run = c.seq[i] == c.seq[i - 1] ? run + 1 : 1;
+    longest = std::max(longest, run);
+  }
+  const int tiles = (longest * G + 15) / 16;
+  return tiles <= 2 ? tiles : 4;
+}
+
 // Runs of consecutive columns of one sequence, cut so that a group's query rows (columns x G
-// heads per KV head) fill at most the 16 columns of an MFMA tile.
-static void group_columns(const Cols& c, int G, ColGroups& cg) {
-  const int most = std::max(1, 16 / G);
+// heads per KV head) fill at most the 16 columns of each of its MFMA tiles.
+static void group_columns(const Cols& c, int G, int n_tiles, ColGroups& cg) {
+  const int most = std::max(1, 16 * n_tiles / G);
   cg.n = 0;
   for (int i = 0; i < c.n;) {
     int j = i + 1;
@@ -889,6 +906,7 @@ static void group_columns(const Cols& c, int G, ColGroups& cg) {
 AttnCut attn_cut(const Shape& s, const Cols& c, int n_set) {
   AttnCut cut;
   cut.mfma = attn_use_mfma(s, c, n_set);
+  cut.tiles = 1;
   cut.chunk = 0;
   cut.nb_ref = 0;
   int max_len = 1;
@@ -897,22 +915,31 @@ AttnCut attn_cut(const Shape& s, const Cols& c, int n_set) {
   // saves the merge launch; two dependent launches cost more than the narrower launch loses.
   static const int single_max = env_int("EASYSPEC_ATTN_SINGLE", 256);
   if (cut.mfma) {
-    // one wave per (group of columns, sub-chunk, KV head), kMfmaAttnWaves of them per workgroup,
-    // walking its sub-chunk in super tiles of 64 slots: sub-chunks of a fixed length, grown until
-    // their count fits the partial buffers and the launch is not cut finer than one workgroup per CU
-    // (measured: 8-wide tree level 3061 -> 2997 us against two per CU)
+    // one workgroup per (group of columns, chunk, KV head), walking its chunk in super tiles of 64 slots: chunks of a
+    // fixed length, grown until their count fits the partial buffers and the launch is not cut finer than max_wg
     ColGroups cg;
-    group_columns(c, s.Hq / s.Hkv, cg);
+    cut.tiles = row_tiles(c, s.Hq / s.Hkv);
+    group_columns(c, s.Hq / s.Hkv, cut.tiles, cg);
     const int unit = 64;
     if (max_len <= single_max) {
       cut.chunk = (max_len + unit - 1) / unit * unit;
       cut.n_chunks = 1;
       return cut;
     }
-    static const long max_wg = env_int("EASYSPEC_ATTN_WG", 256);
     int ch = unit;
     auto nch = [&](int ch_) { return (max_len + ch_ - 1) / ch_; };
-    while (ch < 1024 && (nch(ch) > kMaxChunks || (long)nch(ch) * s.Hkv * n_set * cg.n > max_wg * kMfmaAttnWaves)) ch *= 2;
+    auto wgs = [&](int ch_) {
+      long n = 0;
+      for (int i = 0; i < cg.n; ++i) n += (c.pos[cg.first[i] + cg.count[i] - 1] + ch_) / ch_;
+      return n * s.Hkv * n_set;
+    };
+    // Waves aimed at: eight per CU (two per SIMD hide each other's chains) while a workgroup still has four super
+    // tiles to walk, four per CU below that (a launch of few tiles is all start and end): prefill of 16 tokens at
+    // context 8192 4205 us with eight, 4090 us with four; 4 x 6 tokens at contexts 4096 .. 32768 6618 us with four,
+    // 6403 us with eight, no better with 12 or 16.
+    const long few = (long)cu_count() * 4 / cut.tiles, many = 2 * few;
+    const long max_wg = std::max(few, std::min(many, wgs(unit) / 4));
+    while (ch < 1024 && (nch(ch) > kMaxChunks || wgs(ch) > max_wg)) ch += unit;
     cut.chunk = ch;
     cut.n_chunks = nch(ch);
     return cut;
@@ -923,6 +950,7 @@ AttnCut attn_cut(const Shape& s, const Cols& c, int n_set) {
 AttnCut attn_cut_vector(const Shape& s, const Cols& c, int n_set) {
   AttnCut cut;
   cut.mfma = false;
+  cut.tiles = 1;
   cut.chunk = 0;
   int max_len = 1;
   for (int i = 0; i < c.n; ++i) max_len = std::max(max_len, c.pos[i] + 1);
@@ -1004,14 +1032,21 @@ void launch_attn(const Shape& s, const Buffers& b, const Cols& c, int layer0, in
   for (int i = 0; i < c.n; ++i) tree = tree || c.vis_base[i] <= c.pos[i];
   if (cut.mfma) {
     ColGroups cg;
-    group_columns(c, G, cg);
-    const dim3 mg((n_chunks + kMfmaAttnWaves - 1) / kMfmaAttnWaves, s.Hkv, n_set * cg.n);
-    const dim3 blk(64 * kMfmaAttnWaves);
-    const size_t lds = (size_t)kMfmaAttnWaves * 80 * (s.hd / 8) * sizeof(u32x4);  // per wave a 64-slot V tile and a 16-slot K tile
-    if (s.hd == 128 && tree) ES_LAUNCH((attn_mfma_kernel<128, true>), mg, blk, lds, st, a, c, cg, G);
-    else if (s.hd == 128) ES_LAUNCH((attn_mfma_kernel<128, false>), mg, blk, lds, st, a, c, cg, G);
-    else if (tree) ES_LAUNCH((attn_mfma_kernel<64, true>), mg, blk, lds, st, a, c, cg, G);
-    else ES_LAUNCH((attn_mfma_kernel<64, false>), mg, blk, lds, st, a, c, cg, G);
+    group_columns(c, G, cut.tiles, cg);
+    const dim3 mg(n_chunks, s.Hkv, n_set * cg.n), blk(64 * cut.tiles);
+    auto go = [&](auto hd, auto is_tree) {
+      constexpr int HD = decltype(hd)::value;
+      constexpr bool TREE = decltype(is_tree)::value;
+      if (cut.tiles == 4) ES_LAUNCH((attn_mfma_kernel<HD, TREE, 4>), mg, blk, 0, st, a, c, cg, G);
+      else if (cut.tiles == 2) ES_LAUNCH((attn_mfma_kernel<HD, TREE, 2>), mg, blk, 0, st, a, c, cg, G);
+      else ES_LAUNCH((attn_mfma_kernel<HD, TREE, 1>), mg, blk, 0, st, a, c, cg, G);
+    };
+    const std::integral_constant<int, 128> h128{};
+    const std::integral_constant<int, 64> h64{};
+    if (s.hd == 128 && tree) go(h128, std::true_type{});
+    else if (s.hd == 128) go(h128, std::false_type{});
+    else if (tree) go(h64, std::true_type{});
+    else go(h64, std::false_type{});
   } else
   DISPATCH_T(s.dtype, {
     if (s.hd == 128 && tree) launch_attn_g<T, 128, true>(G, grid, nwv, st, a, c);

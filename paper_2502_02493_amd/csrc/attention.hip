@@ -421,7 +421,9 @@ __global__ __launch_bounds__(512) void attn_kernel(AttnArgs a, Cols c) {
     }
   }
   for (; full_batch_at(base); base += Geo::WAVE_SLOTS) process(kFull, base);
-  for (; base < w1; base += Geo::UNIT) process(std::integral_constant<int, kAttnSmallIT>{}, base);
+  // at most two units are left: both in one step (one latency instead of two)
+  if (w1 - base > Geo::UNIT) process(std::integral_constant<int, 2 * kAttnSmallIT>{}, base);
+  else if (base < w1) process(std::integral_constant<int, kAttnSmallIT>{}, base);
 
   if constexpr (kHeadPerLane && !kQuadHeads) {  // back to every lane holding all heads' maximum and sum: through LDS
     float* share = dyn_f + wave * (IT * SPW * LPS * 4) + sub * kShareRow;

@@ -685,7 +685,7 @@ void launch_embed(const Shape& s, const Buffers& b, const Cols& c, const int32_t
 // workgroups and waves; the launch wrappers below and the host-side walk of the weight stream
 // (stream_walk) both read it from there.
 // ------------------------------------------------------------------------------------------
-StreamPlan stream_plan(const Shape& s, int op, int ncols, int n_layers, bool full_layer) {
+StreamPlan stream_plan(const Shape& s, int op, int ncols, int n_layers, bool full_layer, bool twin) {
   StreamPlan p;
   memset(&p, 0, sizeof p);
   p.op = op;
@@ -744,7 +744,7 @@ StreamPlan stream_plan(const Shape& s, int op, int ncols, int n_layers, bool ful
       break;
   }
   p.nkt = p.K / kt;
-  p.nw = pick_waves(dflt_nw, p.nkt, env);
+  p.nw = pick_waves(dflt_nw, p.nkt, p.n_mat, p.n_layers * p.units, twin ? kTwinThreads / 64 : 16, env);
   // Two units per workgroup in two-fragment passes, where the halved launch still fills the CUs (the down
   // projection's 256 workgroups never; the full-layer kernels have no such instantiation)
   p.TP = 1;
@@ -830,7 +830,7 @@ int stream_walk(const Shape& s, const StreamPlan& p, int ncols, StreamWalk* r) {
 bool twin_passes_fit(const Shape& s, int n_cols) {
   static const int ops[] = {EASYSPEC_OP_QKV, EASYSPEC_OP_OPROJ, EASYSPEC_OP_GATEUP, EASYSPEC_OP_DOWN, EASYSPEC_OP_HEAD};
   for (int op : ops)
-    if (64 * stream_plan(s, op, n_cols, 1, false).nw > kTwinThreads) return false;
+    if (64 * stream_plan(s, op, n_cols, 1, false, true).nw > kTwinThreads) return false;
   return true;
 }
 
@@ -849,7 +849,7 @@ bool twin_passes_fit(const Shape& s, int n_cols) {
 
 void launch_qkv(const Shape& s, const Buffers& b, const Cols& c, int layer0, int n_set, hipStream_t st, const Buffers* b2,
                 const Cols* c2) {
-  const StreamPlan p = stream_plan(s, EASYSPEC_OP_QKV, c.n, n_set, false);
+  const StreamPlan p = stream_plan(s, EASYSPEC_OP_QKV, c.n, n_set, false, c2 != nullptr);
   auto args = [&](const Buffers& w) {
     QkvArgs a;
     a.w = (const u32x4*)w.wqkv + (size_t)layer0 * p.layer_pieces;
@@ -878,7 +878,7 @@ void launch_qkv(const Shape& s, const Buffers& b, const Cols& c, int layer0, int
 
 void launch_oproj(const Shape& s, const Buffers& b, const Cols& c, int layer0, int n_set, hipStream_t st, const Buffers* b2,
                   const Cols* c2) {
-  const StreamPlan p = stream_plan(s, EASYSPEC_OP_OPROJ, c.n, n_set, false);
+  const StreamPlan p = stream_plan(s, EASYSPEC_OP_OPROJ, c.n, n_set, false, c2 != nullptr);
   auto args = [&](const Buffers& w) {
     ProjArgs a;
     a.w = (const u32x4*)w.wo + (size_t)layer0 * p.layer_pieces;
@@ -904,7 +904,7 @@ void launch_oproj(const Shape& s, const Buffers& b, const Cols& c, int layer0, i
 
 void launch_gateup(const Shape& s, const Buffers& b, const Cols& c, int layer, int n_layers, const float* ssp, hipStream_t st,
                    const Buffers* b2, const Cols* c2, const float* ssp2) {
-  const StreamPlan p = stream_plan(s, EASYSPEC_OP_GATEUP, c.n, n_layers, false);
+  const StreamPlan p = stream_plan(s, EASYSPEC_OP_GATEUP, c.n, n_layers, false, c2 != nullptr);
   auto args = [&](const Buffers& w, const float* sums) {
     GateUpArgs a;
     a.wg = (const u32x4*)w.wg + (size_t)layer * p.layer_pieces;
@@ -928,7 +928,7 @@ void launch_gateup(const Shape& s, const Buffers& b, const Cols& c, int layer, i
 
 void launch_down(const Shape& s, const Buffers& b, const Cols& c, int layer, int a_next, const float* gain, int n_gain,
                  void* xout, hipStream_t st, const Buffers* b2, const Cols* c2, void* xout2) {
-  const StreamPlan p = stream_plan(s, EASYSPEC_OP_DOWN, c.n, 1, false);
+  const StreamPlan p = stream_plan(s, EASYSPEC_OP_DOWN, c.n, 1, false, c2 != nullptr);
   auto args = [&](const Buffers& w, void* out) {
     ProjArgs a;
     a.w = (const u32x4*)w.wd + (size_t)layer * p.layer_pieces;
@@ -976,7 +976,7 @@ void launch_down_full(const Shape& s, const Buffers& b, const Cols& c, int layer
 
 void launch_head(const Shape& s, const Buffers& b, const Cols& c, float* logits_out, int32_t* tokens_out, hipStream_t st,
                  const Buffers* b2, const Cols* c2) {
-  const StreamPlan p = stream_plan(s, EASYSPEC_OP_HEAD, c.n, 1, false);
+  const StreamPlan p = stream_plan(s, EASYSPEC_OP_HEAD, c.n, 1, false, c2 != nullptr);
   auto args = [&](const Buffers& w) {
     HeadArgs a;
     a.w = (const u32x4*)w.wlm; a.x = w.XA; a.ssp = w.ssp; a.logits = logits_out;

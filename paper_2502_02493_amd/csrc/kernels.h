@@ -119,7 +119,8 @@ struct StreamPlan {
   size_t mat_pieces;    // 16-byte pieces of one packed matrix of one layer
   size_t layer_pieces;  // pieces from one layer to the next inside an array
 };
-StreamPlan stream_plan(const Shape& s, int op, int ncols, int n_layers, bool full_layer);
+// twin: of a launch that serves two passes
+StreamPlan stream_plan(const Shape& s, int op, int ncols, int n_layers, bool full_layer, bool twin = false);
 // What a host walk of the launch found: the highest piece index against the pieces the launch's layers
 // hold, the highest activation element against an operand slot, k-tiles never read, read twice (apart
 // from the deliberate re-reads of a missing last unit), and fragment pieces no lane takes.

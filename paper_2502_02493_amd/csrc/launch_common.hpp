@@ -12,10 +12,25 @@ static inline int env_int(const char* name, int dflt) {
   return v ? atoi(v) : dflt;
 }
 
-// Waves per workgroup (they split K).  `dflt` is the value measured best at the 8B shape for
-// that operation; a wave always keeps at least 8 k-tiles.  EASYSPEC_NW_* overrides for sweeps.
-static inline int pick_waves(int dflt, int nkt, const char* env) {
+static inline int cu_count() {
+  static const int n_cu = [] {
+    int dev = 0, n = 0;
+    if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n < 1) n = 256;
+    return n;
+  }();
+  return n_cu;
+}
+
+// Waves per workgroup (they split K) of a launch of `grid` workgroups whose waves stream RT row tiles side by side.
+// `dflt` is the value measured best at the 8B shape for that operation; a wave always keeps at least eight k-tiles,
+// except where the launch fills less than half of the CUs (small models, where nothing hides a wave's latencies):
+// there as many waves as leave each a single batch of loads, within most_waves.  448-wide fp32 model: QKV (28 k-tiles)
+// with 2 waves, four batches one after the other, 8.9 us a launch, with 7 waves 6.5; gate/up 8.4 -> 6.1; down
+// (74 k-tiles) with 8 waves 6.9, with 10 waves 6.4; an iteration of four forwards 713 -> 595 us, of which the last attention
+// step of two units instead of one is a tenth.  EASYSPEC_NW_* overrides for sweeps.
+static inline int pick_waves(int dflt, int nkt, int RT, int grid, int most_waves, const char* env) {
   const int forced = env_int(env, 0);
+  if (forced <= 0 && grid <= cu_count() / 2) return std::max(1, std::min(most_waves, ceil_div(nkt, batch_len(RT))));
   int nw = forced > 0 ? forced : dflt;
   if (nw > 16) nw = 16;
   while (nw > 1 && nkt / nw < 8) nw /= 2;
@@ -39,15 +54,6 @@ static inline size_t red_bytes(int nw, int rt) { return (size_t)(nw > 1 ? nw - 1
 
 // bf16 with more than 8 columns: hi and lo activation terms take a fragment each
 static inline bool two_fragments(int dtype, const Cols& c) { return dtype == 1 && 2 * c.n > kMaxCols; }
-
-static inline int cu_count() {
-  static const int n_cu = [] {
-    int dev = 0, n = 0;
-    if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n < 1) n = 256;
-    return n;
-  }();
-  return n_cu;
-}
 
 // Two-fragment passes: may the workgroups of a launch of n one-tile workgroups take two row tiles each
 // (every activation fragment load then serves twice the weights)?  Only where the halved launch does

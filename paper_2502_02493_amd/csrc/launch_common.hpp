@@ -26,8 +26,8 @@ static inline int cu_count() {
 // except where the launch fills less than half of the CUs (small models, where nothing hides a wave's latencies):
 // there as many waves as leave each a single batch of loads, within most_waves.  448-wide fp32 model: QKV (28 k-tiles)
 // with 2 waves, four batches one after the other, 8.9 us a launch, with 7 waves 6.5; gate/up 8.4 -> 6.1; down
-// (74 k-tiles) with 8 waves 6.9, with 10 waves 6.4; an iteration of four forwards 713 -> 595 us, of which the last attention
-// step of two units instead of one is a tenth.  EASYSPEC_NW_* overrides for sweeps.
+// (74 k-tiles) with 8 waves 6.9, with 10 waves 6.4; an iteration of four forwards 713 -> 595 us (with the vector attention's
+// last two units taken in one step: 6.9 -> 6.5 us a launch).  EASYSPEC_NW_* overrides for sweeps.
 static inline int pick_waves(int dflt, int nkt, int RT, int grid, int most_waves, const char* env) {
   const int forced = env_int(env, 0);
   if (forced <= 0 && grid <= cu_count() / 2) return std::max(1, std::min(most_waves, ceil_div(nkt, batch_len(RT))));

@@ -99,11 +99,10 @@ constexpr int kWidePart = 512;
 ES_HD constexpr size_t wide_off(int K, int col, int k) {
   return ((size_t)(col >> 4) * (K / 32) + k / 32) * (2 * kWidePart) + ((k & 31) >> 3) * 128 + (col & 15) * 8 + (k & 7);
 }
-// Weights: MFMA row tiles are 16 consecutive rows whatever R the matrix was packed with; the 16-byte piece a lane takes
-// of row tile t in k-tile 0 (rows past the last are the last; consecutive k-tiles lie fragment_pieces(R) apart).
-ES_HD constexpr size_t wide_piece(int lane, int t, int rows, int R, int nkt) {
-  const int f = t * 16 + (lane & 15) < rows ? t * 16 + (lane & 15) : rows - 1;
-  return (size_t)(f / R) * row_tile_pieces(nkt, R) + (lane >> 4) * R + f % R;
+// Weights: first piece of packed row tile t (past the last tile: the last); a lane takes lane_piece(lane, R) of it, and
+// consecutive k-tiles lie fragment_pieces(R) apart.
+ES_HD constexpr size_t wide_tile(int t, int tiles, int R, int nkt) {
+  return (size_t)(t < tiles ? t : tiles - 1) * row_tile_pieces(nkt, R);
 }
 // Workgroup id -> (column block, row block, split of K).  Workgroups go to the eight XCDs in turn: the column blocks of
 // a (row block, split) follow each other on one XCD (they read the same weights), and with eight splits an XCD reads

@@ -11,15 +11,21 @@
 //     while the matrix pipe is full; the plain 16-column kernels (a wave per row tile, operands straight from the L2)
 //     ask the L2 for as many operand bytes as weight bytes at 12 columns.  The halves put two waves on a SIMD
 //     without a second reader of the same operand; their sums meet in LDS at the end.
-//   * Stages of 2 KS k-tiles, the operand double-buffered in LDS, one barrier per stage; weights are requested two
-//     stages ahead, the operand one, LDS fragments two steps ahead.
+//   * Stages of 2 KS k-tiles, the operand in three LDS buffers filled in mid-stage, one barrier per stage; weights are
+//     requested two stages ahead, the operand one, LDS fragments a step ahead.
+//   * Packed tiles are taken as they are (14 rows for gate/up, 12 pairs for QKV at the 8B shape: the spare rows of the
+//     MFMA idle).  Regrouped into 16 consecutive rows a fragment straddles two packed tiles and touches half as many
+//     lines again: gate/up at 24 columns 55 us against 42.
 //   * Few row tiles (QKV, O, down: 256 to 384) are spread over the CUs by splitting K; the fp32 partial sums are added
 //     in split order by the kernel that does what follows anyway (rotary and cache write; residual and norm operand).
-// Measured at the 8B shape, a prefill of 16 x 16 tokens (256 columns): 41.8 -> 9.7 ms (eight pairs of 16-column passes
-// before); gate/up 119 us a layer (120 GFLOP with both terms: 1.0 PFLOP/s), down 78, QKV 33, O 24.  4 x 6 tokens at
-// contexts 4096 .. 32768 (24 columns): 6.57 -> 5.90 ms; gate/up 55 us there (4.3 TB/s).
-// On the way there (256 columns): LDS fragments read next to their use 141 us for the mean of gate/up and QKV; read two
-// steps ahead 100; weights two stages ahead but behind branches 94; unconditional requests 76.
+// Measured at the 8B shape.  A prefill of 16 x 16 tokens (256 columns): 41.8 -> 10.0 ms (eight pairs of 16-column
+// passes before); gate/up 117 us a layer (137 GFLOP with both terms and the idle rows: 1.2 PFLOP/s, where a loop of
+// nothing but these MFMAs on random operands runs at 2.1 and the same kernel without its weight loads takes 0.77 of the
+// time), down 78, QKV 36, O 24.  4 x 6 tokens at contexts 4096 .. 32768 (24 columns): 6.57 -> 5.28 ms, memory-bound:
+// gate/up 42 us (5.6 TB/s), down 24.
+// On the way there (256 columns, mean of gate/up and QKV): LDS fragments read next to their use 141 us; read ahead 100;
+// weights two stages ahead but behind branches 94; unconditional requests 76; three operand buffers the same 76; weight
+// requests spread over the stage, raised wave priority around the products: no change.
 #include "launch_common.hpp"
 
 #include <math.h>
@@ -34,16 +40,16 @@ enum { kEpiPartial = 0, kEpiSilu = 1, kEpiLogits = 2 };
 struct WideArgs {
   const u32x4* w0;  // first matrix (gate; first rotary halves; or the only one)
   const u32x4* w1;  // second matrix of a pair, or null
-  int rows;         // rows of one packed matrix (padded to whole tiles of R: every row can be read)
-  int rows_out;     // rows of the result per matrix
-  int R, nkt;
+  int rows;         // rows of one matrix
+  int R, tiles;     // rows per packed tile, tiles of one matrix
+  int nkt;
   int row_blocks, splits, per_split;  // k-tiles per split
   int col_blocks, col_tiles;          // column blocks of CT tiles; column tiles of the pass
   const u32x4* x;   // operand, 128 pieces per (column tile, k-tile)
   int n;            // columns
   int epi;
-  float* out;       // kEpiPartial: [split][cols16][rows_out * matrices]; kEpiLogits: logits
-  bf16_t* act;      // kEpiSilu: operand of width rows_out
+  float* out;       // kEpiPartial: [split][cols16][rows * matrices]; kEpiLogits: logits
+  bf16_t* act;      // kEpiSilu: operand of width rows
   const float* rs;  // kEpiSilu, kEpiLogits: [cols]
 };
 
@@ -56,29 +62,20 @@ __global__ __launch_bounds__(kWideThreads) void wide_gemm_kernel(WideArgs a, Spa
   static_assert(SK * CT * 128 % kWideThreads == 0, "whole pieces per thread");
   constexpr int RU = PAIR ? RW / 2 : RW;                   // row tiles of a matrix per wave
   constexpr int kStagePieces = SK * CT * 128;
-  __shared__ u32x4 xs[2 * kStagePieces];                   // two stages of [column tile][k-tile of the stage][part][lane]
+  __shared__ u32x4 xs[3 * kStagePieces];                   // three stages of [column tile][k-tile of the stage][part][lane]
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), rg = wave & 3, half = wave >> 2;
   const int unit = wide_unit(blockIdx.x, a.col_blocks), cb = wide_col_block(blockIdx.x, a.col_blocks);
   if (unit >= a.row_blocks * a.splits) return;
   const int rb = unit / a.splits, split = unit % a.splits;
   const int k0 = split * a.per_split, k1 = min(a.nkt, k0 + a.per_split);
   const int t0 = (rb * 4 + rg) * RU, ct0 = cb * CT;
-  const u32x4* wp[RW];
+  // Addresses are a wave-uniform base plus one 32-bit lane offset each (scalar registers, not vector ones).
+  const u32x4* wb[RW];
 #pragma unroll
-  for (int r = 0; r < RW; ++r) {
-    const int t = PAIR ? t0 + r / 2 : t0 + r;
-    wp[r] = (PAIR && (r & 1) ? a.w1 : a.w0) + wide_piece(lane, t, a.rows, a.R, a.nkt);
-  }
+  for (int r = 0; r < RW; ++r)
+    wb[r] = (PAIR && (r & 1) ? a.w1 : a.w0) + wide_tile(PAIR ? t0 + r / 2 : t0 + r, a.tiles, a.R, a.nkt);
   const int w_stride = fragment_pieces(a.R);
-  // operand piece j of this thread: piece i = j * threads + tid of the stage, k-tile i % (SK * 128) / 128 of it, column
-  // tile ct0 + i / (SK * 128) (a missing last tile re-reads its neighbour)
-  const u32x4* xp[NB];
-#pragma unroll
-  for (int j = 0; j < NB; ++j) {
-    const int i = j * kWideThreads + tid, ct = min(ct0 + i / (SK * 128), a.col_tiles - 1);
-    xp[j] = a.x + ((size_t)ct * a.nkt) * 128 + i % (SK * 128);
-  }
-  const u32x4 zero = {0u, 0u, 0u, 0u};
+  const uint32_t w_lane = lane_piece(lane, a.R), x_lane = tid & 127;
   f32x4 acc[RW][CT];
 #pragma unroll
   for (int r = 0; r < RW; ++r)
@@ -86,80 +83,94 @@ __global__ __launch_bounds__(kWideThreads) void wide_gemm_kernel(WideArgs a, Spa
     for (int c = 0; c < CT; ++c) acc[r][c] = f32x4{0.f, 0.f, 0.f, 0.f};
 
   // Weights are requested two stages before they are used (they come from memory: a stage of products does not cover
-  // that latency under load), operand pieces one stage (they come from the L2).  Requests of a stage are issued operand
-  // first, so that waiting for the operand leaves the younger weight requests in flight.  All requests are unconditional
-  // (no branch for the compiler to wait at): past the split's end they repeat its last stage (operand) or k-tile
-  // (weights), whose lines are at hand; the products of k-tiles past the end are skipped.
+  // that latency under load), operand pieces from the middle of one stage to the middle of the next (they come from the
+  // L2).  All requests are unconditional (no branch for the compiler to wait at): k-tiles past the split's end repeat
+  // its last one, whose lines are at hand, and have their weights replaced by zeros before they are multiplied.
   u32x4 w[3][KS][RW], xn[NB];
   auto load_w = [&](int kt, u32x4 (&d)[KS][RW]) {
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
       const size_t at = (size_t)min(kt + half * KS + ks, k1 - 1) * w_stride;
 #pragma unroll
-      for (int r = 0; r < RW; ++r) d[ks][r] = __builtin_nontemporal_load(wp[r] + at);
+      for (int r = 0; r < RW; ++r) d[ks][r] = __builtin_nontemporal_load(wb[r] + at + w_lane);
     }
   };
+  // piece j of this thread: piece i = j * threads + tid of the stage, i.e. piece i % 128 of its (column tile, k-tile)
+  // fragment pair i / 128 (a missing last column tile re-reads its neighbour)
   auto load_x = [&](int kt) {
 #pragma unroll
-    for (int j = 0; j < NB; ++j) xn[j] = xp[j][(size_t)kt * 128];
+    for (int j = 0; j < NB; ++j) {
+      const int f = j * (kWideThreads / 128) + (wave >> 1), ct = min(ct0 + f / SK, a.col_tiles - 1), k = min(kt + f % SK, k1 - 1);
+      xn[j] = (a.x + ((size_t)ct * a.nkt + k) * 128)[x_lane];
+    }
   };
   auto put = [&](int buf) {
 #pragma unroll
     for (int j = 0; j < NB; ++j) xs[buf * kStagePieces + j * kWideThreads + tid] = xn[j];
   };
-  // The products of one stage: KS * CT steps of (hi, lo) fragments, read from LDS two steps before they are used (the
-  // scheduling barriers keep the compiler from moving a read next to its use, where its latency would be exposed)
-  auto products = [&](int buf, const u32x4 (&wa)[KS][RW], int n_ks) {  // of the first n_ks of the half's k-tiles
-    constexpr int AHEAD = CT < 2 ? CT : 2;
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {
-      if (ks >= n_ks) break;  // uniform
-      const u32x4* xb = xs + buf * kStagePieces + (half * KS + ks) * 128 + lane;
-      u32x4 bh[AHEAD + 1], bl[AHEAD + 1];
-#pragma unroll
-      for (int c = -AHEAD; c < CT; ++c) {
-        const int f = c + AHEAD;
-        if (f < CT) {
-          bh[f % (AHEAD + 1)] = xb[f * SK * 128];
-          bl[f % (AHEAD + 1)] = xb[f * SK * 128 + 64];
-        }
-        if (c < 0) continue;
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int r = 0; r < RW; ++r) mma<bf16_t>(acc[r][c], wa[ks][r], bh[c % (AHEAD + 1)]);
-#pragma unroll
-        for (int r = 0; r < RW; ++r) mma<bf16_t>(acc[r][c], wa[ks][r], bl[c % (AHEAD + 1)]);
-        __builtin_amdgcn_sched_barrier(0);
-      }
-    }
+  // A stage is KS * CT steps of (hi, lo) fragments, each read from LDS a step before it is used, across the end of the
+  // stage too (the scheduling barriers keep the compiler from moving a read next to its use, where its latency would be
+  // exposed).  In its middle a stage puts the next stage's operand into LDS; the barrier after that is the only one,
+  // and no wave has anything to wait for at the stage's end.  Three operand buffers: what is overwritten there was
+  // last read in the first of the two stages before, which every wave has left when any passes the barrier between.
+  constexpr int STEPS = KS * CT, AHEAD = 1, MID = STEPS / 2;
+  static_assert(3 * STEPS % (AHEAD + 1) == 0, "fragment registers return to their place after three stages");
+  const u32x4* const xl = xs + half * KS * 128 + lane;
+  u32x4 bh[AHEAD + 1], bl[AHEAD + 1];
+  auto fetch = [&](int slot, int buf, int st) {
+    const u32x4* f = xl + buf * kStagePieces + ((st % CT) * SK + st / CT) * 128;
+    bh[slot] = f[0];
+    bl[slot] = f[64];
   };
   if (k0 < k1) {
-    const int k_last = k0 + (k1 - k0 - 1) / SK * SK;  // first k-tile of the last stage
-    int kt = k0, buf = 0;
+    int kt = k0;
     load_x(k0);
     load_w(k0, w[0]);
     load_w(k0 + SK, w[1]);
     put(0);
+    load_x(k0 + SK);
     __syncthreads();
-    // one stage; the weight registers rotate by name (a copy would wait for the requests).  False: it was the last.
-    auto step = [&](u32x4 (&now)[KS][RW], u32x4 (&later)[KS][RW]) {
-      load_x(min(kt + SK, k_last));
-      load_w(kt + 2 * SK, later);
+#pragma unroll
+    for (int i = 0; i < AHEAD; ++i) fetch(i, 0, i);
+    // the stage in buffer I, its weights in w[I] (registers rotate by name: a copy would wait for the requests)
+    auto stage = [&](auto which) {
+      constexpr int I = decltype(which)::value, N = (I + 1) % 3, L = (I + 2) % 3;
+      load_w(kt + 2 * SK, w[L]);
+      if (kt + SK > k1) {  // uniform; only the last stage
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks)
+          if (kt + half * KS + ks >= k1) {
+#pragma unroll
+            for (int r = 0; r < RW; ++r) w[I][ks][r] = u32x4{0u, 0u, 0u, 0u};
+          }
+      }
       __builtin_amdgcn_sched_barrier(0);
-      products(buf, now, k1 - kt - half * KS);
+#pragma unroll
+      for (int st = 0; st < STEPS; ++st) {
+        const int ks = st / CT, c = st % CT, j = I * STEPS + st, at = j % (AHEAD + 1), to = (j + AHEAD) % (AHEAD + 1);
+        if (st == MID) {
+          put(N);
+          __syncthreads();
+          load_x(kt + 2 * SK);
+        }
+        if (st + AHEAD < STEPS) fetch(to, I, st + AHEAD);
+        else fetch(to, N, st + AHEAD - STEPS);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int r = 0; r < RW; ++r) mma<bf16_t>(acc[r][c], w[I][ks][r], bh[at]);
+#pragma unroll
+        for (int r = 0; r < RW; ++r) mma<bf16_t>(acc[r][c], w[I][ks][r], bl[at]);
+        __builtin_amdgcn_sched_barrier(0);
+      }
       kt += SK;
-      if (kt >= k1) return false;
-      buf ^= 1;
-      put(buf);
-      __syncthreads();
-      return true;
+      return kt < k1;
     };
-    while (step(w[0], w[2]) && step(w[1], w[0]) && step(w[2], w[1])) {
+    while (stage(std::integral_constant<int, 0>{}) && stage(std::integral_constant<int, 1>{}) && stage(std::integral_constant<int, 2>{})) {
     }
   }
   // the second half's sums onto the first's, through the LDS of the operand stages, as many column tiles at a time as fit
   {
-    constexpr int PER = 2 * kStagePieces / (4 * RW * 64), CC = PER < CT ? PER : CT;
+    constexpr int PER = 3 * kStagePieces / (4 * RW * 64), CC = PER < CT ? PER : CT;
     static_assert(PER >= 1, "a column tile's sums fit");
     f32x4* red = reinterpret_cast<f32x4*>(xs) + (size_t)rg * CC * RW * 64 + lane;
 #pragma unroll
@@ -182,43 +193,48 @@ __global__ __launch_bounds__(kWideThreads) void wide_gemm_kernel(WideArgs a, Spa
     if (half == 1) return;
   }
 
-  const int row4 = (lane >> 4) * 4;
+  const int row4 = (lane >> 4) * 4;  // of the tile
 #pragma unroll
   for (int c = 0; c < CT; ++c) {
     const int col = (ct0 + c) * 16 + (lane & 15);
     if (col >= a.n) continue;
-    if (a.epi == kEpiPartial) {
-      const int width = PAIR ? 2 * a.rows_out : a.rows_out;
+    if (a.epi == kEpiPartial) {  // R and the rows are multiples of four
+      const int width = PAIR ? 2 * a.rows : a.rows;
       float* o = a.out + ((size_t)split * (a.col_tiles * 16) + col) * width;
 #pragma unroll
       for (int r = 0; r < RW; ++r) {
-        const int row = (PAIR ? t0 + r / 2 : t0 + r) * 16 + row4;
-        if (row < a.rows_out) *reinterpret_cast<f32x4*>(o + (PAIR && (r & 1) ? a.rows_out : 0) + row) = acc[r][c];
+        const int t = PAIR ? t0 + r / 2 : t0 + r, row = t * a.R + row4;
+        if (row4 < a.R && row < a.rows) *reinterpret_cast<f32x4*>(o + (PAIR && (r & 1) ? a.rows : 0) + row) = acc[r][c];
       }
     } else if (PAIR) {  // kEpiSilu
       const float rs = a.rs[col];
 #pragma unroll
       for (int p = 0; p < RU; ++p) {
-        const int row = (t0 + p) * 16 + row4;
-        if (row >= a.rows_out) continue;
+        const int row = (t0 + p) * a.R + row4;
         float o[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
           const float g = acc[PAIR ? 2 * p : 0][c][i] * rs, u = acc[PAIR ? 2 * p + 1 : 0][c][i] * rs;
           o[i] = (g / (1.0f + expf(-g))) * u;
         }
-        store_act4<bf16_t>(a.act + wide_off(a.rows_out, col, row), kWidePart, o[0], o[1], o[2], o[3]);
+        if (a.R == 16) {
+          if (row < a.rows) store_act4<bf16_t>(a.act + wide_off(a.rows, col, row), kWidePart, o[0], o[1], o[2], o[3]);
+        } else {
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            if (row4 + i < a.R && row + i < a.rows) store_act1<bf16_t>(a.act + wide_off(a.rows, col, row + i), kWidePart, o[i]);
+        }
       }
     } else {  // kEpiLogits
       const float rs = a.rs[col];
       const int e = span_entry(sp, col);
-      float* o = a.out + ((size_t)sp.seq[e] * sp.tok_pitch + (col - sp.first[e])) * a.rows_out;
+      float* o = a.out + ((size_t)sp.seq[e] * sp.tok_pitch + (col - sp.first[e])) * a.rows;
 #pragma unroll
       for (int r = 0; r < RW; ++r) {
-        const int row = (t0 + r) * 16 + row4;
+        const int row = (t0 + r) * a.R + row4;
 #pragma unroll
         for (int i = 0; i < 4; ++i)
-          if (row + i < a.rows_out) o[row + i] = acc[r][c][i] * rs;
+          if (row + i < a.rows) o[row + i] = acc[r][c][i] * rs;
       }
     }
   }
@@ -391,9 +407,7 @@ __global__ __launch_bounds__(1024) void wide_argmax_kernel(const float* __restri
 // ------------------------------------------------------------------------------------------
 // Launches
 // ------------------------------------------------------------------------------------------
-// a stage is at most 8 k-tiles of 2 KB per column tile (kWideSlack): what the last stage of the last column tile may read past the end
-constexpr size_t kWideSlack = 8 * 2048;
-size_t wide_operand_bytes(int cols, int K) { return (size_t)cols * K * 2 * sizeof(bf16_t) + kWideSlack; }
+size_t wide_operand_bytes(int cols, int K) { return (size_t)cols * K * 2 * sizeof(bf16_t); }
 size_t wide_partial_bytes(const Shape& s) {
   return (size_t)kWideSplitCols * std::max(s.RQKV, s.d) * sizeof(float);
 }
@@ -406,12 +420,25 @@ struct WideCut {
 };
 static WideCut wide_cut(int tiles, int nkt, int ct, bool pair, bool split_k) {
   WideCut c;
-  c.col_blocks = (ct + 7) / 8;
-  c.CT = std::max(2, (ct + c.col_blocks - 1) / c.col_blocks);
-  if (c.CT == 7) c.CT = 8;  // seven tiles of one k-tile are no whole number of pieces per thread
-  // Four row tiles per wave where the columns make the product compute-bound (an LDS read then serves four MFMAs); two
-  // where the weight stream bounds it: twice the workgroups.
-  c.RW = c.CT >= 5 ? 4 : 2;
+  // Up to 64 columns the weight stream is what bounds the product: two row tiles per wave, the most workgroups.  More:
+  // four row tiles per wave, so that an LDS read serves four MFMAs, and as many column blocks (on one XCD, reading the
+  // same weights) as make the launch's rounds of one workgroup per CU, times the column tiles of each, the least.
+  // gate/up and all, 8 layers, one column block against two: 8B shape (128 row blocks) 96 columns 1643 -> 1494 us, 128
+  // columns 1927 -> 1590; Qwen2-7B shape (148) 1584 -> 1763 and 1784 -> 1889, hence the rule.  Split products fill the
+  // CUs whatever the blocks.
+  auto tiles_of = [&](int blocks) {
+    const int t = std::max(2, (ct + blocks - 1) / blocks);
+    return t == 7 ? 8 : t;  // seven tiles of one k-tile are no whole number of pieces per thread
+  };
+  c.RW = ct > 4 ? 4 : 2;
+  c.col_blocks = ct > 4 && split_k ? 2 : (ct + 7) / 8;
+  if (ct > 4 && !split_k) {
+    const int rows = (tiles + (pair ? 7 : 15)) / (pair ? 8 : 16);
+    auto cost = [&](int blocks) { return (rows * blocks + cu_count() - 1) / cu_count() * tiles_of(blocks); };
+    for (int n = c.col_blocks + 1; n <= 4 && tiles_of(n) >= 3; ++n)
+      if (cost(n) < cost(c.col_blocks)) c.col_blocks = n;
+  }
+  c.CT = tiles_of(c.col_blocks);
   const int per_wg = 4 * (pair ? c.RW / 2 : c.RW);
   c.row_blocks = (tiles + per_wg - 1) / per_wg;
   c.splits = 1;
@@ -420,21 +447,24 @@ static WideCut wide_cut(int tiles, int nkt, int ct, bool pair, bool split_k) {
     // as many splits as fill the CUs once, at least 8 k-tiles each, within the room for the partial sums
     const int most = std::max(1, std::min(nkt / 8, kWideSplitCols / (ct * 16)));
     const int want = std::max(1, std::min(most, cu_count() / (c.row_blocks * c.col_blocks)));
-    c.per_split = (nkt + want - 1) / want;
+    c.per_split = ((nkt + want - 1) / want + 1) & ~1;  // whole stages (of two k-tiles or more) if K allows
     c.splits = (nkt + c.per_split - 1) / c.per_split;
   }
   return c;
 }
 
 template <bool PAIR>
-static void launch_wide_gemm_ct(const WideArgs& a, const Spans& sp, int CT, hipStream_t st) {
+static void launch_wide_gemm_ct(const WideArgs& a, const Spans& sp, const WideCut& c, hipStream_t st) {
   const dim3 grid(wide_grid(a.row_blocks * a.splits, a.col_blocks)), blk(kWideThreads);
-  switch (CT) {  // row tiles per wave as in wide_cut
-    case 2: ES_LAUNCH((wide_gemm_kernel<2, 2, 4, PAIR>), grid, blk, 0, st, a, sp); break;
-    case 3: ES_LAUNCH((wide_gemm_kernel<2, 3, 2, PAIR>), grid, blk, 0, st, a, sp); break;
-    case 4: ES_LAUNCH((wide_gemm_kernel<2, 4, 2, PAIR>), grid, blk, 0, st, a, sp); break;
-    case 5: ES_LAUNCH((wide_gemm_kernel<4, 5, 2, PAIR>), grid, blk, 0, st, a, sp); break;
-    case 6: ES_LAUNCH((wide_gemm_kernel<4, 6, 1, PAIR>), grid, blk, 0, st, a, sp); break;
+  // k-tiles per half and stage: two where the registers hold three sets of weights for them
+  switch (c.RW * 10 + c.CT) {
+    case 22: ES_LAUNCH((wide_gemm_kernel<2, 2, 2, PAIR>), grid, blk, 0, st, a, sp); break;
+    case 23: ES_LAUNCH((wide_gemm_kernel<2, 3, 2, PAIR>), grid, blk, 0, st, a, sp); break;
+    case 24: ES_LAUNCH((wide_gemm_kernel<2, 4, 2, PAIR>), grid, blk, 0, st, a, sp); break;
+    case 43: ES_LAUNCH((wide_gemm_kernel<4, 3, 2, PAIR>), grid, blk, 0, st, a, sp); break;
+    case 44: ES_LAUNCH((wide_gemm_kernel<4, 4, 2, PAIR>), grid, blk, 0, st, a, sp); break;
+    case 45: ES_LAUNCH((wide_gemm_kernel<4, 5, 2, PAIR>), grid, blk, 0, st, a, sp); break;
+    case 46: ES_LAUNCH((wide_gemm_kernel<4, 6, 1, PAIR>), grid, blk, 0, st, a, sp); break;
     default: ES_LAUNCH((wide_gemm_kernel<4, 8, 1, PAIR>), grid, blk, 0, st, a, sp); break;
   }
 }
@@ -443,24 +473,24 @@ static void launch_wide_gemm_ct(const WideArgs& a, const Spans& sp, int CT, hipS
 static int launch_wide_gemm(WideArgs a, const Spans& sp, bool pair, bool split_k, hipStream_t st) {
   a.n = sp.n;
   a.col_tiles = col_tiles_of(sp);
-  const WideCut c = wide_cut((a.rows_out + 15) / 16, a.nkt, a.col_tiles, pair, split_k);
+  const WideCut c = wide_cut(a.tiles, a.nkt, a.col_tiles, pair, split_k);
   a.col_blocks = c.col_blocks;
   a.row_blocks = c.row_blocks;
   a.splits = c.splits;
   a.per_split = c.per_split;
-  if (pair) launch_wide_gemm_ct<true>(a, sp, c.CT, st);
-  else launch_wide_gemm_ct<false>(a, sp, c.CT, st);
+  if (pair) launch_wide_gemm_ct<true>(a, sp, c, st);
+  else launch_wide_gemm_ct<false>(a, sp, c, st);
   return c.splits;
 }
 
-static WideArgs wide_args(const void* w0, const void* w1, int rows_out, int R, int K, const void* x, int epi) {
+static WideArgs wide_args(const void* w0, const void* w1, int rows, int R, int K, const void* x, int epi) {
   WideArgs a;
   memset(&a, 0, sizeof a);
   a.w0 = (const u32x4*)w0;
   a.w1 = (const u32x4*)w1;
-  a.rows_out = rows_out;
-  a.rows = (rows_out + R - 1) / R * R;
+  a.rows = rows;
   a.R = R;
+  a.tiles = (rows + R - 1) / R;
   a.nkt = K / 32;
   a.x = (const u32x4*)x;
   a.epi = epi;

@@ -421,9 +421,15 @@ __global__ __launch_bounds__(512) void attn_kernel(AttnArgs a, Cols c) {
     }
   }
   for (; full_batch_at(base); base += Geo::WAVE_SLOTS) process(kFull, base);
-  // at most two units are left: both in one step (one latency instead of two)
-  if (w1 - base > Geo::UNIT) process(std::integral_constant<int, 2 * kAttnSmallIT>{}, base);
-  else if (base < w1) process(std::integral_constant<int, kAttnSmallIT>{}, base);
+  // At most two units are left.  Vector scores: both in one step (one latency instead of two).  Scores from the matrix
+  // cores: a step each; a third shape of the batch code costs the 7-head instantiation more than the latency
+  // (Qwen2-7B shape, context 4096: 2677 us a draft step against 2651).
+  if constexpr (kScoresByMfma) {
+    for (; base < w1; base += Geo::UNIT) process(std::integral_constant<int, kAttnSmallIT>{}, base);
+  } else {
+    if (w1 - base > Geo::UNIT) process(std::integral_constant<int, 2 * kAttnSmallIT>{}, base);
+    else if (base < w1) process(std::integral_constant<int, kAttnSmallIT>{}, base);
+  }
 
   if constexpr (kHeadPerLane && !kQuadHeads) {  // back to every lane holding all heads' maximum and sum: through LDS
     float* share = dyn_f + wave * (IT * SPW * LPS * 4) + sub * kShareRow;
@@ -672,11 +678,21 @@ __global__ __launch_bounds__(64 * NW, NW == 1 ? 1 : 2) void attn_mfma_kernel(Att
   const int piece = tid % PIECES, sl0 = tid / PIECES;
   constexpr int SL = 64 * NW / PIECES;  // slots one load of the workgroup covers
   u32x4 kf[NL], vf[NL];
+  const char* kb = reinterpret_cast<const char*>(kc);
+  const char* vb = reinterpret_cast<const char*>(vc);
   auto request = [&](int base) {
+    if (base + 64 <= ws1) {  // uniform: a whole tile lies one constant apart (32-bit offsets: a head's rows are at most 16 MB)
+      const uint32_t at = (uint32_t)(base + sl0) * (HD * 2) + piece * 16;
 #pragma unroll
-    for (int j = 0; j < NL; ++j) kf[j] = __builtin_nontemporal_load(kc + (size_t)min(base + sl0 + j * SL, ws1 - 1) * PIECES + piece);
+      for (int j = 0; j < NL; ++j) kf[j] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(kb + (at + j * (SL * HD * 2))));
 #pragma unroll
-    for (int j = 0; j < NL; ++j) vf[j] = __builtin_nontemporal_load(vc + (size_t)min(base + sl0 + j * SL, ws1 - 1) * PIECES + piece);
+      for (int j = 0; j < NL; ++j) vf[j] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(vb + (at + j * (SL * HD * 2))));
+    } else {
+#pragma unroll
+      for (int j = 0; j < NL; ++j) kf[j] = __builtin_nontemporal_load(kc + (size_t)min(base + sl0 + j * SL, ws1 - 1) * PIECES + piece);
+#pragma unroll
+      for (int j = 0; j < NL; ++j) vf[j] = __builtin_nontemporal_load(vc + (size_t)min(base + sl0 + j * SL, ws1 - 1) * PIECES + piece);
+    }
   };
   request(ws0);
 
@@ -696,7 +712,8 @@ __global__ __launch_bounds__(64 * NW, NW == 1 ? 1 : 2) void attn_mfma_kernel(Att
   f32x4 o[ET];
 #pragma unroll
   for (int et = 0; et < ET; ++et) o[et] = f32x4{0.f, 0.f, 0.f, 0.f};
-  float m_run = -INFINITY, l_run = 0.f;  // l_run: this lane's 16 slots per super tile only
+  float m_run = -INFINITY, l_run = 0.f;  // m_run: of the unscaled scores; l_run: this lane's 16 slots per super tile only
+  const float scale2 = a.scale * 1.44269504088896340736f;  // log2(e)
 
   for (int base = ws0; base < ws1; base += 64) {
     if (base > ws0) __syncthreads();  // every wave has read the previous tile
@@ -731,14 +748,9 @@ __global__ __launch_bounds__(64 * NW, NW == 1 ? 1 : 2) void attn_mfma_kernel(Att
 #pragma unroll
       for (int t = 0; t < 4; ++t) st[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, ka[t]), ql[kt], st[t], 0, 0, 0);
     }
-    float sc[4][4];
-    if (base + 64 <= n_all) {  // wave-uniform: a super tile that every query row sees whole needs no mask
-#pragma unroll
-      for (int t = 0; t < 4; ++t)  // (padding rows get finite scores of a zero query; they are never stored)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) sc[t][i] = st[t][i] * a.scale;
-    } else {
-#pragma unroll
+    // Scores stay unscaled: scale and log2(e) go into the exponential's argument, one fused multiply-add per score
+    if (base + 64 > n_all) {  // wave-uniform: a super tile that every query row sees whole needs no mask
+#pragma unroll              // (padding rows get finite scores of a zero query; they are never stored)
       for (int t = 0; t < 4; ++t)
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
@@ -746,19 +758,20 @@ __global__ __launch_bounds__(64 * NW, NW == 1 ? 1 : 2) void attn_mfma_kernel(Att
           // no short circuit: the shift amount is masked instead of guarded, so that this stays straight-line code
           const bool seen = !TREE || (int)(slot < vbase) | (int)((vmask >> ((slot - vbase) & 63)) & 1ull);
           const bool valid = (int)row_ok & (int)(slot < n_slots) & (int)seen;
-          sc[t][i] = valid ? st[t][i] * a.scale : -INFINITY;
+          st[t][i] = valid ? st[t][i] : -INFINITY;
         }
     }
     float bm = -INFINITY;
 #pragma unroll
     for (int t = 0; t < 4; ++t)
 #pragma unroll
-      for (int i = 0; i < 4; ++i) bm = fmaxf(bm, sc[t][i]);
+      for (int i = 0; i < 4; ++i) bm = fmaxf(bm, st[t][i]);
     bm = fmaxf(bm, __shfl_xor(bm, 16, 64));  // the four quarters of a row must share the reference:
     bm = fmaxf(bm, __shfl_xor(bm, 32, 64));  // their slots are summed by one instruction below
     const float m_new = fmaxf(m_run, bm);
     const float m_ref = m_new == -INFINITY ? 0.f : m_new;  // nothing visible so far: exponentials give 0
-    const float alpha = __expf(m_run - m_ref);
+    const float ref2 = m_ref * scale2;
+    const float alpha = __builtin_amdgcn_exp2f((m_run - m_ref) * scale2);
     m_run = m_new;
     l_run *= alpha;
     if (__builtin_amdgcn_ballot_w64(alpha != 1.0f) != 0) {  // wave-uniform: once the running maxima have settled nothing is rescaled
@@ -772,7 +785,7 @@ __global__ __launch_bounds__(64 * NW, NW == 1 ? 1 : 2) void attn_mfma_kernel(Att
       float pv[8];
 #pragma unroll
       for (int j = 0; j < 8; ++j) {
-        pv[j] = __expf(sc[2 * h + (j >> 2)][j & 3] - m_ref);
+        pv[j] = __builtin_amdgcn_exp2f(fmaf(st[2 * h + (j >> 2)][j & 3], scale2, -ref2));
         l_run += pv[j];
       }
       split_bf16x8(pv, ph[h], pl[h]);
@@ -829,7 +842,7 @@ __global__ __launch_bounds__(64 * NW, NW == 1 ? 1 : 2) void attn_mfma_kernel(Att
     for (int et = 0; et < ET; ++et)
       *reinterpret_cast<f32x4*>(a.PO + (prow * pitch + chunk) * HD + et * 16 + q4 * 4) = o[et];
     if (q4 == 0) {
-      a.PM[prow * pitch + chunk] = m_run;
+      a.PM[prow * pitch + chunk] = m_run * a.scale;
       a.PL[prow * pitch + chunk] = l_run;
     }
   }

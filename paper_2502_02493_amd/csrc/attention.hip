@@ -11,7 +11,7 @@ namespace es {
 
 // ------------------------------------------------------------------------------------------
 // Decode attention over the KV caches of a set's layers, split along the context.
-// One workgroup = (context chunk, KV head, layer x column); it serves the G query heads that
+// One workgroup = (column and context chunk, KV head, layer); it serves the G query heads that
 // share the KV head.  A K or V row (hd elements) is spread over LPS lanes, 16 bytes each, so a
 // wave load covers SPW = 64/LPS consecutive slots (1 KB, coalesced).  Each wave walks its own
 // contiguous run of slots in batches of IT loads per operand, all issued before the first is
@@ -100,14 +100,41 @@ struct AttnGeom {
 
 extern __shared__ float dyn_f[];
 
+// The chunks of a launch's columns: column i has first[i + 1] - first[i] of them, and its workgroups, [KV head][chunk], are
+// those from first[i] * Hkv on of the grid's first extent.  Columns of unequal length have unequal numbers of chunks; a
+// grid of (longest column's chunks) x KV heads x columns left its empty workgroups on the same XCDs again and again
+// (workgroup ids go to the eight XCDs in turn): contexts 4096 / 8192 / 16384 / 32768, attention and merge of a one-layer
+// set 64 -> 48 us, of a four-layer set 173 -> 166 (Qwen2-7B shape 37 -> 32, 112 -> 89).  Columns of one sequence keep
+// the distance of whole columns, a multiple of eight with eight KV heads, and so the XCD on which they meet each
+// other's K and V.
+// Columns of equal chunk counts (even != 0: one sequence, most batches of like lengths) keep the plain grid (chunk,
+// KV head, layer x column), which needs no division to find its place.
+struct ChunkMap {
+  int32_t even;
+  int32_t first[kMaxCols + 1];  // INT_MAX from the column count + 1 on
+};
+
 // TREE: the columns are nodes of token trees and carry a visibility mask; without it every
 // slot up to the column's own is visible and the mask logic costs no registers.
 template <typename T, int HD, int G, bool TREE>
-__global__ __launch_bounds__(512) void attn_kernel(AttnArgs a, Cols c) {
+__global__ __launch_bounds__(512) void attn_kernel(AttnArgs a, Cols c, ChunkMap map) {
   typedef AttnGeom<T, HD> Geo;
   constexpr int EPL = Geo::EPL, LPS = Geo::LPS, SPW = Geo::SPW, IT = kAttnIT;
-  const int chunk = blockIdx.x, kvh = blockIdx.y;
-  const int li = blockIdx.z / c.n, col = blockIdx.z % c.n;
+  int li, col, kvh, chunk;
+  if (map.even) {
+    chunk = blockIdx.x;
+    kvh = blockIdx.y;
+    li = blockIdx.z / c.n;
+    col = blockIdx.z % c.n;
+  } else {
+    li = blockIdx.y;
+    col = 0;
+#pragma unroll
+    for (int i = 1; i < kMaxCols; ++i) col += (int)blockIdx.x / a.Hkv >= map.first[i];
+    const int of_col = blockIdx.x - map.first[col] * a.Hkv, chunks = map.first[col + 1] - map.first[col];
+    kvh = of_col / chunks;
+    chunk = of_col % chunks;
+  }
   const int n_slots = c.pos[col] + 1;
   // slots below vis_base are all visible; slot vis_base + i (i < 64) only if bit i is set (the
   // column's row of a token tree's mask).  Causal columns have vis_base = n_slots.
@@ -911,7 +938,7 @@ __global__ __launch_bounds__(HD) void attn_merge_kernel(AttnArgs a, Src c) {
 }
 
 template <typename T, int HD, bool TREE>
-static void launch_attn_g(int G, dim3 grid, int nwv, hipStream_t st, AttnArgs a, const Cols& c) {
+static void launch_attn_g(int G, dim3 grid, int nwv, hipStream_t st, AttnArgs a, const Cols& c, const ChunkMap& map) {
   // partial state of every slot group of the workgroup if that fits the default 64 KB of
   // dynamic LDS, else of every wave
   const int groups = nwv * AttnGeom<T, HD>::SPW;
@@ -923,11 +950,11 @@ static void launch_attn_g(int G, dim3 grid, int nwv, hipStream_t st, AttnArgs a,
     lds = std::max(lds, (size_t)nwv * kAttnIT * AttnGeom<T, HD>::SPW * HD * sizeof(T));
   const dim3 blk(64 * nwv);
   switch (G) {
-    case 1: ES_LAUNCH((attn_kernel<T, HD, 1, TREE>), grid, blk, lds, st, a, c); break;
-    case 2: ES_LAUNCH((attn_kernel<T, HD, 2, TREE>), grid, blk, lds, st, a, c); break;
-    case 4: ES_LAUNCH((attn_kernel<T, HD, 4, TREE>), grid, blk, lds, st, a, c); break;
-    case 7: ES_LAUNCH((attn_kernel<T, HD, 7, TREE>), grid, blk, lds, st, a, c); break;
-    case 8: ES_LAUNCH((attn_kernel<T, HD, 8, TREE>), grid, blk, lds, st, a, c); break;
+    case 1: ES_LAUNCH((attn_kernel<T, HD, 1, TREE>), grid, blk, lds, st, a, c, map); break;
+    case 2: ES_LAUNCH((attn_kernel<T, HD, 2, TREE>), grid, blk, lds, st, a, c, map); break;
+    case 4: ES_LAUNCH((attn_kernel<T, HD, 4, TREE>), grid, blk, lds, st, a, c, map); break;
+    case 7: ES_LAUNCH((attn_kernel<T, HD, 7, TREE>), grid, blk, lds, st, a, c, map); break;
+    case 8: ES_LAUNCH((attn_kernel<T, HD, 8, TREE>), grid, blk, lds, st, a, c, map); break;
     default: break;  // rejected at create
   }
 }
@@ -1105,7 +1132,6 @@ void launch_attn(const Shape& s, const Buffers& b, const Cols& c, int layer0, in
   a.CH = cut.chunk; a.nch_ref = cut.n_chunks; a.nb_ref = cut.nb_ref;
   a.scale = 1.0f / sqrtf((float)s.hd);
   const int G = s.Hq / s.Hkv;
-  const dim3 grid(n_chunks, s.Hkv, n_set * c.n);
   // one chunk per context: eight waves share the whole context of a (layer, column, KV head) and
   // no merge launch is needed; several chunks: four waves per chunk
   const int nwv = attn_waves(cut);
@@ -1129,13 +1155,26 @@ void launch_attn(const Shape& s, const Buffers& b, const Cols& c, int layer0, in
     else if (s.hd == 128) go(h128, std::false_type{});
     else if (tree) go(h64, std::true_type{});
     else go(h64, std::false_type{});
-  } else
-  DISPATCH_T(s.dtype, {
-    if (s.hd == 128 && tree) launch_attn_g<T, 128, true>(G, grid, nwv, st, a, c);
-    else if (s.hd == 128) launch_attn_g<T, 128, false>(G, grid, nwv, st, a, c);
-    else if (tree) launch_attn_g<T, 64, true>(G, grid, nwv, st, a, c);
-    else launch_attn_g<T, 64, false>(G, grid, nwv, st, a, c);
-  });
+  } else {
+    ChunkMap map;
+    int total = 0;
+    map.even = 1;
+    for (int i = 0; i <= kMaxCols; ++i) {
+      map.first[i] = i <= c.n ? total : INT_MAX;
+      if (i >= c.n) continue;
+      int nch = 0, w0, w1;
+      attn_ranges(s, cut, c.pos[i] + 1, 0, 0, &nch, &w0, &w1);  // the kernel's own count
+      total += nch;
+      if (nch != n_chunks) map.even = 0;
+    }
+    const dim3 grid = map.even ? dim3(n_chunks, s.Hkv, n_set * c.n) : dim3(total * s.Hkv, n_set);
+    DISPATCH_T(s.dtype, {
+      if (s.hd == 128 && tree) launch_attn_g<T, 128, true>(G, grid, nwv, st, a, c, map);
+      else if (s.hd == 128) launch_attn_g<T, 128, false>(G, grid, nwv, st, a, c, map);
+      else if (tree) launch_attn_g<T, 64, true>(G, grid, nwv, st, a, c, map);
+      else launch_attn_g<T, 64, false>(G, grid, nwv, st, a, c, map);
+    });
+  }
   if (n_chunks > 1) {
     const dim3 mgrid(n_set * c.n, s.Hq);
     DISPATCH_T(s.dtype, {

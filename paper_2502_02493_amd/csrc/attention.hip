@@ -806,7 +806,9 @@ __global__ __launch_bounds__(64 * NW, NW == 1 ? 1 : 2) void attn_mfma_kernel(Att
       for (int et = 0; et < ET; ++et) o[et] *= alpha;
     }
     // B operands of P.V: MFMA number h takes slots q4*16 + h*8 .. +8 of this lane = tiles 2h, 2h+1
-    bf16x8 ph[2], pl[2];
+    // Wide passes carry probabilities in three terms, all 24 bits: the shorter contexts among them would otherwise be the
+    // vector kernel's, which keeps probabilities in fp32.
+    bf16x8 ph[2], pl[2], pr[2];
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
       float pv[8];
@@ -816,6 +818,18 @@ __global__ __launch_bounds__(64 * NW, NW == 1 ? 1 : 2) void attn_mfma_kernel(Att
         l_run += pv[j];
       }
       split_bf16x8(pv, ph[h], pl[h]);
+      if constexpr (Src::kWide) {
+        float rest[8], hi[8], lo[8];
+        unpack<bf16_t>(__builtin_bit_cast(u32x4, ph[h]), hi);
+        unpack<bf16_t>(__builtin_bit_cast(u32x4, pl[h]), lo);
+#pragma unroll
+        for (int j = 0; j < 8; ++j) rest[j] = (pv[j] - hi[j]) - lo[j];
+        uint32_t r4[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) r4[j] = pack_bf16x2(rest[2 * j], rest[2 * j + 1]);
+        const u32x4 rv = {r4[0], r4[1], r4[2], r4[3]};
+        pr[h] = __builtin_bit_cast(bf16x8, rv);
+      }
     }
     // A operands: V^T row e = et*16 + lane%16, the 8 slots q4*16 + h*8 + j, by the LDS transposing
     // read (ds_read_b64_tr_b16): in a group of 16 lanes, lane i offers the 8 bytes at its address
@@ -838,6 +852,7 @@ __global__ __launch_bounds__(64 * NW, NW == 1 ? 1 : 2) void attn_mfma_kernel(Att
         const bf16x8 va = __builtin_bit_cast(bf16x8, both);
         o[et] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va, ph[h], o[et], 0, 0, 0);
         o[et] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va, pl[h], o[et], 0, 0, 0);
+        if constexpr (Src::kWide) o[et] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va, pr[h], o[et], 0, 0, 0);
       }
     }
   }

@@ -595,8 +595,8 @@ __global__ __launch_bounds__(512) void attn_kernel(AttnArgs a, Cols c, ChunkMap 
 // heads of up to 16 NW / G columns of one sequence (the tokens of a calibration, the nodes of a tree
 // level) — are the columns of NW MFMA tiles of 16, one tile per wave of the workgroup, so K and V
 // are read once per group of columns and the per-slot arithmetic leaves the vector ALUs:
-//   S^T[slot][row]  = K[slot][:] . Q[row][:]      A = K (rows = slots), B = Q^T, two-term bf16 q
-//   O^T[e][row]    += V^T[e][slot] P^T[slot][row]  A = V^T, B = P^T, two-term bf16 p
+//   S^T[slot][row]  = K[slot][:] . Q[row][:]      A = K (rows = slots), B = Q^T, two-term bf16 q (wide passes: three)
+//   O^T[e][row]    += V^T[e][slot] P^T[slot][row]  A = V^T, B = P^T, two-term bf16 p (wide passes: three)
 // A workgroup walks its chunk of the context in super tiles of 64 slots: its waves load the K and V
 // rows of a tile together (coalesced) and put them into LDS (XOR-swizzled 16-byte pieces; V is read
 // back with the transposing LDS read), each wave then takes its own 16 query rows through scores,
@@ -723,8 +723,8 @@ __global__ __launch_bounds__(64 * NW, NW == 1 ? 1 : 2) void attn_mfma_kernel(Att
   };
   request(ws0);
 
-  // B operands of S^T: this row's query, hi and lo bf16 terms, k-group q4 of every k-tile
-  bf16x8 qh[KT], ql[KT];
+  // B operands of S^T: this row's query, hi and lo bf16 terms, k-group q4 of every k-tile; wide passes: a third term
+  bf16x8 qh[KT], ql[KT], qr[Src::kWide ? KT : 1];
   {
     const float* qp = a.Q + ((size_t)li * kMaxCols + col) * HQ + (kvh * G + g) * HD + q4 * 8;
 #pragma unroll
@@ -733,6 +733,7 @@ __global__ __launch_bounds__(64 * NW, NW == 1 ? 1 : 2) void attn_mfma_kernel(Att
 #pragma unroll
       for (int e = 0; e < 8; ++e) x[e] = row_ok ? qp[kt * 32 + e] : 0.f;
       split_bf16x8(x, qh[kt], ql[kt]);
+      if constexpr (Src::kWide) qr[kt] = third_bf16x8(x, qh[kt], ql[kt]);
     }
   }
 
@@ -774,6 +775,10 @@ __global__ __launch_bounds__(64 * NW, NW == 1 ? 1 : 2) void attn_mfma_kernel(Att
       for (int t = 0; t < 4; ++t) st[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, ka[t]), qh[kt], st[t], 0, 0, 0);
 #pragma unroll
       for (int t = 0; t < 4; ++t) st[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, ka[t]), ql[kt], st[t], 0, 0, 0);
+      if constexpr (Src::kWide) {
+#pragma unroll
+        for (int t = 0; t < 4; ++t) st[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, ka[t]), qr[kt], st[t], 0, 0, 0);
+      }
     }
     // Scores stay unscaled: scale and log2(e) go into the exponential's argument, one fused multiply-add per score
     if (base + 64 > n_all) {  // wave-uniform: a super tile that every query row sees whole needs no mask
@@ -806,8 +811,11 @@ __global__ __launch_bounds__(64 * NW, NW == 1 ? 1 : 2) void attn_mfma_kernel(Att
       for (int et = 0; et < ET; ++et) o[et] *= alpha;
     }
     // B operands of P.V: MFMA number h takes slots q4*16 + h*8 .. +8 of this lane = tiles 2h, 2h+1
-    // Wide passes carry probabilities in three terms, all 24 bits: the shorter contexts among them would otherwise be the
-    // vector kernel's, which keeps probabilities in fp32.
+    // Wide passes carry queries and probabilities in three terms, all 24 bits: the shorter contexts among them would
+    // otherwise be the vector kernel's, which keeps probabilities in fp32, and queries too with heads of 64 elements or
+    // one or two query heads per KV head.  Median error of a row against 64 bits, one layer, 2048 wide, heads of 64: 6.8e-6
+    // with two-term queries, 6.1e-6 with three, 6.1e-6 in passes of 16 columns; 8B shape, 32 layers, 16 x 16 tokens at
+    // contexts 512 .. 1067: 4.7e-5, 4.2e-5 and 4.8e-5.  The third query term costs nothing measurable (that call 9935 and 9939 us).
     bf16x8 ph[2], pl[2], pr[2];
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
@@ -818,18 +826,7 @@ __global__ __launch_bounds__(64 * NW, NW == 1 ? 1 : 2) void attn_mfma_kernel(Att
         l_run += pv[j];
       }
       split_bf16x8(pv, ph[h], pl[h]);
-      if constexpr (Src::kWide) {
-        float rest[8], hi[8], lo[8];
-        unpack<bf16_t>(__builtin_bit_cast(u32x4, ph[h]), hi);
-        unpack<bf16_t>(__builtin_bit_cast(u32x4, pl[h]), lo);
-#pragma unroll
-        for (int j = 0; j < 8; ++j) rest[j] = (pv[j] - hi[j]) - lo[j];
-        uint32_t r4[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) r4[j] = pack_bf16x2(rest[2 * j], rest[2 * j + 1]);
-        const u32x4 rv = {r4[0], r4[1], r4[2], r4[3]};
-        pr[h] = __builtin_bit_cast(bf16x8, rv);
-      }
+      if constexpr (Src::kWide) pr[h] = third_bf16x8(pv, ph[h], pl[h]);
     }
     // A operands: V^T row e = et*16 + lane%16, the 8 slots q4*16 + h*8 + j, by the LDS transposing
     // read (ds_read_b64_tr_b16): in a group of 16 lanes, lane i offers the 8 bytes at its address

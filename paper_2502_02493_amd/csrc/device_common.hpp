@@ -92,6 +92,18 @@ __device__ __forceinline__ void split_bf16x8(const float (&x)[8], bf16x8& hi, bf
   lo = __builtin_bit_cast(bf16x8, lv);
 }
 
+// ... and what those two terms leave of x, as a third: with it all 24 bits
+__device__ __forceinline__ bf16x8 third_bf16x8(const float (&x)[8], bf16x8 hi, bf16x8 lo) {
+  const u32x4 hv = __builtin_bit_cast(u32x4, hi), lv = __builtin_bit_cast(u32x4, lo);
+  uint32_t r[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j)
+    r[j] = pack_bf16x2((x[2 * j] - __uint_as_float(hv[j] << 16)) - __uint_as_float(lv[j] << 16),
+                       (x[2 * j + 1] - __uint_as_float(hv[j] & 0xFFFF0000u)) - __uint_as_float(lv[j] & 0xFFFF0000u));
+  const u32x4 rv = {r[0], r[1], r[2], r[3]};
+  return __builtin_bit_cast(bf16x8, rv);
+}
+
 template <typename T>
 __device__ __forceinline__ float load1(const T* p);
 template <>

@@ -595,7 +595,7 @@ __global__ __launch_bounds__(512) void attn_kernel(AttnArgs a, Cols c, ChunkMap 
 // heads of up to 16 NW / G columns of one sequence (the tokens of a calibration, the nodes of a tree
 // level) — are the columns of NW MFMA tiles of 16, one tile per wave of the workgroup, so K and V
 // are read once per group of columns and the per-slot arithmetic leaves the vector ALUs:
-//   S^T[slot][row]  = K[slot][:] . Q[row][:]      A = K (rows = slots), B = Q^T, two-term bf16 q (wide passes: three)
+//   S^T[slot][row]  = K[slot][:] . Q[row][:]      A = K (rows = slots), B = Q^T, two-term bf16 q (queries_in_fp32: three)
 //   O^T[e][row]    += V^T[e][slot] P^T[slot][row]  A = V^T, B = P^T, two-term bf16 p (wide passes: three)
 // A workgroup walks its chunk of the context in super tiles of 64 slots: its waves load the K and V
 // rows of a tile together (coalesced) and put them into LDS (XOR-swizzled 16-byte pieces; V is read
@@ -625,6 +625,7 @@ struct PassCols {
   Cols c;
   ColGroups cg;
   static constexpr bool kWide = false;
+  static constexpr int kQueryTerms = 2;
   __device__ __forceinline__ int n_groups() const { return cg.n; }
   __device__ __forceinline__ void group(int i, int& first, int& cnt, int& seq) const {
     first = cg.first[i];
@@ -632,12 +633,14 @@ struct PassCols {
     seq = c.seq[first];
   }
 };
+template <int QT>
 struct SpanCols {
   Spans sp;
   int32_t n;                       // groups
   int32_t first_group[kWideSeqs];  // first group of entry e (INT_MAX: no such entry)
   int32_t most;                    // columns of a full group
   static constexpr bool kWide = true;
+  static constexpr int kQueryTerms = QT;  // bf16 terms of a query: two or three (queries_in_fp32)
   __device__ __forceinline__ int n_groups() const { return n; }
 };
 typedef short v4i16 __attribute__((ext_vector_type(4)));
@@ -723,8 +726,9 @@ __global__ __launch_bounds__(64 * NW, NW == 1 ? 1 : 2) void attn_mfma_kernel(Att
   };
   request(ws0);
 
-  // B operands of S^T: this row's query, hi and lo bf16 terms, k-group q4 of every k-tile; wide passes: a third term
-  bf16x8 qh[KT], ql[KT], qr[Src::kWide ? KT : 1];
+  // B operands of S^T: this row's query, hi and lo bf16 terms, k-group q4 of every k-tile; a third term where asked for
+  constexpr bool Q3 = Src::kQueryTerms == 3;
+  bf16x8 qh[KT], ql[KT], qr[Q3 ? KT : 1];
   {
     const float* qp = a.Q + ((size_t)li * kMaxCols + col) * HQ + (kvh * G + g) * HD + q4 * 8;
 #pragma unroll
@@ -733,7 +737,7 @@ __global__ __launch_bounds__(64 * NW, NW == 1 ? 1 : 2) void attn_mfma_kernel(Att
 #pragma unroll
       for (int e = 0; e < 8; ++e) x[e] = row_ok ? qp[kt * 32 + e] : 0.f;
       split_bf16x8(x, qh[kt], ql[kt]);
-      if constexpr (Src::kWide) qr[kt] = third_bf16x8(x, qh[kt], ql[kt]);
+      if constexpr (Q3) qr[kt] = third_bf16x8(x, qh[kt], ql[kt]);
     }
   }
 
@@ -775,7 +779,7 @@ __global__ __launch_bounds__(64 * NW, NW == 1 ? 1 : 2) void attn_mfma_kernel(Att
       for (int t = 0; t < 4; ++t) st[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, ka[t]), qh[kt], st[t], 0, 0, 0);
 #pragma unroll
       for (int t = 0; t < 4; ++t) st[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, ka[t]), ql[kt], st[t], 0, 0, 0);
-      if constexpr (Src::kWide) {
+      if constexpr (Q3) {
 #pragma unroll
         for (int t = 0; t < 4; ++t) st[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, ka[t]), qr[kt], st[t], 0, 0, 0);
       }
@@ -811,11 +815,8 @@ __global__ __launch_bounds__(64 * NW, NW == 1 ? 1 : 2) void attn_mfma_kernel(Att
       for (int et = 0; et < ET; ++et) o[et] *= alpha;
     }
     // B operands of P.V: MFMA number h takes slots q4*16 + h*8 .. +8 of this lane = tiles 2h, 2h+1
-    // Wide passes carry queries and probabilities in three terms, all 24 bits: the shorter contexts among them would
-    // otherwise be the vector kernel's, which keeps probabilities in fp32, and queries too with heads of 64 elements or
-    // one or two query heads per KV head.  Median error of a row against 64 bits, one layer, 2048 wide, heads of 64: 6.8e-6
-    // with two-term queries, 6.1e-6 with three, 6.1e-6 in passes of 16 columns; 8B shape, 32 layers, 16 x 16 tokens at
-    // contexts 512 .. 1067: 4.7e-5, 4.2e-5 and 4.8e-5.  The third query term costs nothing measurable (that call 9935 and 9939 us).
+    // Wide passes carry probabilities in three terms, all 24 bits: the shorter contexts among them would otherwise be the
+    // vector kernel's, which keeps probabilities in fp32.
     bf16x8 ph[2], pl[2], pr[2];
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
@@ -1196,8 +1197,31 @@ void launch_attn(const Shape& s, const Buffers& b, const Cols& c, int layer0, in
   }
 }
 
+// Would the vector kernel, with queries in fp32, take any of the passes of at most kMaxCols columns that a wide pass stands
+// for?  (It holds them in fp32 with heads of 64 elements, or with one or two query heads per KV head.)  Then the wide launch takes
+// queries in three bf16 terms, all 24 bits; otherwise in two, as those passes do.  Median error of a row against 64
+// bits, one layer, 2048 wide, heads of 64: 6.8e-6 with two terms, 6.1e-6 with three and in passes of 16 columns.  8B shape
+// (two terms on either route), 32 layers, 16 x 16 tokens at contexts 512 .. 1067, 32 draws: 6.4e-5 wide, 6.5e-5 in passes
+// of 16 columns.  Where it is not needed the third term is not free: 9810 and 9890 us for that call, 5280 and 5330 us
+// for 4 x 6 tokens at contexts 4096 .. 32768.
+static bool queries_in_fp32(const Shape& s, const Spans& sp) {
+  if (s.hd == 128 && s.Hq / s.Hkv >= 4) return false;
+  Cols c;
+  c.n = 0;
+  for (int e = 0; e < sp.n_seq; ++e) {
+    const int n = sp.first[e + 1] - sp.first[e];
+    if (c.n + n > kMaxCols) {
+      if (!attn_use_mfma(s, c, 1)) return true;
+      c.n = 0;
+    }
+    for (int i = 0; i < n; ++i, ++c.n) c.seq[c.n] = sp.seq[e], c.pos[c.n] = sp.pos0[e] + i;
+  }
+  return !attn_use_mfma(s, c, 1);
+}
+
 // Attention of a wide pass: always the matrix-core kernel, one launch for the columns of every sequence.
-void launch_wide_attn(const Shape& s, const Buffers& b, const WideBuffers& w, const Spans& sp, int layer, hipStream_t st) {
+template <int QT>
+static void launch_wide_attn_terms(const Shape& s, const Buffers& b, const WideBuffers& w, const Spans& sp, int layer, hipStream_t st) {
   const int G = s.Hq / s.Hkv;
   int longest = 1, max_len = 1;
   for (int e = 0; e < sp.n_seq; ++e) {
@@ -1206,7 +1230,7 @@ void launch_wide_attn(const Shape& s, const Buffers& b, const WideBuffers& w, co
     max_len = std::max(max_len, sp.pos0[e] + n);
   }
   const int want = (longest * G + 15) / 16, tiles = want <= 2 ? want : 4;
-  SpanCols src;
+  SpanCols<QT> src;
   src.sp = sp;
   src.most = std::max(1, 16 * tiles / G);
   src.n = 0;
@@ -1239,13 +1263,18 @@ void launch_wide_attn(const Shape& s, const Buffers& b, const WideBuffers& w, co
   const dim3 grid(a.nch_ref, s.Hkv, src.n), blk(64 * tiles);
   auto go = [&](auto hd) {
     constexpr int HD = decltype(hd)::value;
-    if (tiles == 4) ES_LAUNCH((attn_mfma_kernel<HD, false, 4, SpanCols>), grid, blk, 0, st, a, src, G);
-    else if (tiles == 2) ES_LAUNCH((attn_mfma_kernel<HD, false, 2, SpanCols>), grid, blk, 0, st, a, src, G);
-    else ES_LAUNCH((attn_mfma_kernel<HD, false, 1, SpanCols>), grid, blk, 0, st, a, src, G);
+    if (tiles == 4) ES_LAUNCH((attn_mfma_kernel<HD, false, 4, SpanCols<QT>>), grid, blk, 0, st, a, src, G);
+    else if (tiles == 2) ES_LAUNCH((attn_mfma_kernel<HD, false, 2, SpanCols<QT>>), grid, blk, 0, st, a, src, G);
+    else ES_LAUNCH((attn_mfma_kernel<HD, false, 1, SpanCols<QT>>), grid, blk, 0, st, a, src, G);
     if (a.nch_ref > 1) ES_LAUNCH((attn_merge_kernel<bf16_t, HD, Spans>), dim3(sp.n, s.Hq), dim3(HD), 0, st, a, sp);
   };
   if (s.hd == 128) go(std::integral_constant<int, 128>{});
   else go(std::integral_constant<int, 64>{});
+}
+
+void launch_wide_attn(const Shape& s, const Buffers& b, const WideBuffers& w, const Spans& sp, int layer, hipStream_t st) {
+  if (queries_in_fp32(s, sp)) launch_wide_attn_terms<3>(s, b, w, sp, layer, st);
+  else launch_wide_attn_terms<2>(s, b, w, sp, layer, st);
 }
 
 }  // namespace es

@@ -104,6 +104,21 @@ __device__ __forceinline__ bf16x8 third_bf16x8(const float (&x)[8], bf16x8 hi, b
   return __builtin_bit_cast(bf16x8, rv);
 }
 
+// Is any of eight packed bf16 infinite or NaN (all exponent bits set: adding one to the exponent carries into the sign)?
+__device__ __forceinline__ bool any_nonfinite(u32x4 v) {
+  uint32_t carry = 0;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) carry |= (v[i] & 0x7F807F80u) + 0x00800080u;
+  return (carry & 0x80008000u) != 0;
+}
+// ... and the same with those that are cleared
+__device__ __forceinline__ u32x4 clear_nonfinite(u32x4 v) {
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+    v[i] &= ((v[i] & 0x7F80u) == 0x7F80u ? 0xFFFF0000u : 0xFFFFFFFFu) & ((v[i] & 0x7F800000u) == 0x7F800000u ? 0x0000FFFFu : 0xFFFFFFFFu);
+  return v;
+}
+
 template <typename T>
 __device__ __forceinline__ float load1(const T* p);
 template <>

@@ -19,8 +19,9 @@
 //   (3) accept_draw_kernel     one workgroup per sequence: running sum over the chunk sums in
 //                              index order, then inside the chunk the draw lands in.
 // Bound by fp64 latency and three dependent launches, not by the 5.6 MB of logits.  gamma 5, vocabulary 128 256:
-// stats 25.1 -> 9.3 us (256 threads reading a slice twice, an fp64 division per exponential), weights 23.6 -> 5.7 (one
-// thread took all decisions), draw 7.2 -> 6.1; the whole call 57.7 -> 23.1 us.
+// stats 25.1 -> 9.7 us (256 threads reading a slice twice, an fp64 division per exponential; 9.3 with a product by 1 / T
+// and sums against each thread's own maximum, which round once more), weights 23.6 -> 5.7 (one
+// thread took all decisions), draw 7.2 -> 6.1; the whole call 57 -> 21.5 us.
 #include "kernels.h"
 
 #include <mutex>
@@ -79,6 +80,13 @@ __device__ __forceinline__ AcceptWs accept_ws(double* base, int b, int gamma, in
   return w;
 }
 
+// x / T as the division rounds it, without one: y = 1 / T rounded to nearest, q = x y, then one step q + (x - q T) y with
+// fused multiply-adds (Markstein 1990: correctly rounded if y is).  Infinities and NaNs keep the product.
+__device__ __forceinline__ double quotient(double x, double T, double y) {
+  const double q = x * y;
+  return fabs(q) < INFINITY ? fma(fma(-q, T, x), y, q) : q;
+}
+
 // rows 0..gamma are the target's, rows gamma+1..2*gamma the draft's.  grid (kStatSlices, rows, batch)
 __global__ __launch_bounds__(kAcceptThreads) void accept_stats_kernel(const float* __restrict__ draft_logits,
                                                                        const float* __restrict__ target_logits, int gamma, int V,
@@ -90,32 +98,35 @@ __global__ __launch_bounds__(kAcceptThreads) void accept_stats_kernel(const floa
                                 : draft_logits + ((size_t)b * gamma + (j - gamma - 1)) * V;
   const int per = (V + kStatSlices - 1) / kStatSlices;
   const int v0 = min(V, slice * per), v1 = min(V, v0 + per);
-  const double inv_T = 1.0 / T;
-  float mx = -INFINITY;  // of this thread's logits
-  double z = 0.0;        // sum exp((l - mx) / T) over them
-  for (int base = v0; base < v1; base += kStatRegs * kAcceptThreads) {
-    float l[kStatRegs];
-    float m = mx;
+  const bool held = v1 - v0 <= kStatRegs * kAcceptThreads;  // uniform: the slice stays in registers between the two passes over it
+  float l[kStatRegs];
+  auto load = [&](int base) {
 #pragma unroll
     for (int i = 0; i < kStatRegs; ++i) {
       const int v = base + i * kAcceptThreads + threadIdx.x;
       l[i] = v < v1 ? row[v] : -INFINITY;
     }
+  };
+  float mx = -INFINITY;
+  for (int base = v0; base < v1; base += kStatRegs * kAcceptThreads) {
+    load(base);
 #pragma unroll
-    for (int i = 0; i < kStatRegs; ++i) m = fmaxf(m, l[i]);
-    const double ref = m == -INFINITY ? 0.0 : (double)m;  // only minus infinities so far: they add exp(-inf) = 0
-    if (base > v0) z *= exp(((double)mx - ref) * inv_T);
+    for (int i = 0; i < kStatRegs; ++i) mx = fmaxf(mx, l[i]);
+  }
+  mx = block_max(mx, sh_f);
+  const double ref = mx == -INFINITY ? 0.0 : (double)mx;  // nothing but minus infinities: they add exp(-inf) = 0
+  const double inv_T = 1.0 / T;
+  double z = 0.0;
+  for (int base = v0; base < v1; base += kStatRegs * kAcceptThreads) {
+    if (!held) load(base);
 #pragma unroll
     for (int i = 0; i < kStatRegs; ++i)
-      if (base + i * kAcceptThreads < v1) z += exp(((double)l[i] - ref) * inv_T);  // uniform; slots past the end add 0
-    mx = m;
+      if (base + i * kAcceptThreads < v1) z += exp(quotient((double)l[i] - ref, T, inv_T));  // uniform; slots past the end add 0
   }
-  const float all = block_max(mx, sh_f);
-  if (mx != all) z *= exp(((double)mx - (all == -INFINITY ? 0.0 : (double)all)) * inv_T);
   z = block_sum(z, sh_d);
   if (threadIdx.x == 0) {
     double* o = accept_ws(ws, b, gamma, V).stats + ((size_t)j * kStatSlices + slice) * 2;
-    o[0] = (double)all;  // -inf for an empty slice; its sum is 0
+    o[0] = (double)mx;  // -inf for an empty slice; its sum is 0
     o[1] = z;
   }
 }

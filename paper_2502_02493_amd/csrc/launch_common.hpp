@@ -23,14 +23,19 @@ static inline int cu_count() {
 
 // Waves per workgroup (they split K) of a launch of `grid` workgroups whose waves stream RT row tiles side by side.
 // `dflt` is the value measured best at the 8B shape for that operation; a wave always keeps at least eight k-tiles,
-// except where the launch fills less than half of the CUs (small models, where nothing hides a wave's latencies):
-// there as many waves as leave each a single batch of loads, within most_waves.  448-wide fp32 model: QKV (28 k-tiles)
-// with 2 waves, four batches one after the other, 8.9 us a launch, with 7 waves 6.5; gate/up 8.4 -> 6.1; down
-// (74 k-tiles) with 8 waves 6.9, with 10 waves 6.4; an iteration of four forwards 713 -> 595 us (with the vector attention's
-// last two units taken in one step: 6.9 -> 6.5 us a launch).  EASYSPEC_NW_* overrides for sweeps.
+// except where the launch fills less than half of the CUs (small models, where nothing hides a wave's latencies) and
+// kSmallWaves of them leave each a single batch of loads: there it is as many as that takes.  us a launch, before and
+// with that: 448-wide fp32 model QKV (28 k-tiles) 2 waves 9.3, 7 waves 7.2; gate/up 9.1 -> 6.8; down (74 k-tiles) 8
+// waves 7.9, 10 waves 7.3; 768-wide, QKV 4 waves 9.6, 12 waves 8.7; 1536-wide bf16, QKV 4 waves 8.3, 12 waves 7.7.
+// An iteration of four forwards of the 448-wide model 713 -> 595 us (with the vector attention's last two units taken in
+// one step: 6.9 -> 6.5 us a launch).  Sixteen waves are no better where they do and worse where they would need a second
+// batch: fp32 QKV of 1024-, 1280- and 1536-wide models 9.7, 12.9 and 12.7 us against 9.5, 11.3 and 11.3 with 8, down of
+// a 2048-wide one 25.3 against 23.8.  EASYSPEC_NW_* overrides for sweeps.
+constexpr int kSmallWaves = 12;
 static inline int pick_waves(int dflt, int nkt, int RT, int grid, int most_waves, const char* env) {
   const int forced = env_int(env, 0);
-  if (forced <= 0 && grid <= cu_count() / 2) return std::max(1, std::min(most_waves, ceil_div(nkt, batch_len(RT))));
+  const int one_batch = ceil_div(nkt, batch_len(RT));
+  if (forced <= 0 && grid <= cu_count() / 2 && one_batch <= std::min(kSmallWaves, most_waves)) return one_batch;
   int nw = forced > 0 ? forced : dflt;
   if (nw > 16) nw = 16;
   while (nw > 1 && nkt / nw < 8) nw /= 2;

@@ -188,10 +188,13 @@ extern "C" int easyspec_create(const easyspec_config* cfg, void* hip_stream, eas
     ALLOC_WORK(ctx, b.amax_val, kMaxCols * nblk * sizeof(float));
     ALLOC_WORK(ctx, b.amax_idx, kMaxCols * nblk * sizeof(int32_t));
     // A calibration of more columns than one pass holds runs its passes two at a time (the weight kernels serve
-    // both from one read of the weights): the second pass of a pair works in a workspace set of its own.
+    // both from one read of the weights): the second pass of a pair works in a workspace set of its own.  bf16 models
+    // run such a calibration as one wide pass and get that set only where pairs are asked for (tests).
+    const bool many = (long)s.B * cfg->max_calib_tokens > kMaxCols;
+    const char* pair_env = getenv("EASYSPEC_PAIR_PASSES");
     Buffers& b2 = ctx->b2;
     b2 = b;
-    ctx->has_b2 = (long)s.B * cfg->max_calib_tokens > kMaxCols;
+    ctx->has_b2 = many && (s.dtype != EASYSPEC_DTYPE_BF16 || (pair_env && atoi(pair_env) != 0));
     if (ctx->has_b2) {
       ALLOC_WORK(ctx, b2.H, (size_t)kMaxCols * s.d * sizeof(float));
       ALLOC_WORK(ctx, b2.ssp, (size_t)kMaxCols * (s.d / 16) * sizeof(float));
@@ -209,9 +212,8 @@ extern "C" int easyspec_create(const easyspec_config* cfg, void* hip_stream, eas
       ALLOC_WORK(ctx, b2.amax_idx, kMaxCols * nblk * sizeof(int32_t));
       b2.ssp_set = nullptr;  // full-layer mode never runs two passes together
     }
-    // bf16 models run such a calibration as one wide pass instead
     WideBuffers& w = ctx->w;
-    if (ctx->has_b2 && s.dtype == EASYSPEC_DTYPE_BF16) {
+    if (many && s.dtype == EASYSPEC_DTYPE_BF16) {
       w.cols = std::min((s.B * cfg->max_calib_tokens + 15) / 16 * 16, kWideCols);
       ALLOC_WORK(ctx, w.H, (size_t)w.cols * s.d * sizeof(float));
       ALLOC_WORK(ctx, w.rs, (size_t)w.cols * sizeof(float));
@@ -579,7 +581,7 @@ extern "C" int easyspec_calibrate(easyspec_ctx* ctx, const int32_t* tokens, cons
   Cols held;  // a pass waiting for a partner
   memset(&held, 0, sizeof held);
   bool holding = false;
-  const char* pair_env = getenv("EASYSPEC_PAIR_PASSES");  // tests: 0 = one pass at a time, 1 = pairs; read at every call
+  const char* pair_env = getenv("EASYSPEC_PAIR_PASSES");  // tests: 0 = one pass at a time, 1 = pairs (bf16: if set when the context was made); read at every call
   const bool pair_passes = !pair_env || atoi(pair_env) != 0;
   if (!pair_env && total > kMaxCols && total <= ctx->w.cols) {
     // bf16 models: all columns in one wide pass

@@ -61,6 +61,20 @@ int easyspec_attention_cut(const easyspec_config *cfg, const int32_t *ctx_lens, 
 int easyspec_weight_walk(const easyspec_config *cfg, int32_t op, int32_t n_cols, int32_t n_layers_in_set, int32_t full_layer,
                          int64_t *report);
 
+/* Host model of one matrix product (op: EASYSPEC_OP_QKV, _OPROJ, _GATEUP, _DOWN or _HEAD) of a wide pass (a calibration of
+ * more than 16 columns of a bf16 model) of n_cols columns, 17..256: how it is cut, and, evaluated with the kernel's own index
+ * functions for every workgroup, wave and stage, what it loads, multiplies and stores.  Host arithmetic only.  report (host,
+ * EASYSPEC_WIDE_FIELDS entries):
+ *   [0] row tiles and [1] column tiles per wave, [2] k-tiles per half stage, [3] column blocks, [4] row blocks,
+ *   [5] splits of K, [6] k-tiles per split, [7] grid, [8] 1 if there is a kernel for [0] and [1],
+ *   [9] highest weight piece read, [10] pieces of a matrix, [11] reads outside it,
+ *   [12] highest operand piece read, [13] pieces of the operand, [14] reads outside it,
+ *   [15] products (row tile, k-tile, column tile) of the launch, [16] never formed, [17] formed more than once,
+ *   [18] LDS fragments taken for another column or k-tile, [19] splits without a k-tile,
+ *   [20] highest partial sum stored, [21] partial sums there is room for (0: the product is not split). */
+#define EASYSPEC_WIDE_FIELDS 22
+int easyspec_wide_walk(const easyspec_config *cfg, int32_t op, int32_t n_cols, int64_t *report);
+
 /* Host model of how the vector attention kernel, where it takes its scores from the matrix cores (bf16
  * caches, head_dim 128, 4 to 8 query heads per KV head), passes a batch of n_loads x 4 K rows (n_loads = 2:
  * a short step, 8: a full batch) through a wave's LDS into MFMA A fragments, evaluated with the kernel's own

@@ -1031,6 +1031,23 @@ extern "C" int easyspec_weight_walk(const easyspec_config* cfg, int32_t op, int3
   return EASYSPEC_OK;
 }
 
+extern "C" int easyspec_wide_walk(const easyspec_config* cfg, int32_t op, int32_t n_cols, int64_t* report) {
+  const int rc = check_config(cfg);
+  if (rc != EASYSPEC_OK) return rc;
+  if (!report) return fail(nullptr, EASYSPEC_EINVAL, "wide_walk: NULL argument");
+  if (op != EASYSPEC_OP_QKV && op != EASYSPEC_OP_OPROJ && op != EASYSPEC_OP_GATEUP && op != EASYSPEC_OP_DOWN && op != EASYSPEC_OP_HEAD)
+    return fail(nullptr, EASYSPEC_EINVAL, "wide_walk: op %d is no matrix product", op);
+  if (cfg->dtype != EASYSPEC_DTYPE_BF16) return fail(nullptr, EASYSPEC_EINVAL, "wide_walk: only bf16 models have wide passes");
+  if (n_cols <= kMaxCols || n_cols > kWideCols) return fail(nullptr, EASYSPEC_EINVAL, "wide_walk: n_cols must be %d..%d", kMaxCols + 1, kWideCols);
+  Shape s;
+  shape_of(cfg, s);
+  WideWalk w;
+  wide_walk(s, op, n_cols, &w);
+  static_assert(sizeof w == EASYSPEC_WIDE_FIELDS * sizeof(int64_t), "the report lists every field in order");
+  memcpy(report, &w, sizeof w);
+  return EASYSPEC_OK;
+}
+
 extern "C" int64_t easyspec_step_bytes(const easyspec_ctx* ctx) {
   if (!ctx) return 0;
   const Shape& s = ctx->s;

@@ -130,6 +130,13 @@ struct StreamWalk {
   long long tiles, missed_tiles, repeated_tiles, reread_tiles, uncovered_pieces;
 };
 int stream_walk(const Shape& s, const StreamPlan& p, int ncols, StreamWalk* r);
+// ... and of a product of a wide pass of n_cols columns: its cut, and what its workgroups load, multiply and store.
+struct WideWalk {
+  long long RW, CT, KS, col_blocks, row_blocks, splits, per_split, grid, kernel;
+  long long w_max, w_pieces, w_out_of_range, x_max, x_pieces, x_out_of_range;
+  long long products, missed, repeated, misplaced, empty_splits, out_max, out_room;
+};
+int wide_walk(const Shape& s, int op, int n_cols, WideWalk* r);
 
 // Launch wrappers (all asynchronous on `st`).
 // Packed matrices: row tiles of R <= 16 rows (see repack_kernel).
@@ -183,8 +190,9 @@ void launch_down(const Shape& s, const Buffers& b, const Cols& c, int layer, int
                  void* xout2 = nullptr);
 void launch_head(const Shape& s, const Buffers& b, const Cols& c, float* logits_out, int32_t* tokens_out,
                  hipStream_t st, const Buffers* b2 = nullptr, const Cols* c2 = nullptr);
-// Wide passes.  Every matrix product but gate/up leaves fp32 partial sums per split of K; the *_finish launches add
-// them in split order and do what follows (bias, rotary, cache write; residual, norm operand).
+// Wide passes.  The QKV, O and down products leave fp32 partial sums per split of K, which the launch after each adds in
+// split order and does what follows (bias, rotary, cache write; residual, norm operand); gate/up and the head are not split
+// and write activations and logits themselves.
 size_t wide_operand_bytes(int cols, int K);
 size_t wide_partial_bytes(const Shape& s);
 void launch_wide_embed(const Shape& s, const Buffers& b, const WideBuffers& w, const Spans& sp, const int32_t* tokens, hipStream_t st);

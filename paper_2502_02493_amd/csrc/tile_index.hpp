@@ -104,6 +104,17 @@ ES_HD constexpr size_t wide_off(int K, int col, int k) {
 ES_HD constexpr size_t wide_tile(int t, int tiles, int R, int nkt) {
   return (size_t)(t < tiles ? t : tiles - 1) * row_tile_pieces(nkt, R);
 }
+// A workgroup's four row groups take `per_wave` row tiles of a matrix each, one group after the other.
+ES_HD constexpr int wide_row_tile(int row_block, int row_group, int per_wave) { return (row_block * 4 + row_group) * per_wave; }
+// A stage is 2 KS k-tiles, the first KS for the waves of half 0: k-tile ks of a half in the stage that begins at k-tile kt.
+ES_HD constexpr int wide_k_tile(int kt, int half, int ks, int KS) { return kt + half * KS + ks; }
+// First operand piece of (column tile, k-tile): 64 of the hi part, 64 of the lo part.
+ES_HD constexpr size_t wide_x_piece(int col_tile, int k, int nkt) { return ((size_t)col_tile * nkt + k) * 128; }
+// A stage's fragments in LDS: number f holds column tile f / (2 KS) and k-tile f % (2 KS) of the block and the stage; step st
+// (of KS CT) of a half multiplies with column tile st % CT and k-tile st / CT of the half's.
+ES_HD constexpr int wide_step_fragment(int st, int half, int CT, int KS) { return (st % CT) * (2 * KS) + half * KS + st / CT; }
+// k-tiles per half and stage: two where the registers hold three sets of weights for them.
+ES_HD constexpr int wide_stage_tiles(int CT) { return CT >= 6 ? 1 : 2; }
 // Workgroup id -> (column block, row block, split of K).  Workgroups go to the eight XCDs in turn: the column blocks of
 // a (row block, split) follow each other on one XCD (they read the same weights), and with eight splits an XCD reads
 // one split's operand only.  unit >= row blocks * splits: nothing to do.

@@ -31,6 +31,9 @@
 #include <math.h>
 #include <string.h>
 
+#include <algorithm>
+#include <vector>
+
 #include "../../include/easyspec_instrument.h"
 
 namespace es {
@@ -68,7 +71,7 @@ __global__ __launch_bounds__(kWideThreads) void wide_gemm_kernel(WideArgs a, Spa
   if (unit >= a.row_blocks * a.splits) return;
   const int rb = unit / a.splits, split = unit % a.splits;
   const int k0 = split * a.per_split, k1 = min(a.nkt, k0 + a.per_split);
-  const int t0 = (rb * 4 + rg) * RU, ct0 = cb * CT;
+  const int t0 = wide_row_tile(rb, rg, RU), ct0 = cb * CT;
   // Addresses are a wave-uniform base plus one 32-bit lane offset each (scalar registers, not vector ones).
   const u32x4* wb[RW];
 #pragma unroll
@@ -90,7 +93,7 @@ __global__ __launch_bounds__(kWideThreads) void wide_gemm_kernel(WideArgs a, Spa
   auto load_w = [&](int kt, u32x4 (&d)[KS][RW]) {
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
-      const size_t at = (size_t)min(kt + half * KS + ks, k1 - 1) * w_stride;
+      const size_t at = (size_t)min(wide_k_tile(kt, half, ks, KS), k1 - 1) * w_stride;
 #pragma unroll
       for (int r = 0; r < RW; ++r) d[ks][r] = __builtin_nontemporal_load(wb[r] + at + w_lane);
     }
@@ -101,7 +104,7 @@ __global__ __launch_bounds__(kWideThreads) void wide_gemm_kernel(WideArgs a, Spa
 #pragma unroll
     for (int j = 0; j < NB; ++j) {
       const int f = j * (kWideThreads / 128) + (wave >> 1), ct = min(ct0 + f / SK, a.col_tiles - 1), k = min(kt + f % SK, k1 - 1);
-      xn[j] = (a.x + ((size_t)ct * a.nkt + k) * 128)[x_lane];
+      xn[j] = (a.x + wide_x_piece(ct, k, a.nkt))[x_lane];
     }
   };
   auto put = [&](int buf) {
@@ -115,10 +118,10 @@ __global__ __launch_bounds__(kWideThreads) void wide_gemm_kernel(WideArgs a, Spa
   // last read in the first of the two stages before, which every wave has left when any passes the barrier between.
   constexpr int STEPS = KS * CT, AHEAD = 1, MID = STEPS / 2;
   static_assert(3 * STEPS % (AHEAD + 1) == 0, "fragment registers return to their place after three stages");
-  const u32x4* const xl = xs + half * KS * 128 + lane;
+  const u32x4* const xl = xs + lane;
   u32x4 bh[AHEAD + 1], bl[AHEAD + 1];
   auto fetch = [&](int slot, int buf, int st) {
-    const u32x4* f = xl + buf * kStagePieces + ((st % CT) * SK + st / CT) * 128;
+    const u32x4* f = xl + buf * kStagePieces + wide_step_fragment(st, half, CT, KS) * 128;
     bh[slot] = f[0];
     bl[slot] = f[64];
   };
@@ -139,7 +142,7 @@ __global__ __launch_bounds__(kWideThreads) void wide_gemm_kernel(WideArgs a, Spa
       if (kt + SK > k1) {  // uniform; only the last stage
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks)
-          if (kt + half * KS + ks >= k1) {
+          if (wide_k_tile(kt, half, ks, KS) >= k1) {
 #pragma unroll
             for (int r = 0; r < RW; ++r) w[I][ks][r] = u32x4{0u, 0u, 0u, 0u};
           }
@@ -453,48 +456,123 @@ static WideCut wide_cut(int tiles, int nkt, int ct, bool pair, bool split_k) {
   return c;
 }
 
+// the (RW, CT) there are kernels for: every cut that wide_cut makes
+#define WIDE_KERNELS(X) X(2, 2) X(2, 3) X(2, 4) X(4, 3) X(4, 4) X(4, 5) X(4, 6) X(4, 8)
+
 template <bool PAIR>
 static void launch_wide_gemm_ct(const WideArgs& a, const Spans& sp, const WideCut& c, hipStream_t st) {
   const dim3 grid(wide_grid(a.row_blocks * a.splits, a.col_blocks)), blk(kWideThreads);
-  // k-tiles per half and stage: two where the registers hold three sets of weights for them
-  switch (c.RW * 10 + c.CT) {
-    case 22: ES_LAUNCH((wide_gemm_kernel<2, 2, 2, PAIR>), grid, blk, 0, st, a, sp); break;
-    case 23: ES_LAUNCH((wide_gemm_kernel<2, 3, 2, PAIR>), grid, blk, 0, st, a, sp); break;
-    case 24: ES_LAUNCH((wide_gemm_kernel<2, 4, 2, PAIR>), grid, blk, 0, st, a, sp); break;
-    case 43: ES_LAUNCH((wide_gemm_kernel<4, 3, 2, PAIR>), grid, blk, 0, st, a, sp); break;
-    case 44: ES_LAUNCH((wide_gemm_kernel<4, 4, 2, PAIR>), grid, blk, 0, st, a, sp); break;
-    case 45: ES_LAUNCH((wide_gemm_kernel<4, 5, 2, PAIR>), grid, blk, 0, st, a, sp); break;
-    case 46: ES_LAUNCH((wide_gemm_kernel<4, 6, 1, PAIR>), grid, blk, 0, st, a, sp); break;
-    default: ES_LAUNCH((wide_gemm_kernel<4, 8, 1, PAIR>), grid, blk, 0, st, a, sp); break;
+#define WIDE_CASE(RW, CT) \
+  case RW * 10 + CT: ES_LAUNCH((wide_gemm_kernel<RW, CT, wide_stage_tiles(CT), PAIR>), grid, blk, 0, st, a, sp); break;
+  switch (c.RW * 10 + c.CT) { WIDE_KERNELS(WIDE_CASE) }
+#undef WIDE_CASE
+}
+
+// What a wide product is of: rows of one matrix, rows per packed tile, K; two matrices side by side; partial sums per split.
+struct WideShape {
+  int rows, R, K;
+  bool pair, split_k;
+};
+static WideShape wide_shape(const Shape& s, int op) {
+  switch (op) {
+    case EASYSPEC_OP_QKV: return {s.RQKV / 2, s.R_qkv, s.d, true, true};
+    case EASYSPEC_OP_OPROJ: return {s.d, 16, s.HQ, false, true};
+    case EASYSPEC_OP_GATEUP: return {s.F, s.R_ffn, s.d, true, false};
+    case EASYSPEC_OP_DOWN: return {s.d, 16, s.F, false, true};
+    default: return {s.V, 16, s.d, false, false};  // EASYSPEC_OP_HEAD
   }
 }
 
 // Fills in the cut and launches; returns the number of splits.
-static int launch_wide_gemm(WideArgs a, const Spans& sp, bool pair, bool split_k, hipStream_t st) {
-  a.n = sp.n;
-  a.col_tiles = col_tiles_of(sp);
-  const WideCut c = wide_cut(a.tiles, a.nkt, a.col_tiles, pair, split_k);
-  a.col_blocks = c.col_blocks;
-  a.row_blocks = c.row_blocks;
-  a.splits = c.splits;
-  a.per_split = c.per_split;
-  if (pair) launch_wide_gemm_ct<true>(a, sp, c, st);
-  else launch_wide_gemm_ct<false>(a, sp, c, st);
-  return c.splits;
-}
-
-static WideArgs wide_args(const void* w0, const void* w1, int rows, int R, int K, const void* x, int epi) {
+static int launch_wide_gemm(const Shape& s, int op, const void* w0, const void* w1, const void* x, int epi, void* out, const float* rs,
+                            const Spans& sp, hipStream_t st) {
+  const WideShape w = wide_shape(s, op);
   WideArgs a;
   memset(&a, 0, sizeof a);
   a.w0 = (const u32x4*)w0;
   a.w1 = (const u32x4*)w1;
-  a.rows = rows;
-  a.R = R;
-  a.tiles = (rows + R - 1) / R;
-  a.nkt = K / 32;
+  a.rows = w.rows;
+  a.R = w.R;
+  a.tiles = ceil_div(w.rows, w.R);
+  a.nkt = w.K / 32;
   a.x = (const u32x4*)x;
   a.epi = epi;
-  return a;
+  if (epi == kEpiSilu) a.act = (bf16_t*)out;
+  else a.out = (float*)out;
+  a.rs = rs;
+  a.n = sp.n;
+  a.col_tiles = col_tiles_of(sp);
+  const WideCut c = wide_cut(a.tiles, a.nkt, a.col_tiles, w.pair, w.split_k);
+  a.col_blocks = c.col_blocks;
+  a.row_blocks = c.row_blocks;
+  a.splits = c.splits;
+  a.per_split = c.per_split;
+  if (w.pair) launch_wide_gemm_ct<true>(a, sp, c, st);
+  else launch_wide_gemm_ct<false>(a, sp, c, st);
+  return c.splits;
+}
+
+// Host model of one product: every workgroup, wave and stage computes, through the kernel's own index functions, the weight
+// and operand pieces it loads, the LDS fragments it multiplies and the partial sums it stores.
+int wide_walk(const Shape& s, int op, int n_cols, WideWalk* r) {
+  memset(r, 0, sizeof *r);
+  const WideShape w = wide_shape(s, op);
+  const int tiles = ceil_div(w.rows, w.R), nkt = w.K / 32, col_tiles = (n_cols + 15) / 16, n_mat = w.pair ? 2 : 1;
+  const WideCut c = wide_cut(tiles, nkt, col_tiles, w.pair, w.split_k);
+  const int KS = wide_stage_tiles(c.CT), per_wave = w.pair ? c.RW / 2 : c.RW, width = w.rows * n_mat;
+  r->RW = c.RW; r->CT = c.CT; r->KS = KS;
+  r->col_blocks = c.col_blocks; r->row_blocks = c.row_blocks; r->splits = c.splits; r->per_split = c.per_split;
+  r->grid = wide_grid(c.row_blocks * c.splits, c.col_blocks);
+  r->w_pieces = (long long)tiles * row_tile_pieces(nkt, w.R);
+  r->x_pieces = (long long)wide_x_piece(col_tiles, 0, nkt);
+  r->products = (long long)n_mat * tiles * nkt * col_tiles;
+  r->out_room = w.split_k ? (long long)(wide_partial_bytes(s) / sizeof(float)) : 0;
+#define WIDE_CASE(RW_, CT_) r->kernel |= c.RW == RW_ && c.CT == CT_;
+  WIDE_KERNELS(WIDE_CASE)
+#undef WIDE_CASE
+  int most_lane = 0;
+  for (int lane = 0; lane < 64; ++lane) most_lane = std::max(most_lane, (int)lane_piece(lane, w.R));
+  for (int half = 0; half < 2; ++half)
+    for (int st = 0; st < KS * c.CT; ++st) {
+      const int f = wide_step_fragment(st, half, c.CT, KS);
+      r->misplaced += f / (2 * KS) != st % c.CT || f % (2 * KS) != wide_k_tile(0, half, st / c.CT, KS);
+    }
+  std::vector<unsigned char> seen((size_t)r->products, 0);
+  for (int id = 0; id < r->grid; ++id) {
+    const int unit = wide_unit(id, c.col_blocks), ct0 = wide_col_block(id, c.col_blocks) * c.CT;
+    if (unit >= c.row_blocks * c.splits) continue;
+    const int rb = unit / c.splits, split = unit % c.splits, k0 = split * c.per_split, k1 = std::min(nkt, k0 + c.per_split);
+    if (k0 >= k1) ++r->empty_splits;
+    for (int rg = 0; rg < 4; ++rg)
+      for (int i = 0; i < c.RW; ++i) {
+        const int m = w.pair ? i & 1 : 0, t = wide_row_tile(rb, rg, per_wave) + (w.pair ? i / 2 : i);
+        const long long base = (long long)wide_tile(t, tiles, w.R, nkt);
+        for (int kt = k0; kt < k1; kt += 2 * KS)
+          for (int half = 0; half < 2; ++half)
+            for (int ks = 0; ks < KS; ++ks) {
+              const int k = wide_k_tile(kt, half, ks, KS), at = std::min(k, k1 - 1);
+              const long long piece = base + (long long)at * fragment_pieces(w.R) + most_lane;
+              r->w_max = std::max(r->w_max, piece);
+              r->w_out_of_range += piece - most_lane < 0 || piece >= r->w_pieces;
+              for (int ct = ct0; ct < ct0 + c.CT; ++ct) {
+                const long long x = (long long)wide_x_piece(std::min(ct, col_tiles - 1), at, nkt) + 127;
+                r->x_max = std::max(r->x_max, x);
+                r->x_out_of_range += x >= r->x_pieces;
+                if (k >= k1 || t >= tiles || ct >= col_tiles) continue;  // zeroed, a repeat of the last tile, not stored
+                unsigned char& n = seen[(((size_t)m * tiles + t) * nkt + k) * col_tiles + ct];
+                if (n < 255) ++n;
+              }
+            }
+        const int col = std::min((ct0 + c.CT) * 16, n_cols) - 1, row = std::min((t + 1) * w.R, w.rows) - 1;
+        if (w.split_k && t < tiles)
+          r->out_max = std::max(r->out_max, ((long long)split * (col_tiles * 16) + col) * width + (long long)m * w.rows + row);
+      }
+  }
+  for (unsigned char n : seen) {
+    r->missed += n == 0;
+    r->repeated += n > 1;
+  }
+  return 0;
 }
 
 void launch_wide_embed(const Shape& s, const Buffers& b, const WideBuffers& w, const Spans& sp, const int32_t* tokens, hipStream_t st) {
@@ -506,10 +584,8 @@ void launch_wide_qkv(const Shape& s, const Buffers& b, const WideBuffers& w, con
   const int n_pairs = s.RQKV / 2;
   const size_t half_pieces = tile_stride(n_pairs, s.d, s.dtype, s.R_qkv);
   const u32x4* wl = (const u32x4*)b.wqkv + (size_t)layer * 2 * half_pieces;
-  WideArgs a = wide_args(wl, wl + half_pieces, n_pairs, s.R_qkv, s.d, w.X, kEpiPartial);
-  a.out = w.P;
   WideQkvArgs q;
-  q.splits = launch_wide_gemm(a, sp, true, true, st);
+  q.splits = launch_wide_gemm(s, EASYSPEC_OP_QKV, wl, wl + half_pieces, w.X, kEpiPartial, w.P, nullptr, sp, st);
   q.P = w.P; q.rs = w.rs;
   q.bias = s.has_bias ? b.bqkv + (size_t)layer * s.RQKV : nullptr;
   q.rope = b.rope;
@@ -525,10 +601,8 @@ void launch_wide_proj(const Shape& s, const Buffers& b, const WideBuffers& w, co
                       bool last, hipStream_t st) {
   const int K = down ? s.F : s.HQ;
   const u32x4* wl = (const u32x4*)(down ? b.wd : b.wo) + (size_t)layer * tile_stride(s.d, K, s.dtype);
-  WideArgs a = wide_args(wl, nullptr, s.d, 16, K, down ? w.ACT : w.AO, kEpiPartial);
-  a.out = w.P;
   WideResidArgs r;
-  r.splits = launch_wide_gemm(a, sp, false, true, st);
+  r.splits = launch_wide_gemm(s, down ? EASYSPEC_OP_DOWN : EASYSPEC_OP_OPROJ, wl, nullptr, down ? w.ACT : w.AO, kEpiPartial, w.P, nullptr, sp, st);
   r.P = w.P; r.gain = gain; r.cols16 = col_tiles_of(sp) * 16; r.d = s.d; r.last = last ? 1 : 0;
   r.inv_d = 1.0f / (float)s.d; r.eps = s.eps;
   r.xh = (bf16_t*)b.XA;
@@ -538,18 +612,12 @@ void launch_wide_proj(const Shape& s, const Buffers& b, const WideBuffers& w, co
 
 void launch_wide_gateup(const Shape& s, const Buffers& b, const WideBuffers& w, const Spans& sp, int layer, hipStream_t st) {
   const size_t off = (size_t)layer * tile_stride(s.F, s.d, s.dtype, s.R_ffn);
-  WideArgs a = wide_args((const u32x4*)b.wg + off, (const u32x4*)b.wu + off, s.F, s.R_ffn, s.d, w.X, kEpiSilu);
-  a.act = (bf16_t*)w.ACT;
-  a.rs = w.rs;
-  launch_wide_gemm(a, sp, true, false, st);
+  launch_wide_gemm(s, EASYSPEC_OP_GATEUP, (const u32x4*)b.wg + off, (const u32x4*)b.wu + off, w.X, kEpiSilu, w.ACT, w.rs, sp, st);
 }
 
 void launch_wide_head(const Shape& s, const Buffers& b, const WideBuffers& w, const Spans& sp, float* logits, int32_t* tokens_out,
                       hipStream_t st) {
-  WideArgs a = wide_args(b.wlm, nullptr, s.V, 16, s.d, w.X, kEpiLogits);
-  a.out = logits;
-  a.rs = w.rs;
-  launch_wide_gemm(a, sp, false, false, st);
+  launch_wide_gemm(s, EASYSPEC_OP_HEAD, b.wlm, nullptr, w.X, kEpiLogits, logits, w.rs, sp, st);
   ES_LAUNCH(wide_argmax_kernel, dim3(sp.n_seq), dim3(1024), 0, st, logits, s.V, tokens_out, sp);
 }
 

@@ -2,7 +2,9 @@
 sequence by sequence, and against the same calibration run in passes of at most 16 columns (EASYSPEC_PAIR_PASSES=0;
 same precision, other summation order: the oracle tolerance).  Column counts at the edges of the column tiles (17, 32,
 33), of the column blocks (128, 129) and of the range (256); ragged token counts, idle sequences, fuzzy slots to drop,
-contexts of one and of several chunks; next tokens, logits of last rows and of all rows, caches, lengths, hidden rows."""
+contexts of one and of several chunks; next tokens, logits of last rows and of all rows, caches, lengths, hidden rows.
+Every kernel that a cut of a product can choose is run, and each case asserts the cuts it is there for: (row tiles per
+wave, column tiles, column blocks)."""
 import numpy as np
 import pytest
 
@@ -21,11 +23,14 @@ def gpu():
     return gpu_harness
 
 
-def run_case(oracle, gpu, monkeypatch, cfg, seed, ctxs, n_calib, max_calib, all_rows, check=None, fuzzy_first=1):
-    """check: the sequences compared with the oracle (default: all)."""
+def run_case(oracle, gpu, monkeypatch, cfg, seed, ctxs, n_calib, max_calib, all_rows, check=None, fuzzy_first=1, cuts=None):
+    """check: the sequences compared with the oracle (default: all).  cuts: what the products' cuts have to be."""
     import torch
     import paper_2502_02493_amd as es
     B = len(ctxs)
+    for op, want in (cuts or {}).items():
+        r = es.easyspec_wide_walk(es.make_config(cfg, B, 64, max_calib), getattr(es, "EASYSPEC_OP_" + op), sum(n_calib))
+        assert (r["row_tiles"], r["col_tiles"], r["col_blocks"]) == want, (op, r)
     w = synth.make_weights(cfg, seed)
     max_ctx = max(ctxs) + fuzzy_first + max_calib + 8
     toks = synth.make_tokens(seed + 1, B * (max_calib + fuzzy_first), cfg["vocab"]).reshape(B, -1)
@@ -87,32 +92,52 @@ def run_case(oracle, gpu, monkeypatch, cfg, seed, ctxs, n_calib, max_calib, all_
         assert gpu.rel_l2(vv, so.V[:, :, :so.precise]) < kv_tol
 
 
-@pytest.mark.parametrize("shape,n_calib,ctxs,all_rows", [
-    ("tiny", [16, 1], [40, 300], True),                                     # 17: the second column tile holds one column
-    ("tiny", [9, 0, 16, 7], [33, 5, 257, 64], False),                       # 32, one sequence idle
-    ("tiny_qwen", [11, 11, 11], [9, 320, 63], True),                        # 33: three tiles; biases, 7 heads per KV head
-    ("tiny_qwen", [16, 5, 16, 16, 3], [100, 2, 258, 31, 64], False),        # 56
-    ("tiny", [16, 15, 14, 13, 12, 11], [20, 70, 257, 3, 129, 64], True),    # 81: six tiles, four row tiles per wave
+@pytest.mark.parametrize("shape,n_calib,ctxs,all_rows,cut", [
+    ("tiny", [16, 1], [40, 300], True, (2, 2, 1)),                                     # 17: the second column tile holds one column
+    ("tiny", [9, 0, 16, 7], [33, 5, 257, 64], False, (2, 2, 1)),                       # 32, one sequence idle
+    ("tiny_qwen", [11, 11, 11], [9, 320, 63], True, (2, 3, 1)),                        # 33: three tiles; biases, 7 heads per KV head
+    ("tiny_qwen", [16, 5, 16, 16, 3], [100, 2, 258, 31, 64], False, (2, 4, 1)),        # 56
+    ("tiny", [16, 15, 14, 13, 12, 11], [20, 70, 257, 3, 129, 64], True, (4, 3, 2)),    # 81: six tiles in two blocks, four row tiles per wave
 ])
-def test_small_models(oracle, gpu, monkeypatch, shape, n_calib, ctxs, all_rows):
-    run_case(oracle, gpu, monkeypatch, synth.model_shape(shape, dtype="bf16"), 1300 + sum(n_calib), ctxs, n_calib, 16, all_rows)
+def test_small_models(oracle, gpu, monkeypatch, shape, n_calib, ctxs, all_rows, cut):
+    run_case(oracle, gpu, monkeypatch, synth.model_shape(shape, dtype="bf16"), 1300 + sum(n_calib), ctxs, n_calib, 16, all_rows,
+             cuts={op: cut for op in ("QKV", "OPROJ", "GATEUP", "DOWN", "HEAD")})
 
 
-@pytest.mark.parametrize("total", [112, 128, 129, 200, 256])
-def test_column_blocks(oracle, gpu, monkeypatch, total):
-    """Seven and eight column tiles in one block, then two blocks of five, seven and eight tiles (129 fills one column of
-    its ninth tile)."""
+@pytest.mark.parametrize("total,split,whole", [(112, (4, 4, 2), (4, 3, 3)), (128, (4, 4, 2), (4, 3, 3)), (129, (4, 5, 2), (4, 3, 3)),
+                                               (177, (4, 6, 2), (4, 3, 4)), (200, (4, 8, 2), (4, 4, 4)), (256, (4, 8, 2), (4, 4, 4))])
+def test_column_blocks(oracle, gpu, monkeypatch, total, split, whole):
+    """Products whose K may be split: two blocks of four, five (129 fills one column of the ninth tile), six and eight column
+    tiles; gate/up and the head of a small model: three and four blocks of three and four."""
     n = [16] * (total // 16) + ([total % 16] if total % 16 else [])
     ctxs = [(37 * i) % 290 + 1 for i in range(len(n))]
     run_case(oracle, gpu, monkeypatch, synth.model_shape("tiny", dtype="bf16"), 1400 + total, ctxs, n, 16, total == 129,
-             check=[0, len(n) // 2, len(n) - 1])
+             check=[0, len(n) // 2, len(n) - 1], cuts=dict(QKV=split, OPROJ=split, DOWN=split, GATEUP=whole, HEAD=whole))
 
 
-@pytest.mark.parametrize("n_calib", [[6, 6, 6, 6], [16, 16, 3, 16, 16]])
-def test_8b_layer_shape(oracle, gpu, monkeypatch, n_calib):
-    """The 8B layer shape (packed tiles of 14 and 12 rows, split K) at 3 layers."""
-    cfg = synth.model_shape("llama3_8b", n_layers=3, vocab=4096)
-    run_case(oracle, gpu, monkeypatch, cfg, 1500 + sum(n_calib), [300, 40, 700, 129, 8][:len(n_calib)], n_calib, 16, False, check=[0, 2])
+@pytest.mark.parametrize("n_seq,cut", [(5, (4, 5, 1)), (6, (4, 6, 1)), (8, (4, 8, 1))])
+def test_head_of_all_rows_in_one_block(oracle, gpu, monkeypatch, n_seq, cut):
+    """A vocabulary whose row blocks fill the CUs: the logits of every column from one block of five, six and eight tiles."""
+    ctxs = [(53 * i) % 280 + 1 for i in range(n_seq)]
+    run_case(oracle, gpu, monkeypatch, synth.model_shape("tiny", dtype="bf16", vocab=65536), 1700 + n_seq, ctxs, [16] * n_seq, 16, True,
+             check=[0, n_seq - 1], cuts=dict(HEAD=cut))
+
+
+@pytest.mark.parametrize("n_calib,layers,cut", [([6, 6, 6, 6], 3, (2, 2, 1)), ([16, 16, 3, 16, 16], 3, (4, 3, 2)), ([16] * 16, 5, (4, 8, 2))])
+def test_8b_layer_shape(oracle, gpu, monkeypatch, n_calib, layers, cut):
+    """The 8B layer shape (packed tiles of 14 and 12 rows, split K): 24, 67 and 256 columns."""
+    cfg = synth.model_shape("llama3_8b", n_layers=layers, vocab=4096)
+    ctxs = ([300, 40, 700, 129, 8] + [90 + 41 * i for i in range(11)])[:len(n_calib)]
+    run_case(oracle, gpu, monkeypatch, cfg, 1500 + sum(n_calib), ctxs, n_calib, 16, False, check=[0, 2], cuts=dict(GATEUP=cut))
+
+
+@pytest.mark.parametrize("n_seq,cut", [(5, (4, 5, 1)), (6, (4, 6, 1)), (16, (4, 6, 3))])
+def test_qwen2_7b_layer_shape(oracle, gpu, monkeypatch, n_seq, cut):
+    """The Qwen2-7B layer shape (biases, 7 heads of 128 elements per KV head, 18 944 rows of gate and up) at 3 layers:
+    80, 96 and 256 columns."""
+    cfg = synth.model_shape("qwen2_7b", n_layers=3, vocab=4096)
+    ctxs = [(211 * i) % 700 + 20 for i in range(n_seq)]
+    run_case(oracle, gpu, monkeypatch, cfg, 1750 + n_seq, ctxs, [16] * n_seq, 16, False, check=[0, 3], cuts=dict(GATEUP=cut))
 
 
 def test_head_dim_128_one_head_per_kv(oracle, gpu, monkeypatch):

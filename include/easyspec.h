@@ -179,8 +179,10 @@ int easyspec_draft_tree_step(easyspec_ctx *ctx, const int32_t *tokens_in, const 
  * Up to 16 tokens in all are one forward pass of 16 token columns.  More tokens: a bf16 model runs them as one wide
  * pass, every weight matrix read once; an fp32 model packs the sequences in index order into passes of 16 columns, a
  * sequence's tokens staying together, and two consecutive passes of equal column counts run together, each weight
- * matrix being read once for both.  The results do not depend on the packing
- * beyond the last bits of fp32 arithmetic. */
+ * matrix being read once for both.  The results depend on the packing by the order of fp32 sums only: the last bits in
+ * an fp32 model.  In a bf16 model a last bit can round a cache entry to the neighbouring bf16 value, which the layers
+ * that follow carry on, so a sequence's logits and cache can differ by such roundings with how many tokens the other
+ * sequences bring (8B shape: a few 1e-4 in relative 2-norm, as far as either is from a 64-bit evaluation). */
 int easyspec_calibrate(easyspec_ctx *ctx, const int32_t *tokens, const int32_t *n_tokens,
                        int32_t *next_token_out, float *logits_out, int32_t logits_rows);
 

@@ -609,9 +609,10 @@ __global__ __launch_bounds__(512) void attn_kernel(AttnArgs a, Cols c, ChunkMap 
 // Sharing the tile between the waves reads K and V once for up to 64 query rows and leaves a wave
 // few enough registers (its share of the tile instead of all of it) that two or more run on a SIMD.
 // Before (every wave alone with up to 16 query rows and a tile of its own, one wave per SIMD) and now: prefill of
-// 16 tokens at context 8192 4495 -> 4143 us, calibration of 4 x 6 tokens at contexts 4096 .. 32768 7353 -> 6570 us,
-// tree levels of 4 and 12 nodes at context 2048 6092 -> 5946 us together.  Two row tiles per wave instead (one
-// chain for 32 rows): 4553, 7875 and 6171 us; the registers of a private 64-slot tile leave one wave per SIMD.
+// 16 tokens at context 8192 4482 -> 4098 us; tree levels of 4 and 12 nodes at context 2048 6089 -> 5970 us together on one
+// box, 6075 -> 6018 on another.  (4 x 6 tokens at contexts 4096 .. 32768 as two passes of 12 columns, which they no
+// longer run as: 7353 -> 6570 us.)  Two row tiles per wave instead (one chain for 32 rows): 4553 us for the prefill, 6171 for
+// the levels; the registers of a private 64-slot tile leave one wave per SIMD.
 // grid = (chunks, Hkv, k * groups), block = 64 * NW.
 // ------------------------------------------------------------------------------------------
 struct ColGroups {
@@ -1013,7 +1014,7 @@ static void launch_attn_g(int G, dim3 grid, int nwv, hipStream_t st, AttnArgs a,
 
 // Matrix-core attention or the vector-ALU kernel?  The MFMA kernel reads K and V once per group
 // of columns of a sequence and does the per-slot arithmetic on the matrix cores, but its
-// per-wave chain (LDS transposes between the two products) is longer; measured, it wins once a
+// per-wave chain (LDS transposes between the two products) is longer; it wins once a
 // launch holds several columns of a sequence and enough (column, layer, slot) work: tree levels,
 // long calibrations.  Single columns (plain draft steps) and short 1-layer launches stay on the
 // vector kernel.  EASYSPEC_ATTN_MFMA = 0 / 2 forces never / always (bf16 only).
@@ -1028,9 +1029,13 @@ static bool attn_use_mfma(const Shape& s, const Cols& c, int n_set) {
     shared = shared || (i > 0 && c.seq[i] == c.seq[i - 1]);
     max_len = std::max(max_len, c.pos[i] + 1);
   }
-  // a launch over one layer with fewer than 5 columns keeps too few waves busy on the matrix cores (the
-  // partial buffers cap the sub-chunks at kMaxChunks): 4-token calibration at context 8192, 3778 us
-  // against 3699 us with the vector kernel; with 5 tokens 3830 against 3872 us, with 6 3834 against 3999 us
+  // Where the line was drawn (30 000 units, five columns in a single layer) was measured with a kernel whose waves had a tile
+  // each, and has not been moved since they share one.  With this kernel, 8B shape, us a call on the vector and the
+  // matrix-core kernel: 4 / 6 / 8 / 12 tokens at context 2048 2990 / 3266 / 3349 / 3727 and 3044 / 3293 / 3391 / 3586;
+  // 3 / 4 / 5 / 6 tokens at 8192 3414 / 3435 / 3645 / 3735 and 3391 / 3412 / 3456 / 3474; 16 tokens at 512 3607 and 3671;
+  // two tree levels of 4 / 8 / 12 nodes at 2048 in sets of four layers 5488 / 5881 / 6586 and 5432 / 5610 / 6055.  The
+  // rule is right at these but for 12 tokens at 2048 (4 %) and 3 or 4 at 8192 (0.7 %); at the Qwen2-7B shape it is 2 %
+  // off for 4 and 6 tokens at context 4096 (3081 and 3226 us, matrix cores 3009 and 3147).
   return shared && (long)n_set * c.n * max_len >= min_work && (n_set > 1 || c.n >= 5);
 }
 

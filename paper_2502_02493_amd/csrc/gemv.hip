@@ -739,7 +739,8 @@ StreamPlan stream_plan(const Shape& s, int op, int ncols, int n_layers, bool ful
       p.units = (s.V + 15) / 16;
       p.mat_pieces = p.layer_pieces = tile_stride(s.V, s.d, s.dtype);
       p.n_layers = 1;
-      dflt_nw = 4;
+      // vocabularies that leave half of the CUs idle: more waves, as for one layer's QKV (2000 words, 4096 wide, fp32: 10.9 -> 9.5 us)
+      dflt_nw = p.units <= cu_count() / 2 ? 8 : 4;
       env = "EASYSPEC_NW_HEAD";
       break;
   }

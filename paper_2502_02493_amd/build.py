@@ -8,7 +8,7 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libeasyspec.so")
-SOURCES = ["easyspec.cpp", "gemv.hip", "attention.hip", "wide.hip", "util.hip", "accept.hip"]
+SOURCES = ["easyspec.cpp", "gemv.hip", "attention.hip", "wide.hip", "resident.hip", "util.hip", "accept.hip"]
 HEADERS = [os.path.join(CSRC, "kernels.h"), os.path.join(CSRC, "device_common.hpp"), os.path.join(CSRC, "launch_common.hpp"), os.path.join(CSRC, "tile_index.hpp"),
            os.path.join(HERE, "..", "include", "easyspec.h"), os.path.join(HERE, "..", "include", "easyspec_instrument.h")]
 

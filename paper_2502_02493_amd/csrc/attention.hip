@@ -72,25 +72,6 @@ __host__ __device__ __forceinline__ void wave_range(int s0, int s1, int unit, in
 constexpr int kAttnIT = 8;       // loads in flight per operand per lane
 constexpr int kAttnSmallIT = 2;  // the same for the short steps that finish a wave's share
 
-// Sum over aligned groups of N lanes (8, 16 or 32), every lane of a group receiving the total,
-// with data-parallel-primitive operand swizzles (lane^1 and lane^2 inside quads, then the
-// mirrored lane of the other half of 8 and of 16 lanes) instead of LDS permutes.  Same operand
-// pairs as an xor butterfly, hence the same bits.
-template <int CTRL>
-__device__ __forceinline__ float dpp_f32(float v) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xF, 0xF, true));
-}
-template <int N>
-__device__ __forceinline__ float group_sum(float v) {
-  static_assert(N == 8 || N == 16 || N == 32, "group size");
-  v += dpp_f32<0xB1>(v);   // quad_perm [1,0,3,2]
-  v += dpp_f32<0x4E>(v);   // quad_perm [2,3,0,1]
-  v += dpp_f32<0x141>(v);  // row_half_mirror
-  if (N >= 16) v += dpp_f32<0x140>(v);  // row_mirror
-  if (N >= 32) v += __shfl_xor(v, 16, 64);
-  return v;
-}
-
 template <typename T, int HD>
 struct AttnGeom {
   static constexpr int EPL = Tr<T>::EPL, LPS = HD / EPL, SPW = 64 / LPS;

@@ -9,6 +9,7 @@
 #include <stdio.h>
 #include <stdlib.h>
 #include <string.h>
+#include <unistd.h>
 
 #include <algorithm>
 #include <string>
@@ -26,6 +27,7 @@ struct easyspec_ctx {
   Buffers b2;      // a second set of per-pass workspaces (same weights and caches): the second of two passes run together
   bool has_b2;
   WideBuffers w;   // wide passes (bf16 models whose calibrations can exceed one pass); w.cols == 0: none
+  Resident r;      // small models: whole passes in one launch; r.ctl == null: separate launches
   const float* last_H;  // residual rows of the most recent pass
   hipStream_t stream;
   bool weights_loaded;
@@ -140,6 +142,7 @@ extern "C" int easyspec_create(const easyspec_config* cfg, void* hip_stream, eas
   ctx->last_H = nullptr;
   ctx->has_b2 = false;
   memset(&ctx->w, 0, sizeof ctx->w);
+  memset(&ctx->r, 0, sizeof ctx->r);
   ctx->prof_op = -1;
   ctx->timer = LaunchTimer{nullptr, nullptr, 0, 0, 0};
   ctx->parallel_mode = EASYSPEC_PARALLEL_ATTENTION;
@@ -223,6 +226,19 @@ extern "C" int easyspec_create(const easyspec_config* cfg, void* hip_stream, eas
       ALLOC_WORK(ctx, w.ACT, wide_operand_bytes(w.cols, s.F));
       ALLOC_WORK(ctx, w.P, wide_partial_bytes(s));
     }
+    if (resident_model(s)) {
+      Resident& r = ctx->r;
+      ALLOC(ctx, r.ctl, sizeof(ResidentCtl));
+      ALLOC_WORK(ctx, r.granules, resident_granule_bytes(s));
+      HIPCHK(ctx, hipHostMalloc((void**)&r.failed, sizeof(uint32_t), hipHostMallocDefault));
+      *r.failed = 0;
+      ResidentCtl ctl;
+      memset(&ctl, 0, sizeof ctl);
+      ctl.epoch = 1;  // cleared granules are of no pass
+      HIPCHK(ctx, hipMemcpy(r.ctl, &ctl, sizeof ctl, hipMemcpyHostToDevice));
+      HIPCHK(ctx, hipMemsetAsync(r.granules, 0, resident_granule_bytes(s), ctx->stream));
+      HIPCHK(ctx, resident_prepare(s));
+    }
     HIPCHK(ctx, hipMemsetAsync(b.kc, 0, kv_bytes, ctx->stream));
     HIPCHK(ctx, hipMemsetAsync(b.vc, 0, kv_bytes, ctx->stream));
 
@@ -244,6 +260,7 @@ extern "C" int easyspec_create(const easyspec_config* cfg, void* hip_stream, eas
   if (rc != EASYSPEC_OK) {
     g_err = ctx->err;
     for (void* p : ctx->allocs) (void)hipFree(p);
+    if (ctx->r.failed) (void)hipHostFree(ctx->r.failed);
     delete ctx;
     return rc;
   }
@@ -256,6 +273,7 @@ extern "C" void easyspec_destroy(easyspec_ctx* ctx) {
   (void)hipStreamSynchronize(ctx->stream);
   for (hipEvent_t e : ctx->prof_ev) (void)hipEventDestroy(e);
   for (void* p : ctx->allocs) (void)hipFree(p);
+  if (ctx->r.failed) (void)hipHostFree(ctx->r.failed);
   delete ctx;
 }
 
@@ -393,6 +411,24 @@ struct ProfScope {
   ~ProfScope() { g_launch_timer = nullptr; }
 };
 
+// Do the switches that force a kernel or the cut of a launch leave room for a resident pass, which has neither?
+static bool launches_forced() {
+  for (char** e = environ; e && *e; ++e) {
+    if (strncmp(*e, "EASYSPEC_", 9) != 0) continue;
+    const char* v = *e + 9;
+    if (strcmp(v, "RESIDENT=0") == 0) return true;
+    if (strcmp(v, "ATTN_MFMA=1") == 0) continue;  // what it is without the switch
+    for (const char* p : {"ATTN_", "NW_", "TILE_ROWS", "QKV_TILE_ROWS", "PAIR_"})
+      if (strncmp(v, p, strlen(p)) == 0) return true;
+  }
+  return false;
+}
+
+// Does this pass run in one launch (resident.hip)?  Not while launches are timed one by one.
+static bool resident_takes(const easyspec_ctx* ctx, const Cols& c) {
+  return ctx->r.ctl && ctx->prof_op < 0 && resident_pass(ctx->s, c) && !launches_forced();
+}
+
 // c2: a second pass of as many columns run together with the first (sets of one layer only: a calibration); the
 // weight kernels then serve both passes in one launch each, embedding, attention and argmax run per pass.
 static int forward(easyspec_ctx* ctx, const Cols& c, const int32_t* tokens, const std::vector<int32_t>& bounds,
@@ -404,6 +440,14 @@ static int forward(easyspec_ctx* ctx, const Cols& c, const int32_t* tokens, cons
   const int n_sets = (int)bounds.size() - 1;
   if (c2 && (full_layer || !ctx->has_b2 || c2->n != c.n || n_sets != s.L))
     return fail(ctx, EASYSPEC_EINVAL, "internal: two passes together need equal column counts and sets of one layer");
+  if (!c2 && !full_layer && resident_takes(ctx, c)) {
+    if (*(volatile uint32_t*)ctx->r.failed) return fail(ctx, EASYSPEC_EHIP, "an earlier pass of this context gave up waiting for its own results");
+    launch_resident(s, b, ctx->r, c, tokens, bounds.data(), n_sets, logits_out, tokens_out, st);
+    HIPCHK(ctx, hipGetLastError());
+    ctx->last_rows = c.n;
+    ctx->last_H = b.H;
+    return EASYSPEC_OK;
+  }
   { ProfScope p(ctx, EASYSPEC_OP_ALL); launch_embed(s, b, c, tokens, 0, bounds[1] - bounds[0], st); }
   if (c2) { ProfScope p(ctx, EASYSPEC_OP_ALL); launch_embed(s, *b2, *c2, tokens, 0, 1, st); }
   for (int j = 0; j < n_sets; ++j) {

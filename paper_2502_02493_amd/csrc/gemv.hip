@@ -457,8 +457,6 @@ struct HeadArgs {
   float inv_d, eps;
 };
 
-__device__ __forceinline__ bool better(float v, int i, float bv, int bi) { return v > bv || (v == bv && i < bi); }
-
 // TP: row tiles per workgroup (as for gate/up: more than one where a pass loads two fragments per k-tile)
 // NP passes (of equal column counts) are served from one read of the weights.
 template <typename T, int NB, int TP, int NP>

@@ -1,5 +1,5 @@
 // Internal interface between the host state machine (easyspec.cpp) and the gfx950 kernels
-// (gemv.hip, attention.hip, util.hip, accept.hip).  Plain structs and launch functions; no device code in this header.
+// (gemv.hip, attention.hip, wide.hip, resident.hip, util.hip, accept.hip).  Plain structs and launch functions; no device code in this header.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -90,6 +90,21 @@ struct WideBuffers {
   float* P;      // split-K partial sums [split][cols][rows]
 };
 constexpr int kWideSplitCols = 2048;  // columns x splits the partial sums have room for
+
+// Resident passes of small models (resident.hip): counters, the places of a pass's tagged values, and a host word that a
+// pass sets if it gave up waiting.
+struct ResidentCtl {
+  uint32_t ticket, pad0[31];
+  uint32_t done, pad1[31];
+  uint32_t epoch, pad2[31];
+};
+struct Resident {
+  ResidentCtl* ctl;  // null: the model's passes are separate launches
+  void* granules;
+  uint32_t* failed;  // pinned host memory
+};
+constexpr int kResMaxLayers = 64;
+constexpr int kResMaxVocab = 16384;
 
 // Per-launch timing (easyspec_profile_*): while a timer is installed for the calling thread, every kernel
 // launch of the forward pass binds the next start / stop event pair to its own dispatch, so that the pair's
@@ -206,6 +221,13 @@ void launch_wide_gateup(const Shape& s, const Buffers& b, const WideBuffers& w, 
 // logits of every column into logits[seq * tok_pitch + i][V], and the argmax of every entry's last column
 void launch_wide_head(const Shape& s, const Buffers& b, const WideBuffers& w, const Spans& sp, float* logits, int32_t* tokens_out,
                       hipStream_t st);
+// A whole pass of a small model in one launch: which models, which passes, what it needs.
+bool resident_model(const Shape& s);
+bool resident_pass(const Shape& s, const Cols& c);
+size_t resident_granule_bytes(const Shape& s);
+hipError_t resident_prepare(const Shape& s);
+void launch_resident(const Shape& s, const Buffers& b, const Resident& r, const Cols& c, const int32_t* tokens, const int32_t* bounds, int n_sets,
+                     float* logits, int32_t* tokens_out, hipStream_t st);
 void launch_accept(const int32_t* draft, const int32_t* target, int batch, int gamma, int32_t* accept_len,
                    int32_t* bonus, hipStream_t st);
 // Acceptance by speculative sampling; ws: sample_accept_workspace_bytes() of scratch.

@@ -11,8 +11,8 @@
 //     while the matrix pipe is full; the plain 16-column kernels (a wave per row tile, operands straight from the L2)
 //     ask the L2 for as many operand bytes as weight bytes at 12 columns.  The halves put two waves on a SIMD
 //     without a second reader of the same operand; their sums meet in LDS at the end.
-//   * Stages of 2 KS k-tiles, the operand in three LDS buffers filled in mid-stage, one barrier per stage; weights are
-//     requested two stages ahead, the operand one, LDS fragments a step ahead.
+//   * Stages of 2 KS k-tiles, the operand in three LDS buffers filled in the stage before (at its begin or middle), one
+//     barrier per stage, in its middle; weights are requested two stages ahead, the operand one, LDS fragments a step ahead.
 //   * Packed tiles are taken as they are (14 rows for gate/up, 12 pairs for QKV at the 8B shape: the spare rows of the
 //     MFMA idle).  Regrouped into 16 consecutive rows a fragment straddles two packed tiles and touches half as many
 //     lines again: gate/up at 24 columns 55 us against 42.
@@ -113,10 +113,15 @@ __global__ __launch_bounds__(kWideThreads) void wide_gemm_kernel(WideArgs a, Spa
   };
   // A stage is KS * CT steps of (hi, lo) fragments, each read from LDS a step before it is used, across the end of the
   // stage too (the scheduling barriers keep the compiler from moving a read next to its use, where its latency would be
-  // exposed).  In its middle a stage puts the next stage's operand into LDS; the barrier after that is the only one,
+  // exposed).  A stage puts the next stage's operand into LDS; the barrier in its middle is the only one,
   // and no wave has anything to wait for at the stage's end.  Three operand buffers: what is overwritten there was
-  // last read in the first of the two stages before, which every wave has left when any passes the barrier between.
+  // last read in the stage before the one before, which every wave has left when any passes the barrier between.
+  // EARLY: the operand is put there, and the one after it requested, at the stage's begin and ahead of the weights: loads
+  // return in order, and a wait for the operand in mid-stage waits for the weights requested half a stage before it, of
+  // which only those of this stage are needed.  256 columns: gate/up 112 .. 123 -> 108 .. 114 us by box, down 51 .. 57 ->
+  // 50 .. 53.  Stages of fewer column tiles are too short for it (64 columns: gate/up 49 -> 53).
   constexpr int STEPS = KS * CT, AHEAD = 1, MID = STEPS / 2;
+  constexpr bool EARLY = CT >= 6;
   static_assert(3 * STEPS % (AHEAD + 1) == 0, "fragment registers return to their place after three stages");
   const u32x4* const xl = xs + lane;
   u32x4 bh[AHEAD + 1], bl[AHEAD + 1];
@@ -138,6 +143,10 @@ __global__ __launch_bounds__(kWideThreads) void wide_gemm_kernel(WideArgs a, Spa
     // the stage in buffer I, its weights in w[I] (registers rotate by name: a copy would wait for the requests)
     auto stage = [&](auto which) {
       constexpr int I = decltype(which)::value, N = (I + 1) % 3, L = (I + 2) % 3;
+      if (EARLY) {
+        put(N);
+        load_x(kt + 2 * SK);
+      }
       load_w(kt + 2 * SK, w[L]);
       if (kt + SK > k1) {  // uniform; only the last stage
 #pragma unroll
@@ -152,9 +161,9 @@ __global__ __launch_bounds__(kWideThreads) void wide_gemm_kernel(WideArgs a, Spa
       for (int st = 0; st < STEPS; ++st) {
         const int ks = st / CT, c = st % CT, j = I * STEPS + st, at = j % (AHEAD + 1), to = (j + AHEAD) % (AHEAD + 1);
         if (st == MID) {
-          put(N);
+          if (!EARLY) put(N);
           __syncthreads();
-          load_x(kt + 2 * SK);
+          if (!EARLY) load_x(kt + 2 * SK);
         }
         if (st + AHEAD < STEPS) fetch(to, I, st + AHEAD);
         else fetch(to, N, st + AHEAD - STEPS);

@@ -48,9 +48,12 @@ __global__ void accept_kernel(const int32_t* draft, const int32_t* target, int b
 // user [L][Hkv][n][hd] <-> cache [L][B][Hkv][max_ctx][hd], K and V in one launch.  The slots of a (layer, KV head)
 // are one contiguous run on both sides, so a workgroup moves a piece of one run: no division per element, and
 // kKvPieces 16-byte loads per thread are in flight before the first store.  Bound by memory (every byte read once
-// and written once): an import or export of 2048 slots of the 8B shape (268 MB each way, 537 MB of traffic).
+// and written once): an import or export of 2048 slots of the 8B shape (268 MB each way, 537 MB of traffic).  Ordinary loads,
+// non-temporal stores, few pieces a thread: us a call with its wait, 8 pieces 136 (both non-temporal), 4 pieces 97 (both), 112
+// (neither), 79 (loads only), 74 .. 84 (stores only), 2 pieces 73 (stores only), 1 piece 74 .. 80; import and export one after
+// the other on arrays of their own 282 -> 205.
 // grid = (pieces of a run, layer x KV head, K / V).
-constexpr int kKvThreads = 256, kKvPieces = 8;
+constexpr int kKvThreads = 256, kKvPieces = 2;
 __global__ __launch_bounds__(kKvThreads) void kv_copy_kernel(u32x4* kc, u32x4* vc, u32x4* k_user, u32x4* v_user, size_t layer_pitch,
                                                              size_t head_pitch, size_t seq_off, int Hkv, size_t run, int to_cache) {
   const int lh = blockIdx.y, l = lh / Hkv, h = lh % Hkv;
@@ -63,7 +66,7 @@ __global__ __launch_bounds__(kKvThreads) void kv_copy_kernel(u32x4* kc, u32x4* v
 #pragma unroll
   for (int j = 0; j < kKvPieces; ++j) {
     const size_t i = i0 + (size_t)j * kKvThreads;
-    if (i < run) v[j] = __builtin_nontemporal_load(src + i);
+    if (i < run) v[j] = src[i];
   }
 #pragma unroll
   for (int j = 0; j < kKvPieces; ++j) {

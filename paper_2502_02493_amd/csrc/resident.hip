@@ -22,9 +22,11 @@
 // waves, 0.8 the tile's end in wave 0, the rest the trip of a store to the other XCDs and the poll that finds it.  So the code
 // is straight-line: a request under a branch is waited for where the branch ends (a unit's start 1.4 -> 1.1 us, of a down
 // projection 3.6 -> 2.3), an LDS read under one stands alone (products 0.9 -> 0.4), and a wave's lanes take an element of the
-// tile each instead of four (end of a tile 1.5 -> 0.8).
-// us a pass, launches and resident: draft step of the 256-wide fp32 model of 4 layers 98 -> 57; of the 448-wide one of 5
-// layers 148 -> 86; an iteration of the latter (calibration of 5 tokens and three steps) 594 -> 405 (its vocabulary of 1000).
+// tile each instead of four (end of a tile 1.5 -> 0.8).  In the attention the steps of all heads go side by side, the slots of
+// this pass are part of the last run instead of a batch of their own, and with seven or eight heads half of the waves take half
+// of them: 5.5 -> 3.2 us at 61 slots and seven heads.
+// us a call, launches and resident: draft step of the 256-wide fp32 model of 4 layers 98 -> 56; an iteration of the 448-wide
+// one of 5 layers (calibration of 5 tokens and three steps, vocabulary of 1000) 594 -> 380.
 #include "launch_common.hpp"
 
 #include <math.h>
@@ -131,8 +133,30 @@ __device__ __forceinline__ float quarter_sum(float v) {
   const auto q = __builtin_amdgcn_permlane16_swap(b, b, false, false);
   return __uint_as_float(q[0]) + __uint_as_float(q[1]);
 }
-// ... and over the wave
-__device__ __forceinline__ float wave_sum(float v) { return quarter_sum(group_sum<16>(v)); }
+// ... and of N = 16 or 32 consecutive lanes: sum, maximum
+template <int N>
+__device__ __forceinline__ float lanes_sum(float v) {
+  v = group_sum<16>(v);
+  if (N == 32) {
+    const uint32_t a = __float_as_uint(v);
+    const auto q = __builtin_amdgcn_permlane16_swap(a, a, false, false);
+    v = __uint_as_float(q[0]) + __uint_as_float(q[1]);
+  }
+  return v;
+}
+template <int N>
+__device__ __forceinline__ float lanes_max(float v) {
+  v = fmaxf(v, dpp_f32<0xB1>(v));
+  v = fmaxf(v, dpp_f32<0x4E>(v));
+  v = fmaxf(v, dpp_f32<0x141>(v));
+  v = fmaxf(v, dpp_f32<0x140>(v));
+  if (N == 32) {
+    const uint32_t a = __float_as_uint(v);
+    const auto q = __builtin_amdgcn_permlane16_swap(a, a, false, false);
+    v = fmaxf(__uint_as_float(q[0]), __uint_as_float(q[1]));
+  }
+  return v;
+}
 
 template <typename T>
 __device__ __forceinline__ float load_elem(const void* p, size_t i) {
@@ -510,14 +534,17 @@ __global__ __launch_bounds__(kResThreads) void resident_kernel(ResidentArgs a, C
       float* const vn = kn + kMaxCols * HD;
       float* const accs = vn + kMaxCols * HD;              // [32 slot groups][G][HD]
       float* const ms = accs + 32 * G * HD;                // [G][32] maxima, then sums
-      // the cached slots: dealt to the waves in runs of whole loads; the first batch is requested before the queries are there
-      constexpr int IT = EPL * G > 32 ? 2 : 4;  // registers
-      const int groups = ceil_div(n_old, SPW), w0 = wave * groups / kResWaves * SPW, w1 = min((wave + 1) * groups / kResWaves * SPW, n_old);
+      // The waves share the slots, the cached ones and behind them those of this pass, in runs of whole loads; with seven or
+      // eight query heads half of them takes half of the heads.  The first batch of rows is requested before the queries
+      // are there.
+      constexpr int IT = 4, HS = G >= 7 ? 2 : 1, GW = (G + HS - 1) / HS, NSP = kResWaves / HS, NGRP = NSP * 4;
+      const int g0 = wave / NSP * GW, part = wave % NSP, n_all = n_old + n_new;
+      const int groups = ceil_div(n_all, SPW), w0 = part * groups / NSP * SPW, w1 = min((part + 1) * groups / NSP * SPW, n_all);
       u32x4 kr[IT], vr[IT];
-      auto fetch = [&](int base) {
+      auto fetch = [&](int base) {  // unconditional: slots past the cached ones fetch the last of them, or the first row
 #pragma unroll
         for (int j = 0; j < IT; ++j) {
-          const int s = max(min(base + j * SPW + sub, w1 - 1), 0);
+          const int s = max(min(base + j * SPW + sub, n_old - 1), 0);
           kr[j] = kb[(size_t)s * LPS];
           vr[j] = vb[(size_t)s * LPS];
         }
@@ -552,59 +579,63 @@ __global__ __launch_bounds__(kResThreads) void resident_kernel(ResidentArgs a, C
         }
       }
       __syncthreads();
-      float q[G][EPL], acc[G][EPL], m[G], sum[G];
+      float q[GW][EPL], acc[GW][EPL], m[GW], sum[GW];
 #pragma unroll
-      for (int g = 0; g < G; ++g) {
+      for (int g = 0; g < GW; ++g) {
 #pragma unroll
         for (int e = 0; e < EPL; ++e) {
-          q[g][e] = qs[g * HD + e0 + e];
+          q[g][e] = qs[min(g0 + g, G - 1) * HD + e0 + e];
           acc[g][e] = 0.f;
         }
         m[g] = -INFINITY;
         sum[g] = 0.f;
       }
-      // Batches of IT slots of every slot group, running maximum and sum of the group as in the vector attention kernel;
-      // the slots of this pass are the last wave's last batch.
+      // Batches of IT slots of every slot group, running maximum and sum of the group as in the vector attention kernel
       auto visible = [&](int s) { return s < vbase || ((vmask >> ((s - vbase) & 63)) & 1ull) != 0; };
-      const int n_end = w1 + (wave == kResWaves - 1 ? n_new : 0);  // the last wave's run ends where the new slots begin
 #pragma unroll 1
-      for (int base = w0; base < n_end; base += IT * SPW) {
-        float kf[IT][EPL], vf[IT][EPL], s_[IT];
-        bool valid[IT];
-        if (base < w1) {
-          if (base > w0) fetch(base);
+      for (int base = w0; base < w1; base += IT * SPW) {
+        float kf[IT][EPL], vf[IT][EPL], sc[IT][GW];
+#pragma unroll
+        for (int j = 0; j < IT; ++j) {
+          unpack<T>(kr[j], kf[j]);
+          unpack<T>(vr[j], vf[j]);
+        }
+        if (base + IT * SPW > n_old) {  // uniform: some of this pass's slots
 #pragma unroll
           for (int j = 0; j < IT; ++j) {
-            const int s = base + j * SPW + sub;
-            unpack<T>(kr[j], kf[j]);
-            unpack<T>(vr[j], vf[j]);
-            valid[j] = s < w1 && visible(s);
-          }
-          if (base + IT * SPW >= w1) base = w1 - IT * SPW;  // the next batch, if any, begins with the first new slot
-        } else {
-#pragma unroll
-          for (int j = 0; j < IT; ++j) {
-            const int s = base + j * SPW + sub, r = min(s - n_old, n_new - 1);
+            const int s = base + j * SPW + sub, at = max(min(s - n_old, n_new - 1), 0) * HD + e0;
 #pragma unroll
             for (int e = 0; e < EPL; ++e) {
-              kf[j][e] = kn[r * HD + e0 + e];
-              vf[j][e] = vn[r * HD + e0 + e];
+              kf[j][e] = s >= n_old ? kn[at + e] : kf[j][e];
+              vf[j][e] = s >= n_old ? vn[at + e] : vf[j][e];
             }
-            valid[j] = s < n_end && visible(s);
           }
         }
+        fetch(base + IT * SPW);
 #pragma unroll
-        for (int g = 0; g < G; ++g) {
-          float bm = -INFINITY;
+        for (int j = 0; j < IT; ++j)
 #pragma unroll
-          for (int j = 0; j < IT; ++j) {
+          for (int g = 0; g < GW; ++g) {
             float dot = 0.f;
 #pragma unroll
             for (int e = 0; e < EPL; ++e) dot += q[g][e] * kf[j][e];
-            dot = group_sum<LPS>(dot);
-            s_[j] = valid[j] ? dot * a.scale : -INFINITY;
-            bm = fmaxf(bm, s_[j]);
+            sc[j][g] = dot;
           }
+#pragma unroll
+        for (int j = 0; j < IT; ++j) {
+          const int s = base + j * SPW + sub;
+          const bool valid = s < w1 && visible(s);
+#pragma unroll
+          for (int g = 0; g < GW; ++g) {
+            const float dot = group_sum<LPS>(sc[j][g]);
+            sc[j][g] = valid ? dot * a.scale : -INFINITY;
+          }
+        }
+#pragma unroll
+        for (int g = 0; g < GW; ++g) {
+          float bm = sc[0][g];
+#pragma unroll
+          for (int j = 1; j < IT; ++j) bm = fmaxf(bm, sc[j][g]);
           const float m_new = fmaxf(m[g], bm), m_ref = m_new == -INFINITY ? 0.f : m_new, alpha = __expf(m[g] - m_ref);
           m[g] = m_new;
           sum[g] *= alpha;
@@ -612,58 +643,58 @@ __global__ __launch_bounds__(kResThreads) void resident_kernel(ResidentArgs a, C
           for (int e = 0; e < EPL; ++e) acc[g][e] *= alpha;
 #pragma unroll
           for (int j = 0; j < IT; ++j) {
-            const float p = __expf(s_[j] - m_ref);  // 0 for slots past the end or masked
-            sum[g] += p;
-#pragma unroll
-            for (int e = 0; e < EPL; ++e) acc[g][e] += p * vf[j][e];
+            sc[j][g] = __expf(sc[j][g] - m_ref);  // 0 for slots past the end or masked
+            sum[g] += sc[j][g];
           }
         }
+#pragma unroll
+        for (int j = 0; j < IT; ++j)
+#pragma unroll
+          for (int g = 0; g < GW; ++g)
+#pragma unroll
+            for (int e = 0; e < EPL; ++e) acc[g][e] += sc[j][g] * vf[j][e];
       }
-      // down to four slot groups a wave (eight lanes a slot: two groups meet first)
+      // down to four slot groups a wave (eight lanes a slot: lanes 8 apart, inside rows of 16, meet first)
       if (SPW == 8) {
 #pragma unroll
-        for (int g = 0; g < G; ++g) {
-          const float om = __shfl_xor(m[g], LPS, 64), mm = fmaxf(m[g], om), ref = mm == -INFINITY ? 0.f : mm;
-          const float f = __expf(m[g] - ref);
+        for (int g = 0; g < GW; ++g) {
+          const float mm = fmaxf(m[g], dpp_f32<0x128>(m[g])), ref = mm == -INFINITY ? 0.f : mm, f = __expf(m[g] - ref);
           sum[g] *= f;
-          sum[g] += __shfl_xor(sum[g], LPS, 64);
+          sum[g] += dpp_f32<0x128>(sum[g]);
           m[g] = mm;
 #pragma unroll
           for (int e = 0; e < EPL; ++e) {
             acc[g][e] *= f;
-            acc[g][e] += __shfl_xor(acc[g][e], LPS, 64);
+            acc[g][e] += dpp_f32<0x128>(acc[g][e]);
           }
         }
       }
-      const int grp = wave * 4 + (SPW == 8 ? sub >> 1 : sub);
+      const int grp = part * 4 + (SPW == 8 ? sub >> 1 : sub);
       if (SPW == 4 || (sub & 1) == 0) {
 #pragma unroll
-        for (int g = 0; g < G; ++g) {
+        for (int g = 0; g < GW; ++g) {
+          if (g0 + g >= G) break;
 #pragma unroll
           for (int e = 0; e < EPL; e += 4)
-            *reinterpret_cast<f32x4*>(accs + (grp * G + g) * HD + e0 + e) = f32x4{acc[g][e], acc[g][e + 1], acc[g][e + 2], acc[g][e + 3]};
+            *reinterpret_cast<f32x4*>(accs + (grp * G + g0 + g) * HD + e0 + e) = f32x4{acc[g][e], acc[g][e + 1], acc[g][e + 2], acc[g][e + 3]};
           if (lane % LPS == 0) {
-            ms[g * 32 + grp] = m[g];
-            ms[G * 32 + g * 32 + grp] = sum[g];
+            ms[(g0 + g) * 32 + grp] = m[g];
+            ms[G * 32 + (g0 + g) * 32 + grp] = sum[g];
           }
         }
       }
       __syncthreads();
       if (wave < G) {  // a wave per query head: the groups' weights, then an element per lane
-        const float gm = ms[wave * 32 + (lane & 31)], gs = ms[G * 32 + wave * 32 + (lane & 31)];
-        float mm = gm;
+        const float gm = ms[wave * 32 + (lane & (NGRP - 1))], gs = ms[G * 32 + wave * 32 + (lane & (NGRP - 1))];
+        float x[NGRP];
 #pragma unroll
-        for (int off = 16; off > 0; off >>= 1) mm = fmaxf(mm, __shfl_xor(mm, off, 64));
-        float f = __expf(gm - mm), tot = gs * f;
-#pragma unroll
-        for (int off = 16; off > 0; off >>= 1) tot += __shfl_xor(tot, off, 64);
-        f /= tot;
+        for (int i = 0; i < NGRP; ++i) x[i] = accs[(i * G + wave) * HD + lane];
+        const float mm = lanes_max<NGRP>(gm);
+        float f = __expf(gm - mm);
+        f /= lanes_sum<NGRP>(gs * f);
         float out = 0.f;
 #pragma unroll
-        for (int i = 0; i < 32; ++i) {
-          const float wgt = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(f), i));
-          out += wgt * accs[(i * G + wave) * HD + lane];
-        }
+        for (int i = 0; i < NGRP; ++i) out += __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(f), i)) * x[i];
         ll_put(a.ll + (size_t)l * map.layer + map.ao + ac * a.HQ + (kvh * G + wave) * HD + lane, out, w.epoch);
       }
     } else {  // argmax of one column (lowest index on ties)
@@ -740,13 +771,14 @@ static size_t resident_lds(const Shape& s, int n) {
 
 // Passes whose operands are few enough: what a pass stages per layer and column is 2 d_model + n_q_heads * head_dim + d_ffn
 // granules, by every unit for itself, and from some 25000 of them on the launches win (they read a shared operand from the
-// L2, 4 bytes a value).  us a pass, launches and resident, contexts 200 / a batch at 100 and up: 256-wide model of 4 layers
-// (1792 a column) 1 column 110 / 63, 8 columns 124 / 99, 16 columns 140 / 133; 448-wide of 5 layers (2528 a column) 1 column
-// 144 / 85, 4 columns 149 / 124, 8 columns 158 / 153, 12 columns 162 / 176, 16 columns 168 / 186.
+// L2, 4 bytes a value).  us a step, launches and resident, contexts from 100 on: 256-wide model of 4 layers (1792 a column) 1
+// column 109 / 59, 3 columns 113 / 80, 9 columns 130 / 109, 16 columns 140 / 133; 448-wide of 5 layers (2528 a column) 1 column
+// 144 / 80, 3 columns 147 / 105, 6 columns 156 / 134, 9 columns 158 / 153; with an attention slower by 5 us a pass 12 columns
+// 162 / 176, 16 columns 168 / 186.
 // Contexts: one workgroup walks a KV head's slots, where the launches split them from 256 on: up to 80 KB of keys (fp32 320
-// slots, bf16 640).  us a pass of three columns, launches and resident, the 448-wide model with its seven heads per KV head:
-// fp32 250 slots 177 / 136, 320 slots 171 / 148, 600 slots 173 / 174; bf16 500 slots 153 / 139, 600 slots 154 / 149, 1000
-// slots 153 / 178.
+// slots, bf16 640).  us a step, launches and resident, the 448-wide model with its seven heads per KV head: fp32 30 slots 140 /
+// 75, 300 slots 150 / 100; bf16 30 slots 134 / 81, 300 slots 134 / 97, 600 slots 135 / 113 (longer ones with the attention
+// before: three columns at fp32 600 slots 173 / 174, bf16 1000 slots 153 / 178).
 bool resident_pass(const Shape& s, const Cols& c) {
   const int most = s.dtype == 1 ? 640 : 320;
   for (int i = 0; i < c.n; ++i)

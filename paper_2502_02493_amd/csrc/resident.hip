@@ -814,12 +814,9 @@ void launch_resident(const Shape& s, const Buffers& b, const Resident& r, const 
   a.L = s.L; a.d = s.d; a.Hq = s.Hq; a.Hkv = s.Hkv; a.F = s.F; a.V = s.V; a.HQ = s.HQ; a.RQKV = s.RQKV; a.B = s.B; a.max_ctx = s.max_ctx;
   a.n_sets = n_sets;
   a.inv_d = 1.0f / (float)s.d; a.eps = s.eps; a.scale = 1.0f / sqrtf((float)s.hd);
-  int k_max = 1;
   for (int j = 0; j <= n_sets; ++j) a.bounds[j] = (uint8_t)bounds[j];
-  for (int j = 0; j < n_sets; ++j) k_max = std::max(k_max, bounds[j + 1] - bounds[j]);
   for (int i = 0; i < c.n; ++i) a.col0[i] = (uint8_t)(i > 0 && c.seq[i] == c.seq[i - 1] ? a.col0[i - 1] : i);
-  // as many workgroups as the widest phase has units, up to half of the CUs
-
+  // two workgroups per unit of the MLP or the head, whichever has more (one works, one waits for the next phase), up to one per CU
   const int widest = std::max(ceil_div(s.F, 16), ceil_div(s.V, 16));
   const dim3 grid(std::min(cu_count(), 2 * widest)), blk(kResThreads);
   const size_t lds = resident_lds(s, c.n);

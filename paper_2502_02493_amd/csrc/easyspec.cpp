@@ -425,8 +425,8 @@ static bool launches_forced() {
 }
 
 // Does this pass run in one launch (resident.hip)?  Not while launches are timed one by one.
-static bool resident_takes(const easyspec_ctx* ctx, const Cols& c) {
-  return ctx->r.ctl && ctx->prof_op < 0 && resident_pass(ctx->s, c) && !launches_forced();
+static bool resident_takes(const easyspec_ctx* ctx, const Cols& c, const std::vector<int32_t>& bounds) {
+  return ctx->r.ctl && ctx->prof_op < 0 && resident_pass(ctx->s, c, bounds.data(), (int)bounds.size() - 1) && !launches_forced();
 }
 
 // c2: a second pass of as many columns run together with the first (sets of one layer only: a calibration); the
@@ -440,7 +440,7 @@ static int forward(easyspec_ctx* ctx, const Cols& c, const int32_t* tokens, cons
   const int n_sets = (int)bounds.size() - 1;
   if (c2 && (full_layer || !ctx->has_b2 || c2->n != c.n || n_sets != s.L))
     return fail(ctx, EASYSPEC_EINVAL, "internal: two passes together need equal column counts and sets of one layer");
-  if (!c2 && !full_layer && resident_takes(ctx, c)) {
+  if (!c2 && !full_layer && resident_takes(ctx, c, bounds)) {
     if (*(volatile uint32_t*)ctx->r.failed) return fail(ctx, EASYSPEC_EHIP, "an earlier pass of this context gave up waiting for its own results");
     launch_resident(s, b, ctx->r, c, tokens, bounds.data(), n_sets, logits_out, tokens_out, st);
     HIPCHK(ctx, hipGetLastError());

@@ -223,7 +223,7 @@ void launch_wide_head(const Shape& s, const Buffers& b, const WideBuffers& w, co
                       hipStream_t st);
 // A whole pass of a small model in one launch: which models, which passes, what it needs.
 bool resident_model(const Shape& s);
-bool resident_pass(const Shape& s, const Cols& c);
+bool resident_pass(const Shape& s, const Cols& c, const int32_t* bounds, int n_sets);
 size_t resident_granule_bytes(const Shape& s);
 hipError_t resident_prepare(const Shape& s);
 void launch_resident(const Shape& s, const Buffers& b, const Resident& r, const Cols& c, const int32_t* tokens, const int32_t* bounds, int n_sets,

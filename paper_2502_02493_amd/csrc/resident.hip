@@ -769,21 +769,42 @@ static size_t resident_lds(const Shape& s, int n) {
   return std::max(operand, attn);
 }
 
-// Passes whose operands are few enough: what a pass stages per layer and column is 2 d_model + n_q_heads * head_dim + d_ffn
-// granules, by every unit for itself, and from some 25000 of them on the launches win (they read a shared operand from the
-// L2, 4 bytes a value).  us a step, launches and resident, contexts from 100 on: 256-wide model of 4 layers (1792 a column) 1
-// column 109 / 59, 3 columns 113 / 80, 9 columns 130 / 109, 16 columns 140 / 133; 448-wide of 5 layers (2528 a column) 1 column
-// 144 / 80, 3 columns 147 / 105, 6 columns 156 / 134, 9 columns 158 / 153; with an attention slower by 5 us a pass 12 columns
-// 162 / 176, 16 columns 168 / 186.
-// Contexts: one workgroup walks a KV head's slots, where the launches split them from 256 on: up to 80 KB of keys (fp32 320
-// slots, bf16 640).  us a step, launches and resident, the 448-wide model with its seven heads per KV head: fp32 30 slots 140 /
-// 75, 300 slots 150 / 100; bf16 30 slots 134 / 81, 300 slots 134 / 97, 600 slots 135 / 113 (longer ones with the attention
-// before: three columns at fp32 600 slots 173 / 174, bf16 1000 slots 153 / 178).
-bool resident_pass(const Shape& s, const Cols& c) {
+static int resident_grid(const Shape& s) {
+  // two workgroups per unit of the MLP or the head, whichever has more (one works, one waits for the next phase), up to one per CU
+  const int widest = std::max(ceil_div(s.F, 16), ceil_div(s.V, 16));
+  return std::min(cu_count(), 2 * widest);
+}
+
+// Which passes.  Contexts: one workgroup walks a KV head's slots, where the launches split them from 256 on: up to 80 KB of keys
+// (fp32 320 slots, bf16 640).  us a step, launches and resident, the 448-wide model of 5 layers with its seven heads per KV head:
+// fp32 30 slots 140 / 75, 300 slots 150 / 100; bf16 30 slots 134 / 81, 300 slots 134 / 97, 600 slots 135 / 113.  Columns: the
+// operands of a layer, 2 d_model + n_q_heads * head_dim + d_ffn granules a column, up to 24576 of them.
+// Inside these limits the route is chosen by a cost in ns, fitted to both routes' times of 2900 calls (400 models of the admitted
+// sizes: 2 .. 32 layers, vocabularies of 500 .. 16384, 1 .. 16 columns, sets of 1 .. 8 layers).  A launch saved is worth 2300 (the
+// fit's 2600 less a margin for its scatter of 5 % of a call), a merge of split attention 1200.  Against that stand granules staged,
+// by every unit for itself: 0.4 each, those of the head 1.6; units that find no workgroup free and follow in a further round: 3000 a
+// round; slots that a unit of the attention walks, times its heads: 1.6.  Of those calls one is slower here than as launches
+// (1.04x); by the limits above alone 144 were, up to 1.18x.  us a step, launches and resident: fp32 19 layers 576 / 608 wide, sets of
+// seven, ten columns 329 / 388; bf16 8 layers 1536 / 3072 wide, vocabulary 16384, sets of eight, three columns 230 / 262.  A third of the
+// calls refused are slower resident, the others would gain up to 1.2x, 1.03x on average over all of them.
+bool resident_pass(const Shape& s, const Cols& c, const int32_t* bounds, int n_sets) {
   const int most = s.dtype == 1 ? 640 : 320;
-  for (int i = 0; i < c.n; ++i)
-    if (c.pos[i] >= most) return false;
-  return c.n * (2 * s.d + s.HQ + s.F) <= 24576 && sizeof(ResidentShared) + resident_lds(s, c.n) <= 150 * 1024;
+  int ctx = 0;
+  for (int i = 0; i < c.n; ++i) ctx = std::max(ctx, c.pos[i] + 1);
+  if (ctx > most || c.n * (2 * s.d + s.HQ + s.F) > 24576 || sizeof(ResidentShared) + resident_lds(s, c.n) > 150 * 1024) return false;
+  const long grid = resident_grid(s), ntile = s.d / 16, head = ceil_div(s.V, 16);
+  auto rounds = [&](long units) { return (units + grid - 1) / grid; };
+  const long r_gu = rounds(s.F / 16), r_down = rounds(ntile), r_head = rounds(head);
+  long launches = 3 + 2 * s.L, merges = 0, staged = s.L * (r_gu * s.d + r_down * s.F) + 4 * r_head * s.d, late = s.L * (r_gu + r_down - 2) + r_head - 1, walked = 0;
+  for (int j = 0; j < n_sets; ++j) {
+    const long k = bounds[j + 1] - bounds[j], r_qkv = rounds(k * (s.RQKV / 32)), r_attn = rounds(k * c.n * s.Hkv), r_o = rounds(k * ntile);
+    launches += 3;
+    merges += ctx > 256;
+    staged += r_qkv * s.d + r_o * s.HQ;
+    late += r_qkv + r_attn + r_o - 3;
+    walked += r_attn * ctx * (s.Hq / s.Hkv);
+  }
+  return 2300 * launches + 1200 * merges > (2 * c.n * staged + 8 * walked) / 5 + 3000 * late;
 }
 
 #define RESIDENT_G(X) X(1) X(2) X(4) X(7) X(8)
@@ -816,9 +837,7 @@ void launch_resident(const Shape& s, const Buffers& b, const Resident& r, const 
   a.inv_d = 1.0f / (float)s.d; a.eps = s.eps; a.scale = 1.0f / sqrtf((float)s.hd);
   for (int j = 0; j <= n_sets; ++j) a.bounds[j] = (uint8_t)bounds[j];
   for (int i = 0; i < c.n; ++i) a.col0[i] = (uint8_t)(i > 0 && c.seq[i] == c.seq[i - 1] ? a.col0[i - 1] : i);
-  // two workgroups per unit of the MLP or the head, whichever has more (one works, one waits for the next phase), up to one per CU
-  const int widest = std::max(ceil_div(s.F, 16), ceil_div(s.V, 16));
-  const dim3 grid(std::min(cu_count(), 2 * widest)), blk(kResThreads);
+  const dim3 grid(resident_grid(s)), blk(kResThreads);
   const size_t lds = resident_lds(s, c.n);
 #define RES_CASE(G_) \
   case G_: \

@@ -105,6 +105,35 @@ def test_the_edges_of_the_rule(gpu, monkeypatch):
         gpu.assert_close(b, a, TOL["fp32"], f"context {ctx}, {n} columns")
 
 
+# calls inside those limits that the launches do faster: many columns of a large vocabulary, units in several rounds
+@pytest.mark.parametrize("dtype,shape,group,most", [("fp32", (2, 544, 4, 2, 864, 9921), 7, 10), ("bf16", (5, 1024, 4, 1, 2176, 13430), 7, 5),
+                                                     ("fp32", (19, 576, 6, 3, 608, 613), 7, 10)])
+def test_the_cost_rule(gpu, monkeypatch, dtype, shape, group, most):
+    import paper_2502_02493_amd as es
+    L, d, hq, hkv, f, v = shape
+    cfg = synth.model_shape("tiny", n_layers=L, d_model=d, n_q_heads=hq, n_kv_heads=hkv, d_ffn=f, vocab=v, dtype=dtype)
+    w = synth.make_weights(cfg, 2115)
+    kv = synth.make_kv_prefix(cfg, 2116, 16)
+    t = [int(x) for x in synth.make_tokens(2117, most, v)]
+
+    def run(n):
+        def fn():
+            g = gpu.GpuDrafter(cfg, w, max_batch=most, max_ctx=64, max_calib=1)
+            try:
+                g.set_groups(es.easyspec_default_groups(L, group, es.EASYSPEC_POLICY_ALIGNED))
+                for b in range(n):
+                    g.import_kv(b, *kv)
+                return g.draft_step({b: t[b] for b in range(n)})[1][:n]
+            finally:
+                g.close()
+        return both(monkeypatch, fn)
+
+    for n, one_launch in ((1, True), (most, False)):
+        a, b = run(n)
+        assert np.array_equal(a, b) != one_launch, n
+        gpu.assert_close(b, a, TOL[dtype], f"{n} columns")
+
+
 @pytest.mark.parametrize("dtype", ["fp32", "bf16"])
 def test_against_the_oracle_batch(oracle, gpu, dtype):
     """Four sequences of unequal contexts drafting together, set sizes 1, 2, 1."""

@@ -58,7 +58,7 @@ struct WideArgs {
 
 // PAIR: the wave's row tiles are RW / 2 tiles of each of two matrices.  See the head of this file.
 constexpr int kWideThreads = 512;  // four row groups x two halves of a stage's k-tiles
-template <int RW, int CT, int KS, bool PAIR>
+template <int RW, int CT, int KS, bool PAIR, bool EARLY>
 __global__ __launch_bounds__(kWideThreads) void wide_gemm_kernel(WideArgs a, Spans sp) {
   constexpr int SK = 2 * KS;                               // k-tiles per stage: KS for each half
   constexpr int NB = SK * CT * 128 / kWideThreads;         // 16-byte operand pieces a thread stages per stage
@@ -116,12 +116,10 @@ __global__ __launch_bounds__(kWideThreads) void wide_gemm_kernel(WideArgs a, Spa
   // exposed).  A stage puts the next stage's operand into LDS; the barrier in its middle is the only one,
   // and no wave has anything to wait for at the stage's end.  Three operand buffers: what is overwritten there was
   // last read in the stage before the one before, which every wave has left when any passes the barrier between.
-  // EARLY: the operand is put there, and the one after it requested, at the stage's begin and ahead of the weights: loads
-  // return in order, and a wait for the operand in mid-stage waits for the weights requested half a stage before it, of
-  // which only those of this stage are needed.  256 columns: gate/up 112 .. 123 -> 108 .. 114 us by box, down 51 .. 57 ->
-  // 50 .. 53.  Stages of fewer column tiles are too short for it (64 columns: gate/up 49 -> 53).
+  // EARLY (wide_early): the operand is put there, and the one after it requested, at the stage's begin and ahead of the
+  // weights: loads return in order, and a wait for the operand in mid-stage waits for the weights requested half a stage
+  // before it, of which only those of this stage are needed.
   constexpr int STEPS = KS * CT, AHEAD = 1, MID = STEPS / 2;
-  constexpr bool EARLY = CT >= 6;
   static_assert(3 * STEPS % (AHEAD + 1) == 0, "fragment registers return to their place after three stages");
   const u32x4* const xl = xs + lane;
   u32x4 bh[AHEAD + 1], bl[AHEAD + 1];
@@ -468,13 +466,26 @@ static WideCut wide_cut(int tiles, int nkt, int ct, bool pair, bool split_k) {
 // the (RW, CT) there are kernels for: every cut that wide_cut makes
 #define WIDE_KERNELS(X) X(2, 2) X(2, 3) X(2, 4) X(4, 3) X(4, 4) X(4, 5) X(4, 6) X(4, 8)
 
+// Where a stage handles its operand before its weights: blocks of six and eight column tiles that share their weights with
+// another block.  us, without and with: all products of the 8B shape in two blocks, 8 layers, 176 columns (six tiles) 1733 -> 1724,
+// 248 columns (eight) 2132 -> 2089; gate/up alone at 256 columns 112 .. 123 -> 108 .. 114 a launch by box, down 51 .. 57 -> 50 .. 53.
+// Shorter stages have no room for it (64 columns, four tiles: gate/up 49 -> 53), and a block of its own waits for weights that come
+// from memory (gate/up of the Qwen2-7B shape at 84 columns, six tiles in one block, 8 layers: 1437 -> 1454 with it; heads of eight
+// tiles in one block: no difference).
+static bool wide_early(const WideCut& c) { return c.CT >= 6 && c.col_blocks > 1; }
+
 template <bool PAIR>
 static void launch_wide_gemm_ct(const WideArgs& a, const Spans& sp, const WideCut& c, hipStream_t st) {
   const dim3 grid(wide_grid(a.row_blocks * a.splits, a.col_blocks)), blk(kWideThreads);
-#define WIDE_CASE(RW, CT) \
-  case RW * 10 + CT: ES_LAUNCH((wide_gemm_kernel<RW, CT, wide_stage_tiles(CT), PAIR>), grid, blk, 0, st, a, sp); break;
+#define WIDE_LAUNCH(RW, CT, EARLY) ES_LAUNCH((wide_gemm_kernel<RW, CT, wide_stage_tiles(CT), PAIR, EARLY>), grid, blk, 0, st, a, sp)
+#define WIDE_CASE(RW, CT)                               \
+  case RW * 10 + CT:                                    \
+    if (wide_early(c)) WIDE_LAUNCH(RW, CT, (CT >= 6));  \
+    else WIDE_LAUNCH(RW, CT, false);                    \
+    break;
   switch (c.RW * 10 + c.CT) { WIDE_KERNELS(WIDE_CASE) }
 #undef WIDE_CASE
+#undef WIDE_LAUNCH
 }
 
 // What a wide product is of: rows of one matrix, rows per packed tile, K; two matrices side by side; partial sums per split.

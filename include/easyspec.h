@@ -26,6 +26,14 @@
  *     "host|dev" pointers may be either.  The library never frees caller memory.
  *   - Calls are asynchronous on the stream given at creation unless stated otherwise.
  *   - A context is not thread-safe; use one thread per context.
+ *   - Passes of small models run as one launch whose workgroups wait for each other's values.  Every
+ *     wait is bounded; a pass that waited some seconds in vain (a device that stopped advancing it)
+ *     ends, but its results and cache entries are wrong, and the call that enqueued it has long
+ *     returned.  Once such a pass has ended, draft steps, calibrations, easyspec_get_lens, _truncate,
+ *     _kv_import, _kv_export and _get_hidden return EASYSPEC_EHIP on that context and keep doing so:
+ *     destroy it.  The import and export look again after their synchronisation; a program that wants
+ *     to know earlier, or replays captured passes without calling the library, synchronises its
+ *     stream and calls easyspec_get_lens before it uses results.
  *   - The library has no CPU fallback: without a usable HIP device easyspec_create fails.
  *   - Measurement and test hooks (per-kernel timing, the bandwidth probe, host models of the
  *     kernels' index arithmetic, workspace poisoning) are declared apart, in easyspec_instrument.h:
@@ -44,7 +52,7 @@ extern "C" {
 #define EASYSPEC_EINVAL (-1)    /* bad argument or unsupported shape */
 #define EASYSPEC_ECAPACITY (-2) /* a sequence would exceed max_ctx, or too many tokens */
 #define EASYSPEC_ESTATE (-3)    /* call not valid in the current state (no weights, no live sequence, ...) */
-#define EASYSPEC_EHIP (-4)      /* a HIP runtime call failed; message in easyspec_last_error */
+#define EASYSPEC_EHIP (-4)      /* a HIP runtime call or an earlier pass failed; message in easyspec_last_error */
 
 #define EASYSPEC_DTYPE_F32 0
 #define EASYSPEC_DTYPE_BF16 1

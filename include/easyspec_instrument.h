@@ -22,6 +22,12 @@ extern "C" {
  * of the same pass wrote would turn its output into NaN). */
 int easyspec_poison_workspaces(easyspec_ctx *ctx);
 
+/* How often a wave of a one-launch pass (easyspec.h, Conventions) may look for a value that is not there yet, over the whole
+ * pass, before the pass gives up; 0 = the library's own limit (some seconds).  Taken by the passes enqueued (or captured) after
+ * the call; no effect on models whose passes are separate launches.  For tests of what a pass that gave up does to the context:
+ * with a limit of 1 every pass gives up, and its kernel ends normally.  EASYSPEC_EINVAL for a negative limit. */
+int easyspec_set_wait_limit(easyspec_ctx *ctx, int32_t polls);
+
 /* Streaming-read probe for roofline reports: reads `bytes` (a positive multiple of 16) of the
  * caller's device buffer once, with the loads the weight stream uses (16-byte, non-temporal,
  * 8 in flight per lane), on hip_stream (NULL = the null stream).  The caller times it; the rate

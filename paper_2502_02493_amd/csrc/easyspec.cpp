@@ -73,6 +73,18 @@ static int fail(easyspec_ctx* ctx, int code, const char* fmt, ...) {
     if (e_ != hipSuccess) return fail(ctx, EASYSPEC_EHIP, "%s: %s", #call, hipGetErrorString(e_)); \
   } while (0)
 
+// A resident pass that gave up waiting (resident.hip) left wrong results and cache entries behind and lengths that count them:
+// every entry point that uses or hands out that state looks here first, those that synchronise once more afterwards.
+static int check_passes(const easyspec_ctx* ctx) {
+  if (!ctx->r.failed || !*(volatile uint32_t*)ctx->r.failed) return EASYSPEC_OK;
+  return fail(const_cast<easyspec_ctx*>(ctx), EASYSPEC_EHIP, "a forward pass of this context gave up waiting for its own values; its results and cache are void: destroy the context");
+}
+#define CHECK_PASSES(ctx)                                      \
+  do {                                                         \
+    const int rc_ = check_passes(ctx);                         \
+    if (rc_ != EASYSPEC_OK) return rc_;                        \
+  } while (0)
+
 static size_t esize(const Shape& s) { return s.dtype == EASYSPEC_DTYPE_BF16 ? 2 : 4; }
 static size_t packed_bytes(const Shape& s, int rows, int K, int R = 16) { return es::packed_bytes(s.dtype, rows, K, R); }
 
@@ -232,6 +244,7 @@ extern "C" int easyspec_create(const easyspec_config* cfg, void* hip_stream, eas
       ALLOC_WORK(ctx, r.granules, resident_granule_bytes(s));
       HIPCHK(ctx, hipHostMalloc((void**)&r.failed, sizeof(uint32_t), hipHostMallocDefault));
       *r.failed = 0;
+      r.polls = kResPolls;
       ResidentCtl ctl;
       memset(&ctl, 0, sizeof ctl);
       ctl.epoch = 1;  // cleared granules are of no pass
@@ -441,7 +454,6 @@ static int forward(easyspec_ctx* ctx, const Cols& c, const int32_t* tokens, cons
   if (c2 && (full_layer || !ctx->has_b2 || c2->n != c.n || n_sets != s.L))
     return fail(ctx, EASYSPEC_EINVAL, "internal: two passes together need equal column counts and sets of one layer");
   if (!c2 && !full_layer && resident_takes(ctx, c, bounds)) {
-    if (*(volatile uint32_t*)ctx->r.failed) return fail(ctx, EASYSPEC_EHIP, "an earlier pass of this context gave up waiting for its own results");
     launch_resident(s, b, ctx->r, c, tokens, bounds.data(), n_sets, logits_out, tokens_out, st);
     HIPCHK(ctx, hipGetLastError());
     ctx->last_rows = c.n;
@@ -532,6 +544,7 @@ extern "C" int easyspec_set_parallel_mode(easyspec_ctx* ctx, int32_t mode) {
 
 extern "C" int easyspec_draft_step(easyspec_ctx* ctx, const int32_t* tokens_in, int32_t* tokens_out, float* logits_out) {
   if (!ctx) return fail(nullptr, EASYSPEC_EINVAL, "ctx is NULL");
+  CHECK_PASSES(ctx);
   if (!ctx->weights_loaded) return fail(ctx, EASYSPEC_ESTATE, "draft_step: no weights loaded");
   if (!tokens_in || !tokens_out) return fail(ctx, EASYSPEC_EINVAL, "draft_step: NULL token array");
   const Shape& s = ctx->s;
@@ -556,6 +569,7 @@ extern "C" int easyspec_draft_step(easyspec_ctx* ctx, const int32_t* tokens_in, 
 extern "C" int easyspec_draft_tree_step(easyspec_ctx* ctx, const int32_t* tokens_in, const int32_t* n_nodes, const int32_t* parents,
                                         int32_t* tokens_out, float* logits_out) {
   if (!ctx) return fail(nullptr, EASYSPEC_EINVAL, "ctx is NULL");
+  CHECK_PASSES(ctx);
   if (!ctx->weights_loaded) return fail(ctx, EASYSPEC_ESTATE, "draft_tree_step: no weights loaded");
   if (!tokens_in || !n_nodes || !parents || !tokens_out) return fail(ctx, EASYSPEC_EINVAL, "draft_tree_step: NULL argument");
   const Shape& s = ctx->s;
@@ -605,6 +619,7 @@ extern "C" int easyspec_draft_tree_step(easyspec_ctx* ctx, const int32_t* tokens
 extern "C" int easyspec_calibrate(easyspec_ctx* ctx, const int32_t* tokens, const int32_t* n_tokens, int32_t* next_token_out,
                                   float* logits_out, int32_t logits_rows) {
   if (!ctx) return fail(nullptr, EASYSPEC_EINVAL, "ctx is NULL");
+  CHECK_PASSES(ctx);
   if (!ctx->weights_loaded) return fail(ctx, EASYSPEC_ESTATE, "calibrate: no weights loaded");
   if (!tokens || !n_tokens || !next_token_out) return fail(ctx, EASYSPEC_EINVAL, "calibrate: NULL argument");
   if (logits_rows != 0 && logits_rows != 1) return fail(ctx, EASYSPEC_EINVAL, "calibrate: logits_rows must be 0 or 1");
@@ -796,6 +811,7 @@ extern "C" int easyspec_accept_static(const int32_t* draft, const float* draft_l
 
 extern "C" int easyspec_get_lens(const easyspec_ctx* ctx, int32_t* precise, int32_t* fuzzy) {
   if (!ctx) return fail(nullptr, EASYSPEC_EINVAL, "ctx is NULL");
+  CHECK_PASSES(ctx);
   for (int b = 0; b < ctx->s.B; ++b) {
     if (precise) precise[b] = ctx->precise[b];
     if (fuzzy) fuzzy[b] = ctx->fuzzy[b];
@@ -805,6 +821,7 @@ extern "C" int easyspec_get_lens(const easyspec_ctx* ctx, int32_t* precise, int3
 
 extern "C" int easyspec_truncate(easyspec_ctx* ctx, int32_t b, int32_t new_len) {
   if (!ctx) return fail(nullptr, EASYSPEC_EINVAL, "ctx is NULL");
+  CHECK_PASSES(ctx);
   if (b < 0 || b >= ctx->s.B) return fail(ctx, EASYSPEC_EINVAL, "truncate: sequence %d out of range", b);
   if (new_len < 0 || new_len > ctx->precise[b]) return fail(ctx, EASYSPEC_EINVAL, "truncate: length %d outside 0..%d", new_len, ctx->precise[b]);
   ctx->precise[b] = new_len;
@@ -841,7 +858,7 @@ static int kv_xfer(easyspec_ctx* ctx, int32_t b, void* k, void* v, int32_t n, in
     launch_kv_copy(s, ctx->b, b, k, v, n, to_cache, st);
     HIPCHK(ctx, hipGetLastError());
     HIPCHK(ctx, hipStreamSynchronize(st));
-    return EASYSPEC_OK;
+    return check_passes(ctx);
   }
   void *dk = nullptr, *dv = nullptr;
   HIPCHK(ctx, hipMalloc(&dk, bytes));
@@ -861,7 +878,7 @@ static int kv_xfer(easyspec_ctx* ctx, int32_t b, void* k, void* v, int32_t n, in
       HIPCHK(ctx, hipMemcpyAsync(v, dv, bytes, hipMemcpyDefault, st));
     }
     HIPCHK(ctx, hipStreamSynchronize(st));
-    return EASYSPEC_OK;
+    return check_passes(ctx);
   };
   const int rc = body();
   (void)hipFree(dk);
@@ -871,6 +888,7 @@ static int kv_xfer(easyspec_ctx* ctx, int32_t b, void* k, void* v, int32_t n, in
 
 extern "C" int easyspec_kv_import(easyspec_ctx* ctx, int32_t b, const void* k, const void* v, int32_t n_slots) {
   if (!ctx) return fail(nullptr, EASYSPEC_EINVAL, "ctx is NULL");
+  CHECK_PASSES(ctx);
   if (b < 0 || b >= ctx->s.B) return fail(ctx, EASYSPEC_EINVAL, "kv_import: sequence %d out of range", b);
   if (n_slots < 0 || n_slots > ctx->s.max_ctx) return fail(ctx, EASYSPEC_ECAPACITY, "kv_import: %d slots exceed max_ctx %d", n_slots, ctx->s.max_ctx);
   if (n_slots > 0 && (!k || !v)) return fail(ctx, EASYSPEC_EINVAL, "kv_import: NULL argument");
@@ -884,6 +902,7 @@ extern "C" int easyspec_kv_import(easyspec_ctx* ctx, int32_t b, const void* k, c
 
 extern "C" int easyspec_kv_export(easyspec_ctx* ctx, int32_t b, void* k, void* v, int32_t n_slots) {
   if (!ctx) return fail(nullptr, EASYSPEC_EINVAL, "ctx is NULL");
+  CHECK_PASSES(ctx);
   if (b < 0 || b >= ctx->s.B) return fail(ctx, EASYSPEC_EINVAL, "kv_export: sequence %d out of range", b);
   if (n_slots < 0 || n_slots > ctx->s.max_ctx) return fail(ctx, EASYSPEC_ECAPACITY, "kv_export: %d slots exceed max_ctx %d", n_slots, ctx->s.max_ctx);
   if (n_slots > 0 && (!k || !v)) return fail(ctx, EASYSPEC_EINVAL, "kv_export: NULL argument");
@@ -892,6 +911,7 @@ extern "C" int easyspec_kv_export(easyspec_ctx* ctx, int32_t b, void* k, void* v
 
 extern "C" int easyspec_get_hidden(easyspec_ctx* ctx, float* out, int32_t max_rows, int32_t* n_rows) {
   if (!ctx) return fail(nullptr, EASYSPEC_EINVAL, "ctx is NULL");
+  CHECK_PASSES(ctx);
   if (!out || !n_rows) return fail(ctx, EASYSPEC_EINVAL, "get_hidden: NULL argument");
   if (ctx->last_rows == 0) return fail(ctx, EASYSPEC_ESTATE, "get_hidden: no forward has run");
   if (max_rows < ctx->last_rows) return fail(ctx, EASYSPEC_ECAPACITY, "get_hidden: %d rows needed", ctx->last_rows);
@@ -904,6 +924,13 @@ extern "C" int easyspec_poison_workspaces(easyspec_ctx* ctx) {
   if (!ctx) return fail(nullptr, EASYSPEC_EINVAL, "ctx is NULL");
   // all bits set: a NaN in float32 and in bf16, -1 as an index
   for (const auto& w : ctx->work) HIPCHK(ctx, hipMemsetAsync(w.first, 0xFF, w.second, ctx->stream));
+  return EASYSPEC_OK;
+}
+
+extern "C" int easyspec_set_wait_limit(easyspec_ctx* ctx, int32_t polls) {
+  if (!ctx) return fail(nullptr, EASYSPEC_EINVAL, "ctx is NULL");
+  if (polls < 0) return fail(ctx, EASYSPEC_EINVAL, "set_wait_limit: %d polls", polls);
+  ctx->r.polls = polls ? polls : kResPolls;
   return EASYSPEC_OK;
 }
 
@@ -939,7 +966,7 @@ extern "C" int easyspec_profile_end(easyspec_ctx* ctx, int32_t* n_launches, floa
   }
   *n_launches = (int32_t)(ctx->timer.used / 2);
   *total_ms = sum;
-  return EASYSPEC_OK;
+  return check_passes(ctx);
 }
 
 extern "C" int easyspec_stream_read(const void* buf, int64_t bytes, float* sink, void* hip_stream) {

@@ -102,7 +102,9 @@ struct Resident {
   ResidentCtl* ctl;  // null: the model's passes are separate launches
   void* granules;
   uint32_t* failed;  // pinned host memory
+  int32_t polls;     // polls of one wave, over the whole pass, that may find a value not there yet
 };
+constexpr int kResPolls = 1 << 22;  // about a microsecond each
 constexpr int kResMaxLayers = 64;
 constexpr int kResMaxVocab = 16384;
 

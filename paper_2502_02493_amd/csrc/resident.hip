@@ -12,7 +12,7 @@
 //   * Units are numbered in the order of the launches they replace and handed out by a ticket counter.  A unit only waits
 //     for units of smaller numbers, and those are done or in the hands of workgroups that run: the pass advances however few
 //     of its workgroups the device has room for, whatever else runs beside it.  (Every wait also ends after a bounded
-//     number of polls; a pass that gave up reports it to the context.)
+//     number of polls; a pass that gave up sets a host word, which the context's entry points look at.)
 //   * A workgroup holds one ticket at a time and there are twice as many as the widest phase has units, so that the next
 //     phases' units are already waiting, their weights on the way into registers, when their operands arrive.  A model is
 //     "small" if a wave's share of a row tile fits there in one go (resident_model).
@@ -42,7 +42,6 @@ constexpr int kResThreads = 512, kResWaves = 8;
 constexpr int kResRT2 = 6, kResRT1 = 12;  // k-tiles per wave that fit the registers: two row tiles side by side, one
 constexpr int kResTiles = 96;             // row tiles of 16 of the model width (partial sums of squares in LDS)
 constexpr int kResRedPitch = 20;          // floats per column of 16 rows in the reduction buffer (bank spread)
-constexpr int kResPolls = 1 << 22;        // about a microsecond each
 
 struct ResidentArgs {
   const u32x4 *wqkv, *wo, *wg, *wu, *wd, *wlm;
@@ -58,6 +57,7 @@ struct ResidentArgs {
   ResidentCtl* ctl;
   granule_t* ll;
   uint32_t* failed;
+  int polls;
   int L, d, Hq, Hkv, F, V, HQ, RQKV, B, max_ctx, n_sets;
   float inv_d, eps, scale;
   uint8_t bounds[kResMaxLayers + 1];
@@ -327,7 +327,7 @@ __global__ __launch_bounds__(kResThreads) void resident_kernel(ResidentArgs a, C
   granule_t* const cand = a.ll + (size_t)a.L * map.layer;  // [column][row tile of the head][value, index]
   Poll w;
   w.epoch = __hip_atomic_load(&a.ctl->epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  w.left = kResPolls;
+  w.left = a.polls;
   w.failed = a.failed;
   // A workgroup asks for its next unit when the sums of this one are on their way (wave 1; wave 0 finishes the unit).
   auto ask_next = [&] {
@@ -831,7 +831,7 @@ void launch_resident(const Shape& s, const Buffers& b, const Resident& r, const 
   a.g_any = (const float*)r.granules;
   a.kc = b.kc; a.vc = b.vc; a.H = b.H;
   a.tokens = tokens; a.logits = logits; a.tokens_out = tokens_out;
-  a.ctl = r.ctl; a.ll = (granule_t*)r.granules; a.failed = r.failed;
+  a.ctl = r.ctl; a.ll = (granule_t*)r.granules; a.failed = r.failed; a.polls = r.polls;
   a.L = s.L; a.d = s.d; a.Hq = s.Hq; a.Hkv = s.Hkv; a.F = s.F; a.V = s.V; a.HQ = s.HQ; a.RQKV = s.RQKV; a.B = s.B; a.max_ctx = s.max_ctx;
   a.n_sets = n_sets;
   a.inv_d = 1.0f / (float)s.d; a.eps = s.eps; a.scale = 1.0f / sqrtf((float)s.hd);

@@ -16,7 +16,7 @@ extern "C" {
 
 /* Fill every workspace a forward pass uses between its kernels (residual stream, norm operands and partial
  * sums, queries, attention output and split-KV partials, parked Attnoutputs, MLP activations, argmax
- * candidates) with NaN bit patterns, on the context's stream.  Weights, the KV cache and the lengths are not
+ * candidates; the values of one-launch passes, which then carry no pass's tag) with NaN bit patterns, on the context's stream.  Weights, the KV cache and the lengths are not
  * touched.  A forward pass writes each of these before it reads it, so a call between two passes must
  * change no result bit: for tests of exactly that (a kernel that read a workspace entry no earlier kernel
  * of the same pass wrote would turn its output into NaN). */
@@ -100,6 +100,10 @@ int easyspec_attention_stage_walk(int32_t n_loads, int64_t *report);
  * pair's elapsed time is that kernel's begin-to-end time.  With EASYSPEC_OP_ALL every launch of
  * the forward pass is timed, which is what a kernel trace does and gives the figures that compare
  * with one (a timed kernel that follows an untimed one also counts part of its predecessor's tail).
+ * Passes of small models that are one launch otherwise run as separate launches between profile_begin
+ * and profile_end, whatever the class: the launches of the classes are what is timed, and the one launch
+ * does the work of all.  The time of that one is the call's (the caller's own events around it), and the
+ * results of timed passes may differ from the untimed ones' in their last bits.
  * profile_end synchronises the stream and returns the number of timed launches, the sum of their
  * durations in milliseconds and, where launch_ms / launch_op are not NULL (host, max_launches
  * entries each), every launch's duration and kernel class in launch order (the embedding gather

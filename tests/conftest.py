@@ -17,3 +17,11 @@ def oracle():
     from oracle import easyspec_oracle as eso
     eso.lib()
     return eso
+
+
+@pytest.fixture(params=["one launch", "launches"])
+def route(request, monkeypatch):
+    """Passes of small models as the library runs them (one launch where that is faster), and all as separate launches."""
+    if request.param == "launches":
+        monkeypatch.setenv("EASYSPEC_RESIDENT", "0")
+    return request.param

@@ -149,6 +149,7 @@ def test_error_paths_leave_state_unchanged(gpu):
         es.easyspec_destroy(ctx)
 
 
+@pytest.mark.usefixtures("route")
 @pytest.mark.parametrize("dtype", ["fp32", "bf16"])
 def test_dropped_fuzzy_slots_are_never_read(gpu, dtype):
     """After calibration the slots beyond the precise length are dead: filling them with NaN
@@ -187,14 +188,17 @@ def test_dropped_fuzzy_slots_are_never_read(gpu, dtype):
     assert np.array_equal(a1, b1) and np.array_equal(a2, b2)
 
 
+@pytest.mark.usefixtures("route")
 @pytest.mark.parametrize("shape,dtype,bounds", [("tiny", "fp32", [0, 1, 3, 4]), ("tiny", "bf16", [0, 4]),
                                                 ("tiny_qwen", "bf16", [0, 1, 4, 5])])
 def test_workspaces_hold_nothing_between_calls(gpu, monkeypatch, shape, dtype, bounds):
     """Every workspace between the kernels of a pass (residual stream, norm operands and partial sums,
     queries, attention outputs, split-KV partials, parked Attnoutputs, MLP activations, argmax candidates)
-    is filled with NaN before every call: logits, drafted ids and the cache keep every bit.  Covers
-    prefill in chunks, split-KV attention with a merge (context beyond one chunk), chain steps, a tree
-    level on the vector kernel and on the matrix cores, a two-fragment calibration, and the full-layer mode."""
+    is filled with NaN before every call: logits, drafted ids and the cache keep every bit.  As launches it
+    covers prefill in chunks, split-KV attention with a merge (context beyond one chunk), chain steps, a tree
+    level on the vector kernel and on the matrix cores, a two-fragment calibration, and the full-layer mode;
+    as the library runs them the one-launch passes take those that fit them (fp32 contexts below 320 slots, bf16
+    all but the widest calibrations and the full-layer mode), the tagged values among the workspaces."""
     import paper_2502_02493_amd as es
     cfg = synth.model_shape(shape, dtype=dtype)
     w = synth.make_weights(cfg, 650)
@@ -284,6 +288,7 @@ def test_per_launch_timing_counts_every_launch(gpu):
         g.close()
 
 
+@pytest.mark.usefixtures("route")
 def test_repeated_runs_are_bit_identical(gpu):
     """Fixed summation orders everywhere: the same calls give the same bits."""
     cfg = synth.model_shape("tiny_qwen", dtype="bf16")

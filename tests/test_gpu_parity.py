@@ -5,7 +5,8 @@ on logits and hidden states, with a bound on the largest single deviation beside
 plain oracle (no activation rounding) the required 2e-2; token ids and lengths exact (ids are compared
 wherever the oracle's top-1/top-2 logit gap exceeds the numerical noise floor, so that a genuine
 near-tie between two vocabulary entries cannot fail a correct kernel; the count of skipped
-comparisons is asserted to be small)."""
+comparisons is asserted to be small).  Small models run both as the library runs them and as separate
+launches (fixture `route`)."""
 import numpy as np
 import pytest
 
@@ -107,6 +108,7 @@ def iteration_parity(oracle, gpu, cfg, seed, bounds, prompt_len, gamma, n_iters=
         g.close()
 
 
+@pytest.mark.usefixtures("route")
 @pytest.mark.parametrize("bounds", [[0, 1, 3, 4], [0, 1, 2, 3, 4], [0, 2, 4], [0, 4]])
 def test_tiny_fp32(oracle, gpu, bounds):
     """Config 1: tiny fp32 decoder, prompt 128, group size 2 (packed policy gives {0},{1,2},{3}),
@@ -123,17 +125,20 @@ def test_tiny_fp32_default_strategy_is_config1(oracle, gpu):
         assert list(es.easyspec_default_groups(L, N, pol)) == list(oracle.default_groups(L, N, name))
 
 
+@pytest.mark.usefixtures("route")
 @pytest.mark.parametrize("dtype", ["fp32", "bf16"])
 def test_tiny_qwen_shape(oracle, gpu, dtype):
     """7 query heads per KV head, QKV bias, head_dim 64, vocabulary not a multiple of 16."""
     iteration_parity(oracle, gpu, synth.model_shape("tiny_qwen", dtype=dtype), 200, [0, 1, 4, 5], 37, 5)
 
 
+@pytest.mark.usefixtures("route")
 @pytest.mark.parametrize("bounds", [[0, 1, 3, 4], [0, 4]])
 def test_tiny_bf16(oracle, gpu, bounds):
     iteration_parity(oracle, gpu, synth.model_shape("tiny", dtype="bf16"), 300, bounds, 70, 4)
 
 
+@pytest.mark.usefixtures("route")
 @pytest.mark.parametrize("shape,bounds", [("tiny", [0, 1, 3, 4]), ("tiny", [0, 4]), ("tiny_qwen", [0, 1, 4, 5])])
 def test_tiny_bf16_against_plain_oracle(oracle, gpu, shape, bounds):
     """The HIP path against an oracle that shares none of its numeric design: activations unrounded,

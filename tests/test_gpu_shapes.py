@@ -230,6 +230,7 @@ def test_batch4_ragged_long_contexts(oracle, gpu):
         g.close()
 
 
+@pytest.mark.usefixtures("route")
 @pytest.mark.parametrize("dtype", ["fp32", "bf16"])
 def test_batch16_ragged_contexts(oracle, gpu, dtype):
     """Sixteen sequences whose contexts run from 1 slot to several split-KV chunks in one launch: every

@@ -80,12 +80,14 @@ def tree_parity(oracle, gpu, cfg, seed, bounds, prompt_len, widths, max_ctx=None
         g.close()
 
 
+@pytest.mark.usefixtures("route")
 @pytest.mark.parametrize("bounds", [[0, 1, 3, 4], [0, 4]])
 @pytest.mark.parametrize("dtype", ["fp32", "bf16"])
 def test_tree_tiny(oracle, gpu, bounds, dtype):
     tree_parity(oracle, gpu, synth.model_shape("tiny", dtype=dtype), 500, bounds, 70, [4, 4, 4, 4])
 
 
+@pytest.mark.usefixtures("route")
 def test_tree_widths_of_the_ablation(oracle, gpu):
     """Tree widths 1, 4, 8, 12 (the paper's ablation, Sec. 4.3), five levels: up to 60 nodes."""
     cfg = synth.model_shape("tiny", dtype="bf16")
@@ -93,6 +95,7 @@ def test_tree_widths_of_the_ablation(oracle, gpu):
         tree_parity(oracle, gpu, cfg, 510 + width, [0, 1, 3, 4], 33, [width] * 5)
 
 
+@pytest.mark.usefixtures("route")
 def test_tree_qwen_shape_ragged(oracle, gpu):
     """7 query heads per KV head, bias, head_dim 64; a tree region that straddles an attention chunk boundary."""
     cfg = synth.model_shape("tiny_qwen", dtype="bf16")
@@ -123,6 +126,7 @@ def test_tree_chunk_without_visible_slot(oracle, gpu, monkeypatch):
         tree_parity(oracle, gpu, cfg, 540, [0, 1, 3, 4], prompt_len, [16, 16, 16, 16], make_levels=levels_with_late_roots)
 
 
+@pytest.mark.usefixtures("route")
 def test_tree_two_sequences_ragged(oracle, gpu):
     """Two sequences with different contexts grow different trees in the same calls (3 + 2 nodes,
     then 4 + 5 nodes); a third call extends only the second sequence."""

@@ -13,8 +13,9 @@
 //     for units of smaller numbers, and those are done or in the hands of workgroups that run: the pass advances however few
 //     of its workgroups the device has room for, whatever else runs beside it.  (Every wait also ends after a bounded
 //     number of polls; a pass that gave up sets a host word, which the context's entry points look at.)
-//   * A workgroup holds one ticket at a time and there are twice as many as the widest phase has units, so that the next
-//     phases' units are already waiting, their weights on the way into registers, when their operands arrive.  A model is
+//   * A workgroup holds one ticket at a time and there are twice as many as the MLP or the head has units (at most one per CU),
+//     so that the next phases' units are already waiting, their weights on the way into registers, when their operands
+//     arrive.  Phases with more units than that (stacked QKV and O, many heads, large vocabularies) go in rounds.  A model is
 //     "small" if a wave's share of a row tile fits there in one go (resident_model).
 //   * The operand is put into LDS once per workgroup.  Up to four columns of an fp32 model are multiplied on the vector
 //     ALUs (an fp32 MFMA takes 32 cycles for its 16 columns, used or not), everything else on the matrix cores.
@@ -25,7 +26,7 @@
 // tile each instead of four (end of a tile 1.5 -> 0.8).  In the attention the steps of all heads go side by side, the slots of
 // this pass are part of the last run instead of a batch of their own, and with seven or eight heads half of the waves take half
 // of them: 5.5 -> 3.2 us at 61 slots and seven heads.
-// us a call, launches and resident: draft step of the 256-wide fp32 model of 4 layers 98 -> 56; an iteration of the 448-wide
+// Where it is taken: resident_pass.  us a call, launches and resident: draft step of the 256-wide fp32 model of 4 layers 98 -> 56; an iteration of the 448-wide
 // one of 5 layers (calibration of 5 tokens and three steps, vocabulary of 1000) 594 -> 380.
 #include "launch_common.hpp"
 

@@ -49,9 +49,11 @@ __global__ void accept_kernel(const int32_t* draft, const int32_t* target, int b
 // are one contiguous run on both sides, so a workgroup moves a piece of one run: no division per element, and
 // kKvPieces 16-byte loads per thread are in flight before the first store.  Bound by memory (every byte read once
 // and written once): an import or export of 2048 slots of the 8B shape (268 MB each way, 537 MB of traffic).  Ordinary loads,
-// non-temporal stores, few pieces a thread: us a call with its wait, 8 pieces 136 (both non-temporal), 4 pieces 97 (both), 112
-// (neither), 79 (loads only), 74 .. 84 (stores only), 2 pieces 73 (stores only), 1 piece 74 .. 80; import and export one after
-// the other on arrays of their own 282 -> 205.
+// non-temporal stores, two pieces a thread.  us a call with its wait on arrays not used just before, 8 pieces with both
+// non-temporal and this: 136 .. 141 -> 102 .. 104 (5.2 TB/s; the kernel alone 94.5, 5.7 TB/s), 512 slots 47 -> 37, 8192 slots
+// 505 -> 378, 16 slots 15 -> 14.  One import again and again on the same arrays, which the caches then serve in part: 8 pieces
+// 136 (both non-temporal), 4 pieces 97 (both), 112 (neither), 79 (loads only), 74 .. 84 (stores only), 2 pieces 73 (stores
+// only), 1 piece 74 .. 80.
 // grid = (pieces of a run, layer x KV head, K / V).
 constexpr int kKvThreads = 256, kKvPieces = 2;
 __global__ __launch_bounds__(kKvThreads) void kv_copy_kernel(u32x4* kc, u32x4* vc, u32x4* k_user, u32x4* v_user, size_t layer_pitch,

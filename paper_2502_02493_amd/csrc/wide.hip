@@ -18,11 +18,11 @@
 //     lines again: gate/up at 24 columns 55 us against 42.
 //   * Few row tiles (QKV, O, down: 256 to 384) are spread over the CUs by splitting K; the fp32 partial sums are added
 //     in split order by the kernel that does what follows anyway (rotary and cache write; residual and norm operand).
-// Measured at the 8B shape.  A prefill of 16 x 16 tokens (256 columns): 41.8 -> 9.5 .. 10.0 ms (eight pairs of 16-column
-// passes before); gate/up 117 us a layer (137 GFLOP with both terms and the idle rows: 1.2 PFLOP/s, where a loop of
+// Measured at the 8B shape.  A prefill of 16 x 16 tokens (256 columns): 41.8 -> 9.4 .. 9.5 ms (eight pairs of 16-column
+// passes before); gate/up 111 us a layer (137 GFLOP with both terms and the idle rows: 1.2 PFLOP/s, where a loop of
 // nothing but these MFMAs on random operands runs at 2.1 and the same kernel without its weight loads takes 0.77 of the
-// time), down 78, QKV 36, O 24.  4 x 6 tokens at contexts 4096 .. 32768 (24 columns): 6.57 -> 5.2 .. 5.4 ms, memory-bound:
-// gate/up 42 us (5.6 TB/s), down 24.
+// time), down 52, QKV 33, O 23, and 22 for the launches that finish the split ones.  4 x 6 tokens at contexts 4096 .. 32768 (24
+// columns): 6.57 -> 5.2 .. 5.4 ms, memory-bound: gate/up 40 us (5.8 TB/s), down 22.
 // On the way there (256 columns, mean of gate/up and QKV): LDS fragments read next to their use 141 us; read ahead 100;
 // weights two stages ahead but behind branches 94; unconditional requests 76; three operand buffers the same 76; weight
 // requests spread over the stage, raised wave priority around the products: no change.

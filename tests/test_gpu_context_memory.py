@@ -51,7 +51,5 @@ def test_tagged_values_of_small_models():
 
     held(16400)
     one, apart = held(16384), held(16400)
-    # Bound: half-way between room for 2 columns and for 16.  What the device reports as free moves by some 5 MB between two
-    # contexts of one size (pages that the runtime keeps of freed ones), a tenth of the distance to either.
-    column = 64 * 14784 * 8
-    assert one - apart <= 9 * column, (one, apart)
+    values = 64 * 2 * 14784 * 8
+    assert values - (4 << 20) <= one - apart <= values + (8 << 20), (one, apart)

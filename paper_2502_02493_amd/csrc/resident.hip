@@ -59,27 +59,27 @@ struct ResidentArgs {
   granule_t* ll;
   uint32_t* failed;
   int polls;
-  int L, d, Hq, Hkv, F, V, HQ, RQKV, B, max_ctx, n_sets, cols;
+  int L, d, Hq, Hkv, F, V, HQ, RQKV, B, max_ctx, n_sets;
   float inv_d, eps, scale;
   uint8_t bounds[kResMaxLayers + 1];
   uint8_t col0[kMaxCols];  // first column of the column's sequence
 };
 
-// Places of the granules: per layer [columns][...] of q | k | v, attention output, residual before the MLP (its partial
+// Places of the granules: per layer [16 columns][...] of q | k | v, attention output, residual before the MLP (its partial
 // sums of squares behind every column's values), Attnoutput, MLP activations, residual after the MLP; then the argmax candidates.
 struct ResidentMap {
   int qkv, ao, h1, a, act, h2, layer, hp;
 };
-ES_HD ResidentMap resident_map(int d, int HQ, int RQKV, int F, int cols) {
+ES_HD ResidentMap resident_map(int d, int HQ, int RQKV, int F) {
   ResidentMap m;
   m.hp = d + d / 16;
   m.qkv = 0;
-  m.ao = m.qkv + cols * RQKV;
-  m.h1 = m.ao + cols * HQ;
-  m.a = m.h1 + cols * m.hp;
-  m.act = m.a + cols * d;
-  m.h2 = m.act + cols * F;
-  m.layer = m.h2 + cols * m.hp;
+  m.ao = m.qkv + kMaxCols * RQKV;
+  m.h1 = m.ao + kMaxCols * HQ;
+  m.a = m.h1 + kMaxCols * m.hp;
+  m.act = m.a + kMaxCols * d;
+  m.h2 = m.act + kMaxCols * F;
+  m.layer = m.h2 + kMaxCols * m.hp;
   return m;
 }
 
@@ -322,7 +322,7 @@ __global__ __launch_bounds__(kResThreads) void resident_kernel(ResidentArgs a, C
   __shared__ ResidentShared sh;
   void* const xs = dyn_red;
   const int d = a.d, ntile = d / 16;
-  const ResidentMap map = resident_map(d, a.HQ, a.RQKV, a.F, a.cols);
+  const ResidentMap map = resident_map(d, a.HQ, a.RQKV, a.F);
   const int nkt_d = d / KT, nkt_q = a.HQ / KT, nkt_f = a.F / KT;
   const int n_pairs = a.RQKV / 2, u_qkv = ceil_div(n_pairs, 16), u_f = ceil_div(a.F, 16), u_v = ceil_div(a.V, 16);
   granule_t* const cand = a.ll + (size_t)a.L * map.layer;  // [column][row tile of the head][value, index]
@@ -758,13 +758,9 @@ bool resident_model(const Shape& s) {
          s.d / kt <= kResRT2 * kResWaves && s.HQ / kt <= kResRT1 * kResWaves && s.F / kt <= kResRT1 * kResWaves;
 }
 
-// Columns of a pass at most: those whose operands of a layer are 24576 granules (see resident_pass)
-static int resident_cols(const Shape& s) { return std::min(kMaxCols, 24576 / (2 * s.d + s.HQ + s.F)); }
-
 size_t resident_granule_bytes(const Shape& s) {
-  const int cols = resident_cols(s);
-  const ResidentMap m = resident_map(s.d, s.HQ, s.RQKV, s.F, cols);
-  return ((size_t)s.L * m.layer + (size_t)cols * ceil_div(s.V, 16) * 2) * sizeof(granule_t);
+  const ResidentMap m = resident_map(s.d, s.HQ, s.RQKV, s.F);
+  return ((size_t)s.L * m.layer + (size_t)kMaxCols * ceil_div(s.V, 16) * 2) * sizeof(granule_t);
 }
 
 static size_t resident_lds(const Shape& s, int n) {
@@ -796,7 +792,7 @@ bool resident_pass(const Shape& s, const Cols& c, const int32_t* bounds, int n_s
   const int most = s.dtype == 1 ? 640 : 320;
   int ctx = 0;
   for (int i = 0; i < c.n; ++i) ctx = std::max(ctx, c.pos[i] + 1);
-  if (ctx > most || c.n > resident_cols(s) || sizeof(ResidentShared) + resident_lds(s, c.n) > 150 * 1024) return false;
+  if (ctx > most || c.n * (2 * s.d + s.HQ + s.F) > 24576 || sizeof(ResidentShared) + resident_lds(s, c.n) > 150 * 1024) return false;
   const long grid = resident_grid(s), ntile = s.d / 16, head = ceil_div(s.V, 16);
   auto rounds = [&](long units) { return (units + grid - 1) / grid; };
   const long r_gu = rounds(s.F / 16), r_down = rounds(ntile), r_head = rounds(head);
@@ -838,7 +834,7 @@ void launch_resident(const Shape& s, const Buffers& b, const Resident& r, const 
   a.tokens = tokens; a.logits = logits; a.tokens_out = tokens_out;
   a.ctl = r.ctl; a.ll = (granule_t*)r.granules; a.failed = r.failed; a.polls = r.polls;
   a.L = s.L; a.d = s.d; a.Hq = s.Hq; a.Hkv = s.Hkv; a.F = s.F; a.V = s.V; a.HQ = s.HQ; a.RQKV = s.RQKV; a.B = s.B; a.max_ctx = s.max_ctx;
-  a.n_sets = n_sets; a.cols = resident_cols(s);
+  a.n_sets = n_sets;
   a.inv_d = 1.0f / (float)s.d; a.eps = s.eps; a.scale = 1.0f / sqrtf((float)s.hd);
   for (int j = 0; j <= n_sets; ++j) a.bounds[j] = (uint8_t)bounds[j];
   for (int i = 0; i < c.n; ++i) a.col0[i] = (uint8_t)(i > 0 && c.seq[i] == c.seq[i - 1] ? a.col0[i - 1] : i);

@@ -22,11 +22,10 @@ extern "C" {
  * of the same pass wrote would turn its output into NaN). */
 int easyspec_poison_workspaces(easyspec_ctx *ctx);
 
-/* How often a wave of a one-launch pass (easyspec.h, Conventions) may look for a value that is not there yet, over the whole
- * pass, before the pass gives up; 0 = the library's own limit (some seconds).  Taken by the passes enqueued (or captured) after
- * the call; no effect on models whose passes are separate launches.  For tests of what a pass that gave up does to the context:
- * with a limit of 1 every pass gives up, and its kernel ends normally.  EASYSPEC_EINVAL for a negative limit. */
-int easyspec_set_wait_limit(easyspec_ctx *ctx, int32_t polls);
+/* on != 0: the one-launch passes (easyspec.h, Conventions) enqueued or captured after the call give up at the first value that is
+ * not there yet, which every pass meets; their kernels end normally.  For tests of what that does to the context.  There is such
+ * a kernel for fp32 models with two query heads per KV head, EASYSPEC_EINVAL for others. */
+int easyspec_force_give_up(easyspec_ctx *ctx, int32_t on);
 
 /* Streaming-read probe for roofline reports: reads `bytes` (a positive multiple of 16) of the
  * caller's device buffer once, with the loads the weight stream uses (16-byte, non-temporal,

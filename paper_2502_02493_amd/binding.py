@@ -23,7 +23,7 @@ EXPORTS = ["easyspec_create", "easyspec_destroy", "easyspec_load_weights", "easy
            "easyspec_default_groups", "easyspec_draft_step", "easyspec_calibrate", "easyspec_greedy_accept", "easyspec_greedy_accept_host",
            "easyspec_accept", "easyspec_accept_workspace_bytes", "easyspec_accept_static", "easyspec_accept_static_max_bytes", "easyspec_draft_tree_step", "easyspec_set_parallel_mode", "easyspec_stream_read", "easyspec_stream_read_sink_floats", "easyspec_attention_cut", "easyspec_weight_walk", "easyspec_wide_walk", "easyspec_attention_stage_walk",
            "easyspec_get_lens", "easyspec_truncate", "easyspec_kv_import", "easyspec_kv_export",
-           "easyspec_get_hidden", "easyspec_poison_workspaces", "easyspec_set_wait_limit", "easyspec_step_bytes", "easyspec_profile_begin", "easyspec_profile_end",
+           "easyspec_get_hidden", "easyspec_poison_workspaces", "easyspec_force_give_up", "easyspec_step_bytes", "easyspec_profile_begin", "easyspec_profile_end",
            "easyspec_last_error"]
 EASYSPEC_OP_QKV, EASYSPEC_OP_ATTN, EASYSPEC_OP_OPROJ, EASYSPEC_OP_GATEUP, EASYSPEC_OP_DOWN, EASYSPEC_OP_HEAD, EASYSPEC_OP_ALL = range(7)
 
@@ -86,7 +86,7 @@ def load_library():
         L.easyspec_get_hidden.argtypes = [vp, vp, i32, C.POINTER(i32)]
         L.easyspec_step_bytes.argtypes = [vp]
         L.easyspec_poison_workspaces.argtypes = [vp]
-        L.easyspec_set_wait_limit.argtypes = [vp, i32]
+        L.easyspec_force_give_up.argtypes = [vp, i32]
         L.easyspec_stream_read.argtypes = [vp, C.c_int64, vp, vp]
         L.easyspec_stream_read_sink_floats.argtypes = []
         L.easyspec_attention_cut.argtypes = [C.POINTER(easyspec_config), vp, i32, i32, vp, vp]
@@ -308,8 +308,8 @@ def easyspec_poison_workspaces(ctx):
     _check(load_library().easyspec_poison_workspaces(ctx), ctx)
 
 
-def easyspec_set_wait_limit(ctx, polls: int):
-    _check(load_library().easyspec_set_wait_limit(ctx, int(polls)), ctx)
+def easyspec_force_give_up(ctx, on: bool):
+    _check(load_library().easyspec_force_give_up(ctx, int(on)), ctx)
 
 
 def easyspec_step_bytes(ctx) -> int:

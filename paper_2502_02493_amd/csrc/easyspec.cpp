@@ -244,7 +244,6 @@ extern "C" int easyspec_create(const easyspec_config* cfg, void* hip_stream, eas
       ALLOC_WORK(ctx, r.granules, resident_granule_bytes(s));
       HIPCHK(ctx, hipHostMalloc((void**)&r.failed, sizeof(uint32_t), hipHostMallocDefault));
       *r.failed = 0;
-      r.polls = kResPolls;
       ResidentCtl ctl;
       memset(&ctl, 0, sizeof ctl);
       ctl.epoch = 1;  // cleared granules are of no pass
@@ -927,10 +926,10 @@ extern "C" int easyspec_poison_workspaces(easyspec_ctx* ctx) {
   return EASYSPEC_OK;
 }
 
-extern "C" int easyspec_set_wait_limit(easyspec_ctx* ctx, int32_t polls) {
+extern "C" int easyspec_force_give_up(easyspec_ctx* ctx, int32_t on) {
   if (!ctx) return fail(nullptr, EASYSPEC_EINVAL, "ctx is NULL");
-  if (polls < 0) return fail(ctx, EASYSPEC_EINVAL, "set_wait_limit: %d polls", polls);
-  ctx->r.polls = polls ? polls : kResPolls;
+  if (!resident_hasty_model(ctx->s)) return fail(ctx, EASYSPEC_EINVAL, "force_give_up: only fp32 models of one-launch passes with two query heads per KV head");
+  ctx->r.hasty = on != 0;
   return EASYSPEC_OK;
 }
 

@@ -102,9 +102,8 @@ struct Resident {
   ResidentCtl* ctl;  // null: the model's passes are separate launches
   void* granules;
   uint32_t* failed;  // pinned host memory
-  int32_t polls;     // polls of one wave, over the whole pass, that may find a value not there yet
+  int32_t hasty;     // 1: passes give up at the first value that is not there yet (tests)
 };
-constexpr int kResPolls = 1 << 22;  // about a microsecond each
 constexpr int kResMaxLayers = 64;
 constexpr int kResMaxVocab = 16384;
 
@@ -228,6 +227,7 @@ bool resident_model(const Shape& s);
 bool resident_pass(const Shape& s, const Cols& c, const int32_t* bounds, int n_sets);
 size_t resident_granule_bytes(const Shape& s);
 hipError_t resident_prepare(const Shape& s);
+bool resident_hasty_model(const Shape& s);  // is there a kernel for Resident::hasty?
 void launch_resident(const Shape& s, const Buffers& b, const Resident& r, const Cols& c, const int32_t* tokens, const int32_t* bounds, int n_sets,
                      float* logits, int32_t* tokens_out, hipStream_t st);
 void launch_accept(const int32_t* draft, const int32_t* target, int batch, int gamma, int32_t* accept_len,

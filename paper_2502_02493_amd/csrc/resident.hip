@@ -43,6 +43,7 @@ constexpr int kResThreads = 512, kResWaves = 8;
 constexpr int kResRT2 = 6, kResRT1 = 12;  // k-tiles per wave that fit the registers: two row tiles side by side, one
 constexpr int kResTiles = 96;             // row tiles of 16 of the model width (partial sums of squares in LDS)
 constexpr int kResRedPitch = 20;          // floats per column of 16 rows in the reduction buffer (bank spread)
+constexpr int kResPolls = 1 << 22;        // about a microsecond each
 
 struct ResidentArgs {
   const u32x4 *wqkv, *wo, *wg, *wu, *wd, *wlm;
@@ -58,7 +59,6 @@ struct ResidentArgs {
   ResidentCtl* ctl;
   granule_t* ll;
   uint32_t* failed;
-  int polls;
   int L, d, Hq, Hkv, F, V, HQ, RQKV, B, max_ctx, n_sets;
   float inv_d, eps, scale;
   uint8_t bounds[kResMaxLayers + 1];
@@ -316,7 +316,8 @@ __device__ __forceinline__ void resident_gemm(const ResidentArgs& a, int tid, in
 
 enum { kPhQkv, kPhAttn, kPhO, kPhGateUp, kPhDown, kPhHead, kPhArgmax, kPhEnd };
 
-template <typename T, int G>
+// POLLS: how many polls a wave may make in vain over the whole pass.  A constant: as an argument it costs a pass 0.6 .. 1 us.
+template <typename T, int G, int POLLS = kResPolls>
 __global__ __launch_bounds__(kResThreads) void resident_kernel(ResidentArgs a, Cols c) {
   constexpr int HD = 64, EPL = Tr<T>::EPL, KT = Tr<T>::KT, LPS = HD / EPL, SPW = 64 / LPS;
   __shared__ ResidentShared sh;
@@ -328,7 +329,7 @@ __global__ __launch_bounds__(kResThreads) void resident_kernel(ResidentArgs a, C
   granule_t* const cand = a.ll + (size_t)a.L * map.layer;  // [column][row tile of the head][value, index]
   Poll w;
   w.epoch = __hip_atomic_load(&a.ctl->epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  w.left = a.polls;
+  w.left = POLLS;
   w.failed = a.failed;
   // A workgroup asks for its next unit when the sums of this one are on their way (wave 1; wave 0 finishes the unit).
   auto ask_next = [&] {
@@ -817,9 +818,16 @@ static const void* resident_fn(int G) {
   return nullptr;
 }
 
+bool resident_hasty_model(const Shape& s) { return resident_model(s) && s.dtype == 0 && s.Hq == 2 * s.Hkv; }
+
 hipError_t resident_prepare(const Shape& s) {
   const void* f = s.dtype == 1 ? resident_fn<bf16_t>(s.Hq / s.Hkv) : resident_fn<float>(s.Hq / s.Hkv);
-  return hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 150 * 1024 - (int)sizeof(ResidentShared));
+  const int lds = 150 * 1024 - (int)sizeof(ResidentShared);
+  if (resident_hasty_model(s)) {
+    const hipError_t e = hipFuncSetAttribute((const void*)resident_kernel<float, 2, 1>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    if (e != hipSuccess) return e;
+  }
+  return hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
 }
 
 void launch_resident(const Shape& s, const Buffers& b, const Resident& r, const Cols& c, const int32_t* tokens, const int32_t* bounds, int n_sets,
@@ -832,7 +840,7 @@ void launch_resident(const Shape& s, const Buffers& b, const Resident& r, const 
   a.g_any = (const float*)r.granules;
   a.kc = b.kc; a.vc = b.vc; a.H = b.H;
   a.tokens = tokens; a.logits = logits; a.tokens_out = tokens_out;
-  a.ctl = r.ctl; a.ll = (granule_t*)r.granules; a.failed = r.failed; a.polls = r.polls;
+  a.ctl = r.ctl; a.ll = (granule_t*)r.granules; a.failed = r.failed;
   a.L = s.L; a.d = s.d; a.Hq = s.Hq; a.Hkv = s.Hkv; a.F = s.F; a.V = s.V; a.HQ = s.HQ; a.RQKV = s.RQKV; a.B = s.B; a.max_ctx = s.max_ctx;
   a.n_sets = n_sets;
   a.inv_d = 1.0f / (float)s.d; a.eps = s.eps; a.scale = 1.0f / sqrtf((float)s.hd);
@@ -840,6 +848,10 @@ void launch_resident(const Shape& s, const Buffers& b, const Resident& r, const 
   for (int i = 0; i < c.n; ++i) a.col0[i] = (uint8_t)(i > 0 && c.seq[i] == c.seq[i - 1] ? a.col0[i - 1] : i);
   const dim3 grid(resident_grid(s)), blk(kResThreads);
   const size_t lds = resident_lds(s, c.n);
+  if (r.hasty) {
+    ES_LAUNCH((resident_kernel<float, 2, 1>), grid, blk, lds, st, a, c);
+    return;
+  }
 #define RES_CASE(G_) \
   case G_: \
     if (s.dtype == 1) ES_LAUNCH((resident_kernel<bf16_t, G_>), grid, blk, lds, st, a, c); \

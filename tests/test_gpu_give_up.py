@@ -1,6 +1,6 @@
 """What a one-launch pass of a small model that gave up waiting does to its context (include/easyspec.h, Conventions): every entry
 point that uses or hands out the context's state refuses, whatever route the call would take, and another context is untouched.
-The give-up is forced from the host by a limit of one poll on the kernel's own bounded wait; the kernel ends normally."""
+The give-up is forced from the host, which picks the kernel whose own bounded wait has a limit of one poll; it ends normally."""
 import numpy as np
 import pytest
 
@@ -70,11 +70,11 @@ def test_every_entry_point_refuses(pair, monkeypatch):
     import paper_2502_02493_amd as es
     a, b, st = pair
     want = b.draft_step({0: 9})[1]
-    es.easyspec_set_wait_limit(a.ctx, 1)
+    es.easyspec_force_give_up(a.ctx, 1)
     es.easyspec_draft_step(a.ctx, a.tok_in, a.tok_out, a.logits)  # gives up; returns before it does
     st.synchronize()
     refuses_everything(a, monkeypatch)
-    es.easyspec_set_wait_limit(a.ctx, 0)                           # for good: what the pass left behind stays wrong
+    es.easyspec_force_give_up(a.ctx, 0)                           # for good: what the pass left behind stays wrong
     refuses(es.easyspec_get_lens, a.ctx, 2)
     es.easyspec_truncate(b.ctx, 0, 4)
     assert np.array_equal(b.draft_step({0: 9})[1], want)           # the other context goes on
@@ -86,7 +86,7 @@ def test_calls_that_synchronise_look_again(pair, entry):
     import paper_2502_02493_amd as es
     a, _, _ = pair
     k = np.zeros((a.cfg["n_layers"], a.cfg["n_kv_heads"], 4, a.cfg["head_dim"]), np.float32)
-    es.easyspec_set_wait_limit(a.ctx, 1)
+    es.easyspec_force_give_up(a.ctx, 1)
     es.easyspec_draft_step(a.ctx, a.tok_in, a.tok_out, a.logits)
     if entry == "profile_end":
         es.easyspec_profile_begin(a.ctx, es.EASYSPEC_OP_ALL, 4)
@@ -102,10 +102,10 @@ def test_a_replayed_pass(pair, monkeypatch):
     import paper_2502_02493_amd as es
     a, _, st = pair
     graph = torch.cuda.CUDAGraph()
-    es.easyspec_set_wait_limit(a.ctx, 1)
+    es.easyspec_force_give_up(a.ctx, 1)
     with torch.cuda.graph(graph, stream=st):
         es.easyspec_draft_step(a.ctx, a.tok_in, a.tok_out, a.logits)
-    es.easyspec_set_wait_limit(a.ctx, 0)
+    es.easyspec_force_give_up(a.ctx, 0)
     with torch.cuda.stream(st):
         a.draft_step({0: 5})                                       # a pass with the ordinary limit: all is well
         graph.replay()
@@ -113,14 +113,14 @@ def test_a_replayed_pass(pair, monkeypatch):
     refuses_everything(a, monkeypatch)
 
 
-def test_the_limit_of_a_model_of_launches(gpu):
+@pytest.mark.parametrize("over", [dict(head_dim=128, n_kv_heads=2), dict(dtype="bf16"), dict(n_kv_heads=1)])
+def test_models_without_such_a_kernel(gpu, over):
     import paper_2502_02493_amd as es
-    cfg = synth.model_shape("tiny", head_dim=128, n_q_heads=2, n_kv_heads=2)
+    cfg = synth.model_shape("tiny", **over)
     g = gpu.GpuDrafter(cfg, synth.make_weights(cfg, 2201), max_batch=1, max_ctx=64, max_calib=16)
     try:
-        es.easyspec_set_wait_limit(g.ctx, 1)                       # no effect: nothing waits
         with pytest.raises(es.EasySpecError) as e:
-            es.easyspec_set_wait_limit(g.ctx, -1)
+            es.easyspec_force_give_up(g.ctx, 1)
         assert e.value.code == es.EASYSPEC_EINVAL
         assert np.isfinite(g.calibrate({0: [1, 2, 3]})[1][0]).all()
         assert int(g.lens()[0][0]) == 3

@@ -788,7 +788,8 @@ static int resident_grid(const Shape& s) {
 // round; slots that a unit of the attention walks, times its heads: 1.6.  Of those calls one is slower here than as launches
 // (1.04x); by the limits above alone 144 were, up to 1.18x.  us a step, launches and resident: fp32 19 layers 576 / 608 wide, sets of
 // seven, ten columns 329 / 388; bf16 8 layers 1536 / 3072 wide, vocabulary 16384, sets of eight, three columns 230 / 262.  A third of the
-// calls refused are slower resident, the others would gain up to 1.2x, 1.03x on average over all of them.
+// calls refused are slower resident, the others would gain up to 1.2x, 1.03x on average over all of them.  Of 1311 calls of 260 other
+// models that the rule takes, one timed slower (1.05x).
 bool resident_pass(const Shape& s, const Cols& c, const int32_t* bounds, int n_sets) {
   const int most = s.dtype == 1 ? 640 : 320;
   int ctx = 0;

@@ -238,11 +238,16 @@ __device__ __forceinline__ bool folded(int ncols) {
 // vector registers and a branch for every operand fragment spilled registers in the two-fragment O and down projections and
 // took about a hundred instructions a batch; with uniform addresses and one branch a batch: prefill of 16 tokens at context
 // 8192 4120 -> 4071 us, Qwen2-7B step 2692 -> 2636, 6-token calibration 3372 -> 3340 (runs of one build differ by 0.4 to 1.5 %).
-template <typename T, int RT, int NB, int NP>
-__device__ __forceinline__ void gemm_loop(const u32x4* const (&w)[RT], const u32x4* const (&x)[NP], const uint32_t (&x_lane)[NB], int xs, bool colok,
-                                          int nkt, f32x4 (&acc)[NP][RT], int w_lane, int w_stride) {
+//
+// meanwhile(0) is called once, by every wave, when its first batch of weights has been requested: whatever else a kernel has to
+// fetch or work out before its stream ends belongs there.  meanwhile(1) follows when its second batch has been requested (what
+// was fetched has arrived by then), or at the end if there is none.  NW, the waves of the workgroup, is an argument of the kernels:
+// blockDim lies behind the arguments, in a cache line of its own that a wave would wait for a second time before its first load.
+template <typename T, int RT, int NB, int NP, class Meanwhile>
+__device__ __forceinline__ void gemm_loop(const u32x4* const (&w)[RT], const u32x4* const (&x)[NP], const uint32_t (&x_lane)[NB], int xs, const bool& colok,
+                                          int nkt, int NW, f32x4 (&acc)[NP][RT], int w_lane, int w_stride, const Meanwhile& meanwhile) {
   constexpr int U = batch_len(RT);  // k-tiles per batch: 8 KB of weights in flight per wave
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), NW = blockDim.x >> 6;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   // w_lane: the lane's 16-byte piece of a weight fragment, w_stride: pieces per fragment (lane and 64 for tiles of 16 rows).
   // A tile's address is a uniform base and the lane's 32-bit offset: no vector registers per tile.
   const uint32_t w_byte = (uint32_t)w_lane * 16;
@@ -250,7 +255,7 @@ __device__ __forceinline__ void gemm_loop(const u32x4* const (&w)[RT], const u32
   const u32x4 zero = {0u, 0u, 0u, 0u};
   // One batch.  The last, partial one has the same shape with the loads past the end switched off (wave-uniform), so
   // that the remaining tiles are still fetched together instead of one latency at a time.
-  auto batch = [&](int kt, auto partial) {
+  auto batch = [&](int kt, auto partial, auto&& requested) {
     constexpr bool PARTIAL = decltype(partial)::value;
     u32x4 a[RT][U], b[NP][NB][U];
     uint32_t wb = w_byte;
@@ -261,6 +266,7 @@ __device__ __forceinline__ void gemm_loop(const u32x4* const (&w)[RT], const u32
 #pragma unroll
       for (int r = 0; r < RT; ++r) a[r][u] = in ? __builtin_nontemporal_load(piece(w[r] + (size_t)batch_tile(kt, u, NW) * w_stride, wb)) : zero;
     }
+    requested();
     // the lanes of columns that are not there leave their registers as they are: what they hold only reaches those columns of the product
 #pragma unroll
     for (int p = 0; p < NP; ++p)
@@ -296,134 +302,109 @@ __device__ __forceinline__ void gemm_loop(const u32x4* const (&w)[RT], const u32
     }
   };
   int kt = wave;
-  for (; batch_is_full(kt, U, NW, nkt); kt = next_batch(kt, U, NW)) batch(kt, std::false_type{});
-  if (kt < nkt) batch(kt, std::true_type{});
+  const auto first = [&] {
+    asm volatile("" ::: "memory");  // the requests stay ahead of it
+    meanwhile(std::integral_constant<int, 0>{});
+  };
+  const auto second = [&] {
+    asm volatile("" ::: "memory");
+    meanwhile(std::integral_constant<int, 1>{});
+  };
+  const auto nothing = [] {};
+  if (batch_is_full(kt, U, NW, nkt)) {
+    batch(kt, std::false_type{}, first);
+    kt = next_batch(kt, U, NW);
+    if (batch_is_full(kt, U, NW, nkt)) {
+      batch(kt, std::false_type{}, second);
+      kt = next_batch(kt, U, NW);
+      for (; batch_is_full(kt, U, NW, nkt); kt = next_batch(kt, U, NW)) batch(kt, std::false_type{}, nothing);
+      if (kt < nkt) batch(kt, std::true_type{}, nothing);
+    } else {
+      if (kt < nkt) batch(kt, std::true_type{}, nothing);
+      second();
+    }
+  } else {
+    if (kt < nkt) batch(kt, std::true_type{}, first);
+    else first();
+    second();
+  }
 }
 
 // NB is chosen by the host per launch: 1 when the activations have one term (fp32) or the
 // columns fold (at most 8), else 2.  Separate instantiations keep the common one-fragment path
 // free of the second path's registers.  x[p]: the operand of pass p (all passes have ncols columns).
-template <typename T, int RT, int NB, int NP>
-__device__ __forceinline__ void gemm_accumulate(const u32x4* const (&w)[RT], const T* const (&x)[NP], int K, int ncols,
-                                                f32x4 (&acc)[NP][RT], int w_lane = -1, int w_stride = 64) {
+template <typename T, int RT, int NB, int NP, class Meanwhile>
+__device__ __forceinline__ void gemm_accumulate(const u32x4* const (&w)[RT], const T* const (&x)[NP], int K, int ncols, int NW,
+                                                f32x4 (&acc)[NP][RT], int w_lane, int w_stride, const Meanwhile& meanwhile) {
   constexpr int EPL = Tr<T>::EPL, KT = Tr<T>::KT, PARTS = Tr<T>::PARTS;
   const int lane = threadIdx.x & 63;
   const int nkt = K / KT;
-  if (w_lane < 0) w_lane = lane;  // full tiles: fragment piece i belongs to lane i
-  // NB == 1: lane column c < ncols reads the hi term of column c, column ncols + c its lo term
-  long o[NB];
-#pragma unroll
-  for (int q = 0; q < NB; ++q) o[q] = x_fragment_elems(EPL, PARTS, NB, ncols, K, lane, q);
-  const bool colok = o[0] >= 0;
   const u32x4* xp[NP];
 #pragma unroll
   for (int p = 0; p < NP; ++p) xp[p] = reinterpret_cast<const u32x4*>(x[p]);
   uint32_t x_lane[NB];
-#pragma unroll
-  for (int q = 0; q < NB; ++q) x_lane[q] = (uint32_t)(colok ? o[q] : 0) * sizeof(T);
+  bool colok = false;
   const u32x4* const(&xc)[NP] = xp;
   const uint32_t(&xl)[NB] = x_lane;
-  gemm_loop<T, RT, NB, NP>(w, xc, xl, xtile_stride<T>(ncols), colok, nkt, acc, w_lane, w_stride);
-}
-
-// one pass
-template <typename T, int RT, int NB>
-__device__ __forceinline__ void gemm_accumulate(const u32x4* const (&w)[RT], const T* __restrict__ x, int K, int ncols,
-                                                f32x4 (&acc)[RT], int w_lane = -1, int w_stride = 64) {
-  const T* const xs[1] = {x};
-  gemm_accumulate<T, RT, NB, 1>(w, xs, K, ncols, reinterpret_cast<f32x4(&)[1][RT]>(acc), w_lane, w_stride);
-}
-
-// After reduce_waves, in the wave that holds the totals: add the lo-term columns onto the
-// hi-term columns when the contraction ran folded.  All 64 lanes must call it.
-template <typename T, int RT>
-__device__ __forceinline__ void fold_columns(f32x4 (&acc)[RT], int ncols) {
-  if (!folded<T>(ncols)) return;
+  gemm_loop<T, RT, NB, NP>(w, xc, xl, xtile_stride<T>(ncols), colok, nkt, NW, acc, w_lane, w_stride, [&](auto when) {
+    meanwhile(when);
+    if (decltype(when)::value != 0) return;
+    // NB == 1: lane column c < ncols reads the hi term of column c, column ncols + c its lo term
 #pragma unroll
-  for (int r = 0; r < RT; ++r)
-#pragma unroll
-    for (int i = 0; i < 4; ++i) acc[r][i] += __shfl_down(acc[r][i], ncols, 64);
+    for (int q = 0; q < NB; ++q) {
+      const long o = x_fragment_elems(EPL, PARTS, NB, ncols, K, lane, q);
+      colok = o >= 0;  // the same for every q
+      x_lane[q] = (uint32_t)(colok ? o : 0) * sizeof(T);
+    }
+  });
 }
 
-// Sum the waves' partial accumulators through LDS in wave order; true for the wave that holds
-// the total (wave 0).  red: (NW-1)*RT*64 f32x4.
+// After its stream a workgroup's waves put their partial tiles into LDS, [wave][row tile][16 columns][kRedPitch] floats, and a thread
+// each adds up and finishes the elements (row, column) of the tiles: element i has row i % 16, column i / 16.
+// A launch's start and end are bound by instructions: a wave issues one in four cycles or more, so a hundred of them in a row
+// are a fifth of a microsecond that nothing hides.  One wave that finished four elements a lane and folded the terms by
+// shuffles did four times the instructions at a launch's end; operands of the end, the norm's scale and the kernel's own
+// dimensions stood in front of its first load (215 to 447 instructions, now 70 to 120).  us a call, before and after both: 6-token calibration
+// of the 8B shape 3354 -> 3225 (195 launches), draft step 2698 -> 2642 (107), prefill of 16 tokens 4055 -> 3983, tree levels of 4 and
+// 12 nodes 5986 -> 5828, Qwen2-7B step 2660 -> 2617.
+constexpr int kRedPitch = 20;  // bank spread; rows of four stay 16-byte pieces
+ES_HD constexpr int red_floats(int nw, int rt) { return nw * rt * (kMaxCols * kRedPitch); }
 template <int RT>
-__device__ __forceinline__ bool reduce_waves(f32x4 (&acc)[RT], f32x4* red) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, NW = blockDim.x >> 6;
-  if (NW == 1) return true;
-  if (wave > 0) {
+__device__ __forceinline__ void put_partials(const f32x4 (&acc)[RT], float* red) {
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  float* d = red + red_floats(wave, RT) + (lane & 15) * kRedPitch + (lane >> 4) * 4;
 #pragma unroll
-    for (int r = 0; r < RT; ++r) red[((wave - 1) * RT + r) * 64 + lane] = acc[r];
-  }
-  __syncthreads();
-  if (wave == 0) {
-    for (int w = 1; w < NW; ++w) {
+  for (int r = 0; r < RT; ++r) *reinterpret_cast<f32x4*>(d + red_floats(r, 1)) = acc[r];
+}
+// Element (row, col) of row tile r: the waves in order, the lo-term column (when the contraction ran folded) onto the hi-term one.
+template <typename T, int RT>
+__device__ __forceinline__ float tile_sum(const float* red, int NW, int r, int row, int col, int ncols) {
+  const float* p = red + red_floats(r, 1) + col * kRedPitch + row;
+  const bool fold = folded<T>(ncols);
+  const int lo = fold ? ncols * kRedPitch : 0;
+  float s = 0.f, l = 0.f;
+  auto add = [&](auto n, const float* q) {  // straight-line: the reads go out together
+    float v[decltype(n)::value], u[decltype(n)::value];
 #pragma unroll
-      for (int r = 0; r < RT; ++r) acc[r] += red[((w - 1) * RT + r) * 64 + lane];
+    for (int w = 0; w < decltype(n)::value; ++w) {
+      v[w] = q[red_floats(w, RT)];
+      if (Tr<T>::PARTS == 2) u[w] = q[red_floats(w, RT) + lo];
     }
-  }
-  return wave == 0;
-}
-
-// rstd[col] = rsqrt(sum_t ssp[col][t] / d + eps), summed in a fixed order.  Ends with a barrier.
-__device__ __forceinline__ void compute_rstd(const float* __restrict__ ssp, int ntile, int ncols, float inv_d, float eps,
-                                             float* s_rstd) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, NW = blockDim.x >> 6;
-  for (int col = wave; col < ncols; col += NW) {
-    float s = 0.f;
-    for (int t = lane; t < ntile; t += 64) s += ssp[col * ntile + t];
 #pragma unroll
-    for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
-    if (lane == 0) s_rstd[col] = 1.0f / sqrtf(s * inv_d + eps);
-  }
-  __syncthreads();
-}
-
-// The same quantity with its loads issued BEFORE the weight stream of the workgroup starts and
-// its arithmetic done after: the L2 latency of the partial sums then hides behind the stream
-// instead of sitting in the tail of the kernel.  Covers d <= 4096 and up to two columns per
-// wave (the common cases); otherwise rstd_finish falls back to compute_rstd.  Same summation
-// order as compute_rstd, so both give identical bits.
-struct RstdPre {
-  float v[2][4];
-  bool fast;
-};
-
-__device__ __forceinline__ void rstd_issue(const float* __restrict__ ssp, int ntile, int ncols, RstdPre& p) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, NW = blockDim.x >> 6;
-  p.fast = ntile <= 256 && ncols <= 2 * NW;
-  if (!p.fast) return;
-#pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    const int col = wave + i * NW;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int t = lane + 64 * j;
-      p.v[i][j] = (col < ncols && t < ntile) ? ssp[col * ntile + t] : 0.f;
+    for (int w = 0; w < decltype(n)::value; ++w) {
+      s += v[w];
+      if (Tr<T>::PARTS == 2) l += u[w];
     }
+  };
+  if (NW == 8) {
+    add(std::integral_constant<int, 8>{}, p);
+  } else if (NW == 4) {
+    add(std::integral_constant<int, 4>{}, p);
+  } else {
+#pragma unroll 1
+    for (int w = 0; w < NW; ++w) add(std::integral_constant<int, 1>{}, p + red_floats(w, RT));
   }
-}
-
-// Ends with a barrier unless the caller's reduce_waves provides one (NW > 1).
-__device__ __forceinline__ void rstd_finish(const float* __restrict__ ssp, int ntile, int ncols, float inv_d, float eps,
-                                            const RstdPre& p, float* s_rstd) {
-  if (!p.fast) {
-    compute_rstd(ssp, ntile, ncols, inv_d, eps, s_rstd);
-    return;
-  }
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, NW = blockDim.x >> 6;
-#pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    const int col = wave + i * NW;
-    float s = 0.f;
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-      if (lane + 64 * j < ntile) s += p.v[i][j];
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
-    if (lane == 0 && col < ncols) s_rstd[col] = 1.0f / sqrtf(s * inv_d + eps);
-  }
-  if (NW == 1) __syncthreads();
+  return fold ? s + l : s;
 }
 
 // Sum over aligned groups of N lanes (8, 16 or 32), every lane of a group receiving the total,
@@ -443,6 +424,69 @@ __device__ __forceinline__ float group_sum(float v) {
   if (N >= 16) v += dpp_f32<0x140>(v);  // row_mirror
   if (N >= 32) v += __shfl_xor(v, 16, 64);
   return v;
+}
+// ... and over all 64, without a trip through LDS
+__device__ __forceinline__ float wave_sum(float v) {
+  const uint32_t a = __float_as_uint(group_sum<16>(v));
+  const auto q = __builtin_amdgcn_permlane16_swap(a, a, false, false);
+  const uint32_t b = __float_as_uint(__uint_as_float(q[0]) + __uint_as_float(q[1]));
+  const auto h = __builtin_amdgcn_permlane32_swap(b, b, false, false);
+  return __uint_as_float(h[0]) + __uint_as_float(h[1]);
+}
+
+// rstd[col] = rsqrt(sum_t ssp[col][t] / d + eps), summed in a fixed order; a barrier has to follow.
+__device__ __forceinline__ void compute_rstd(const float* __restrict__ ssp, int ntile, int ncols, int NW, float inv_d, float eps,
+                                             float* s_rstd) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  for (int col = wave; col < ncols; col += NW) {
+    float s = 0.f;
+    for (int t = lane; t < ntile; t += 64) s += ssp[col * ntile + t];
+    s = wave_sum(s);
+    if (lane == 0) s_rstd[col] = 1.0f / sqrtf(s * inv_d + eps);
+  }
+}
+
+// The same quantity with its loads issued BEFORE the weight stream of the workgroup starts and
+// its arithmetic done after: the L2 latency of the partial sums then hides behind the stream
+// instead of sitting in the tail of the kernel.  Covers d <= 4096 and up to two columns per
+// wave (the common cases); otherwise rstd_finish falls back to compute_rstd.  Same summation
+// order as compute_rstd, so both give identical bits.
+struct RstdPre {
+  float v[2][4];
+  bool fast;
+};
+
+__device__ __forceinline__ void rstd_issue(const float* __restrict__ ssp, int ntile, int ncols, int NW, RstdPre& p) {
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  p.fast = ntile <= 256 && ncols <= 2 * NW;
+  if (!p.fast) return;
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int col = wave + i * NW;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) p.v[i][j] = 0.f;
+    if (col >= ncols) continue;  // uniform
+    const float* row = ssp + col * ntile;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) p.v[i][j] = lane + 64 * j < ntile ? row[lane + 64 * j] : 0.f;
+  }
+}
+
+// A barrier has to follow.
+__device__ __forceinline__ void rstd_finish(const float* __restrict__ ssp, int ntile, int ncols, int NW, float inv_d, float eps,
+                                            const RstdPre& p, float* s_rstd) {
+  if (!p.fast) {
+    compute_rstd(ssp, ntile, ncols, NW, inv_d, eps, s_rstd);
+    return;
+  }
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int col = wave + i * NW;
+    if (col >= ncols) break;  // uniform
+    const float s = wave_sum(p.v[i][0] + p.v[i][1] + p.v[i][2] + p.v[i][3]);
+    if (lane == 0) s_rstd[col] = 1.0f / sqrtf(s * inv_d + eps);
+  }
 }
 
 // argmax order: the lowest index on ties
@@ -466,11 +510,10 @@ struct Twin {
   Args a[2];
   Cols c[2];
 };
-// pass p's piece of the reduction buffer ((NW - 1) * RT * 64 f32x4 each)
+// pass p's piece of the reduction buffer
 template <int RT>
-__device__ __forceinline__ f32x4* red_of_pass(int p) {
-  const int NW = blockDim.x >> 6;
-  return dyn_red + (size_t)p * (NW > 1 ? NW - 1 : 0) * RT * 64;
+__device__ __forceinline__ float* red_of_pass(int p, int NW) {
+  return reinterpret_cast<float*>(dyn_red) + p * red_floats(NW, RT);
 }
 
 }  // namespace es

@@ -17,9 +17,10 @@ namespace es {
 // pair = head * hd/2 + e, and packed as two matrices of (Hq + 2 Hkv) * hd/2 rows each (first and
 // second halves).  Unit of work: the same tile of R pairs of both, so that a pair sits in one
 // lane.  R is 16, or 12 where that fills the CUs better (qkv_tile_rows); a lane's four rows stay
-// inside one head because R and hd/2 are multiples of 4.  grid = k * ceil(ceil(pairs / R) / TP).
+// inside one head because R and hd/2 are multiples of 4.  grid = (ceil(ceil(pairs / R) / TP), k).
 // ------------------------------------------------------------------------------------------
 struct QkvArgs {
+  int nw;  // waves of a workgroup
   const u32x4* w;  // layer layer0
   size_t w_layer_stride;
   const void* x;  // XA: k operand slots of 16 x d
@@ -30,7 +31,7 @@ struct QkvArgs {
   void* kc;
   void* vc;
   int layer0, d, Hq, Hkv, hd, B, max_ctx;
-  int R;  // pairs per tile
+  int R, units;  // pairs per tile, tiles per layer
   float inv_d, eps;
 };
 
@@ -43,9 +44,8 @@ __device__ __forceinline__ void qkv_body(const QkvArgs* const (&ap)[NP], const C
   const int ncols = cp[0]->n;
   const int KT = Tr<T>::KT;
   const int nkt = a.d / KT;
-  const int half = a.hd / 2;
-  const int R = a.R, n_pairs = (a.Hq + 2 * a.Hkv) * half, units = ceil_div(n_pairs, R), nwg = ceil_div(units, TP);
-  const int li = blockIdx.x / nwg, u0 = (blockIdx.x % nwg) * TP;
+  const int R = a.R, units = a.units;
+  const int li = blockIdx.y, u0 = blockIdx.x * TP;
   const u32x4* wl = a.w + (size_t)li * a.w_layer_stride;
   const u32x4* w[2 * TP];
 #pragma unroll
@@ -54,93 +54,79 @@ __device__ __forceinline__ void qkv_body(const QkvArgs* const (&ap)[NP], const C
     w[2 * p] = wl + (size_t)u * row_tile_pieces(nkt, R);
     w[2 * p + 1] = wl + (size_t)(units + u) * row_tile_pieces(nkt, R);
   }
-  // operands of the epilogue (wave 0 only) and of the norm scale are fetched before the weight
-  // stream starts, so that their latency does not sit in the tail of the kernel
-  const int lane = threadIdx.x & 63, col = lane & 15;
-  const int row0 = (lane >> 4) * 4;  // of the tile
-  const int RQKV = (a.Hq + 2 * a.Hkv) * a.hd;
-  const bool col_ok = threadIdx.x < 64 && col < ncols;
-  bool rows_ok[TP];
-  int head[TP], e0[TP];
-  f32x4 b_lo[TP], b_hi[TP];
-#pragma unroll
-  for (int p = 0; p < TP; ++p) {
-    const int pair0 = (u0 + p) * R + row0;  // first of the lane's four pairs
-    rows_ok[p] = u0 + p < units && row0 < R && pair0 < n_pairs;
-    head[p] = rows_ok[p] ? pair0 / half : 0;
-    e0[p] = rows_ok[p] ? pair0 % half : 0;  // element inside the head, < hd/2
-    b_lo[p] = b_hi[p] = f32x4{0.f, 0.f, 0.f, 0.f};
-    if (col_ok && rows_ok[p] && a.bias) {
-      b_lo[p] = *reinterpret_cast<const f32x4*>(a.bias + (size_t)li * RQKV + head[p] * a.hd + e0[p]);
-      b_hi[p] = *reinterpret_cast<const f32x4*>(a.bias + (size_t)li * RQKV + head[p] * a.hd + e0[p] + half);
-    }
-  }
-  int pos[NP], seq[NP];
-  f32x4 cs01[NP][TP], cs23[NP][TP];
   const T* x[NP];
-  RstdPre pre[NP];
   f32x4 acc[NP][2 * TP];
 #pragma unroll
   for (int q = 0; q < NP; ++q) {
-    const Cols& c = *cp[q];
-    pos[q] = col_ok ? c.pos[col] : 0;
-    seq[q] = col_ok ? c.seq[col] : 0;
-#pragma unroll
-    for (int p = 0; p < TP; ++p) {
-      cs01[q][p] = cs23[q][p] = f32x4{1.f, 0.f, 1.f, 0.f};
-      if (col_ok && rows_ok[p] && head[p] < a.Hq + a.Hkv) {
-        const f32x4* rp = reinterpret_cast<const f32x4*>(a.rope + (size_t)c.rope_pos[col] * half + e0[p]);  // 4 x (cos, sin)
-        cs01[q][p] = rp[0];
-        cs23[q][p] = rp[1];
-      }
-    }
     x[q] = reinterpret_cast<const T*>(ap[q]->x) + (size_t)li * Tr<T>::PARTS * kMaxCols * a.d;
-    rstd_issue(ap[q]->ssp, a.d / 16, ncols, pre[q]);
 #pragma unroll
     for (int p = 0; p < 2 * TP; ++p) acc[q][p] = f32x4{0.f, 0.f, 0.f, 0.f};
   }
-  // a tile of R < 16 pairs: the lanes of the missing rows re-read the last row (their results are dropped)
-  const u32x4* const(&wc)[2 * TP] = w;
-  const T* const(&xc)[NP] = x;
-  gemm_accumulate<T, 2 * TP, NB, NP>(wc, xc, a.d, ncols, acc, lane_piece(lane, R), fragment_pieces(R));
-  bool mine = false;
-#pragma unroll
-  for (int q = 0; q < NP; ++q) {
-    rstd_finish(ap[q]->ssp, a.d / 16, ncols, a.inv_d, a.eps, pre[q], s_rstd[q]);
-    mine = reduce_waves<2 * TP>(acc[q], red_of_pass<2 * TP>(q));
-  }
-  if (!mine) return;
-#pragma unroll
-  for (int q = 0; q < NP; ++q) fold_columns<T, 2 * TP>(acc[q], ncols);  // all 64 lanes
-
-  if (col >= ncols) return;
-#pragma unroll
-  for (int q = 0; q < NP; ++q) {
-    const float r = s_rstd[q][col];
+  // this thread's element of the tiles: a rotation pair of one column, and what its end needs besides the sums
+  const int half = a.hd / 2, n_pairs = (a.Hq + 2 * a.Hkv) * half, log2_half = a.hd == 128 ? 6 : 5;
+  const int row = threadIdx.x & 15;
+  float b_lo[TP], b_hi[TP];
+  float2 cs[NP][TP];
+  RstdPre pre[NP];
+  auto operands = [&](int col) {
 #pragma unroll
     for (int p = 0; p < TP; ++p) {
-      if (!rows_ok[p]) continue;
-      const float cosv[4] = {cs01[q][p][0], cs01[q][p][2], cs23[q][p][0], cs23[q][p][2]},
-                  sinv[4] = {cs01[q][p][1], cs01[q][p][3], cs23[q][p][1], cs23[q][p][3]};
-      float lo[4], hi[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        // identity rotation (cos 1, sin 0) for the V rows; bias 0 without bias
-        const float v0 = acc[q][2 * p][i] * r + b_lo[p][i], v1 = acc[q][2 * p + 1][i] * r + b_hi[p][i];
-        lo[i] = v0 * cosv[i] - v1 * sinv[i];
-        hi[i] = v1 * cosv[i] + v0 * sinv[i];
+      const int pair = (u0 + p) * R + row, head = pair >> log2_half, e = pair & (half - 1);
+      const bool ok = u0 + p < units && row < R && pair < n_pairs && col < ncols;
+      b_lo[p] = b_hi[p] = 0.f;
+      if (ok && a.bias) {
+        const float* bp = a.bias + (size_t)li * (2 * n_pairs) + head * a.hd + e;
+        b_lo[p] = bp[0];
+        b_hi[p] = bp[half];
       }
-      if (head[p] < a.Hq) {
-        float* qo = ap[q]->q + ((size_t)li * kMaxCols + col) * (a.Hq * a.hd) + head[p] * a.hd + e0[p];
-        store4<float>(qo, lo[0], lo[1], lo[2], lo[3]);
-        store4<float>(qo + half, hi[0], hi[1], hi[2], hi[3]);
-      } else {
-        const bool is_k = head[p] < a.Hq + a.Hkv;
-        const int kvh = is_k ? head[p] - a.Hq : head[p] - a.Hq - a.Hkv;
-        T* base = reinterpret_cast<T*>(is_k ? a.kc : a.vc);
-        T* row = base + ((((size_t)(a.layer0 + li) * a.B + seq[q]) * a.Hkv + kvh) * a.max_ctx + pos[q]) * a.hd + e0[p];
-        store4<T>(row, lo[0], lo[1], lo[2], lo[3]);
-        store4<T>(row + half, hi[0], hi[1], hi[2], hi[3]);
+#pragma unroll
+      for (int q = 0; q < NP; ++q) {
+        cs[q][p] = float2{1.f, 0.f};  // no rotation for the V rows
+        if (ok && head < a.Hq + a.Hkv) cs[q][p] = a.rope[(size_t)cp[q]->rope_pos[col] * half + e];
+      }
+    }
+  };
+  const u32x4* const(&wc)[2 * TP] = w;
+  const T* const(&xc)[NP] = x;
+  // a tile of R < 16 pairs: the lanes of the missing rows re-read the last row (their results are dropped)
+  gemm_accumulate<T, 2 * TP, NB, NP>(wc, xc, a.d, ncols, a.nw, acc, lane_piece(threadIdx.x & 63, R), fragment_pieces(R), [&](auto when) {
+    if (decltype(when)::value == 0) {
+#pragma unroll
+      for (int q = 0; q < NP; ++q) rstd_issue(ap[q]->ssp, a.d / 16, ncols, a.nw, pre[q]);
+      operands(threadIdx.x >> 4);
+    } else {
+#pragma unroll
+      for (int q = 0; q < NP; ++q) rstd_finish(ap[q]->ssp, a.d / 16, ncols, a.nw, a.inv_d, a.eps, pre[q], s_rstd[q]);
+    }
+  });
+#pragma unroll
+  for (int q = 0; q < NP; ++q) put_partials<2 * TP>(acc[q], red_of_pass<2 * TP>(q, a.nw));
+  __syncthreads();
+  for (int i = threadIdx.x; i < 16 * ncols; i += 64 * a.nw) {
+    const int col = i >> 4;
+    if (i >= 64 * a.nw) operands(col);  // more elements than threads
+#pragma unroll
+    for (int q = 0; q < NP; ++q) {
+      const float r = s_rstd[q][col];
+#pragma unroll
+      for (int p = 0; p < TP; ++p) {
+        const int pair = (u0 + p) * R + row, head = pair >> log2_half, e = pair & (half - 1);
+        if (u0 + p >= units || row >= R || pair >= n_pairs) continue;
+        const float* red = red_of_pass<2 * TP>(q, a.nw);
+        const float v0 = tile_sum<T, 2 * TP>(red, a.nw, 2 * p, row, col, ncols) * r + b_lo[p], v1 = tile_sum<T, 2 * TP>(red, a.nw, 2 * p + 1, row, col, ncols) * r + b_hi[p];
+        const float lo = v0 * cs[q][p].x - v1 * cs[q][p].y, hi = v1 * cs[q][p].x + v0 * cs[q][p].y;
+        if (head < a.Hq) {
+          float* qo = ap[q]->q + ((size_t)li * kMaxCols + col) * (a.Hq * a.hd) + head * a.hd + e;
+          qo[0] = lo;
+          qo[half] = hi;
+        } else {
+          const bool is_k = head < a.Hq + a.Hkv;
+          const int kvh = is_k ? head - a.Hq : head - a.Hq - a.Hkv;
+          T* kv = reinterpret_cast<T*>(is_k ? a.kc : a.vc) +
+                  ((((size_t)(a.layer0 + li) * a.B + cp[q]->seq[col]) * a.Hkv + kvh) * a.max_ctx + cp[q]->pos[col]) * a.hd + e;
+          store1<T>(kv, lo);
+          store1<T>(kv + half, hi);
+        }
       }
     }
   }
@@ -163,9 +149,10 @@ __global__ __launch_bounds__(kTwinThreads) void qkv_twin_kernel(Twin<QkvArgs> t)
 // launch (k > 1), or one down projection (k = 1).  Layer 0 of the launch updates the
 // residual: h = H + acc (+ Attnoutput of the next layer), writes H, the sum of squares of h
 // and T(h * gain_j) for the consumer(s) that come next; the other layers only store their
-// Attnoutput for later.  grid = k * ceil(d/16 / TP).
+// Attnoutput for later.  grid = (ceil(d/16 / TP), k).
 // ------------------------------------------------------------------------------------------
 struct ProjArgs {
+  int nw;  // waves of a workgroup
   const u32x4* w;
   size_t w_layer_stride;
   const void* x;  // k operand slots of 16 x K in T
@@ -185,77 +172,70 @@ template <typename T, int NB, int TP, int NP>
 __device__ __forceinline__ void proj_resid_body(const ProjArgs* const (&ap)[NP], const Cols* const (&cp)[NP]) {
   const ProjArgs& a = *ap[0];  // what the passes share: weights, gains, shape, a_add, n_gain
   const int ncols = cp[0]->n;
-  const int KT = Tr<T>::KT;
-  const int nkt = a.K / KT;
-  const int ntile = a.d / 16, nwg = ceil_div(ntile, TP);
-  const int li = blockIdx.x / nwg, t0 = (blockIdx.x % nwg) * TP;
+  const int nkt = a.K / Tr<T>::KT;
+  const int ntile = a.d / 16;
+  const int li = blockIdx.y, t0 = blockIdx.x * TP;
   const u32x4* w[TP];
 #pragma unroll
   for (int p = 0; p < TP; ++p)  // a missing last tile re-reads its neighbour (results dropped)
     w[p] = a.w + (size_t)li * a.w_layer_stride + (size_t)clamped_unit(t0, p, ntile) * row_tile_pieces(nkt, 16);
-  // residual-update operands (wave 0 of a layer-0 workgroup) are fetched before the weight stream
-  const int lane = threadIdx.x & 63, col = lane & 15;
-  const bool ok = col < ncols;
   const T* x[NP];
-  f32x4 h_in[NP][TP], a_in[NP][TP], g_in[TP], acc[NP][TP];
-#pragma unroll
-  for (int p = 0; p < TP; ++p) {
-    g_in[p] = f32x4{0.f, 0.f, 0.f, 0.f};
-    const int r0 = (t0 + p) * 16 + (lane >> 4) * 4;
-    if (threadIdx.x < 64 && li == 0 && ok && t0 + p < ntile) g_in[p] = *reinterpret_cast<const f32x4*>(a.gain + r0);
-  }
+  f32x4 acc[NP][TP];
 #pragma unroll
   for (int q = 0; q < NP; ++q) {
     x[q] = reinterpret_cast<const T*>(ap[q]->x) + (size_t)li * Tr<T>::PARTS * kMaxCols * a.K;
 #pragma unroll
+    for (int p = 0; p < TP; ++p) acc[q][p] = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
+  // this thread's element of the tiles, and what it is added to (the workgroups of layer 0)
+  const int row = threadIdx.x & 15;
+  float h_in[NP][TP], a_in[NP][TP], g_in[TP];
+  auto operands = [&](int col) {
+#pragma unroll
     for (int p = 0; p < TP; ++p) {
-      h_in[q][p] = a_in[q][p] = acc[q][p] = f32x4{0.f, 0.f, 0.f, 0.f};
-      const int r0 = (t0 + p) * 16 + (lane >> 4) * 4;
-      if (threadIdx.x < 64 && li == 0 && ok && t0 + p < ntile) {
-        h_in[q][p] = *reinterpret_cast<const f32x4*>(ap[q]->H + (size_t)col * a.d + r0);
-        if (a.a_add >= 0) a_in[q][p] = *reinterpret_cast<const f32x4*>(ap[q]->A + ((size_t)a.a_add * kMaxCols + col) * a.d + r0);
+      const int r0 = (t0 + p) * 16 + row;
+      const bool ok = li == 0 && col < ncols && t0 + p < ntile;
+      g_in[p] = ok ? a.gain[r0] : 0.f;
+#pragma unroll
+      for (int q = 0; q < NP; ++q) {
+        h_in[q][p] = ok ? ap[q]->H[(size_t)col * a.d + r0] : 0.f;
+        a_in[q][p] = ok && a.a_add >= 0 ? ap[q]->A[((size_t)a.a_add * kMaxCols + col) * a.d + r0] : 0.f;
       }
     }
-  }
+  };
   const u32x4* const(&wc)[TP] = w;
   const T* const(&xc)[NP] = x;
-  gemm_accumulate<T, TP, NB, NP>(wc, xc, a.K, ncols, acc);
-  bool mine = false;
+  gemm_accumulate<T, TP, NB, NP>(wc, xc, a.K, ncols, a.nw, acc, threadIdx.x & 63, 64, [&](auto when) {
+    if (decltype(when)::value == 0) operands(threadIdx.x >> 4);
+  });
 #pragma unroll
-  for (int q = 0; q < NP; ++q) mine = reduce_waves<TP>(acc[q], red_of_pass<TP>(q));
-  if (!mine) return;
+  for (int q = 0; q < NP; ++q) put_partials<TP>(acc[q], red_of_pass<TP>(q, a.nw));
+  __syncthreads();
+  for (int i = threadIdx.x; i < 16 * ncols; i += 64 * a.nw) {
+    const int col = i >> 4;
+    if (i >= 64 * a.nw) operands(col);  // more elements than threads
 #pragma unroll
-  for (int q = 0; q < NP; ++q) fold_columns<T, TP>(acc[q], ncols);  // all 64 lanes
-
+    for (int q = 0; q < NP; ++q) {
+      const ProjArgs& aq = *ap[q];
 #pragma unroll
-  for (int q = 0; q < NP; ++q) {
-    const ProjArgs& aq = *ap[q];
-#pragma unroll
-    for (int p = 0; p < TP; ++p) {
-      const int t = t0 + p;
-      if (t >= ntile) break;
-      const int r0 = t * 16 + (lane >> 4) * 4;
-      if (li > 0) {
-        if (ok) store4<float>(aq.A + ((size_t)li * kMaxCols + col) * a.d + r0, acc[q][p][0], acc[q][p][1], acc[q][p][2], acc[q][p][3]);
-        continue;
-      }
-      float ss = 0.f;
-      if (ok) {
-        float* hp = aq.H + (size_t)col * a.d + r0;
-        f32x4 h = h_in[q][p];
-        h += acc[q][p];
-        if (a.a_add >= 0) h += a_in[q][p];
-        *reinterpret_cast<f32x4*>(hp) = h;
-        for (int j = 0; j < a.n_gain; ++j) {
-          const f32x4 g = j == 0 ? g_in[p] : *reinterpret_cast<const f32x4*>(a.gain + (size_t)j * a.d + r0);
-          T* xo = reinterpret_cast<T*>(aq.xout) + (size_t)j * Tr<T>::PARTS * kMaxCols * a.d + xoff<T>(ncols, a.d, col, r0);
-          store_act4<T>(xo, (size_t)kMaxCols * a.d, h[0] * g[0], h[1] * g[1], h[2] * g[2], h[3] * g[3]);
+      for (int p = 0; p < TP; ++p) {
+        const int t = t0 + p, r0 = t * 16 + row;
+        if (t >= ntile) break;
+        const float sum = tile_sum<T, TP>(red_of_pass<TP>(q, a.nw), a.nw, p, row, col, ncols);
+        if (li > 0) {
+          aq.A[((size_t)li * kMaxCols + col) * a.d + r0] = sum;
+          continue;
         }
-        ss = h[0] * h[0] + h[1] * h[1] + h[2] * h[2] + h[3] * h[3];
+        const float h = h_in[q][p] + sum + a_in[q][p];
+        aq.H[(size_t)col * a.d + r0] = h;
+        T* xo = reinterpret_cast<T*>(aq.xout) + xoff<T>(ncols, a.d, col, r0);
+        for (int j = 0; j < a.n_gain; ++j) {
+          const float g = j == 0 ? g_in[p] : a.gain[(size_t)j * a.d + r0];
+          store_act1<T>(xo + (size_t)j * Tr<T>::PARTS * kMaxCols * a.d, (size_t)kMaxCols * a.d, h * g);
+        }
+        const float ss = group_sum<16>(h * h);
+        if (row == 0) aq.ssp[col * ntile + t] = ss;
       }
-      ss += __shfl_xor(ss, 16, 64);
-      ss += __shfl_xor(ss, 32, 64);
-      if (ok && lane < 16) aq.ssp[col * ntile + t] = ss;
     }
   }
 }
@@ -285,6 +265,7 @@ __global__ __launch_bounds__(kTwinThreads) void proj_resid_twin_kernel(Twin<Proj
 //     T(h * gain_j) for the n_gain consumers that come next, like proj_resid_kernel.
 // ------------------------------------------------------------------------------------------
 struct ProjFullArgs {
+  int nw;  // waves of a workgroup
   const u32x4* w;
   size_t w_layer_stride;
   const void* x;  // k operand slots of 16 x K in T
@@ -301,51 +282,44 @@ template <typename T, int NB>
 __global__ __launch_bounds__(1024) void proj_full_kernel(ProjFullArgs a, Cols c) {
   const int nkt = a.K / Tr<T>::KT;
   const int ntile = a.d / 16;
-  const int li = a.down ? 0 : blockIdx.x / ntile, t = blockIdx.x % ntile;
-  const int lane = threadIdx.x & 63, col = lane & 15;
-  const bool ok = col < c.n;
-  const int r0 = t * 16 + (lane >> 4) * 4;
-  f32x4 acc[1] = {{0.f, 0.f, 0.f, 0.f}};
+  const int li = blockIdx.y, t = blockIdx.x;
+  f32x4 acc[1][1] = {{{0.f, 0.f, 0.f, 0.f}}};
   const int n_sum = a.down ? a.k : 1;
   for (int j = 0; j < n_sum; ++j) {  // uniform over the workgroup
     const int l = li + j;
     const u32x4* const w[1] = {a.w + (size_t)l * a.w_layer_stride + (size_t)t * row_tile_pieces(nkt, 16)};
-    gemm_accumulate<T, 1, NB>(w, reinterpret_cast<const T*>(a.x) + (size_t)l * Tr<T>::PARTS * kMaxCols * a.K, a.K, c.n, acc);
+    const T* const x[1] = {reinterpret_cast<const T*>(a.x) + (size_t)l * Tr<T>::PARTS * kMaxCols * a.K};
+    gemm_accumulate<T, 1, NB, 1>(w, x, a.K, c.n, a.nw, acc, threadIdx.x & 63, 64, [](auto) {});
   }
-  if (!reduce_waves<1>(acc, dyn_red)) return;
-  fold_columns<T, 1>(acc, c.n);
-
-  float ss = 0.f;
-  if (ok) {
-    f32x4 h = *reinterpret_cast<const f32x4*>(a.H + (size_t)col * a.d + r0);
-    h += acc[0];
+  put_partials<1>(acc[0], red_of_pass<1>(0, a.nw));
+  __syncthreads();
+  const int row = threadIdx.x & 15, r0 = t * 16 + row;
+  for (int i = threadIdx.x; i < 16 * c.n; i += 64 * a.nw) {
+    const int col = i >> 4;
+    const float sum = tile_sum<T, 1>(red_of_pass<1>(0, a.nw), a.nw, 0, row, col, c.n);
+    float h = a.H[(size_t)col * a.d + r0] + sum;
+    T* xo = reinterpret_cast<T*>(a.xout) + xoff<T>(c.n, a.d, col, r0);
     if (a.down) {
-      for (int j = 0; j < a.k; ++j) h += *reinterpret_cast<const f32x4*>(a.A + ((size_t)j * kMaxCols + col) * a.d + r0);
-      *reinterpret_cast<f32x4*>(a.H + (size_t)col * a.d + r0) = h;
-      for (int j = 0; j < a.n_gain; ++j) {
-        const f32x4 g = *reinterpret_cast<const f32x4*>(a.gain + (size_t)j * a.d + r0);
-        T* xo = reinterpret_cast<T*>(a.xout) + (size_t)j * Tr<T>::PARTS * kMaxCols * a.d + xoff<T>(c.n, a.d, col, r0);
-        store_act4<T>(xo, (size_t)kMaxCols * a.d, h[0] * g[0], h[1] * g[1], h[2] * g[2], h[3] * g[3]);
-      }
+      for (int j = 0; j < a.k; ++j) h += a.A[((size_t)j * kMaxCols + col) * a.d + r0];
+      a.H[(size_t)col * a.d + r0] = h;
+      for (int j = 0; j < a.n_gain; ++j)
+        store_act1<T>(xo + (size_t)j * Tr<T>::PARTS * kMaxCols * a.d, (size_t)kMaxCols * a.d, h * a.gain[(size_t)j * a.d + r0]);
     } else {
-      store4<float>(a.A + ((size_t)li * kMaxCols + col) * a.d + r0, acc[0][0], acc[0][1], acc[0][2], acc[0][3]);
-      const f32x4 g = *reinterpret_cast<const f32x4*>(a.gain + (size_t)li * a.d + r0);
-      T* xo = reinterpret_cast<T*>(a.xout) + (size_t)li * Tr<T>::PARTS * kMaxCols * a.d + xoff<T>(c.n, a.d, col, r0);
-      store_act4<T>(xo, (size_t)kMaxCols * a.d, h[0] * g[0], h[1] * g[1], h[2] * g[2], h[3] * g[3]);
+      a.A[((size_t)li * kMaxCols + col) * a.d + r0] = sum;
+      store_act1<T>(xo + (size_t)li * Tr<T>::PARTS * kMaxCols * a.d, (size_t)kMaxCols * a.d, h * a.gain[(size_t)li * a.d + r0]);
     }
-    ss = h[0] * h[0] + h[1] * h[1] + h[2] * h[2] + h[3] * h[3];
+    const float ss = group_sum<16>(h * h);
+    if (row == 0) a.ssp[(size_t)li * kMaxCols * ntile + col * ntile + t] = ss;
   }
-  ss += __shfl_xor(ss, 16, 64);
-  ss += __shfl_xor(ss, 32, 64);
-  if (ok && lane < 16) a.ssp[(size_t)li * kMaxCols * ntile + col * ntile + t] = ss;
 }
 
 // ------------------------------------------------------------------------------------------
 // Gate and up projections + SiLU(gate) * up of one layer, or of the k layers of a set each on
 // its own input (full-layer mode): layer li of the launch reads operand slot li of x with
-// partial sums slot li and writes operand slot li of act.  grid = k * ceil(ceil(F / R) / TP).
+// partial sums slot li and writes operand slot li of act.  grid = (ceil(ceil(F / R) / TP), k).
 // ------------------------------------------------------------------------------------------
 struct GateUpArgs {
+  int nw;  // waves of a workgroup
   const u32x4* wg;
   const u32x4* wu;
   size_t w_layer_stride;
@@ -353,7 +327,7 @@ struct GateUpArgs {
   const float* ssp;  // [k][16][d/16]
   void* act;  // k operand slots of 16 x F in T
   int d, F;
-  int R;      // rows per weight tile (tile_rows() of F), ntile = ceil(F / R) workgroups per layer
+  int R, units;  // rows per weight tile (tile_rows() of F), tiles per layer
   float inv_d, eps;
 };
 
@@ -366,8 +340,8 @@ __device__ __forceinline__ void gateup_body(const GateUpArgs* const (&ap)[NP], c
   const GateUpArgs& a = *ap[0];  // what the passes share: weights and shape
   const int ncols = cp[0]->n;
   const int nkt = a.d / Tr<T>::KT;
-  const int R = a.R, ntile = ceil_div(a.F, R), nunit = ceil_div(ntile, TP);
-  const int li = blockIdx.x / nunit, t0 = (blockIdx.x % nunit) * TP;
+  const int R = a.R, ntile = a.units;
+  const int li = blockIdx.y, t0 = blockIdx.x * TP;
   const u32x4* w[2 * TP];
 #pragma unroll
   for (int p = 0; p < TP; ++p) {
@@ -384,48 +358,35 @@ __device__ __forceinline__ void gateup_body(const GateUpArgs* const (&ap)[NP], c
   for (int q = 0; q < NP; ++q) {
     ssp[q] = ap[q]->ssp + (size_t)li * kMaxCols * (a.d / 16);
     x[q] = reinterpret_cast<const T*>(ap[q]->x) + (size_t)li * Tr<T>::PARTS * kMaxCols * a.d;
-    rstd_issue(ssp[q], a.d / 16, ncols, pre[q]);
 #pragma unroll
     for (int p = 0; p < 2 * TP; ++p) acc[q][p] = f32x4{0.f, 0.f, 0.f, 0.f};
   }
   // a tile of R < 16 rows: the lanes of the missing rows re-read the last row (their results are dropped)
   const u32x4* const(&wc)[2 * TP] = w;
   const T* const(&xc)[NP] = x;
-  gemm_accumulate<T, 2 * TP, NB, NP>(wc, xc, a.d, ncols, acc, lane_piece(threadIdx.x & 63, R), fragment_pieces(R));
-  bool mine = false;
+  gemm_accumulate<T, 2 * TP, NB, NP>(wc, xc, a.d, ncols, a.nw, acc, lane_piece(threadIdx.x & 63, R), fragment_pieces(R), [&](auto when) {
 #pragma unroll
-  for (int q = 0; q < NP; ++q) {
-    rstd_finish(ssp[q], a.d / 16, ncols, a.inv_d, a.eps, pre[q], s_rstd[q]);
-    mine = reduce_waves<2 * TP>(acc[q], red_of_pass<2 * TP>(q));
-  }
-  if (!mine) return;
+    for (int q = 0; q < NP; ++q) {
+      if (decltype(when)::value == 0) rstd_issue(ssp[q], a.d / 16, ncols, a.nw, pre[q]);
+      else rstd_finish(ssp[q], a.d / 16, ncols, a.nw, a.inv_d, a.eps, pre[q], s_rstd[q]);
+    }
+  });
 #pragma unroll
-  for (int q = 0; q < NP; ++q) fold_columns<T, 2 * TP>(acc[q], ncols);  // all 64 lanes
-  const int lane = threadIdx.x & 63, col = lane & 15;
-  if (col >= ncols) return;
-  const int row0 = (lane >> 4) * 4;  // of the tile
+  for (int q = 0; q < NP; ++q) put_partials<2 * TP>(acc[q], red_of_pass<2 * TP>(q, a.nw));
+  __syncthreads();
+  const int row = threadIdx.x & 15;
+  for (int i = threadIdx.x; i < 16 * ncols; i += 64 * a.nw) {
+    const int col = i >> 4;
 #pragma unroll
-  for (int q = 0; q < NP; ++q) {
-    const float r = s_rstd[q][col];
-    T* dst = reinterpret_cast<T*>(ap[q]->act) + (size_t)li * Tr<T>::PARTS * kMaxCols * a.F;
+    for (int q = 0; q < NP; ++q) {
+      const float r = s_rstd[q][col];
+      T* dst = reinterpret_cast<T*>(ap[q]->act) + (size_t)li * Tr<T>::PARTS * kMaxCols * a.F;
 #pragma unroll
-    for (int p = 0; p < TP; ++p) {
-      const int t = t0 + p;
-      if (t >= ntile) break;
-      float o[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const float g = acc[q][2 * p][i] * r, u = acc[q][2 * p + 1][i] * r;
-        o[i] = (g / (1.0f + expf(-g))) * u;
-      }
-      if (R == 16) {
-        store_act4<T>(dst + xoff<T>(ncols, a.F, col, t * 16 + row0), (size_t)kMaxCols * a.F, o[0], o[1], o[2], o[3]);
-      } else {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int f = t * R + row0 + i;
-          if (row0 + i < R && f < a.F) store_act1<T>(dst + xoff<T>(ncols, a.F, col, f), (size_t)kMaxCols * a.F, o[i]);
-        }
+      for (int p = 0; p < TP; ++p) {
+        const int f = (t0 + p) * R + row;
+        const float* red = red_of_pass<2 * TP>(q, a.nw);
+        const float g = tile_sum<T, 2 * TP>(red, a.nw, 2 * p, row, col, ncols) * r, u = tile_sum<T, 2 * TP>(red, a.nw, 2 * p + 1, row, col, ncols) * r;
+        if (t0 + p < ntile && row < R && f < a.F) store_act1<T>(dst + xoff<T>(ncols, a.F, col, f), (size_t)kMaxCols * a.F, (g / (1.0f + expf(-g))) * u);
       }
     }
   }
@@ -447,6 +408,7 @@ __global__ __launch_bounds__(kTwinThreads) void gateup_twin_kernel(Twin<GateUpAr
 // LM head: logits + argmax candidates per row tile (lowest index wins ties).  grid = ceil(ceil(V/16) / TP).
 // ------------------------------------------------------------------------------------------
 struct HeadArgs {
+  int nw;  // waves of a workgroup
   const u32x4* w;
   const void* x;  // XA slot 0: T(h * g_final)
   const float* ssp;
@@ -475,54 +437,49 @@ __device__ __forceinline__ void head_body(const HeadArgs* const (&ap)[NP], const
 #pragma unroll
   for (int q = 0; q < NP; ++q) {
     x[q] = reinterpret_cast<const T*>(ap[q]->x);
-    rstd_issue(ap[q]->ssp, a.d / 16, ncols, pre[q]);
 #pragma unroll
     for (int p = 0; p < TP; ++p) acc[q][p] = f32x4{0.f, 0.f, 0.f, 0.f};
   }
   const u32x4* const(&wc)[TP] = w;
   const T* const(&xc)[NP] = x;
-  gemm_accumulate<T, TP, NB, NP>(wc, xc, a.d, ncols, acc);
-  bool mine = false;
+  gemm_accumulate<T, TP, NB, NP>(wc, xc, a.d, ncols, a.nw, acc, threadIdx.x & 63, 64, [&](auto when) {
 #pragma unroll
-  for (int q = 0; q < NP; ++q) {
-    rstd_finish(ap[q]->ssp, a.d / 16, ncols, a.inv_d, a.eps, pre[q], s_rstd[q]);
-    mine = reduce_waves<TP>(acc[q], red_of_pass<TP>(q));
-  }
-  if (!mine) return;
+    for (int q = 0; q < NP; ++q) {
+      if (decltype(when)::value == 0) rstd_issue(ap[q]->ssp, a.d / 16, ncols, a.nw, pre[q]);
+      else rstd_finish(ap[q]->ssp, a.d / 16, ncols, a.nw, a.inv_d, a.eps, pre[q], s_rstd[q]);
+    }
+  });
 #pragma unroll
-  for (int q = 0; q < NP; ++q) fold_columns<T, TP>(acc[q], ncols);  // all 64 lanes
-  const int lane = threadIdx.x & 63, col = lane & 15;
-  const bool ok = col < ncols;
+  for (int q = 0; q < NP; ++q) put_partials<TP>(acc[q], red_of_pass<TP>(q, a.nw));
+  __syncthreads();
+  const int row = threadIdx.x & 15;
+  for (int i = threadIdx.x; i < 16 * ncols; i += 64 * a.nw) {
+    const int col = i >> 4;
 #pragma unroll
-  for (int q = 0; q < NP; ++q) {
-    const HeadArgs& aq = *ap[q];
-    const Cols& c = *cp[q];
-    const float r = ok ? s_rstd[q][col] : 0.f;
+    for (int q = 0; q < NP; ++q) {
+      const HeadArgs& aq = *ap[q];
+      const float r = s_rstd[q][col];
 #pragma unroll
-    for (int p = 0; p < TP; ++p) {
-      const int t = t0 + p;
-      if (t >= a.nblk) break;
-      const int r0 = t * 16 + (lane >> 4) * 4;
-      float bv = -INFINITY;
-      int bi = 0x7FFFFFFF;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int row = r0 + i;
-        const float v = acc[q][p][i] * r;
-        if (ok && row < a.V) {
-          if (aq.logits && c.logit_row[col] >= 0) aq.logits[(size_t)c.logit_row[col] * a.V + row] = v;
-          if (better(v, row, bv, bi)) { bv = v; bi = row; }
+      for (int p = 0; p < TP; ++p) {
+        const int t = t0 + p, v_row = t * 16 + row;
+        if (t >= a.nblk) break;
+        const float v = tile_sum<T, TP>(red_of_pass<TP>(q, a.nw), a.nw, p, row, col, ncols) * r;
+        float bv = -INFINITY;
+        int bi = 0x7FFFFFFF;
+        if (v_row < a.V) {
+          if (aq.logits && cp[q]->logit_row[col] >= 0) aq.logits[(size_t)cp[q]->logit_row[col] * a.V + v_row] = v;
+          if (better(v, v_row, bv, bi)) { bv = v; bi = v_row; }
         }
-      }
 #pragma unroll
-      for (int off = 16; off <= 32; off <<= 1) {
-        const float ov = __shfl_xor(bv, off, 64);
-        const int oi = __shfl_xor(bi, off, 64);
-        if (better(ov, oi, bv, bi)) { bv = ov; bi = oi; }
-      }
-      if (ok && lane < 16) {
-        aq.cand_val[(size_t)col * a.nblk + t] = bv;
-        aq.cand_idx[(size_t)col * a.nblk + t] = bi;
+        for (int off = 1; off <= 8; off <<= 1) {
+          const float ov = __shfl_xor(bv, off, 64);
+          const int oi = __shfl_xor(bi, off, 64);
+          if (better(ov, oi, bv, bi)) { bv = ov; bi = oi; }
+        }
+        if (row == 0) {
+          aq.cand_val[(size_t)col * a.nblk + t] = bv;
+          aq.cand_idx[(size_t)col * a.nblk + t] = bi;
+        }
       }
     }
   }
@@ -833,6 +790,8 @@ bool twin_passes_fit(const Shape& s, int n_cols) {
   return true;
 }
 
+static dim3 plan_grid(const StreamPlan& p) { return dim3(p.grid / p.n_layers, p.n_layers); }
+
 // One pass, or (c2 given) two passes of equal column counts in one launch of the same shape, with a reduction
 // buffer for each pass.
 #define ES_LAUNCH_PASSES(K1, K2, grid, nw, lds, st, a, c, a2, c2)                     \
@@ -840,9 +799,9 @@ bool twin_passes_fit(const Shape& s, int n_cols) {
     if (c2) {                                                                         \
       Twin<std::decay_t<decltype(a)>> tw;                                             \
       tw.a[0] = a; tw.a[1] = a2; tw.c[0] = c; tw.c[1] = *(c2);                        \
-      ES_LAUNCH(K2, dim3(grid), dim3(64 * (nw)), 2 * (lds), st, tw);                  \
+      ES_LAUNCH(K2, grid, dim3(64 * (nw)), 2 * (lds), st, tw);                  \
     } else {                                                                          \
-      ES_LAUNCH(K1, dim3(grid), dim3(64 * (nw)), lds, st, a, c);                      \
+      ES_LAUNCH(K1, grid, dim3(64 * (nw)), lds, st, a, c);                      \
     }                                                                                 \
   } while (0)
 
@@ -851,6 +810,7 @@ void launch_qkv(const Shape& s, const Buffers& b, const Cols& c, int layer0, int
   const StreamPlan p = stream_plan(s, EASYSPEC_OP_QKV, c.n, n_set, false, c2 != nullptr);
   auto args = [&](const Buffers& w) {
     QkvArgs a;
+    a.nw = p.nw;
     a.w = (const u32x4*)w.wqkv + (size_t)layer0 * p.layer_pieces;
     a.w_layer_stride = p.layer_pieces;
     a.x = w.XA;
@@ -861,18 +821,18 @@ void launch_qkv(const Shape& s, const Buffers& b, const Cols& c, int layer0, int
     a.kc = w.kc;
     a.vc = w.vc;
     a.layer0 = layer0; a.d = s.d; a.Hq = s.Hq; a.Hkv = s.Hkv; a.hd = s.hd; a.B = s.B; a.max_ctx = s.max_ctx;
-    a.R = p.R;
+    a.R = p.R; a.units = p.units;
     a.inv_d = 1.0f / (float)s.d; a.eps = s.eps;
     return a;
   };
   const QkvArgs a = args(b), a2 = args(b2 ? *b2 : b);
   if (p.TP == 2) {
     // two tiles per workgroup share every fragment load (12-wide tree level 3292 -> 3282 us)
-    ES_LAUNCH_PASSES((qkv_kernel<bf16_t, 2, 2>), (qkv_twin_kernel<bf16_t, 2, 2>), p.grid, p.nw, red_bytes(p.nw, 4), st, a, c, a2, c2);
+    ES_LAUNCH_PASSES((qkv_kernel<bf16_t, 2, 2>), (qkv_twin_kernel<bf16_t, 2, 2>), plan_grid(p), p.nw, red_bytes(p.nw, 4), st, a, c, a2, c2);
     return;
   }
   DISPATCH_TNB(s.dtype, p.NB == 2,
-               ES_LAUNCH_PASSES((qkv_kernel<T, NB, 1>), (qkv_twin_kernel<T, NB, 1>), p.grid, p.nw, red_bytes(p.nw, 2), st, a, c, a2, c2));
+               ES_LAUNCH_PASSES((qkv_kernel<T, NB, 1>), (qkv_twin_kernel<T, NB, 1>), plan_grid(p), p.nw, red_bytes(p.nw, 2), st, a, c, a2, c2));
 }
 
 void launch_oproj(const Shape& s, const Buffers& b, const Cols& c, int layer0, int n_set, hipStream_t st, const Buffers* b2,
@@ -880,6 +840,7 @@ void launch_oproj(const Shape& s, const Buffers& b, const Cols& c, int layer0, i
   const StreamPlan p = stream_plan(s, EASYSPEC_OP_OPROJ, c.n, n_set, false, c2 != nullptr);
   auto args = [&](const Buffers& w) {
     ProjArgs a;
+    a.nw = p.nw;
     a.w = (const u32x4*)w.wo + (size_t)layer0 * p.layer_pieces;
     a.w_layer_stride = p.layer_pieces;
     a.x = w.AO;
@@ -894,11 +855,11 @@ void launch_oproj(const Shape& s, const Buffers& b, const Cols& c, int layer0, i
   const ProjArgs a = args(b), a2 = args(b2 ? *b2 : b);
   if (p.TP == 2) {
     // two row tiles per workgroup share every fragment load (12-wide tree level 3284 -> 3259 us)
-    ES_LAUNCH_PASSES((proj_resid_kernel<bf16_t, 2, 2>), (proj_resid_twin_kernel<bf16_t, 2, 2>), p.grid, p.nw, red_bytes(p.nw, 2), st, a, c, a2, c2);
+    ES_LAUNCH_PASSES((proj_resid_kernel<bf16_t, 2, 2>), (proj_resid_twin_kernel<bf16_t, 2, 2>), plan_grid(p), p.nw, red_bytes(p.nw, 2), st, a, c, a2, c2);
     return;
   }
   DISPATCH_TNB(s.dtype, p.NB == 2,
-               ES_LAUNCH_PASSES((proj_resid_kernel<T, NB, 1>), (proj_resid_twin_kernel<T, NB, 1>), p.grid, p.nw, red_bytes(p.nw, 1), st, a, c, a2, c2));
+               ES_LAUNCH_PASSES((proj_resid_kernel<T, NB, 1>), (proj_resid_twin_kernel<T, NB, 1>), plan_grid(p), p.nw, red_bytes(p.nw, 1), st, a, c, a2, c2));
 }
 
 void launch_gateup(const Shape& s, const Buffers& b, const Cols& c, int layer, int n_layers, const float* ssp, hipStream_t st,
@@ -906,10 +867,11 @@ void launch_gateup(const Shape& s, const Buffers& b, const Cols& c, int layer, i
   const StreamPlan p = stream_plan(s, EASYSPEC_OP_GATEUP, c.n, n_layers, false, c2 != nullptr);
   auto args = [&](const Buffers& w, const float* sums) {
     GateUpArgs a;
+    a.nw = p.nw;
     a.wg = (const u32x4*)w.wg + (size_t)layer * p.layer_pieces;
     a.wu = (const u32x4*)w.wu + (size_t)layer * p.layer_pieces;
     a.w_layer_stride = p.layer_pieces;
-    a.x = w.XM; a.ssp = sums; a.act = w.ACT; a.d = s.d; a.F = s.F; a.R = p.R;
+    a.x = w.XM; a.ssp = sums; a.act = w.ACT; a.d = s.d; a.F = s.F; a.R = p.R; a.units = p.units;
     a.inv_d = 1.0f / (float)s.d; a.eps = s.eps;
     return a;
   };
@@ -918,11 +880,11 @@ void launch_gateup(const Shape& s, const Buffers& b, const Cols& c, int layer, i
     // two fragments per k-tile: two row tiles of each matrix per workgroup, so that four MFMA row tiles
     // share every fragment load (measured: 12-wide tree level 3402 -> 3322 us; with one fragment the
     // larger workgroups lose: 6-token calibration 3377 -> 3411 us, draft step 2676 -> 2731 us)
-    ES_LAUNCH_PASSES((gateup_kernel<bf16_t, 2, 2>), (gateup_twin_kernel<bf16_t, 2, 2>), p.grid, p.nw, red_bytes(p.nw, 4), st, a, c, a2, c2);
+    ES_LAUNCH_PASSES((gateup_kernel<bf16_t, 2, 2>), (gateup_twin_kernel<bf16_t, 2, 2>), plan_grid(p), p.nw, red_bytes(p.nw, 4), st, a, c, a2, c2);
     return;
   }
   DISPATCH_TNB(s.dtype, p.NB == 2,
-               ES_LAUNCH_PASSES((gateup_kernel<T, NB, 1>), (gateup_twin_kernel<T, NB, 1>), p.grid, p.nw, red_bytes(p.nw, 2), st, a, c, a2, c2));
+               ES_LAUNCH_PASSES((gateup_kernel<T, NB, 1>), (gateup_twin_kernel<T, NB, 1>), plan_grid(p), p.nw, red_bytes(p.nw, 2), st, a, c, a2, c2));
 }
 
 void launch_down(const Shape& s, const Buffers& b, const Cols& c, int layer, int a_next, const float* gain, int n_gain,
@@ -930,6 +892,7 @@ void launch_down(const Shape& s, const Buffers& b, const Cols& c, int layer, int
   const StreamPlan p = stream_plan(s, EASYSPEC_OP_DOWN, c.n, 1, false, c2 != nullptr);
   auto args = [&](const Buffers& w, void* out) {
     ProjArgs a;
+    a.nw = p.nw;
     a.w = (const u32x4*)w.wd + (size_t)layer * p.layer_pieces;
     a.w_layer_stride = p.layer_pieces;
     a.x = w.ACT;
@@ -940,12 +903,13 @@ void launch_down(const Shape& s, const Buffers& b, const Cols& c, int layer, int
   };
   const ProjArgs a = args(b, xout), a2 = args(b2 ? *b2 : b, b2 ? xout2 : xout);
   DISPATCH_TNB(s.dtype, p.NB == 2,
-               ES_LAUNCH_PASSES((proj_resid_kernel<T, NB, 1>), (proj_resid_twin_kernel<T, NB, 1>), p.grid, p.nw, red_bytes(p.nw, 1), st, a, c, a2, c2));
+               ES_LAUNCH_PASSES((proj_resid_kernel<T, NB, 1>), (proj_resid_twin_kernel<T, NB, 1>), plan_grid(p), p.nw, red_bytes(p.nw, 1), st, a, c, a2, c2));
 }
 
 void launch_oproj_full(const Shape& s, const Buffers& b, const Cols& c, int layer0, int n_set, hipStream_t st) {
   ProjFullArgs a;
   const StreamPlan p = stream_plan(s, EASYSPEC_OP_OPROJ, c.n, n_set, true);
+  a.nw = p.nw;
   a.w = (const u32x4*)b.wo + (size_t)layer0 * p.layer_pieces;
   a.w_layer_stride = p.layer_pieces;
   a.x = b.AO;
@@ -956,13 +920,14 @@ void launch_oproj_full(const Shape& s, const Buffers& b, const Cols& c, int laye
   a.xout = b.XM;
   a.ssp = b.ssp_set;
   DISPATCH_TNB(s.dtype, p.NB == 2,
-               ES_LAUNCH((proj_full_kernel<T, NB>), dim3(p.grid), dim3(64 * p.nw), red_bytes(p.nw, 1), st, a, c));
+               ES_LAUNCH((proj_full_kernel<T, NB>), plan_grid(p), dim3(64 * p.nw), red_bytes(p.nw, 1), st, a, c));
 }
 
 void launch_down_full(const Shape& s, const Buffers& b, const Cols& c, int layer0, int n_set, const float* gain, int n_gain,
                       void* xout, hipStream_t st) {
   ProjFullArgs a;
   const StreamPlan p = stream_plan(s, EASYSPEC_OP_DOWN, c.n, n_set, true);
+  a.nw = p.nw;
   a.w = (const u32x4*)b.wd + (size_t)layer0 * p.layer_pieces;
   a.w_layer_stride = p.layer_pieces;
   a.x = b.ACT;
@@ -970,7 +935,7 @@ void launch_down_full(const Shape& s, const Buffers& b, const Cols& c, int layer
   a.H = b.H; a.A = b.A;
   a.gain = gain; a.n_gain = n_gain; a.xout = xout; a.ssp = b.ssp;
   DISPATCH_TNB(s.dtype, p.NB == 2,
-               ES_LAUNCH((proj_full_kernel<T, NB>), dim3(p.grid), dim3(64 * p.nw), red_bytes(p.nw, 1), st, a, c));
+               ES_LAUNCH((proj_full_kernel<T, NB>), plan_grid(p), dim3(64 * p.nw), red_bytes(p.nw, 1), st, a, c));
 }
 
 void launch_head(const Shape& s, const Buffers& b, const Cols& c, float* logits_out, int32_t* tokens_out, hipStream_t st,
@@ -978,6 +943,7 @@ void launch_head(const Shape& s, const Buffers& b, const Cols& c, float* logits_
   const StreamPlan p = stream_plan(s, EASYSPEC_OP_HEAD, c.n, 1, false, c2 != nullptr);
   auto args = [&](const Buffers& w) {
     HeadArgs a;
+    a.nw = p.nw;
     a.w = (const u32x4*)w.wlm; a.x = w.XA; a.ssp = w.ssp; a.logits = logits_out;
     a.cand_val = w.amax_val; a.cand_idx = w.amax_idx;
     a.d = s.d; a.V = s.V; a.nblk = p.units;
@@ -987,10 +953,10 @@ void launch_head(const Shape& s, const Buffers& b, const Cols& c, float* logits_
   const HeadArgs a = args(b), a2 = args(b2 ? *b2 : b);
   if (p.TP == 2) {
     // two row tiles per workgroup share every fragment load (12-wide tree level 3309 -> 3276 us; four: the same)
-    ES_LAUNCH_PASSES((head_kernel<bf16_t, 2, 2>), (head_twin_kernel<bf16_t, 2, 2>), p.grid, p.nw, red_bytes(p.nw, 2), st, a, c, a2, c2);
+    ES_LAUNCH_PASSES((head_kernel<bf16_t, 2, 2>), (head_twin_kernel<bf16_t, 2, 2>), plan_grid(p), p.nw, red_bytes(p.nw, 2), st, a, c, a2, c2);
   } else {
     DISPATCH_TNB(s.dtype, p.NB == 2,
-                 ES_LAUNCH_PASSES((head_kernel<T, NB, 1>), (head_twin_kernel<T, NB, 1>), p.grid, p.nw, red_bytes(p.nw, 1), st, a, c, a2, c2));
+                 ES_LAUNCH_PASSES((head_kernel<T, NB, 1>), (head_twin_kernel<T, NB, 1>), plan_grid(p), p.nw, red_bytes(p.nw, 1), st, a, c, a2, c2));
   }
   ES_LAUNCH(argmax_final_kernel, dim3(c.n), dim3(1024), 0, st, a.cand_val, a.cand_idx, a.nblk, tokens_out, c);
   if (c2) ES_LAUNCH(argmax_final_kernel, dim3(c2->n), dim3(1024), 0, st, a2.cand_val, a2.cand_idx, a2.nblk, tokens_out, *c2);

@@ -55,7 +55,7 @@ static inline int pick_waves(int dflt, int nkt, int RT, int grid, int most_waves
     }                                                                                                             \
   } while (0)
 
-static inline size_t red_bytes(int nw, int rt) { return (size_t)(nw > 1 ? nw - 1 : 0) * rt * 64 * sizeof(f32x4); }
+static inline size_t red_bytes(int nw, int rt) { return (size_t)red_floats(nw, rt) * sizeof(float); }
 
 // bf16 with more than 8 columns: hi and lo activation terms take a fragment each
 static inline bool two_fragments(int dtype, const Cols& c) { return dtype == 1 && 2 * c.n > kMaxCols; }

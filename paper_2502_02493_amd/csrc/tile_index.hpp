@@ -68,7 +68,8 @@ ES_HD constexpr size_t xoff_elems(int EPL, int ncols, int K, int col, int k) {
   const int KT = 4 * EPL;
   if (ncols <= kPlainCols) return (size_t)col * K + k;
   const int pitch = xpitch(ncols);
-  return (size_t)(k / KT) * (pitch * KT) + (size_t)((k % KT) / EPL) * (pitch * EPL) + col * EPL + (k % EPL);
+  const unsigned kt = (unsigned)k / KT, in = (unsigned)k % KT;  // unsigned: shifts
+  return (size_t)kt * (pitch * KT) + (in / EPL) * (pitch * EPL) + col * EPL + in % EPL;
 }
 // 16-byte fragments between the fragments of consecutive k-tiles
 ES_HD constexpr int xtile_fragments(int ncols) { return ncols <= kPlainCols ? 4 : 4 * xpitch(ncols); }

@@ -32,40 +32,47 @@ struct AttnArgs {
   float* PL;
   void* AO;
   int layer0, Hq, Hkv, B, max_ctx;
-  int CH;       // fixed-length cut (matrix-core kernel): slots per chunk
-  int nch_ref;  // even cut (vector kernel, nb_ref > 0): chunks of a column of nb_ref batches
-  int nb_ref;
+  int even;        // vector kernel: every column has the same number of chunks
+  int n;           // columns, or groups of them
+  float inv_n;     // 1 / n
+  int CH;       // matrix-core kernel: slots per chunk (0: the vector kernel)
+  int nch_ref;  // wide passes: partials of a head
+  int log2_nwv; // vector kernel: waves per workgroup, 4 or 8
   int direct;   // vector kernel: LDS holds the state of every slot group (see the kernel's last part)
   float scale;
 };
 
-// The split-KV cut of one column: its chunk count and the slot range [s0, s1) of chunk `chunk`
-// (empty for chunk >= nch).  Fixed-length cut: chunks of CH slots.  Even cut: the column's
-// units (of `unit` slots, the smallest step of a wave) are dealt to round(nb * nch_ref / nb_ref)
-// chunks whose unit counts differ by at most one, so that a context of a power-of-two length
-// plus a few drafted tokens does not leave a sliver of a chunk.
-__host__ __device__ __forceinline__ void chunk_range(const AttnArgs& a, int n_slots, int unit, int chunk, int& nch, int& s0,
-                                                     int& s1) {
-  if (a.nb_ref == 0) {
-    nch = (n_slots + a.CH - 1) / a.CH;
-    s0 = chunk * a.CH;
-    s1 = s0 + a.CH < n_slots ? s0 + a.CH : n_slots;
-  } else {
-    const int nb = (n_slots + unit - 1) / unit;
-    nch = (nb * a.nch_ref + a.nb_ref / 2) / a.nb_ref;
-    nch = nch > nb ? nb : nch;
-    nch = nch < 1 ? 1 : nch;
-    s0 = (int)((long)chunk * nb / nch) * unit;
-    s1 = (int)((long)(chunk + 1) * nb / nch) * unit;
-    s1 = s1 < n_slots ? s1 : n_slots;
-  }
+// The split-KV cut of one column for the vector kernel: its nb units (of `unit` slots, the smallest step of a wave) are dealt to
+// nch = round(nb * nch_ref / nb_ref) chunks whose unit counts differ by at most one, the longer ones first, so that a context of
+// a power-of-two length plus a few drafted tokens does not leave a sliver of a chunk.  The host works out count, quotient and
+// remainder for every column (ChunkMap): the kernels divide by nothing.  Four divisions by run-time numbers, two of them in 64 bits, the
+// grid's decoding and the launch's own dimensions stood before a wave's first load of K, 870 instructions in all, and behind the
+// chunk the slot groups were folded one LDS read after the other.  Attention and merge, us a call, before and after: 8B draft step
+// 139 -> 129, 6-token calibration 457 -> 440, 16 tokens at context 8192 (matrix cores) 770 -> 744, tree levels 384 -> 370,
+// Qwen2-7B step 144 -> 136; contexts 4096 .. 32768 unchanged.
+struct ColumnCut {
+  int32_t nch, quot, rest;
+};
+inline ColumnCut column_cut(int nch_ref, int nb_ref, int n_slots, int unit) {
+  const int nb = (n_slots + unit - 1) / unit;
+  int nch = (int)(((long)nb * nch_ref + nb_ref / 2) / nb_ref);
+  nch = nch > nb ? nb : nch;
+  nch = nch < 1 ? 1 : nch;
+  return ColumnCut{nch, nb / nch, nb % nch};
+}
+// slots [s0, s1) of chunk `chunk` < nch
+__host__ __device__ __forceinline__ void chunk_range(const ColumnCut& cut, int n_slots, int unit, int chunk, int& s0, int& s1) {
+  const int u0 = chunk * cut.quot + (chunk < cut.rest ? chunk : cut.rest);
+  s0 = u0 * unit;
+  s1 = (u0 + cut.quot + (chunk < cut.rest ? 1 : 0)) * unit;
+  s1 = s1 < n_slots ? s1 : n_slots;
 }
 
-// The run [w0, w1) of wave `wave` of `nwv` inside the chunk [s0, s1): the chunk's units dealt evenly.
-__host__ __device__ __forceinline__ void wave_range(int s0, int s1, int unit, int wave, int nwv, int& w0, int& w1) {
+// The run [w0, w1) of wave `wave` of 2^log2_nwv inside the chunk [s0, s1): the chunk's units dealt evenly.
+__host__ __device__ __forceinline__ void wave_range(int s0, int s1, int unit, int wave, int log2_nwv, int& w0, int& w1) {
   const int n_units = (s1 - s0 + unit - 1) / unit;
-  w0 = s0 + wave * n_units / nwv * unit;
-  w1 = s0 + (wave + 1) * n_units / nwv * unit;
+  w0 = s0 + (wave * n_units >> log2_nwv) * unit;
+  w1 = s0 + ((wave + 1) * n_units >> log2_nwv) * unit;
   w1 = w1 < s1 ? w1 : s1;
 }
 
@@ -81,19 +88,29 @@ struct AttnGeom {
 
 extern __shared__ float dyn_f[];
 
-// The chunks of a launch's columns: column i has first[i + 1] - first[i] of them, and its workgroups, [KV head][chunk], are
-// those from first[i] * Hkv on of the grid's first extent.  Columns of unequal length have unequal numbers of chunks; a
+// The chunks of a launch's columns: column i has col[i].cut.nch of them, and its workgroups, [KV head][chunk], are
+// those from first[i] on of the grid's first extent.  Columns of unequal length have unequal numbers of chunks; a
 // grid of (longest column's chunks) x KV heads x columns left its empty workgroups on the same XCDs again and again
 // (workgroup ids go to the eight XCDs in turn): contexts 4096 / 8192 / 16384 / 32768, attention and merge of a one-layer
 // set 64 -> 48 us, of a four-layer set 173 -> 166 (Qwen2-7B shape 37 -> 32, 112 -> 89).  Columns of one sequence keep
 // the distance of whole columns, a multiple of eight with eight KV heads, and so the XCD on which they meet each
 // other's K and V.
-// Columns of equal chunk counts (even != 0: one sequence, most batches of like lengths) keep the plain grid (chunk,
+// Columns of equal chunk counts (AttnArgs::even: one sequence, most batches of like lengths) keep the plain grid (chunk,
 // KV head, layer x column), which needs no division to find its place.
-struct ChunkMap {
-  int32_t even;
-  int32_t first[kMaxCols + 1];  // INT_MAX from the column count + 1 on
+// What a workgroup has to know of its column lies together: one scalar load.
+struct ColumnWork {
+  ColumnCut cut;
+  int32_t n_slots, seq, pad[3];
 };
+struct ChunkMap {
+  int32_t first[kMaxCols];  // first workgroup of a column (its first chunk's number times Hkv); INT_MAX: no such column
+  ColumnWork col[kMaxCols];
+};
+// layer and column (group) of a grid index layer * n + column: no division (both are small: off by far less than half a step)
+__device__ __forceinline__ void layer_and_column(const AttnArgs& a, int z, int& li, int& col) {
+  li = __builtin_amdgcn_readfirstlane((int)(((float)z + 0.5f) * a.inv_n));
+  col = z - li * a.n;
+}
 
 // TREE: the columns are nodes of token trees and carry a visibility mask; without it every
 // slot up to the column's own is visible and the mask logic costs no registers.
@@ -102,32 +119,34 @@ __global__ __launch_bounds__(512) void attn_kernel(AttnArgs a, Cols c, ChunkMap 
   typedef AttnGeom<T, HD> Geo;
   constexpr int EPL = Geo::EPL, LPS = Geo::LPS, SPW = Geo::SPW, IT = kAttnIT;
   int li, col, kvh, chunk;
-  if (map.even) {
+  if (a.even) {
     chunk = blockIdx.x;
     kvh = blockIdx.y;
-    li = blockIdx.z / c.n;
-    col = blockIdx.z % c.n;
+    layer_and_column(a, blockIdx.z, li, col);
   } else {
     li = blockIdx.y;
     col = 0;
 #pragma unroll
-    for (int i = 1; i < kMaxCols; ++i) col += (int)blockIdx.x / a.Hkv >= map.first[i];
-    const int of_col = blockIdx.x - map.first[col] * a.Hkv, chunks = map.first[col + 1] - map.first[col];
-    kvh = of_col / chunks;
-    chunk = of_col % chunks;
+    for (int i = 1; i < kMaxCols; ++i) col += (int)blockIdx.x >= map.first[i];
+    const int of_col = blockIdx.x - map.first[col], chunks = map.col[col].cut.nch;
+    kvh = (int)(((float)of_col + 0.5f) / (float)chunks);  // of_col < kMaxChunks * Hkv: off by far less than half a step
+    kvh = __builtin_amdgcn_readfirstlane(kvh);
+    chunk = of_col - kvh * chunks;
   }
-  const int n_slots = c.pos[col] + 1;
+  const ColumnWork cw = map.col[col];
+  const int n_slots = cw.n_slots;
   // slots below vis_base are all visible; slot vis_base + i (i < 64) only if bit i is set (the
   // column's row of a token tree's mask).  Causal columns have vis_base = n_slots.
-  const int vbase = c.vis_base[col];
-  const unsigned long long vmask = c.vis_mask[col];
-  int nch, s0, s1;
-  chunk_range(a, n_slots, Geo::UNIT, chunk, nch, s0, s1);
+  const int vbase = TREE ? c.vis_base[col] : 0;
+  const unsigned long long vmask = TREE ? c.vis_mask[col] : 0;
+  const int nch = cw.cut.nch;
   if (chunk >= nch) return;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, NWV = blockDim.x >> 6;  // 4 or 8 waves
+  int s0, s1;
+  chunk_range(cw.cut, n_slots, Geo::UNIT, chunk, s0, s1);
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), NWV = 1 << a.log2_nwv;  // 4 or 8 waves
   const int sub = lane / LPS, e0 = (lane % LPS) * EPL;
 
-  const size_t rowbase = (((size_t)(a.layer0 + li) * a.B + c.seq[col]) * a.Hkv + kvh) * (size_t)a.max_ctx;
+  const size_t rowbase = (((size_t)(a.layer0 + li) * a.B + cw.seq) * a.Hkv + kvh) * (size_t)a.max_ctx;
   // wave-uniform row bases; a lane's fragment of slot s lies s * HD + e0 elements further (32-bit offsets)
   const char* kb = reinterpret_cast<const char*>(reinterpret_cast<const T*>(a.kc) + rowbase * HD);
   const char* vb = reinterpret_cast<const char*>(reinterpret_cast<const T*>(a.vc) + rowbase * HD);
@@ -166,7 +185,12 @@ __global__ __launch_bounds__(512) void attn_kernel(AttnArgs a, Cols c, ChunkMap 
   }
   auto split_q = [&] {
 #pragma unroll
-    for (int kt = 0; kt < QKT; ++kt) split_bf16x8(q_raw[kt], qh[kt], ql[kt]);
+    for (int kt = 0; kt < QKT; ++kt) {
+      // the compiler would move the conversions, and with them the wait for the queries, in front of the requests for K and V
+#pragma unroll
+      for (int e = 0; e < 8; ++e) asm volatile("" : "+v"(q_raw[kt][e]));
+      split_bf16x8(q_raw[kt], qh[kt], ql[kt]);
+    }
   };
 #pragma unroll
   for (int g = 0; g < G; ++g) {
@@ -186,7 +210,7 @@ __global__ __launch_bounds__(512) void attn_kernel(AttnArgs a, Cols c, ChunkMap 
   // of the slots.  Slots past w1 fetch the run's last row instead (their scores are discarded
   // below): unconditional loads, no branch per load.
   int w0, w1;
-  wave_range(s0, s1, Geo::UNIT, wave, NWV, w0, w1);
+  wave_range(s0, s1, Geo::UNIT, wave, a.log2_nwv, w0, w1);
   auto fetch_k = [&](auto n_loads, int base, u32x4* kr) {
 #pragma unroll
     for (int j = 0; j < decltype(n_loads)::value; ++j) {
@@ -503,21 +527,40 @@ __global__ __launch_bounds__(512) void attn_kernel(AttnArgs a, Cols c, ChunkMap 
       }
     }
     __syncthreads();
-    for (int idx = tid; idx < G * HD / 2; idx += blockDim.x) {
-      const int g = idx / (HD / 2), e = (idx % (HD / 2)) * 2;
-      float m = w_m[g * P];
-      for (int q = 1; q < P; ++q) m = fmaxf(m, w_m[g * P + q]);
-      const float m_ref = m == -INFINITY ? 0.f : m;
-      float l = 0.f, o0 = 0.f, o1 = 0.f;
-      for (int q = 0; q < P; ++q) {  // in group order: the result does not depend on timing
-        const float wgt = __expf(w_m[g * P + q] - m_ref);
-        const float2 v = *reinterpret_cast<const float2*>(w_acc + (q * G + g) * HD + e);
-        l += w_l[g * P + q] * wgt;
-        o0 += v.x * wgt;
-        o1 += v.y * wgt;
+    auto fold = [&](auto n_groups) {
+      constexpr int N = decltype(n_groups)::value;
+      for (int idx = tid; idx < G * HD / 2; idx += 64 * NWV) {
+        const int g = idx / (HD / 2), e = (idx % (HD / 2)) * 2;
+        float mm[N], ll[N];
+        float2 v[N];
+#pragma unroll
+        for (int q = 0; q < N; q += 4) {
+          const f32x4 m4 = *reinterpret_cast<const f32x4*>(w_m + g * N + q), l4 = *reinterpret_cast<const f32x4*>(w_l + g * N + q);
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            mm[q + i] = m4[i];
+            ll[q + i] = l4[i];
+          }
+        }
+#pragma unroll
+        for (int q = 0; q < N; ++q) v[q] = *reinterpret_cast<const float2*>(w_acc + (q * G + g) * HD + e);
+        float m = mm[0];
+#pragma unroll
+        for (int q = 1; q < N; ++q) m = fmaxf(m, mm[q]);
+        const float m_ref = m == -INFINITY ? 0.f : m;
+        float l = 0.f, o0 = 0.f, o1 = 0.f;
+#pragma unroll
+        for (int q = 0; q < N; ++q) {  // in group order: the result does not depend on timing
+          const float wgt = __expf(mm[q] - m_ref);
+          l += ll[q] * wgt;
+          o0 += v[q].x * wgt;
+          o1 += v[q].y * wgt;
+        }
+        emit(g, e, m, l, o0, o1);
       }
-      emit(g, e, m, l, o0, o1);
-    }
+    };
+    if (NWV == 4) fold(std::integral_constant<int, 4 * SPW>{});
+    else fold(std::integral_constant<int, 8 * SPW>{});
   } else {
     // LDS too small for every group: the groups of a wave are combined with shuffles first
 #pragma unroll
@@ -554,7 +597,7 @@ __global__ __launch_bounds__(512) void attn_kernel(AttnArgs a, Cols c, ChunkMap 
       }
     }
     __syncthreads();
-    for (int idx = tid; idx < G * HD / 2; idx += blockDim.x) {
+    for (int idx = tid; idx < G * HD / 2; idx += 64 * NWV) {
       const int g = idx / (HD / 2), e = (idx % (HD / 2)) * 2;
       float m = w_m[g];
       for (int w = 1; w < NWV; ++w) m = fmaxf(m, w_m[w * G + g]);
@@ -597,9 +640,12 @@ __global__ __launch_bounds__(512) void attn_kernel(AttnArgs a, Cols c, ChunkMap 
 // grid = (chunks, Hkv, k * groups), block = 64 * NW.
 // ------------------------------------------------------------------------------------------
 struct ColGroups {
-  int32_t n;                // groups
-  int32_t first[kMaxCols];  // first column of group i
-  int32_t count[kMaxCols];  // its columns (consecutive, same sequence); count * G <= 16 NW
+  int32_t n;  // groups
+  struct Group {
+    int32_t first, count, seq;  // columns (consecutive, same sequence); count * G <= 16 NW
+    int32_t n_max, n_all;       // slots the longest of them attends to; slots below this one are visible to all
+    int32_t pad[3];
+  } g[kMaxCols];
 };
 // What the kernel asks about its columns: those of a pass of at most kMaxCols (PassCols), or of a wide pass, whose
 // columns are given by sequence (SpanCols).
@@ -608,12 +654,6 @@ struct PassCols {
   ColGroups cg;
   static constexpr bool kWide = false;
   static constexpr int kQueryTerms = 2;
-  __device__ __forceinline__ int n_groups() const { return cg.n; }
-  __device__ __forceinline__ void group(int i, int& first, int& cnt, int& seq) const {
-    first = cg.first[i];
-    cnt = cg.count[i];
-    seq = c.seq[first];
-  }
 };
 template <int QT>
 struct SpanCols {
@@ -623,7 +663,6 @@ struct SpanCols {
   int32_t most;                    // columns of a full group
   static constexpr bool kWide = true;
   static constexpr int kQueryTerms = QT;  // bf16 terms of a query: two or three (queries_in_fp32)
-  __device__ __forceinline__ int n_groups() const { return n; }
 };
 typedef short v4i16 __attribute__((ext_vector_type(4)));
 typedef short v8i16 __attribute__((ext_vector_type(8)));
@@ -635,8 +674,11 @@ __global__ __launch_bounds__(64 * NW, NW == 1 ? 1 : 2) void attn_mfma_kernel(Att
   __shared__ bool s_odd[NW];  // causal columns: a wave's part of the V tile holds something that is not finite
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int chunk = blockIdx.x, kvh = blockIdx.y;
-  const int li = blockIdx.z / src.n_groups(), grp = blockIdx.z % src.n_groups();
+  int li = 0, grp = blockIdx.z;  // wide passes are one layer
+  if constexpr (!Src::kWide) layer_and_column(a, blockIdx.z, li, grp);
   int first, cnt, seq, pos_first = 0;  // the group's columns, their sequence, the position of its first (wide passes)
+  int n_max;  // slots the longest column of the group attends to
+  int n_all;  // slots below this one are visible to every column of the group
   if constexpr (Src::kWide) {
     int e = 0;
 #pragma unroll
@@ -646,25 +688,17 @@ __global__ __launch_bounds__(64 * NW, NW == 1 ? 1 : 2) void attn_mfma_kernel(Att
     cnt = min(src.most, src.sp.first[e + 1] - first);
     seq = src.sp.seq[e];
     pos_first = src.sp.pos0[e] + skip;
+    n_max = pos_first + cnt;
+    n_all = pos_first + 1;
   } else {
-    src.group(grp, first, cnt, seq);
+    const ColGroups::Group w = src.cg.g[grp];  // the host has gone through the columns: one scalar load instead of two a column
+    first = w.first; cnt = w.count; seq = w.seq; n_max = w.n_max; n_all = w.n_all;
   }
   const int r = lane & 15, q4 = lane >> 4;  // query row (MFMA column) and quarter / k-group
   const int row = wave * 16 + r;
   const bool active = wave * 16 < cnt * G;  // wave-uniform: a wave without query rows only helps to load the tiles
   const bool row_ok = row < cnt * G;
   const int col = first + (row_ok ? row / G : 0), g = row_ok ? row % G : 0;
-  int n_max = 0;         // slots the longest column of the group attends to
-  int n_all = INT_MAX;   // slots below this one are visible to every column of the group
-  if constexpr (Src::kWide) {
-    n_max = pos_first + cnt;
-    n_all = pos_first + 1;
-  } else {
-    for (int i = 0; i < cnt; ++i) {
-      n_max = max(n_max, src.c.pos[first + i] + 1);
-      n_all = min(n_all, TREE ? min(src.c.pos[first + i] + 1, src.c.vis_base[first + i]) : src.c.pos[first + i] + 1);
-    }
-  }
   const int ws0 = chunk * a.CH;
   if (ws0 >= n_max) return;  // whole workgroup
   const int ws1 = min(ws0 + a.CH, n_max);
@@ -879,9 +913,8 @@ __global__ __launch_bounds__(64 * NW, NW == 1 ? 1 : 2) void attn_mfma_kernel(Att
   l_run += __shfl_xor(l_run, 16, 64);
   l_run += __shfl_xor(l_run, 32, 64);
   if (!row_ok || ws0 >= n_slots) return;  // padding rows; columns that end before this chunk
-  const int nch = (n_slots + a.CH - 1) / a.CH;
   const int head = kvh * G + g;
-  if (nch == 1) {
+  if (n_slots <= a.CH) {  // the whole context
 #pragma unroll
     for (int et = 0; et < ET; ++et) {
       const int e = et * 16 + q4 * 4;
@@ -913,24 +946,29 @@ __global__ __launch_bounds__(64 * NW, NW == 1 ? 1 : 2) void attn_mfma_kernel(Att
 // launch: the kernel boundary is what makes the partials written by workgroups on other XCDs
 // visible (a device-scope fence inside the attention kernel costs an L2 write-back per workgroup
 // and was measured several times slower).  Columns whose context fits one chunk were finished by
-// attn_kernel.  grid = (k * columns, Hq), block = HD: one thread per output element, one small
+// attn_kernel.  grid = (columns, Hq, k), block = HD: one thread per output element, one small
 // workgroup per head, so that the launch is as wide as the partials allow and costs one memory
 // latency whatever the number of heads that share a KV head.
-// Src: Cols, or Spans for the columns of a wide pass (chunks of CH slots, partials nch_ref apart, wide operand).
+// Src: MergeCols, or Spans for the columns of a wide pass (chunks of CH slots, partials nch_ref apart, wide operand).
+// The columns of a merge launch: those of a pass with their chunk counts, or of a wide pass.
+struct MergeCols {
+  int32_t n;
+  int32_t nch[kMaxCols];
+};
 template <typename T, int HD, class Src>
 __global__ __launch_bounds__(HD) void attn_merge_kernel(AttnArgs a, Src c) {
   constexpr bool kWide = std::is_same<Src, Spans>::value;
-  __shared__ float s_w[kMaxChunks];   // exp(m_chunk - m); chunk count <= 64 = one lane each
-  __shared__ float s_lw[kMaxChunks];  // the chunk's sum on the common reference
-  const int li = blockIdx.x / c.n, col = blockIdx.x % c.n, head = blockIdx.y, e = threadIdx.x;
-  int nch, s0_unused, s1_unused;
+  __shared__ float s_w[kMaxChunks];  // exp(m_chunk - m); chunk count <= 64 = one lane each
+  __shared__ float s_tot;            // the chunks' sums on the common reference
+  const int col = blockIdx.x, head = blockIdx.y, li = blockIdx.z, e = threadIdx.x;
+  int nch;
   size_t pitch = kMaxChunks;
   if constexpr (kWide) {
     const int en = span_entry(c, col);
     nch = (c.pos0[en] + (col - c.first[en]) + a.CH) / a.CH;
     pitch = a.nch_ref;
   } else {
-    chunk_range(a, c.pos[col] + 1, AttnGeom<T, HD>::UNIT, 0, nch, s0_unused, s1_unused);
+    nch = c.nch[col];
   }
   if (nch == 1) return;
   const int HQ = a.Hq * HD;
@@ -944,16 +982,13 @@ __global__ __launch_bounds__(HD) void attn_merge_kernel(AttnArgs a, Src c) {
   if (e < 64) {  // the first wave: one lane per chunk
     const float pm = e < nch ? a.PM[row * pitch + e] : -INFINITY;
     const float pl = e < nch ? a.PL[row * pitch + e] : 0.f;
-    float m = pm;
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, 64));
-    const float wgt = __expf(pm - m);
+    const float wgt = __expf(pm - wave_max(pm));
     s_w[e] = wgt;
-    s_lw[e] = pl * wgt;
+    const float all = wave_sum(pl * wgt);
+    if (e == 0) s_tot = all;
   }
   __syncthreads();
-  float tot = 0.f;  // in chunk order so that the result does not depend on a reduction tree
-  for (int ch = 0; ch < nch; ++ch) tot += s_lw[ch];
+  const float tot = s_tot;
   float o = 0.f;
 #pragma unroll
   for (int u = 0; u < 16; ++u) o += pv[u] * (u < nch ? s_w[u] : 0.f);
@@ -1042,10 +1077,12 @@ static void group_columns(const Cols& c, int G, int n_tiles, ColGroups& cg) {
   for (int i = 0; i < c.n;) {
     int j = i + 1;
     while (j < c.n && c.seq[j] == c.seq[i] && j - i < most) ++j;
-    cg.first[cg.n] = i;
-    cg.count[cg.n] = j - i;
-    ++cg.n;
-    i = j;
+    ColGroups::Group& g = cg.g[cg.n++];
+    g.first = i; g.count = j - i; g.seq = c.seq[i]; g.n_max = 0; g.n_all = INT_MAX;
+    for (; i < j; ++i) {
+      g.n_max = std::max(g.n_max, c.pos[i] + 1);
+      g.n_all = std::min(g.n_all, std::min(c.pos[i] + 1, c.vis_base[i]));  // causal columns: vis_base = pos + 1
+    }
   }
 }
 
@@ -1076,7 +1113,7 @@ AttnCut attn_cut(const Shape& s, const Cols& c, int n_set) {
     auto nch = [&](int ch_) { return (max_len + ch_ - 1) / ch_; };
     auto wgs = [&](int ch_) {
       long n = 0;
-      for (int i = 0; i < cg.n; ++i) n += (c.pos[cg.first[i] + cg.count[i] - 1] + ch_) / ch_;
+      for (int i = 0; i < cg.n; ++i) n += (c.pos[cg.g[i].first + cg.g[i].count - 1] + ch_) / ch_;
       return n * s.Hkv * n_set;
     };
     // Waves aimed at: eight per CU (two per SIMD hide each other's chains) while a workgroup still has four super
@@ -1146,20 +1183,22 @@ AttnCut attn_cut_vector(const Shape& s, const Cols& c, int n_set) {
   return cut;
 }
 
+// slots of a wave's smallest step
+static int attn_unit(const Shape& s) { return kAttnSmallIT * (64 / (s.hd * (s.dtype == 1 ? 2 : 4) / 16)); }
+
 int attn_waves(const AttnCut& cut) { return cut.n_chunks == 1 ? 8 : 4; }
 
 void attn_ranges(const Shape& s, const AttnCut& cut, int n_slots, int chunk, int wave, int* nch, int* w0, int* w1) {
-  AttnArgs a;
-  a.CH = cut.chunk; a.nch_ref = cut.n_chunks; a.nb_ref = cut.nb_ref;
-  const int lps = s.hd * (s.dtype == 1 ? 2 : 4) / 16;
-  const int unit = kAttnSmallIT * (64 / lps);
-  int s0, s1;
-  chunk_range(a, n_slots, unit, chunk, *nch, s0, s1);
-  if (chunk >= *nch) {
+  const int unit = attn_unit(s);
+  const ColumnCut cc = column_cut(cut.n_chunks, cut.nb_ref, n_slots, unit);
+  *nch = cc.nch;
+  if (chunk >= cc.nch) {
     *w0 = *w1 = 0;
     return;
   }
-  wave_range(s0, s1, unit, wave, attn_waves(cut), *w0, *w1);
+  int s0, s1;
+  chunk_range(cc, n_slots, unit, chunk, s0, s1);
+  wave_range(s0, s1, unit, wave, attn_waves(cut) == 8 ? 3 : 2, *w0, *w1);
 }
 
 void launch_attn(const Shape& s, const Buffers& b, const Cols& c, int layer0, int n_set, const AttnCut& cut, hipStream_t st) {
@@ -1167,9 +1206,12 @@ void launch_attn(const Shape& s, const Buffers& b, const Cols& c, int layer0, in
   AttnArgs a;
   a.Q = b.Q; a.kc = b.kc; a.vc = b.vc; a.PO = b.PO; a.PM = b.PM; a.PL = b.PL; a.AO = b.AO;
   a.layer0 = layer0; a.Hq = s.Hq; a.Hkv = s.Hkv; a.B = s.B; a.max_ctx = s.max_ctx;
-  a.CH = cut.chunk; a.nch_ref = cut.n_chunks; a.nb_ref = cut.nb_ref;
+  a.CH = cut.chunk; a.nch_ref = cut.n_chunks;
+  a.log2_nwv = attn_waves(cut) == 8 ? 3 : 2;
   a.scale = 1.0f / sqrtf((float)s.hd);
   const int G = s.Hq / s.Hkv;
+  MergeCols mc;
+  mc.n = c.n;
   // one chunk per context: eight waves share the whole context of a (layer, column, KV head) and
   // no merge launch is needed; several chunks: four waves per chunk
   const int nwv = attn_waves(cut);
@@ -1179,6 +1221,9 @@ void launch_attn(const Shape& s, const Buffers& b, const Cols& c, int layer0, in
     PassCols src;
     src.c = c;
     group_columns(c, G, cut.tiles, src.cg);
+    a.n = src.cg.n;
+    a.inv_n = 1.0f / (float)a.n;
+    for (int i = 0; i < c.n; ++i) mc.nch[i] = (c.pos[i] + cut.chunk) / cut.chunk;
     const dim3 mg(n_chunks, s.Hkv, n_set * src.cg.n), blk(64 * cut.tiles);
     auto go = [&](auto hd, auto is_tree) {
       constexpr int HD = decltype(hd)::value;
@@ -1196,16 +1241,20 @@ void launch_attn(const Shape& s, const Buffers& b, const Cols& c, int layer0, in
   } else {
     ChunkMap map;
     int total = 0;
-    map.even = 1;
-    for (int i = 0; i <= kMaxCols; ++i) {
-      map.first[i] = i <= c.n ? total : INT_MAX;
+    a.even = 1;
+    a.n = c.n;
+    a.inv_n = 1.0f / (float)a.n;
+    for (int i = 0; i < kMaxCols; ++i) {
+      map.first[i] = i < c.n ? total * s.Hkv : INT_MAX;
       if (i >= c.n) continue;
-      int nch = 0, w0, w1;
-      attn_ranges(s, cut, c.pos[i] + 1, 0, 0, &nch, &w0, &w1);  // the kernel's own count
-      total += nch;
-      if (nch != n_chunks) map.even = 0;
+      map.col[i].cut = column_cut(n_chunks, cut.nb_ref, c.pos[i] + 1, attn_unit(s));
+      map.col[i].n_slots = c.pos[i] + 1;
+      map.col[i].seq = c.seq[i];
+      mc.nch[i] = map.col[i].cut.nch;
+      total += mc.nch[i];
+      if (mc.nch[i] != n_chunks) a.even = 0;
     }
-    const dim3 grid = map.even ? dim3(n_chunks, s.Hkv, n_set * c.n) : dim3(total * s.Hkv, n_set);
+    const dim3 grid = a.even ? dim3(n_chunks, s.Hkv, n_set * c.n) : dim3(total * s.Hkv, n_set);
     DISPATCH_T(s.dtype, {
       if (s.hd == 128 && tree) launch_attn_g<T, 128, true>(G, grid, nwv, st, a, c, map);
       else if (s.hd == 128) launch_attn_g<T, 128, false>(G, grid, nwv, st, a, c, map);
@@ -1214,10 +1263,10 @@ void launch_attn(const Shape& s, const Buffers& b, const Cols& c, int layer0, in
     });
   }
   if (n_chunks > 1) {
-    const dim3 mgrid(n_set * c.n, s.Hq);
+    const dim3 mgrid(c.n, s.Hq, n_set);
     DISPATCH_T(s.dtype, {
-      if (s.hd == 128) ES_LAUNCH((attn_merge_kernel<T, 128, Cols>), mgrid, dim3(128), 0, st, a, c);
-      else ES_LAUNCH((attn_merge_kernel<T, 64, Cols>), mgrid, dim3(64), 0, st, a, c);
+      if (s.hd == 128) ES_LAUNCH((attn_merge_kernel<T, 128, MergeCols>), mgrid, dim3(128), 0, st, a, mc);
+      else ES_LAUNCH((attn_merge_kernel<T, 64, MergeCols>), mgrid, dim3(64), 0, st, a, mc);
     });
   }
 }
@@ -1283,7 +1332,7 @@ static void launch_wide_attn_terms(const Shape& s, const Buffers& b, const WideB
   AttnArgs a;
   a.Q = w.Q; a.kc = b.kc; a.vc = b.vc; a.PO = b.PO; a.PM = b.PM; a.PL = b.PL; a.AO = w.AO;
   a.layer0 = layer; a.Hq = s.Hq; a.Hkv = s.Hkv; a.B = s.B; a.max_ctx = s.max_ctx;
-  a.CH = ch; a.nch_ref = nch(ch); a.nb_ref = 0; a.direct = 0;
+  a.CH = ch; a.nch_ref = nch(ch); a.log2_nwv = 0; a.direct = 0; a.even = 0; a.n = src.n; a.inv_n = 0.f;
   a.scale = 1.0f / sqrtf((float)s.hd);
   const dim3 grid(a.nch_ref, s.Hkv, src.n), blk(64 * tiles);
   auto go = [&](auto hd) {

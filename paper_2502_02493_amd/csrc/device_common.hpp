@@ -400,6 +400,8 @@ __device__ __forceinline__ float tile_sum(const float* red, int NW, int r, int r
     add(std::integral_constant<int, 8>{}, p);
   } else if (NW == 4) {
     add(std::integral_constant<int, 4>{}, p);
+  } else if (NW == 7) {
+    add(std::integral_constant<int, 7>{}, p);
   } else {
 #pragma unroll 1
     for (int w = 0; w < NW; ++w) add(std::integral_constant<int, 1>{}, p + red_floats(w, RT));
@@ -425,7 +427,18 @@ __device__ __forceinline__ float group_sum(float v) {
   if (N >= 32) v += __shfl_xor(v, 16, 64);
   return v;
 }
-// ... and over all 64, without a trip through LDS
+// ... and over all 64, without a trip through LDS; the maximum likewise
+__device__ __forceinline__ float wave_max(float v) {
+  v = fmaxf(v, dpp_f32<0xB1>(v));
+  v = fmaxf(v, dpp_f32<0x4E>(v));
+  v = fmaxf(v, dpp_f32<0x141>(v));
+  v = fmaxf(v, dpp_f32<0x140>(v));
+  const uint32_t a = __float_as_uint(v);
+  const auto q = __builtin_amdgcn_permlane16_swap(a, a, false, false);
+  const uint32_t b = __float_as_uint(fmaxf(__uint_as_float(q[0]), __uint_as_float(q[1])));
+  const auto h = __builtin_amdgcn_permlane32_swap(b, b, false, false);
+  return fmaxf(__uint_as_float(h[0]), __uint_as_float(h[1]));
+}
 __device__ __forceinline__ float wave_sum(float v) {
   const uint32_t a = __float_as_uint(group_sum<16>(v));
   const auto q = __builtin_amdgcn_permlane16_swap(a, a, false, false);

@@ -8,75 +8,130 @@
 //   bonus ~ max(0, p_m - p'_m) / sum  (m < gamma),  p_gamma  (m = gamma), drawn by inverse CDF in
 //   index order with the given uniform u: the lowest v whose running sum exceeds u * sum.
 //
-// Three launches, all spread over the vocabulary so that no single workgroup has to evaluate
-// 10^5 double-precision exponentials:
-//   (1) accept_stats_kernel    per logit row and vocabulary slice: slice maximum and
-//                              sum exp((l - max) / T)  (combined by the readers); a thread holds its
-//                              logits in registers, so the slice is read once;
-//   (2) accept_weights_kernel  every workgroup repeats the gamma accept decisions (a few dozen
-//                              exponentials, one per thread), then writes the unnormalised bonus weights
-//                              q(v) of its vocabulary chunk and the chunk's sum;
-//   (3) accept_draw_kernel     one workgroup per sequence: running sum over the chunk sums in
-//                              index order, then inside the chunk the draw lands in.
-// Bound by fp64 latency and three dependent launches, not by the 5.6 MB of logits.  gamma 5, vocabulary 128 256:
-// stats 25.1 -> 9.7 us (256 threads reading a slice twice, an fp64 division per exponential; 9.3 with a product by 1 / T
-// and sums against each thread's own maximum, which round once more), weights 23.6 -> 5.7 (one
-// thread took all decisions), draw 7.2 -> 6.1; the whole call 57 -> 21.5 us.
+// Two launches, both spread over the vocabulary so that no single workgroup has to evaluate 10^5 double-precision
+// exponentials:
+//   (1) accept_stats_kernel    per logit row and vocabulary slice: slice maximum and sum exp((l - max) / T)  (combined by
+//                              the readers); a thread holds its logits in registers, so the slice is read once;
+//   (2) accept_draw_kernel     every workgroup repeats the gamma accept decisions (a few exponentials a thread), then adds up
+//                              the unnormalised bonus weights q(v) of its vocabulary chunk.  The last workgroup of a
+//                              sequence to have done so draws: running sum over the chunk sums in index order, then over the
+//                              weights of the chunk the draw lands in, worked out once more (no weight is ever stored).
+// "Last" is told by a counter; it says whose sums have been sent, and (1) marks them all as missing, so the last workgroup sees
+// when they are there.  (No fence, which would write back the L2, and no wait for a store's acknowledgement.)
+// Bound by fp64 latency and two dependent launches, not by the 5.6 MB of logits.  gamma 5, vocabulary 128 256, one sequence: three
+// launches (8 slices of 1024 threads with sixteen exponentials each, weights, draw) 9.7 + 5.7 + 6.1 us, now 6.2 + 10.5; the whole
+// call 21.2 -> 15.6.  Of the second launch 2.3 us were statistics loaded one round after the other, reductions through LDS and the
+// acknowledgement of a chunk sum ahead of the counter.
 #include "kernels.h"
 
 #include <mutex>
 
 namespace es {
 
-constexpr int kStatSlices = 8;     // workgroups per logit row in (1)
-constexpr int kChunk = 2048;       // vocabulary entries per workgroup in (2) = 2 per thread in (3)
-constexpr int kAcceptThreads = 1024;
-constexpr int kStatRegs = 16;      // logits a thread of (1) holds at a time
-constexpr int kDrawThreads = kChunk / 2;
+constexpr int kMinSlices = 8, kMaxSlices = 64;  // workgroups per logit row in (1), a power of two (accept_plan)
+constexpr int kStatThreads = 512;
+constexpr int kStatRegs = 8;       // logits a thread of (1) holds at a time
+constexpr int kDrawThreads = 256;  // threads of (2); 2 or 8 vocabulary entries each
+constexpr int kWsChunk = 2048;     // the workspace has room for a double per so many entries besides one for each
 
+// Reductions over 8, 16, 32 or 64 neighbouring lanes (n, uniform) by operand swizzles, every lane receiving the result; a shuffle
+// through LDS per step would stand in the chain that these kernels are.
+template <int CTRL>
+__device__ __forceinline__ float dpp(float v) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xF, 0xF, true));
+}
+template <int CTRL>
+__device__ __forceinline__ double dpp(double v) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, CTRL, 0xF, 0xF, true);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), CTRL, 0xF, 0xF, true);
+  return __builtin_bit_cast(double, (uint64_t)lo | ((uint64_t)hi << 32));
+}
+template <typename V, class F>
+__device__ __forceinline__ V lanes_fold(V v, int n, const F& f) {
+  v = f(v, dpp<0xB1>(v));   // quad_perm [1,0,3,2]
+  v = f(v, dpp<0x4E>(v));   // quad_perm [2,3,0,1]
+  v = f(v, dpp<0x141>(v));  // row_half_mirror
+  if (n >= 16) v = f(v, dpp<0x140>(v));  // row_mirror
+  if (n >= 32) v = f(v, __shfl_xor(v, 16, 64));
+  if (n >= 64) v = f(v, __shfl_xor(v, 32, 64));
+  return v;
+}
+template <typename V>
+__device__ __forceinline__ V lanes_sum(V v, int n) {
+  return lanes_fold(v, n, [](V a, V b) { return a + b; });
+}
+__device__ __forceinline__ float lanes_max(float v, int n) {
+  return lanes_fold(v, n, [](float a, float b) { return fmaxf(a, b); });
+}
+
+// Over the workgroup of NW waves: the waves' results in order, the same bits in every thread.
+template <int NW>
 __device__ __forceinline__ double block_sum(double v, double* sh) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+  v = lanes_sum(v, 64);
   __syncthreads();  // sh may still be read from the previous call
   if (lane == 0) sh[wave] = v;
   __syncthreads();
   double t = 0.0;
-  for (int w = 0; w < (int)(blockDim.x >> 6); ++w) t += sh[w];  // fixed order: same bits in every thread
+#pragma unroll
+  for (int w = 0; w < NW; ++w) t += sh[w];
   return t;
 }
-
+template <int NW>
 __device__ __forceinline__ float block_max(float v, float* sh) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v = fmaxf(v, __shfl_xor(v, off, 64));
-  __syncthreads();
+  v = lanes_max(v, 64);
   if (lane == 0) sh[wave] = v;
   __syncthreads();
   float t = -INFINITY;
-  for (int w = 0; w < (int)(blockDim.x >> 6); ++w) t = fmaxf(t, sh[w]);
+#pragma unroll
+  for (int w = 0; w < NW; ++w) t = fmaxf(t, sh[w]);
   return t;
 }
 
-// Workspace of one sequence (doubles): [rows][kStatSlices][2] slice statistics, then one double
-// per vocabulary chunk (chunk sums), then q[V], then one slot holding m.
+// How a call is cut.  Slices: more than kMinSlices while the workgroups of (1) are fewer than two per CU or a slice is longer
+// than its threads hold, as long as a slice has two entries a thread and (2) can take a row's slices side by side, four
+// terms a thread at most.  us a call, gamma 5, vocabulary 128 256, with 8 / 16 / 32 / 64 slices: one sequence 19.0 / 15.3 / 15.0 /
+// 15.4, four 27.0 / 23.2 / 23.5 / 25.8, sixteen 67.0 / 61.9 / 59.7 / 68.0; gamma 1, 152 064, one 21.2 / 17.1 / 15.1 / 13.7.
+// Entries per thread of (2): two, eight where chunks of two would make more than four workgroups per CU (each repeats the
+// decisions): one sequence 15.4 us with two, 18.7 with eight; four 23.5 and 25.8; sixteen 61.5 and 59.8.
+struct AcceptPlan {
+  int slices, per, chunks;
+};
+static AcceptPlan accept_plan(int batch, int gamma, int V) {
+  AcceptPlan p;
+  const long rows = 2 * (long)gamma + 1, cus = 256;
+  p.slices = kMinSlices;
+  while (p.slices < kMaxSlices && rows * 2 * p.slices <= 4 * kDrawThreads && V >= 2 * p.slices * 2 * kStatThreads &&
+         (V > p.slices * kStatRegs * kStatThreads || rows * p.slices * batch < 2 * cus))
+    p.slices *= 2;
+  p.per = batch * (((long)V + 2 * kDrawThreads - 1) / (2 * kDrawThreads)) > 4 * cus ? 8 : 2;
+  p.chunks = (V + p.per * kDrawThreads - 1) / (p.per * kDrawThreads);
+  return p;
+}
+
+// Workspace of one sequence (doubles): [rows][slices][2] slice statistics, then the chunk sums; in its last double the
+// counter of (2).  Room for kMinSlices slices and V + V / kWsChunk doubles more: what accept_plan asks for fits (more slices
+// than kMinSlices take at most 2048 doubles and V is at least 16 384 then, the chunks are at most V / 512 + 1).
+// kNoSum: a chunk sum that is not there yet, a NaN with a payload that arithmetic does not make.
+typedef unsigned long long sum_bits;
+constexpr sum_bits kNoSum = 0x7FFC5A3C96E1B482ull;
 struct AcceptWs {
   double* stats;
-  double* chunk_sum;
-  double* q;
-  double* m_slot;
+  sum_bits* chunk_sum;
+  int* done;
 };
 __host__ __device__ inline size_t accept_ws_doubles(int gamma, int V) {
-  const size_t rows = 2 * (size_t)gamma + 1, nchunk = ((size_t)V + kChunk - 1) / kChunk;
-  return rows * kStatSlices * 2 + nchunk + (size_t)V + 1;
+  const size_t rows = 2 * (size_t)gamma + 1, nchunk = ((size_t)V + kWsChunk - 1) / kWsChunk;
+  return rows * kMinSlices * 2 + nchunk + (size_t)V + 1;
 }
-__device__ __forceinline__ AcceptWs accept_ws(double* base, int b, int gamma, int V) {
-  const size_t rows = 2 * (size_t)gamma + 1, nchunk = ((size_t)V + kChunk - 1) / kChunk;
+__device__ __forceinline__ AcceptWs accept_ws(double* base, int b, int gamma, int V, int slices) {
+  const size_t rows = 2 * (size_t)gamma + 1, all = accept_ws_doubles(gamma, V);
   AcceptWs w;
-  w.stats = base + (size_t)b * accept_ws_doubles(gamma, V);
-  w.chunk_sum = w.stats + rows * kStatSlices * 2;
-  w.q = w.chunk_sum + nchunk;
-  w.m_slot = w.q + V;
+  w.stats = base + (size_t)b * all;
+  w.chunk_sum = reinterpret_cast<sum_bits*>(w.stats + rows * slices * 2);
+  w.done = reinterpret_cast<int*>(w.stats + all - 1);
   return w;
 }
 
@@ -87,233 +142,273 @@ __device__ __forceinline__ double quotient(double x, double T, double y) {
   return fabs(q) < INFINITY ? fma(fma(-q, T, x), y, q) : q;
 }
 
-// rows 0..gamma are the target's, rows gamma+1..2*gamma the draft's.  grid (kStatSlices, rows, batch)
-__global__ __launch_bounds__(kAcceptThreads) void accept_stats_kernel(const float* __restrict__ draft_logits,
-                                                                       const float* __restrict__ target_logits, int gamma, int V,
-                                                                       double T, double* __restrict__ ws) {
-  __shared__ double sh_d[kAcceptThreads / 64];
-  __shared__ float sh_f[kAcceptThreads / 64];
+// rows 0..gamma are the target's, rows gamma+1..2*gamma the draft's.  grid (slices, rows, batch)
+__global__ __launch_bounds__(kStatThreads) void accept_stats_kernel(const float* __restrict__ draft_logits,
+                                                                     const float* __restrict__ target_logits, int gamma, int V,
+                                                                     double T, int slices, int chunks,
+                                                                     double* __restrict__ ws_base) {
+  __shared__ double sh_d[kStatThreads / 64];
+  __shared__ float sh_f[kStatThreads / 64];
   const int slice = blockIdx.x, j = blockIdx.y, b = blockIdx.z;
   const float* row = j <= gamma ? target_logits + ((size_t)b * (gamma + 1) + j) * V
                                 : draft_logits + ((size_t)b * gamma + (j - gamma - 1)) * V;
-  const int per = (V + kStatSlices - 1) / kStatSlices;
+  const int per = (V + slices - 1) / slices;
   const int v0 = min(V, slice * per), v1 = min(V, v0 + per);
-  const bool held = v1 - v0 <= kStatRegs * kAcceptThreads;  // uniform: the slice stays in registers between the two passes over it
+  const bool held = v1 - v0 <= kStatRegs * kStatThreads;  // uniform: the slice stays in registers between the two passes over it
   float l[kStatRegs];
   auto load = [&](int base) {
 #pragma unroll
     for (int i = 0; i < kStatRegs; ++i) {
-      const int v = base + i * kAcceptThreads + threadIdx.x;
+      const int v = base + i * kStatThreads + threadIdx.x;
       l[i] = v < v1 ? row[v] : -INFINITY;
     }
   };
   float mx = -INFINITY;
-  for (int base = v0; base < v1; base += kStatRegs * kAcceptThreads) {
+  for (int base = v0; base < v1; base += kStatRegs * kStatThreads) {
     load(base);
 #pragma unroll
     for (int i = 0; i < kStatRegs; ++i) mx = fmaxf(mx, l[i]);
   }
-  mx = block_max(mx, sh_f);
+  mx = block_max<kStatThreads / 64>(mx, sh_f);
   const double ref = mx == -INFINITY ? 0.0 : (double)mx;  // nothing but minus infinities: they add exp(-inf) = 0
   const double inv_T = 1.0 / T;
   double z = 0.0;
-  for (int base = v0; base < v1; base += kStatRegs * kAcceptThreads) {
+  for (int base = v0; base < v1; base += kStatRegs * kStatThreads) {
     if (!held) load(base);
 #pragma unroll
     for (int i = 0; i < kStatRegs; ++i)
-      if (base + i * kAcceptThreads < v1) z += exp(quotient((double)l[i] - ref, T, inv_T));  // uniform; slots past the end add 0
+      if (base + i * kStatThreads < v1) z += exp(quotient((double)l[i] - ref, T, inv_T));  // uniform; slots past the end add 0
   }
-  z = block_sum(z, sh_d);
+  z = block_sum<kStatThreads / 64>(z, sh_d);
+  const AcceptWs ws = accept_ws(ws_base, b, gamma, V, slices);
   if (threadIdx.x == 0) {
-    double* o = accept_ws(ws, b, gamma, V).stats + ((size_t)j * kStatSlices + slice) * 2;
+    double* o = ws.stats + ((size_t)j * slices + slice) * 2;
     o[0] = (double)mx;  // -inf for an empty slice; its sum is 0
     o[1] = z;
+    if (j == 0 && slice == 0) *ws.done = 0;
   }
+  if (j == 0)
+    for (int c = slice * kStatThreads + threadIdx.x; c < chunks; c += slices * kStatThreads) ws.chunk_sum[c] = kNoSum;
 }
 
-// maximum and normaliser of a row from its slice statistics (slices in order)
-__device__ __forceinline__ void row_stats(const double* stats, int row, double T, double* mx, double* z) {
-  const double* s = stats + (size_t)row * kStatSlices * 2;
-  double m = s[0];
-  for (int i = 1; i < kStatSlices; ++i) m = fmax(m, s[2 * i]);
-  double t = 0.0;
-  for (int i = 0; i < kStatSlices; ++i)
-    if (s[2 * i + 1] > 0.0) t += s[2 * i + 1] * exp((s[2 * i] - m) / T);
-  *mx = m;
-  *z = t;
+// Inclusive running sum over the workgroup's threads: inside rows of 16 lanes by operand swizzles, then the rows' and the waves' totals
+// in order.  incl[] holds every thread's afterwards (so that a thread's lower end is the very number that is its
+// neighbour's upper one).
+__device__ __forceinline__ double lane_value(double v, int lane) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)u, lane), hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(u >> 32), lane);
+  return __builtin_bit_cast(double, (uint64_t)lo | ((uint64_t)hi << 32));
+}
+__device__ __forceinline__ void block_scan(double v, double* incl, double* sh) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, row = lane >> 4;
+  v += dpp<0x111>(v);  // row_shr by 1, 2, 4, 8: zeros come in
+  v += dpp<0x112>(v);
+  v += dpp<0x114>(v);
+  v += dpp<0x118>(v);
+  const double t0 = lane_value(v, 15), t1 = t0 + lane_value(v, 31), t2 = t1 + lane_value(v, 47);
+  v += row == 0 ? 0.0 : row == 1 ? t0 : row == 2 ? t1 : t2;
+  __syncthreads();  // sh and incl may still be read from the previous call
+  if (lane == 63) sh[wave] = v;
+  __syncthreads();
+  double before = 0.0;
+  for (int k = 0; k < wave; ++k) before += sh[k];
+  incl[threadIdx.x] = before + v;
+  __syncthreads();
 }
 
-// grid (chunks, batch).  Every workgroup takes the same decisions from the same numbers: the terms of row_stats for
-// every (row, slice) in a thread each, added per row in slice order; then the test of every position in a thread each.
+// grid (chunks, batch); PER: vocabulary entries per thread.  Every workgroup takes the same decisions from the same numbers: a
+// row's slices in as many neighbouring lanes, their terms added by shuffles; then, in every wave, the test of each position in
+// a lane.
 constexpr int kMaxAcceptRows = 2 * 64 + 1;
-__global__ __launch_bounds__(kAcceptThreads) void accept_weights_kernel(const int32_t* __restrict__ draft,
-                                                                         const float* __restrict__ draft_logits,
-                                                                         const float* __restrict__ target_logits,
-                                                                         const float* __restrict__ r, int gamma, int V, double T,
-                                                                         double* __restrict__ ws_base) {
-  __shared__ double sh_d[kAcceptThreads / 64];
-  __shared__ double s_mx[kMaxAcceptRows], s_z[kMaxAcceptRows], s_term[kMaxAcceptRows * kStatSlices];
-  __shared__ signed char s_verdict[64];  // 0 accepted, 1 rejected, -1 not a token
-  __shared__ int s_m;
-  const int chunk = blockIdx.x, b = blockIdx.y, tid = threadIdx.x;
-  const AcceptWs ws = accept_ws(ws_base, b, gamma, V);
+template <int PER>
+__global__ __launch_bounds__(kDrawThreads) void accept_draw_kernel(const int32_t* __restrict__ draft, const float* __restrict__ draft_logits,
+                                                                    const float* __restrict__ target_logits, const float* __restrict__ r,
+                                                                    const float* __restrict__ u, int gamma, int V, double T, int slices,
+                                                                    double* ws_base, int32_t* __restrict__ accept_len,
+                                                                    int32_t* __restrict__ bonus) {
+  constexpr int kChunk = PER * kDrawThreads;
+  __shared__ double s_incl[kDrawThreads], s_wave[kDrawThreads / 64], s_mx[kMaxAcceptRows], s_z[kMaxAcceptRows];
+  __shared__ double s_before;
+  __shared__ int s_flag;
+  const int chunk = blockIdx.x, nchunk = gridDim.x, b = blockIdx.y, tid = threadIdx.x, lane = tid & 63;
+  const AcceptWs ws = accept_ws(ws_base, b, gamma, V, slices);
   const float* tl = target_logits + (size_t)b * (gamma + 1) * V;
   const float* dl = draft_logits + (size_t)b * gamma * V;
-  const int rows = 2 * gamma + 1;
-  for (int i = tid; i < rows * kStatSlices; i += kAcceptThreads) {
-    const double* st = ws.stats + (size_t)(i / kStatSlices) * kStatSlices * 2;
-    double m = st[0];
-#pragma unroll
-    for (int k = 1; k < kStatSlices; ++k) m = fmax(m, st[2 * k]);
-    const double mine = st[2 * (i % kStatSlices)], sum = st[2 * (i % kStatSlices) + 1];
-    s_term[i] = sum > 0.0 ? sum * exp((mine - m) / T) : 0.0;
-    if (i % kStatSlices == 0) s_mx[i / kStatSlices] = m;
-  }
-  __syncthreads();
-  for (int i = tid; i < rows; i += kAcceptThreads) {
-    double t = 0.0;
-#pragma unroll
-    for (int k = 0; k < kStatSlices; ++k) t += s_term[i * kStatSlices + k];
-    s_z[i] = t;
-  }
-  __syncthreads();
-  if (tid < gamma) {
-    const int x = draft[(size_t)b * gamma + tid];
-    int verdict = -1;
-    if (x >= 0 && x < V) {
-      const double p = exp(((double)tl[(size_t)tid * V + x] - s_mx[tid]) / T) / s_z[tid];
-      const double pd = exp(((double)dl[(size_t)tid * V + x] - s_mx[gamma + 1 + tid]) / T) / s_z[gamma + 1 + tid];
-      verdict = (double)r[(size_t)b * gamma + tid] * pd > p ? 1 : 0;
+  const double inv_T = 1.0 / T;
+  // the drafted tokens' logits, on their way while the statistics are combined
+  int token = -1;
+  float t_logit = 0.f, d_logit = 0.f, r_in = 0.f;
+  if (lane < gamma) {
+    token = draft[(size_t)b * gamma + lane];
+    r_in = r[(size_t)b * gamma + lane];
+    if (token >= 0 && token < V) {
+      t_logit = tl[(size_t)lane * V + token];
+      d_logit = dl[(size_t)lane * V + token];
     }
-    s_verdict[tid] = (signed char)verdict;
   }
-  __syncthreads();
-  if (tid == 0) {
-    int m = 0;
-    while (m < gamma && s_verdict[m] == 0) ++m;
-    if (m < gamma && s_verdict[m] < 0) m = -1;  // not a token: reported as accept_len = bonus = -1
-    s_m = m;
-    if (chunk == 0) *ws.m_slot = (double)m;
-  }
-  __syncthreads();
-  const int m = s_m;
-  if (m < 0) return;
-  const double tm = s_mx[m], tz = s_z[m];
-  const double dm = m < gamma ? s_mx[gamma + 1 + m] : 0.0, dz = m < gamma ? s_z[gamma + 1 + m] : 1.0;
-  const float* trow = tl + (size_t)m * V;
-  const float* drow = m < gamma ? dl + (size_t)m * V : nullptr;
-  // each thread owns a contiguous run, so that every sum below is in index order
-  constexpr int PER = kChunk / kAcceptThreads;
-  const int v0 = chunk * kChunk + tid * PER;
-  double mine = 0.0;
+  const int terms = (2 * gamma + 1) * slices;
+  constexpr int TB = 4;  // terms a thread requests side by side: all of them, but for the longest drafts
+  for (int i0 = tid; i0 - tid < terms; i0 += TB * kDrawThreads) {
+    double mine[TB], sum[TB];
 #pragma unroll
-  for (int i = 0; i < PER; ++i) {
-    const int v = v0 + i;
-    if (v < V) {
-      double q = exp(((double)trow[v] - tm) / T) / tz;
-      if (drow) {
-        q -= exp(((double)drow[v] - dm) / T) / dz;
-        q = q > 0.0 ? q : 0.0;
+    for (int k = 0; k < TB; ++k) {
+      const size_t i = min(i0 + k * kDrawThreads, terms - 1);
+      mine[k] = ws.stats[2 * i];
+      sum[k] = ws.stats[2 * i + 1];
+    }
+#pragma unroll
+    for (int k = 0; k < TB; ++k) {
+      const int i = i0 + k * kDrawThreads;  // the slices are a power of two and divide 64: a row's lie in one wave
+      if (i - lane >= terms) break;         // uniform
+      const double m = lanes_max((float)mine[k], slices);  // maxima of floats
+      const double t = lanes_sum(i < terms && sum[k] > 0.0 ? sum[k] * exp(quotient(mine[k] - m, T, inv_T)) : 0.0, slices);
+      if (i < terms && (i & (slices - 1)) == 0) {
+        s_mx[i / slices] = m;
+        s_z[i / slices] = t;
       }
-      ws.q[v] = q;
-      mine += q;
     }
   }
-  const double tot = block_sum(mine, sh_d);
-  if (tid == 0) ws.chunk_sum[chunk] = tot;
-}
-
-// grid (batch), kDrawThreads threads (two vocabulary entries each inside the chosen chunk).
-__global__ __launch_bounds__(kDrawThreads) void accept_draw_kernel(const float* __restrict__ target_logits,
-                                                                    const float* __restrict__ u, int gamma, int V, double T,
-                                                                    double* __restrict__ ws_base, int32_t* __restrict__ accept_len,
-                                                                    int32_t* __restrict__ bonus) {
-  __shared__ double s_incl[kDrawThreads];
-  __shared__ double s_thr, s_before, s_wave[kDrawThreads / 64];
-  __shared__ int s_chunk, s_pick;
-  const int b = blockIdx.x, tid = threadIdx.x;
-  const AcceptWs ws = accept_ws(ws_base, b, gamma, V);
-  const int m = (int)*ws.m_slot;
-  if (m < 0) {
-    if (tid == 0) { accept_len[b] = -1; bonus[b] = -1; }
+  __syncthreads();
+  bool rejected = false;
+  if (lane < gamma && token >= 0 && token < V) {
+    const double p = exp(quotient((double)t_logit - s_mx[lane], T, inv_T)) / s_z[lane];
+    const double pd = exp(quotient((double)d_logit - s_mx[gamma + 1 + lane], T, inv_T)) / s_z[gamma + 1 + lane];
+    rejected = (double)r_in * pd > p;
+  }
+  const bool bad = lane < gamma && !(token >= 0 && token < V);
+  const unsigned long long stop = __ballot(rejected || bad), bads = __ballot(bad);
+  const int m = stop ? __ffsll((long long)stop) - 1 : gamma;
+  if ((bads >> (m & 63)) & 1 & (unsigned long long)(m < gamma)) {  // not a token: reported as accept_len = bonus = -1
+    if (chunk == 0 && tid == 0) {
+      accept_len[b] = -1;
+      bonus[b] = -1;
+    }
     return;
   }
-  const int nchunk = (V + kChunk - 1) / kChunk;
-  double total = 0.0;
-  for (int c0 = 0; c0 < nchunk; c0 += kDrawThreads) {  // chunk sums through LDS: loaded side by side, added in order
-    s_incl[tid] = c0 + tid < nchunk ? ws.chunk_sum[c0 + tid] : 0.0;
-    __syncthreads();
-    if (tid == 0)
-      for (int c = 0; c < min(kDrawThreads, nchunk - c0); ++c) total += s_incl[c];
-    __syncthreads();
-  }
+  const double tm = s_mx[m], tz = s_z[m], inv_tz = 1.0 / tz;
+  bool residual = m < gamma;
+  const double dm = residual ? s_mx[gamma + 1 + m] : 0.0, dz = residual ? s_z[gamma + 1 + m] : 1.0, inv_dz = 1.0 / dz;
+  const float* trow = tl + (size_t)m * V;
+  const float* drow = residual ? dl + (size_t)m * V : trow;
+  auto weight = [&](float t, float dd) {
+    double q = quotient(exp(quotient((double)t - tm, T, inv_T)), tz, inv_tz);
+    if (residual) {
+      q -= quotient(exp(quotient((double)dd - dm, T, inv_T)), dz, inv_dz);
+      q = q > 0.0 ? q : 0.0;
+    }
+    return q;
+  };
+  // each thread owns a contiguous run, so that every sum below is in index order
+  auto run_of = [&](int c, double (&q)[PER]) {
+    const int v0 = c * kChunk + tid * PER;
+    float t[PER], dd[PER];
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+      const int v = min(v0 + i, V - 1);
+      t[i] = trow[v];
+      dd[i] = drow[v];
+    }
+    double s = 0.0;
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+      q[i] = v0 + i < V ? weight(t[i], dd[i]) : 0.0;
+      s += q[i];
+    }
+    return s;
+  };
+  auto send_sum = [&](int c, double v) {
+    __hip_atomic_store(&ws.chunk_sum[c], v == v ? __builtin_bit_cast(sum_bits, v) : 0x7FF8000000000000ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  };
+  double q[PER];
+  const double tot = block_sum<kDrawThreads / 64>(run_of(chunk, q), s_wave);
   if (tid == 0) {
-    const bool rewritten = !(total > 0.0);
-    if (rewritten) {
-      // identical distributions leave no residual (a rejection is then impossible for r < 1): fall
-      // back to the target distribution of that position, evaluated here (rare, slow, correct)
-      double tm, tz;
-      row_stats(ws.stats, m, T, &tm, &tz);
-      const float* trow = target_logits + ((size_t)b * (gamma + 1) + m) * V;
-      total = 0.0;
-      for (int c = 0; c < nchunk; ++c) {
-        double cs = 0.0;
-        for (int v = c * kChunk; v < min(V, (c + 1) * kChunk); ++v) {
-          const double q = exp(((double)trow[v] - tm) / T) / tz;
-          ws.q[v] = q;
-          cs += q;
-        }
-        ws.chunk_sum[c] = cs;
-        total += cs;
-      }
-    }
-    const double thr = (double)u[b] * total;
-    // the chunk sums are still in LDS unless there are more than fit or the fallback has rewritten them
-    const bool held = nchunk <= kDrawThreads && !rewritten;
-    double run = 0.0;
-    int pick = -1;
-    for (int c = 0; c < nchunk; ++c) {
-      const double next = run + (held ? s_incl[c] : ws.chunk_sum[c]);
-      if (next > thr) { pick = c; break; }
-      run = next;
-    }
-    s_thr = thr;
-    s_before = run;
-    s_chunk = pick;  // -1: u * total rounded up to the total
-    s_pick = -1;
+    send_sum(chunk, tot);
+    s_flag = __hip_atomic_fetch_add(ws.done, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == nchunk - 1;
   }
   __syncthreads();
-  const int chunk = s_chunk;
-  if (chunk >= 0) {
-    const int v0 = chunk * kChunk + 2 * tid;
-    const double q0 = v0 < V ? ws.q[v0] : 0.0, q1 = v0 + 1 < V ? ws.q[v0 + 1] : 0.0;
-    // inclusive scan: inside the waves by shuffles, then the waves' totals in order
-    const int lane = tid & 63, wave = tid >> 6;
-    double run = q0 + q1;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-      const double add = __shfl_up(run, off, 64);
-      if (lane >= off) run += add;
+  if (!s_flag) return;
+
+  // The sequence's last workgroup: every thread takes a run of chunks
+  const int cper = (nchunk + kDrawThreads - 1) / kDrawThreads, c0 = min(nchunk, tid * cper), c1 = min(nchunk, c0 + cper);
+  auto chunk_sum = [&](int c) {
+    sum_bits x;
+    do {  // it has been sent: ends when it arrives
+      x = __hip_atomic_load(&ws.chunk_sum[c], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    } while (x == kNoSum);
+    return __builtin_bit_cast(double, x);
+  };
+  auto scan_chunks = [&] {
+    double s = 0.0;
+    for (int c = c0; c < c1; ++c) s += chunk_sum(c);
+    block_scan(s, s_incl, s_wave);
+    return s_incl[kDrawThreads - 1];
+  };
+  double total = scan_chunks();
+  if (!(total > 0.0)) {
+    // identical distributions leave no residual (a rejection is then impossible for r < 1): fall
+    // back to the target distribution of that position (rare, slow, correct)
+    residual = false;
+    for (int c = 0; c < nchunk; ++c) {
+      const double s = block_sum<kDrawThreads / 64>(run_of(c, q), s_wave);
+      if (tid == 0) send_sum(c, s);
     }
-    if (lane == 63) s_wave[wave] = run;
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the old sums are gone when the other waves look
     __syncthreads();
-    double before = 0.0;
-    for (int k = 0; k < wave; ++k) before += s_wave[k];
-    s_incl[tid] = before + run;
-    __syncthreads();
-    const double thr = s_thr;
-    const double excl = s_before + (tid ? s_incl[tid - 1] : 0.0), incl = s_before + s_incl[tid];
-    if (excl <= thr && thr < incl) s_pick = (excl + q0 > thr || !(q1 > 0.0)) ? v0 : v0 + 1;  // at most one thread
-    __syncthreads();
+    total = scan_chunks();
+  }
+  const double thr = (double)u[b] * total;
+  if (tid == 0) s_flag = -1;
+  __syncthreads();
+  {
+    double lo = tid ? s_incl[tid - 1] : 0.0;
+    if (lo <= thr && thr < s_incl[tid])  // at most one thread
+      for (int c = c0; c < c1; ++c) {
+        const double next = c < c1 - 1 ? lo + chunk_sum(c) : INFINITY;
+        if (next > thr) {
+          s_flag = c;
+          s_before = lo;
+          break;
+        }
+        lo = next;
+      }
+  }
+  __syncthreads();
+  const int pick_chunk = s_flag;  // -1: u * total rounded up to the total
+  const double before = s_before;
+  __syncthreads();
+  if (tid == 0) s_flag = -1;
+  if (pick_chunk >= 0) {
+    block_scan(run_of(pick_chunk, q), s_incl, s_wave);
+    double lo = before + (tid ? s_incl[tid - 1] : 0.0);
+    if (lo <= thr && thr < before + s_incl[tid]) {  // at most one thread
+      const int v0 = pick_chunk * kChunk + tid * PER;
+      int pick = -1;
+#pragma unroll
+      for (int i = 0; i < PER; ++i) {
+        if (pick >= 0 && lo > thr) continue;  // found: the running sum is past the threshold
+        if (q[i] > 0.0) pick = v0 + i;
+        lo += q[i];
+      }
+      s_flag = pick;
+    }
+  }
+  __syncthreads();
+  int pick = s_flag;
+  if (pick < 0) {
+    // the sums disagreed in the last bit, or the threshold reached the total: the last token with
+    // positive weight up to the chunk's end (of the vocabulary), or the first
+    int end = min(V, pick_chunk >= 0 ? (pick_chunk + 1) * kChunk : V);
+    for (; pick < 0 && end > 0; end -= kDrawThreads) {
+      const int v = end - 1 - tid;
+      const bool positive = v >= 0 && weight(trow[max(v, 0)], drow[max(v, 0)]) > 0.0;
+      __syncthreads();
+      if (positive) atomicMax(&s_flag, v);
+      __syncthreads();
+      pick = s_flag;
+    }
+    pick = max(pick, 0);
   }
   if (tid == 0) {
-    int pick = s_pick;
-    if (pick < 0) {
-      // the scans disagreed in the last bit, or the threshold reached the total: the last token
-      // with positive weight of the chunk (of the vocabulary)
-      pick = min(V, chunk >= 0 ? (chunk + 1) * kChunk : V) - 1;
-      while (pick > 0 && !(ws.q[pick] > 0.0)) --pick;
-    }
     accept_len[b] = m;
     bonus[b] = pick;
   }
@@ -326,17 +421,19 @@ size_t sample_accept_workspace_bytes(int batch, int gamma, int V) {
 void launch_sample_accept(const int32_t* draft, const float* draft_logits, const float* target_logits, const float* r,
                           const float* u, int batch, int gamma, int V, double T, double* ws, int32_t* accept_len,
                           int32_t* bonus, hipStream_t st) {
-  const int nchunk = (V + kChunk - 1) / kChunk;
-  hipLaunchKernelGGL(accept_stats_kernel, dim3(kStatSlices, 2 * gamma + 1, batch), dim3(kAcceptThreads), 0, st, draft_logits,
-                     target_logits, gamma, V, T, ws);
-  hipLaunchKernelGGL(accept_weights_kernel, dim3(nchunk, batch), dim3(kAcceptThreads), 0, st, draft, draft_logits, target_logits, r,
-                     gamma, V, T, ws);
-  hipLaunchKernelGGL(accept_draw_kernel, dim3(batch), dim3(kDrawThreads), 0, st, target_logits, u, gamma, V, T, ws, accept_len,
-                     bonus);
+  const AcceptPlan p = accept_plan(batch, gamma, V);
+  hipLaunchKernelGGL(accept_stats_kernel, dim3(p.slices, 2 * gamma + 1, batch), dim3(kStatThreads), 0, st, draft_logits, target_logits,
+                     gamma, V, T, p.slices, p.chunks, ws);
+  if (p.per == 2)
+    hipLaunchKernelGGL(accept_draw_kernel<2>, dim3(p.chunks, batch), dim3(kDrawThreads), 0, st, draft, draft_logits, target_logits, r, u,
+                       gamma, V, T, p.slices, ws, accept_len, bonus);
+  else
+    hipLaunchKernelGGL(accept_draw_kernel<8>, dim3(p.chunks, batch), dim3(kDrawThreads), 0, st, draft, draft_logits, target_logits, r, u,
+                       gamma, V, T, p.slices, ws, accept_len, bonus);
 }
 
 // ------------------------------------------------------------------------------------------
-// The same three launches for callers that cannot allocate and bring no workspace: the
+// The same two launches for callers that cannot allocate and bring no workspace: the
 // workspace is a file-scope device array.  Its name is a host-side stand-in, not a device
 // address: the address comes from hipGetSymbolAddress, once per device with that device
 // current (every GPU holds its own copy), and only that pointer is handed to kernels.

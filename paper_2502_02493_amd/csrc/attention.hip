@@ -974,23 +974,28 @@ __global__ __launch_bounds__(64 * NW, NW == 1 ? 1 : 2) void attn_mfma_kernel(Att
 // launch: the kernel boundary is what makes the partials written by workgroups on other XCDs
 // visible (a device-scope fence inside the attention kernel costs an L2 write-back per workgroup
 // and was measured several times slower).  Columns whose context fits one chunk were finished by
-// attn_kernel.  grid = (columns, Hq, k), block = HD: one thread per output element, one small
-// workgroup per head, so that the launch is as wide as the partials allow and costs one memory
-// latency whatever the number of heads that share a KV head.
+// attn_kernel.  A wave per head, HD / 64 adjacent elements per lane, the chunks' weights a lane each and
+// handed round by scalar reads: no LDS, no barrier, one memory latency.  W waves to a workgroup: W heads of a
+// column, or, in a wide pass, one head of W columns, whose outputs lie side by side in the operand (16 bytes each; with
+// eight columns whole lines leave from one workgroup).  grid = (columns, ceil(Hq / W), k), or (ceil(columns / W), Hq).
+// us a launch, a workgroup per head (weights through LDS, a barrier) and now: 256 columns of 32 heads 12.9 -> 7.4 (8192 workgroups
+// took that long to start); 6 columns 4.65 and 4.65, a launch's floor.  Partials past the first 16 by 24 instead of 8 at
+// a time: 24 columns with up to 64 chunks 7.6 -> 6.7.
 // Src: MergeCols, or Spans for the columns of a wide pass (chunks of CH slots, partials nch_ref apart, wide operand).
 // The columns of a merge launch: those of a pass with their chunk counts, or of a wide pass.
 struct MergeCols {
   int32_t n;
   int32_t nch[kMaxCols];
 };
-template <typename T, int HD, class Src>
-__global__ __launch_bounds__(HD) void attn_merge_kernel(AttnArgs a, Src c) {
+template <typename T, int HD, int W, class Src>
+__global__ __launch_bounds__(64 * W) void attn_merge_kernel(AttnArgs a, Src c) {
   constexpr bool kWide = std::is_same<Src, Spans>::value;
-  __shared__ float s_w[kMaxChunks];  // exp(m_chunk - m); chunk count <= 64 = one lane each
-  __shared__ float s_tot;            // the chunks' sums on the common reference
-  const int col = blockIdx.x, head = blockIdx.y, li = blockIdx.z, e = threadIdx.x;
+  constexpr int VE = HD / 64;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int col = kWide ? blockIdx.x * W + wave : blockIdx.x, head = kWide ? blockIdx.y : blockIdx.y * W + wave, li = blockIdx.z;
   int nch;
   size_t pitch = kMaxChunks;
+  if (col >= c.n || head >= a.Hq) return;
   if constexpr (kWide) {
     const int en = span_entry(c, col);
     nch = (c.pos0[en] + (col - c.first[en]) + a.CH) / a.CH;
@@ -999,41 +1004,54 @@ __global__ __launch_bounds__(HD) void attn_merge_kernel(AttnArgs a, Src c) {
     nch = c.nch[col];
   }
   if (nch == 1) return;
-  const int HQ = a.Hq * HD;
+  const int HQ = a.Hq * HD, e = lane * VE;
   const size_t row = ((size_t)li * kMaxCols + col) * a.Hq + head;
-  // every load is issued up front: the first 16 chunk partials of this thread's output element (all
+  // every load is issued up front: the first 16 chunk partials of this lane's output elements (all
   // of them for contexts up to 16 chunks) together with the chunk maxima and sums
   const float* po = a.PO + row * pitch * HD + e;
-  float pv[16];
+  auto partial = [&](int u, float (&v)[VE]) {
+    const float* p = po + (size_t)u * HD;
+    if constexpr (VE == 2) {
+      const float2 x = u < nch ? *reinterpret_cast<const float2*>(p) : make_float2(0.f, 0.f);
+      v[0] = x.x;
+      v[1] = x.y;
+    } else {
+      v[0] = u < nch ? *p : 0.f;
+    }
+  };
+  const float pm = lane < nch ? a.PM[row * pitch + lane] : -INFINITY;  // one lane per chunk: at most 64
+  const float pl = lane < nch ? a.PL[row * pitch + lane] : 0.f;
+  float pv[16][VE];
 #pragma unroll
-  for (int u = 0; u < 16; ++u) pv[u] = u < nch ? po[(size_t)u * HD] : 0.f;
-  if (e < 64) {  // the first wave: one lane per chunk
-    const float pm = e < nch ? a.PM[row * pitch + e] : -INFINITY;
-    const float pl = e < nch ? a.PL[row * pitch + e] : 0.f;
-    const float wgt = __expf(pm - wave_max(pm));
-    s_w[e] = wgt;
-    const float all = wave_sum(pl * wgt);
-    if (e == 0) s_tot = all;
+  for (int u = 0; u < 16; ++u) partial(u, pv[u]);
+  const float wgt = __expf(pm - wave_max(pm)), tot = wave_sum(pl * wgt);
+  float o[VE] = {};
+  auto add = [&](int u, const float (&v)[VE]) {  // u is uniform; past the last chunk both factors are 0
+    const float w = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(wgt), u));
+#pragma unroll
+    for (int i = 0; i < VE; ++i) o[i] += v[i] * w;
+  };
+#pragma unroll
+  for (int u = 0; u < 16; ++u) add(u, pv[u]);
+  for (int c0 = 16; c0 < nch; c0 += 24) {
+    float pw[24][VE];
+#pragma unroll
+    for (int u = 0; u < 24; ++u) partial(c0 + u, pw[u]);  // independent loads
+#pragma unroll
+    for (int u = 0; u < 24; ++u) add(c0 + u, pw[u]);
   }
-  __syncthreads();
-  const float tot = s_tot;
-  float o = 0.f;
-#pragma unroll
-  for (int u = 0; u < 16; ++u) o += pv[u] * (u < nch ? s_w[u] : 0.f);
-  for (int c0 = 16; c0 < nch; c0 += 8) {
-    float pw[8];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) pw[u] = c0 + u < nch ? po[(size_t)(c0 + u) * HD] : 0.f;  // independent loads
-#pragma unroll
-    for (int u = 0; u < 8; ++u) o += pw[u] * (c0 + u < nch ? s_w[c0 + u] : 0.f);
+  T* dst = reinterpret_cast<T*>(a.AO);
+  size_t part;
+  if constexpr (kWide) {
+    dst += wide_off(HQ, col, head * HD + e);
+    part = kWidePart;
+  } else {
+    dst += (size_t)li * Tr<T>::PARTS * kMaxCols * HQ + xoff<T>(c.n, HQ, col, head * HD + e);
+    part = (size_t)kMaxCols * HQ;
   }
-  if constexpr (kWide)
-    store_act1<T>(reinterpret_cast<T*>(a.AO) + wide_off(HQ, col, head * HD + e), kWidePart, o / tot);
-  else
-    store_act1<T>(reinterpret_cast<T*>(a.AO) + (size_t)li * Tr<T>::PARTS * kMaxCols * HQ + xoff<T>(c.n, HQ, col, head * HD + e),
-                  (size_t)kMaxCols * HQ, o / tot);
+  if constexpr (VE == 2) store_act2<T>(dst, part, o[0] / tot, o[1] / tot);
+  else store_act1<T>(dst, part, o[0] / tot);
 }
-
 template <typename T, int HD, bool TREE>
 static void launch_attn_g(int G, dim3 grid, int nwv, hipStream_t st, AttnArgs a, const Cols& c, const ChunkMap& map) {
   // partial state of every slot group of the workgroup if that fits the default 64 KB of
@@ -1291,10 +1309,10 @@ void launch_attn(const Shape& s, const Buffers& b, const Cols& c, int layer0, in
     });
   }
   if (n_chunks > 1) {
-    const dim3 mgrid(c.n, s.Hq, n_set);
+    const dim3 mgrid(c.n, s.Hq, n_set);  // few: a wave each, so that they spread over the CUs
     DISPATCH_T(s.dtype, {
-      if (s.hd == 128) ES_LAUNCH((attn_merge_kernel<T, 128, MergeCols>), mgrid, dim3(128), 0, st, a, mc);
-      else ES_LAUNCH((attn_merge_kernel<T, 64, MergeCols>), mgrid, dim3(64), 0, st, a, mc);
+      if (s.hd == 128) ES_LAUNCH((attn_merge_kernel<T, 128, 1, MergeCols>), mgrid, dim3(64), 0, st, a, mc);
+      else ES_LAUNCH((attn_merge_kernel<T, 64, 1, MergeCols>), mgrid, dim3(64), 0, st, a, mc);
     });
   }
 }
@@ -1368,7 +1386,7 @@ static void launch_wide_attn_terms(const Shape& s, const Buffers& b, const WideB
     if (tiles == 4) ES_LAUNCH((attn_mfma_kernel<HD, false, 4, SpanCols<QT>>), grid, blk, 0, st, a, src, G);
     else if (tiles == 2) ES_LAUNCH((attn_mfma_kernel<HD, false, 2, SpanCols<QT>>), grid, blk, 0, st, a, src, G);
     else ES_LAUNCH((attn_mfma_kernel<HD, false, 1, SpanCols<QT>>), grid, blk, 0, st, a, src, G);
-    if (a.nch_ref > 1) ES_LAUNCH((attn_merge_kernel<bf16_t, HD, Spans>), dim3(sp.n, s.Hq), dim3(HD), 0, st, a, sp);
+    if (a.nch_ref > 1) ES_LAUNCH((attn_merge_kernel<bf16_t, HD, 8, Spans>), dim3(ceil_div(sp.n, 8), s.Hq), dim3(512), 0, st, a, sp);
   };
   if (s.hd == 128) go(std::integral_constant<int, 128>{});
   else go(std::integral_constant<int, 64>{});

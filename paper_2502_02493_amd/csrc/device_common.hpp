@@ -168,6 +168,19 @@ __device__ __forceinline__ void store_act1<bf16_t>(bf16_t* p, size_t part, float
   p->bits = (uint16_t)hi;
   p[part].bits = (uint16_t)float_to_bf16_bits(v - bf16_bits_to_float(hi));
 }
+// two consecutive elements, p aligned to two
+template <typename T>
+__device__ __forceinline__ void store_act2(T* p, size_t part, float a, float b);
+template <>
+__device__ __forceinline__ void store_act2<float>(float* p, size_t, float a, float b) {
+  *reinterpret_cast<float2*>(p) = make_float2(a, b);
+}
+template <>
+__device__ __forceinline__ void store_act2<bf16_t>(bf16_t* p, size_t part, float a, float b) {
+  const uint32_t ha = float_to_bf16_bits(a), hb = float_to_bf16_bits(b);
+  *reinterpret_cast<uint32_t*>(p) = ha | (hb << 16);
+  *reinterpret_cast<uint32_t*>(p + part) = float_to_bf16_bits(a - bf16_bits_to_float(ha)) | (float_to_bf16_bits(b - bf16_bits_to_float(hb)) << 16);
+}
 template <typename T>
 __device__ __forceinline__ void store_act4(T* p, size_t part, float a, float b, float c, float d);
 template <>

@@ -19,12 +19,15 @@
 // "Last" is told by a counter; it says whose sums have been sent, and (1) marks them all as missing, so the last workgroup sees
 // when they are there.  (No fence, which would write back the L2, and no wait for a store's acknowledgement.)
 // Bound by fp64 latency and two dependent launches, not by the 5.6 MB of logits.  gamma 5, vocabulary 128 256, one sequence: three
-// launches (8 slices of 1024 threads with sixteen exponentials each, weights, draw) 9.7 + 5.7 + 6.1 us, now 6.2 + 10.5; the whole
-// call 21.2 -> 15.6.  Of the second launch 2.3 us were statistics loaded one round after the other, reductions through LDS and the
-// acknowledgement of a chunk sum ahead of the counter.
+// launches (8 slices of 1024 threads with sixteen exponentials each, weights, draw) 21.1 us a call, two 13.7.  Of these the first
+// launch takes 4.6 (two workgroups of 24 exponentials a SIMD on the busiest CUs), the boundary 1.2, and of the second the statistics
+// 2.0, decisions 0.7, weights and their sum 0.7, the two counters 1.75 (one for all workgroups: 2.7), the sums 0.95 and the draw 1.3.
+// Requesting a thread's entries of all positions at the start, instead of those of the position that the decisions leave, does not
+// pay: 14.2 (statistics 2.5 us, weights 0.75).
 #include "kernels.h"
 
 #include <mutex>
+#include <type_traits>
 
 namespace es {
 
@@ -47,14 +50,29 @@ __device__ __forceinline__ double dpp(double v) {
   const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), CTRL, 0xF, 0xF, true);
   return __builtin_bit_cast(double, (uint64_t)lo | ((uint64_t)hi << 32));
 }
+// f of the values of lanes l and l ^ 16 (l ^ 32)
+template <bool HALF, class F>
+__device__ __forceinline__ float across(float v, const F& f) {
+  const uint32_t a = __builtin_bit_cast(uint32_t, v);
+  const auto s = HALF ? __builtin_amdgcn_permlane32_swap(a, a, false, false) : __builtin_amdgcn_permlane16_swap(a, a, false, false);
+  return f(__builtin_bit_cast(float, (uint32_t)s[0]), __builtin_bit_cast(float, (uint32_t)s[1]));
+}
+template <bool HALF, class F>
+__device__ __forceinline__ double across(double v, const F& f) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = (uint32_t)u, hi = (uint32_t)(u >> 32);
+  const auto l = HALF ? __builtin_amdgcn_permlane32_swap(lo, lo, false, false) : __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+  const auto h = HALF ? __builtin_amdgcn_permlane32_swap(hi, hi, false, false) : __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+  return f(__builtin_bit_cast(double, (uint64_t)l[0] | ((uint64_t)h[0] << 32)), __builtin_bit_cast(double, (uint64_t)l[1] | ((uint64_t)h[1] << 32)));
+}
 template <typename V, class F>
 __device__ __forceinline__ V lanes_fold(V v, int n, const F& f) {
   v = f(v, dpp<0xB1>(v));   // quad_perm [1,0,3,2]
   v = f(v, dpp<0x4E>(v));   // quad_perm [2,3,0,1]
   v = f(v, dpp<0x141>(v));  // row_half_mirror
   if (n >= 16) v = f(v, dpp<0x140>(v));  // row_mirror
-  if (n >= 32) v = f(v, __shfl_xor(v, 16, 64));
-  if (n >= 64) v = f(v, __shfl_xor(v, 32, 64));
+  if (n >= 32) v = across<false>(v, f);
+  if (n >= 64) v = across<true>(v, f);
   return v;
 }
 template <typename V>
@@ -90,7 +108,7 @@ __device__ __forceinline__ float block_max(float v, float* sh) {
   return t;
 }
 
-// How a call is cut.  Slices: more than kMinSlices while the workgroups of (1) are fewer than two per CU or a slice is longer
+// How a call is cut.  Slices: more than kMinSlices while the workgroups of (1) are fewer than the CUs or a slice is longer
 // than its threads hold, as long as a slice has two entries a thread and (2) can take a row's slices side by side, four
 // terms a thread at most.  us a call, gamma 5, vocabulary 128 256, with 8 / 16 / 32 / 64 slices: one sequence 19.0 / 15.3 / 15.0 /
 // 15.4, four 27.0 / 23.2 / 23.5 / 25.8, sixteen 67.0 / 61.9 / 59.7 / 68.0; gamma 1, 152 064, one 21.2 / 17.1 / 15.1 / 13.7.
@@ -104,7 +122,7 @@ static AcceptPlan accept_plan(int batch, int gamma, int V) {
   const long rows = 2 * (long)gamma + 1, cus = 256;
   p.slices = kMinSlices;
   while (p.slices < kMaxSlices && rows * 2 * p.slices <= 4 * kDrawThreads && V >= 2 * p.slices * 2 * kStatThreads &&
-         (V > p.slices * kStatRegs * kStatThreads || rows * p.slices * batch < 2 * cus))
+         (V > p.slices * kStatRegs * kStatThreads || rows * p.slices * batch < cus))
     p.slices *= 2;
   p.per = batch * (((long)V + 2 * kDrawThreads - 1) / (2 * kDrawThreads)) > 4 * cus ? 8 : 2;
   p.chunks = (V + p.per * kDrawThreads - 1) / (p.per * kDrawThreads);
@@ -113,7 +131,8 @@ static AcceptPlan accept_plan(int batch, int gamma, int V) {
 
 // Workspace of one sequence (doubles): [rows][slices][2] slice statistics, then the chunk sums; in its last double the
 // counter of (2).  Room for kMinSlices slices and V + V / kWsChunk doubles more: what accept_plan asks for fits (more slices
-// than kMinSlices take at most 2048 doubles and V is at least 16 384 then, the chunks are at most V / 512 + 1).
+// than kMinSlices take at most 2048 doubles and V is at least 16 384 then, the chunks are at most V / 512 + 1 and the lines of
+// their groups' counters, from V = 8193 on, V / 512 + 32 doubles).
 // kNoSum: a chunk sum that is not there yet, a NaN with a payload that arithmetic does not make.
 typedef unsigned long long sum_bits;
 constexpr sum_bits kNoSum = 0x7FFC5A3C96E1B482ull;
@@ -134,6 +153,10 @@ __device__ __forceinline__ AcceptWs accept_ws(double* base, int b, int gamma, in
   w.done = reinterpret_cast<int*>(w.stats + all - 1);
   return w;
 }
+// The counter of the group of kGroup chunks that c belongs to: a line of its own each, in front of the last double (a call of more
+// than one group has a vocabulary of more than 8192).
+constexpr int kGroup = 16;
+__device__ __forceinline__ int* group_counter(const AcceptWs& w, int c) { return w.done - 32 * (c / kGroup + 1); }
 
 // x / T as the division rounds it, without one: y = 1 / T rounded to nearest, q = x y, then one step q + (x - q T) y with
 // fused multiply-adds (Markstein 1990: correctly rounded if y is).  Infinities and NaNs keep the product.
@@ -185,10 +208,13 @@ __global__ __launch_bounds__(kStatThreads) void accept_stats_kernel(const float*
     double* o = ws.stats + ((size_t)j * slices + slice) * 2;
     o[0] = (double)mx;  // -inf for an empty slice; its sum is 0
     o[1] = z;
-    if (j == 0 && slice == 0) *ws.done = 0;
   }
   if (j == 0)
-    for (int c = slice * kStatThreads + threadIdx.x; c < chunks; c += slices * kStatThreads) ws.chunk_sum[c] = kNoSum;
+    for (int c = slice * kStatThreads + threadIdx.x; c < chunks; c += slices * kStatThreads) {
+      ws.chunk_sum[c] = kNoSum;
+      if (c % kGroup == 0 && chunks > kGroup) *group_counter(ws, c) = 0;
+      if (c == 0) *ws.done = 0;
+    }
 }
 
 // Inclusive running sum over the workgroup's threads: inside rows of 16 lanes by operand swizzles, then the rows' and the waves' totals
@@ -235,38 +261,59 @@ __global__ __launch_bounds__(kDrawThreads) void accept_draw_kernel(const int32_t
   const float* tl = target_logits + (size_t)b * (gamma + 1) * V;
   const float* dl = draft_logits + (size_t)b * gamma * V;
   const double inv_T = 1.0 / T;
-  // the drafted tokens' logits, on their way while the statistics are combined
+  // Requested in the order of need: loads return in it.  First the drafted tokens, then the statistics, then the tokens' logits.
   int token = -1;
   float t_logit = 0.f, d_logit = 0.f, r_in = 0.f;
   if (lane < gamma) {
     token = draft[(size_t)b * gamma + lane];
     r_in = r[(size_t)b * gamma + lane];
+  }
+  const float u_in = u[b];
+  auto others = [&] {
+    asm volatile("" ::: "memory");  // behind the statistics
     if (token >= 0 && token < V) {
       t_logit = tl[(size_t)lane * V + token];
       d_logit = dl[(size_t)lane * V + token];
     }
-  }
+    asm volatile("" ::: "memory");
+  };
   const int terms = (2 * gamma + 1) * slices;
-  constexpr int TB = 4;  // terms a thread requests side by side: all of them, but for the longest drafts
-  for (int i0 = tid; i0 - tid < terms; i0 += TB * kDrawThreads) {
-    double mine[TB], sum[TB];
+  auto combine = [&](auto side_by_side, int first, const auto& others) {  // that many terms a thread, their chains interleaved
+    constexpr int N = decltype(side_by_side)::value;
+    double mine[N], sum[N], m[N], t[N];
 #pragma unroll
-    for (int k = 0; k < TB; ++k) {
-      const size_t i = min(i0 + k * kDrawThreads, terms - 1);
+    for (int k = 0; k < N; ++k) {
+      const size_t i = min(first + tid + k * kDrawThreads, terms - 1);
       mine[k] = ws.stats[2 * i];
       sum[k] = ws.stats[2 * i + 1];
     }
+    others();
+    // the slices are a power of two and divide 64: a row's lie in one wave
 #pragma unroll
-    for (int k = 0; k < TB; ++k) {
-      const int i = i0 + k * kDrawThreads;  // the slices are a power of two and divide 64: a row's lie in one wave
-      if (i - lane >= terms) break;         // uniform
-      const double m = lanes_max((float)mine[k], slices);  // maxima of floats
-      const double t = lanes_sum(i < terms && sum[k] > 0.0 ? sum[k] * exp(quotient(mine[k] - m, T, inv_T)) : 0.0, slices);
+    for (int k = 0; k < N; ++k) m[k] = lanes_max((float)mine[k], slices);  // maxima of floats
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
+      const double e = sum[k] * exp(quotient(mine[k] - m[k], T, inv_T));
+      t[k] = sum[k] > 0.0 ? e : 0.0;
+    }
+#pragma unroll
+    for (int k = 0; k < N; ++k) t[k] = lanes_sum(t[k], slices);
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
+      const int i = first + tid + k * kDrawThreads;
       if (i < terms && (i & (slices - 1)) == 0) {
-        s_mx[i / slices] = m;
-        s_z[i / slices] = t;
+        s_mx[i / slices] = m[k];
+        s_z[i / slices] = t[k];
       }
     }
+  };
+  if (terms <= kDrawThreads) {
+    combine(std::integral_constant<int, 1>{}, 0, others);
+  } else if (terms <= 2 * kDrawThreads) {
+    combine(std::integral_constant<int, 2>{}, 0, others);
+  } else {
+    combine(std::integral_constant<int, 4>{}, 0, others);
+    for (int first = 4 * kDrawThreads; first < terms; first += 4 * kDrawThreads) combine(std::integral_constant<int, 4>{}, first, [] {});
   }
   __syncthreads();
   bool rejected = false;
@@ -316,34 +363,38 @@ __global__ __launch_bounds__(kDrawThreads) void accept_draw_kernel(const int32_t
     }
     return s;
   };
+  auto load_sum = [&](int c) { return __hip_atomic_load(&ws.chunk_sum[c], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
   auto send_sum = [&](int c, double v) {
     __hip_atomic_store(&ws.chunk_sum[c], v == v ? __builtin_bit_cast(sum_bits, v) : 0x7FF8000000000000ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   };
   double q[PER];
   const double tot = block_sum<kDrawThreads / 64>(run_of(chunk, q), s_wave);
+  // every thread's first chunk sum comes with the counter: for the last workgroup it is there, but for those under way
+  const int cper = (nchunk + kDrawThreads - 1) / kDrawThreads, c0 = min(nchunk, tid * cper), c1 = min(nchunk, c0 + cper);
+  const sum_bits early = load_sum(min(c0, nchunk - 1));
   if (tid == 0) {
     send_sum(chunk, tot);
-    s_flag = __hip_atomic_fetch_add(ws.done, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == nchunk - 1;
+    // Raising one counter takes 11 ns a workgroup, one after the other (2.7 us for 251): a counter for every sixteen
+    // chunks, and one for those that were a group's last.
+    auto raise = [](int* p) { return __hip_atomic_fetch_add(p, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
+    const int group = min(kGroup, nchunk - chunk / kGroup * kGroup), groups = (nchunk + kGroup - 1) / kGroup;
+    s_flag = (groups == 1 || raise(group_counter(ws, chunk)) == group - 1) && raise(ws.done) == (groups == 1 ? nchunk : groups) - 1;
   }
   __syncthreads();
   if (!s_flag) return;
 
   // The sequence's last workgroup: every thread takes a run of chunks
-  const int cper = (nchunk + kDrawThreads - 1) / kDrawThreads, c0 = min(nchunk, tid * cper), c1 = min(nchunk, c0 + cper);
-  auto chunk_sum = [&](int c) {
-    sum_bits x;
-    do {  // it has been sent: ends when it arrives
-      x = __hip_atomic_load(&ws.chunk_sum[c], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    } while (x == kNoSum);
+  auto chunk_sum = [&](int c, sum_bits x = kNoSum) {
+    while (x == kNoSum) x = load_sum(c);  // it has been sent: ends when it arrives
     return __builtin_bit_cast(double, x);
   };
-  auto scan_chunks = [&] {
+  auto scan_chunks = [&](sum_bits first) {
     double s = 0.0;
-    for (int c = c0; c < c1; ++c) s += chunk_sum(c);
+    for (int c = c0; c < c1; ++c) s += chunk_sum(c, c == c0 ? first : kNoSum);
     block_scan(s, s_incl, s_wave);
     return s_incl[kDrawThreads - 1];
   };
-  double total = scan_chunks();
+  double total = scan_chunks(early);
   if (!(total > 0.0)) {
     // identical distributions leave no residual (a rejection is then impossible for r < 1): fall
     // back to the target distribution of that position (rare, slow, correct)
@@ -354,9 +405,9 @@ __global__ __launch_bounds__(kDrawThreads) void accept_draw_kernel(const int32_t
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the old sums are gone when the other waves look
     __syncthreads();
-    total = scan_chunks();
+    total = scan_chunks(kNoSum);
   }
-  const double thr = (double)u[b] * total;
+  const double thr = (double)u_in * total;
   if (tid == 0) s_flag = -1;
   __syncthreads();
   {

@@ -11,12 +11,14 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("batch,gamma,V", [
     (1, 5, 511), (1, 5, 512), (1, 5, 513),      # one chunk, a full one, one entry more
+    (1, 5, 8192), (1, 5, 8193),                 # 16 chunks and one counter, 17 and two groups
     (1, 5, 16383), (1, 5, 16384),               # 8 slices, 16
-    (1, 2, 32768), (1, 5, 65537),               # 32, 64
+    (1, 5, 32768), (1, 1, 65537),               # 32, 64
     (1, 31, 32769),                             # 16: four terms a thread
     (1, 5, 131072), (1, 5, 131073),             # 256 chunks, 257
     (9, 5, 66001),                              # 1161 chunks of two entries a thread: eight
     (5, 1, 300007),                             # slices longer than held, eight entries a thread
+    (2, 20, 140003),                            # 41 rows: 16 slices longer than held
 ])
 def test_cuts(oracle, es, batch, gamma, V):  # noqa: F811
     compare(oracle, es, make_case(3000 + V, batch, gamma, V, 0.9, 0.3), 0.9)

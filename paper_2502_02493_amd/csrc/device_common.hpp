@@ -13,9 +13,9 @@
 //   * The token columns are the MFMA's N dimension (B operand, 16 bytes per lane read from a
 //     small L2-resident activation array, only lanes of live columns load).
 //   * The waves of a workgroup split K between them (interleaved, so the workgroup reads
-//     consecutive KBs), partial accumulators are summed through LDS in a fixed order, and wave
-//     0 runs the epilogue that the operation needs (bias + rotary + cache write, residual
-//     update + next norm input, SiLU*up, logits + argmax).
+//     consecutive KBs), partial accumulators are summed through LDS in a fixed order, and a
+//     thread per element runs the epilogue that the operation needs (bias + rotary + cache
+//     write, residual update + next norm input, SiLU*up, logits + argmax).
 //
 // RMSNorm is split so that no kernel has to normalise before it can start streaming: the
 // producer of a residual vector h writes T(h * gain) for the consumer's gain and the partial

@@ -746,7 +746,8 @@ __global__ __launch_bounds__(64 * NW, NW == 1 ? 1 : 2) void attn_mfma_kernel(Att
 
   // This thread's pieces of a super tile: piece `piece` of slots sl0 + j * 64 NW / PIECES.  The registers are
   // free again once their contents sit in LDS, so the next tile is requested while the current one is still
-  // being worked on; the first one before the queries are fetched.
+  // being worked on; the first one before the queries are converted.
+  // (They are requested behind this row's query all the same: loads return in order.)
   // Loads are unconditional: a slot past the chunk's end (only the last chunk of the longest column has any:
   // chunks are multiples of 64 slots) re-reads the last row; its scores are masked below for every query row,
   // so its probabilities are exact zeros.
@@ -769,18 +770,33 @@ __global__ __launch_bounds__(64 * NW, NW == 1 ? 1 : 2) void attn_mfma_kernel(Att
       for (int j = 0; j < NL; ++j) vf[j] = __builtin_nontemporal_load(vc + (size_t)min(base + sl0 + j * SL, ws1 - 1) * PIECES + piece);
     }
   };
+  // The query in 16-byte pieces, unconditionally (a padding row takes the group's first; its results are dropped): an element at a
+  // time under the row's condition, behind the first tile, a launch took 6.1 us to its first products.  us a call, before and now:
+  // prefill of 16 tokens at context 8192 3862 -> 3757, tree levels of 4 and 12 nodes 5595 -> 5537, 4 x 6 tokens at 4096 .. 32768
+  // 5219 -> 5157, 16 x 16 tokens 9410 -> 9220.
+  f32x4 q_raw[KT][2];
+  {
+    const float* qp = a.Q + ((size_t)li * kMaxCols + col) * HQ + (kvh * G + g) * HD + q4 * 8;
+#pragma unroll
+    for (int kt = 0; kt < KT; ++kt)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) q_raw[kt][h] = *reinterpret_cast<const f32x4*>(qp + kt * 32 + h * 4);
+  }
+  asm volatile("" ::: "memory");
   request(ws0);
 
   // B operands of S^T: this row's query, hi and lo bf16 terms, k-group q4 of every k-tile; a third term where asked for
   constexpr bool Q3 = Src::kQueryTerms == 3;
   bf16x8 qh[KT], ql[KT], qr[Q3 ? KT : 1];
   {
-    const float* qp = a.Q + ((size_t)li * kMaxCols + col) * HQ + (kvh * G + g) * HD + q4 * 8;
 #pragma unroll
     for (int kt = 0; kt < KT; ++kt) {
       float x[8];
 #pragma unroll
-      for (int e = 0; e < 8; ++e) x[e] = row_ok ? qp[kt * 32 + e] : 0.f;
+      for (int e = 0; e < 8; ++e) {
+        x[e] = q_raw[kt][e >> 2][e & 3];
+        asm volatile("" : "+v"(x[e]));  // behind the requests, the conversions too
+      }
       split_bf16x8(x, qh[kt], ql[kt]);
       if constexpr (Q3) qr[kt] = third_bf16x8(x, qh[kt], ql[kt]);
     }
@@ -852,7 +868,7 @@ __global__ __launch_bounds__(64 * NW, NW == 1 ? 1 : 2) void attn_mfma_kernel(Att
       }
     }
     // Scores stay unscaled: scale and log2(e) go into the exponential's argument, one fused multiply-add per score
-    if (edge) {  // padding rows elsewhere get finite scores of a zero query; they are never stored
+    if (edge) {  // padding rows elsewhere get scores of the group's first query; they are never stored
 #pragma unroll
       for (int t = 0; t < 4; ++t)
 #pragma unroll

@@ -677,11 +677,13 @@ struct ColGroups {
 };
 // What the kernel asks about its columns: those of a pass of at most kMaxCols (PassCols), or of a wide pass, whose
 // columns are given by sequence (SpanCols).
+template <int PT>
 struct PassCols {
   Cols c;
   ColGroups cg;
   static constexpr bool kWide = false;
   static constexpr int kQueryTerms = 2;
+  static constexpr int kProbTerms = PT;  // bf16 terms of a probability: two or three (AttnCut::three)
 };
 template <int QT>
 struct SpanCols {
@@ -691,6 +693,7 @@ struct SpanCols {
   int32_t most;                    // columns of a full group
   static constexpr bool kWide = true;
   static constexpr int kQueryTerms = QT;  // bf16 terms of a query: two or three (queries_in_fp32)
+  static constexpr int kProbTerms = 3;
 };
 typedef short v4i16 __attribute__((ext_vector_type(4)));
 typedef short v8i16 __attribute__((ext_vector_type(8)));
@@ -892,8 +895,8 @@ __global__ __launch_bounds__(64 * NW, NW == 1 ? 1 : 2) void attn_mfma_kernel(Att
       for (int et = 0; et < ET; ++et) o[et] *= alpha;
     }
     // B operands of P.V: MFMA number h takes slots q4*16 + h*8 .. +8 of this lane = tiles 2h, 2h+1
-    // Wide passes carry probabilities in three terms, all 24 bits: the shorter contexts among them would otherwise be the
-    // vector kernel's, which keeps probabilities in fp32.
+    // Wide passes, and launches that are here by attn_mfma_rows alone, carry probabilities in three terms, all 24 bits: the vector
+    // kernel, whose the shorter contexts among them would otherwise be, keeps probabilities in fp32.
     bf16x8 ph[2], pl[2], pr[2];
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
@@ -904,7 +907,7 @@ __global__ __launch_bounds__(64 * NW, NW == 1 ? 1 : 2) void attn_mfma_kernel(Att
         l_run += pv[j];
       }
       split_bf16x8(pv, ph[h], pl[h]);
-      if constexpr (Src::kWide) pr[h] = third_bf16x8(pv, ph[h], pl[h]);
+      if constexpr (Src::kProbTerms == 3) pr[h] = third_bf16x8(pv, ph[h], pl[h]);
     }
     // A operands: V^T row e = et*16 + lane%16, the 8 slots q4*16 + h*8 + j, by the LDS transposing
     // read (ds_read_b64_tr_b16): in a group of 16 lanes, lane i offers the 8 bytes at its address
@@ -927,7 +930,7 @@ __global__ __launch_bounds__(64 * NW, NW == 1 ? 1 : 2) void attn_mfma_kernel(Att
         const bf16x8 va = __builtin_bit_cast(bf16x8, both);
         o[et] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va, ph[h], o[et], 0, 0, 0);
         o[et] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va, pl[h], o[et], 0, 0, 0);
-        if constexpr (Src::kWide) o[et] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va, pr[h], o[et], 0, 0, 0);
+        if constexpr (Src::kProbTerms == 3) o[et] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va, pr[h], o[et], 0, 0, 0);
       }
     }
     bool odd = false;
@@ -1090,31 +1093,48 @@ static void launch_attn_g(int G, dim3 grid, int nwv, hipStream_t st, AttnArgs a,
   }
 }
 
-// Matrix-core attention or the vector-ALU kernel?  The MFMA kernel reads K and V once per group
-// of columns of a sequence and does the per-slot arithmetic on the matrix cores, but its
-// per-wave chain (LDS transposes between the two products) is longer; it wins once a
-// launch holds several columns of a sequence and enough (column, layer, slot) work: tree levels,
-// long calibrations.  Single columns (plain draft steps) and short 1-layer launches stay on the
-// vector kernel.  EASYSPEC_ATTN_MFMA = 0 / 2 forces never / always (bf16 only).
-static bool attn_use_mfma(const Shape& s, const Cols& c, int n_set) {
-  const int mode = env_int("EASYSPEC_ATTN_MFMA", 1);  // read at every call: tests switch it between contexts
+// Matrix-core attention or the vector-ALU kernel?  The MFMA kernel reads K and V once per group of columns of a sequence and does
+// the per-slot arithmetic on the matrix cores.  It takes bf16 launches that hold several columns of a sequence and
+//   * enough (column, layer, slot) work, over several layers or at least five columns (attn_mfma_long), or
+//   * heads of 128 elements, four or more per KV head, contexts of more than one piece, and at least 12 query rows of a sequence,
+//     three quarters of a tile (attn_mfma_rows): calibrations of three tokens or more, short ones too.
+// Single columns (plain draft steps) stay on the vector kernel.  EASYSPEC_ATTN_MFMA = 0 / 2 forces never / always (bf16 only).
+// The second line was drawn when the kernel had lost 2.7 us of its start; us a call of 12 layers on the vector and the matrix-core kernel with
+// three terms to a probability.  8B shape, 3 / 4 / 6 / 8 / 12 tokens at context 300 1022 / 1081 / 1114 / 1126 / 1214 and 1028 / 1079 / 1109 /
+// 1127 / 1210, at 2048 1103 / 1109 / 1162 / 1192 / 1315 and 1105 / 1107 / 1145 / 1167 / 1248, at 4096 1139 / 1151 / 1232 / 1274 / 1612 and
+// 1137 / 1140 / 1178 / 1192 / 1279; 2 tokens (two terms) at 2048 1095 and 1099, at 8192 1162 and 1181.  Qwen2-7B shape, 3 / 6 / 12 tokens at
+// 600 1187 / 1233 / 1394 and 1168 / 1214 / 1389, at 2048 1206 / 1261 / 1444 and 1180 / 1234 / 1408.  Two tree levels of 3 / 6 / 12
+// nodes at 600, sets of four, 8B 1880 / 2063 / 2196 and 1869 / 2033 / 2121.  6-token calibration at 2048, 32 layers: 3094 -> 3057.
+static bool attn_mfma_long(const Cols& c, int n_set) {
   const long min_work = env_int("EASYSPEC_ATTN_MFMA_MIN", 30000);
-  if (mode == 0 || s.dtype != 1) return false;
-  if (mode == 2) return true;
   bool shared = false;
   int max_len = 1;
   for (int i = 0; i < c.n; ++i) {
     shared = shared || (i > 0 && c.seq[i] == c.seq[i - 1]);
     max_len = std::max(max_len, c.pos[i] + 1);
   }
-  // Where the line was drawn (30 000 units, five columns in a single layer) was measured with a kernel whose waves had a tile
-  // each, and has not been moved since they share one.  With this kernel, 8B shape, us a call on the vector and the
-  // matrix-core kernel: 4 / 6 / 8 / 12 tokens at context 2048 2990 / 3266 / 3349 / 3727 and 3044 / 3293 / 3391 / 3586;
-  // 3 / 4 / 5 / 6 tokens at 8192 3414 / 3435 / 3645 / 3735 and 3391 / 3412 / 3456 / 3474; 16 tokens at 512 3607 and 3671;
-  // two tree levels of 4 / 8 / 12 nodes at 2048 in sets of four layers 5488 / 5881 / 6586 and 5432 / 5610 / 6055.  The
-  // rule is right at these but for 12 tokens at 2048 (4 %) and 3 or 4 at 8192 (0.7 %); at the Qwen2-7B shape it is 2 %
-  // off for 4 and 6 tokens at context 4096 (3081 and 3226 us, matrix cores 3009 and 3147).
   return shared && (long)n_set * c.n * max_len >= min_work && (n_set > 1 || c.n >= 5);
+}
+static int longest_run(const Cols& c) {
+  int longest = 1;
+  for (int i = 1, run = 1; i < c.n; ++i) {
+    run = c.seq[i] == c.seq[i - 1] ? run + 1 : 1;
+    longest = std::max(longest, run);
+  }
+  return longest;
+}
+constexpr int kAttnOnePiece = 256;  // contexts up to here are one piece (attn_cut)
+static bool attn_mfma_heads(const Shape& s) { return s.hd == 128 && s.Hq / s.Hkv >= 4; }
+static bool attn_mfma_rows(const Shape& s, const Cols& c) {
+  int max_len = 1;
+  for (int i = 0; i < c.n; ++i) max_len = std::max(max_len, c.pos[i] + 1);
+  const int longest = longest_run(c);
+  return attn_mfma_heads(s) && max_len > kAttnOnePiece && longest > 1 && longest * (s.Hq / s.Hkv) >= 12;
+}
+static bool attn_use_mfma(const Shape& s, const Cols& c, int n_set) {
+  const int mode = env_int("EASYSPEC_ATTN_MFMA", 1);  // read at every call: tests switch it between contexts
+  if (mode == 0 || s.dtype != 1) return false;
+  return mode == 2 || attn_mfma_long(c, n_set) || attn_mfma_rows(s, c);
 }
 
 // Waves per workgroup of the matrix-core kernel = tiles of 16 query rows that share K and V: as many as the
@@ -1122,12 +1142,7 @@ static bool attn_use_mfma(const Shape& s, const Cols& c, int n_set) {
 static int row_tiles(const Cols& c, int G) {
   const int forced = env_int("EASYSPEC_ATTN_ROW_TILES", 0);  // tests: read at every call
   if (forced == 1 || forced == 2 || forced == 4) return forced;
-  int longest = 1;
-  for (int i = 1, run = 1; i < c.n; ++i) {
-    run = c.seq[i] == c.seq[i - 1] ? run + 1 : 1;
-    longest = std::max(longest, run);
-  }
-  const int tiles = (longest * G + 15) / 16;
+  const int tiles = (longest_run(c) * G + 15) / 16;
   return tiles <= 2 ? tiles : 4;
 }
 
@@ -1151,6 +1166,7 @@ static void group_columns(const Cols& c, int G, int n_tiles, ColGroups& cg) {
 AttnCut attn_cut(const Shape& s, const Cols& c, int n_set) {
   AttnCut cut;
   cut.mfma = attn_use_mfma(s, c, n_set);
+  cut.three = cut.mfma && attn_mfma_heads(s) && !attn_mfma_long(c, n_set);
   cut.tiles = 1;
   cut.chunk = 0;
   cut.nb_ref = 0;
@@ -1158,7 +1174,7 @@ AttnCut attn_cut(const Shape& s, const Cols& c, int n_set) {
   for (int i = 0; i < c.n; ++i) max_len = std::max(max_len, c.pos[i] + 1);
   // Short contexts: one piece of work per (layer, column, KV head) walks the whole context, which
   // saves the merge launch; two dependent launches cost more than the narrower launch loses.
-  static const int single_max = env_int("EASYSPEC_ATTN_SINGLE", 256);
+  static const int single_max = env_int("EASYSPEC_ATTN_SINGLE", kAttnOnePiece);
   if (cut.mfma) {
     // one workgroup per (group of columns, chunk, KV head), walking its chunk in super tiles of 64 slots: chunks of a
     // fixed length, grown until their count fits the partial buffers and the launch is not cut finer than max_wg
@@ -1195,11 +1211,12 @@ AttnCut attn_cut(const Shape& s, const Cols& c, int n_set) {
 AttnCut attn_cut_vector(const Shape& s, const Cols& c, int n_set) {
   AttnCut cut;
   cut.mfma = false;
+  cut.three = false;
   cut.tiles = 1;
   cut.chunk = 0;
   int max_len = 1;
   for (int i = 0; i < c.n; ++i) max_len = std::max(max_len, c.pos[i] + 1);
-  static const int single_max = env_int("EASYSPEC_ATTN_SINGLE", 256);
+  static const int single_max = env_int("EASYSPEC_ATTN_SINGLE", kAttnOnePiece);
   // Vector kernel: one workgroup of four waves per (chunk, KV head, layer, column).  Every column's
   // units (the slots of a wave's small step) are dealt evenly to its chunks (chunk_range) and a
   // chunk's units evenly to its waves, which work through them in full batches of four units and
@@ -1280,19 +1297,28 @@ void launch_attn(const Shape& s, const Buffers& b, const Cols& c, int layer0, in
   bool tree = false;  // any column that does not see every slot up to its own
   for (int i = 0; i < c.n; ++i) tree = tree || c.vis_base[i] <= c.pos[i];
   if (cut.mfma) {
-    PassCols src;
-    src.c = c;
-    group_columns(c, G, cut.tiles, src.cg);
-    a.n = src.cg.n;
+    ColGroups cg;
+    group_columns(c, G, cut.tiles, cg);
+    a.n = cg.n;
     a.inv_n = 1.0f / (float)a.n;
     for (int i = 0; i < c.n; ++i) mc.nch[i] = (c.pos[i] + cut.chunk) / cut.chunk;
-    const dim3 mg(n_chunks, s.Hkv, n_set * src.cg.n), blk(64 * cut.tiles);
-    auto go = [&](auto hd, auto is_tree) {
+    const dim3 mg(n_chunks, s.Hkv, n_set * cg.n), blk(64 * cut.tiles);
+    auto launch = [&](auto hd, auto is_tree, auto terms) {
       constexpr int HD = decltype(hd)::value;
       constexpr bool TREE = decltype(is_tree)::value;
-      if (cut.tiles == 4) ES_LAUNCH((attn_mfma_kernel<HD, TREE, 4, PassCols>), mg, blk, 0, st, a, src, G);
-      else if (cut.tiles == 2) ES_LAUNCH((attn_mfma_kernel<HD, TREE, 2, PassCols>), mg, blk, 0, st, a, src, G);
-      else ES_LAUNCH((attn_mfma_kernel<HD, TREE, 1, PassCols>), mg, blk, 0, st, a, src, G);
+      typedef PassCols<decltype(terms)::value> Src;
+      Src src;
+      src.c = c;
+      src.cg = cg;
+      if (cut.tiles == 4) ES_LAUNCH((attn_mfma_kernel<HD, TREE, 4, Src>), mg, blk, 0, st, a, src, G);
+      else if (cut.tiles == 2) ES_LAUNCH((attn_mfma_kernel<HD, TREE, 2, Src>), mg, blk, 0, st, a, src, G);
+      else ES_LAUNCH((attn_mfma_kernel<HD, TREE, 1, Src>), mg, blk, 0, st, a, src, G);
+    };
+    auto go = [&](auto hd, auto is_tree) {
+      if constexpr (decltype(hd)::value == 128) {
+        if (cut.three) return launch(hd, is_tree, std::integral_constant<int, 3>{});
+      }
+      launch(hd, is_tree, std::integral_constant<int, 2>{});
     };
     const std::integral_constant<int, 128> h128{};
     const std::integral_constant<int, 64> h64{};

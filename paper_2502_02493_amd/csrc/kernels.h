@@ -172,6 +172,7 @@ void launch_qkv(const Shape& s, const Buffers& b, const Cols& c, int layer0, int
 // How an attention launch over n_set layers cuts the contexts of these columns into split-KV chunks.
 struct AttnCut {
   bool mfma;     // the matrix-core kernel takes the launch (groups of columns of one sequence)
+  bool three;    // matrix-core kernel: probabilities in three bf16 terms (what the vector kernel would have held in fp32)
   int tiles;     // matrix-core kernel: tiles of 16 query rows per workgroup, one per wave (1, 2 or 4)
   int n_chunks;  // chunks of the longest column = grid extent; 1: every context in one piece, no merge launch
   int chunk;     // matrix-core kernel: slots per chunk (fixed length)

@@ -1,0 +1,46 @@
+"""GPU parity of calibrations and tree levels whose route the number of query rows decides (heads of 128, four or seven per KV
+head): one column less and as many as the matrix-core kernel takes, contexts of one piece and one slot more, two sequences of which one has a
+single column; and probabilities in three terms there: closer to the vector kernel than two terms of 16 bits can be."""
+import numpy as np
+import pytest
+
+import easyspec_synth as synth
+from test_gpu_attn_row_tiles import gpu  # noqa: F401
+from test_gpu_nonfinite import run
+from test_gpu_parity import iteration_parity
+from test_gpu_tree import tree_parity
+
+pytestmark = pytest.mark.gpu
+
+
+def shape(G):
+    return synth.model_shape("tiny", dtype="bf16", head_dim=128, n_q_heads=2 * G, n_kv_heads=2)
+
+
+@pytest.mark.parametrize("G,n", [(4, 2), (4, 3), (7, 1), (7, 2), (8, 2), (4, 16)])
+@pytest.mark.parametrize("context", [250, 257 + 64, 700])
+def test_calibration(gpu, monkeypatch, G, n, context):  # noqa: F811
+    """Against the vector kernel, which the oracle tests pin: queries in two terms and probabilities of (at least) 24 bits on both."""
+    cfg = shape(G)
+    w = synth.make_weights(cfg, 1400)
+    toks = {0: [int(x) for x in synth.make_tokens(1401, n, cfg["vocab"])], 1: [5]}
+    got, kv = run(gpu, cfg, w, [context, 300], toks)
+    monkeypatch.setenv("EASYSPEC_ATTN_MFMA", "0")
+    want, kv0 = run(gpu, cfg, w, [context, 300], toks)
+    for b in toks:
+        # sums in another order, products of 48 against 32 bits: 2^-22 an operation; a bf16 cache entry that rounds the other way
+        # costs 2^-9 of one of some 300 slots, and few do
+        rel = np.linalg.norm(got[b] - want[b]) / np.linalg.norm(want[b])
+        assert rel < 2e-4, (b, rel)
+        for x, y in zip(kv[b], kv0[b]):
+            assert (x != y).mean() < 1e-3
+
+
+@pytest.mark.parametrize("G", [4, 7])
+def test_iteration(oracle, gpu, G):  # noqa: F811
+    iteration_parity(oracle, gpu, shape(G), 1410, [0, 1, 3, 4], 300, 4, n_iters=1)
+
+
+@pytest.mark.parametrize("G", [4, 7])
+def test_tree(oracle, gpu, G):  # noqa: F811
+    tree_parity(oracle, gpu, shape(G), 1420, [0, 1, 4], 270, [2, 3, 5])

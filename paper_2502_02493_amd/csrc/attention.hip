@@ -648,7 +648,7 @@ __global__ __launch_bounds__(512) void attn_kernel(AttnArgs a, Cols c, ChunkMap 
 // level) — are the columns of NW MFMA tiles of 16, one tile per wave of the workgroup, so K and V
 // are read once per group of columns and the per-slot arithmetic leaves the vector ALUs:
 //   S^T[slot][row]  = K[slot][:] . Q[row][:]      A = K (rows = slots), B = Q^T, two-term bf16 q (queries_in_fp32: three)
-//   O^T[e][row]    += V^T[e][slot] P^T[slot][row]  A = V^T, B = P^T, two-term bf16 p (wide passes: three)
+//   O^T[e][row]    += V^T[e][slot] P^T[slot][row]  A = V^T, B = P^T, two-term bf16 p (wide passes, AttnCut::three: three)
 // A workgroup walks its chunk of the context in super tiles of 64 slots: its waves load the K and V
 // rows of a tile together (coalesced) and put them into LDS (XOR-swizzled 16-byte pieces; V is read
 // back with the transposing LDS read), each wave then takes its own 16 query rows through scores,

@@ -26,11 +26,8 @@
 // tile each instead of four (end of a tile 1.5 -> 0.8).  In the attention the steps of all heads go side by side, the slots of
 // this pass are part of the last run instead of a batch of their own, and with seven or eight heads half of the waves take half
 // of them: 5.5 -> 3.2 us at 61 slots and seven heads.
-// Where it is taken: resident_pass.  us a call, launches and resident: draft step of the 256-wide fp32 model of 4 layers 98 -> 55; an iteration of the 448-wide
-// one of 5 layers (calibration of 5 tokens and three steps, vocabulary of 1000) 594 -> 377.  (The two trips that the last unit made
-// after its result, for a ticket that could not exist and to leave, were 1.2 and 3.5 of these.)
-// How often a waiting wave asks is a balance, asking slows the stores that it waits for: 64 cycles between polls 54.8 and 377, 256 cycles
-// 55.5 and 380, 640 cycles 57.9 and 390; two requests on the way half a trip apart 58.4 and 397.
+// Where it is taken: resident_pass.  us a call, launches and resident: draft step of the 256-wide fp32 model of 4 layers 98 -> 56; an iteration of the 448-wide
+// one of 5 layers (calibration of 5 tokens and three steps, vocabulary of 1000) 594 -> 380.
 #include "launch_common.hpp"
 
 #include <math.h>
@@ -232,8 +229,6 @@ __device__ __forceinline__ void stage(const ResidentArgs& a, const Operand& o, i
     const float inv_row = 1.0f / (float)row;
     if (total <= kResThreads) {
       stage_part<T, 1>(o, row, total, inv_row, 0, tid, n, w, sh, xs);
-    } else if (total <= 2 * kResThreads) {
-      stage_part<T, 2>(o, row, total, inv_row, 0, tid, n, w, sh, xs);
     } else if (total <= 4 * kResThreads) {
       stage_part<T, 4>(o, row, total, inv_row, 0, tid, n, w, sh, xs);
     } else {
@@ -345,18 +340,6 @@ __global__ __launch_bounds__(kResThreads) void resident_kernel(ResidentArgs a, C
   __syncthreads();
   int ticket = __builtin_amdgcn_readfirstlane(sh.next);
 
-  // The last workgroup to leave sets the counters for the next pass: by then every workgroup has read the epoch and has
-  // taken its last ticket.
-  auto leave = [&] {
-    if (threadIdx.x != 0) return;
-    const uint32_t out = __hip_atomic_fetch_add(&a.ctl->done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (out == gridDim.x - 1) {
-      const uint32_t e = w.epoch + 1;
-      __hip_atomic_store(&a.ctl->ticket, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      __hip_atomic_store(&a.ctl->done, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      __hip_atomic_store(&a.ctl->epoch, e == 0u || e == 0xFFFFFFFFu ? 1u : e, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-  };
   int set = 0, lo = 0, hi = a.bounds[1], layer = 0, ph = kPhQkv, first = 0;
   while (true) {
     // opaque in every round: what a unit derives from these is computed in it, not kept in registers over all others
@@ -719,8 +702,6 @@ __global__ __launch_bounds__(kResThreads) void resident_kernel(ResidentArgs a, C
     } else {  // argmax of one column (lowest index on ties)
       float bv = -INFINITY;
       int bi = 0x7FFFFFFF;
-      // The pass's last unit: there is no further ticket to ask for, and leaving costs no trip at the end
-      if (unit == n - 1) leave();
       const granule_t* src = cand + (size_t)unit * u_v * 2;
       for (int t0 = 0; t0 < u_v; t0 += kResThreads) {
         const int t = min(t0 + tid, u_v - 1);
@@ -751,13 +732,22 @@ __global__ __launch_bounds__(kResThreads) void resident_kernel(ResidentArgs a, C
         }
         if (c.out_idx[unit] >= 0) a.tokens_out[c.out_idx[unit]] = bi;
       }
-      if (unit == n - 1) return;
     }
     ask_next();
     __syncthreads();  // the unit's LDS is free again
     ticket = __builtin_amdgcn_readfirstlane(sh.next);
   }
-  leave();
+  // The last workgroup out sets the counters for the next pass: by then every workgroup has read the epoch and has taken
+  // its last ticket.
+  if (threadIdx.x == 0) {
+    const uint32_t out = __hip_atomic_fetch_add(&a.ctl->done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (out == gridDim.x - 1) {
+      const uint32_t e = w.epoch + 1;
+      __hip_atomic_store(&a.ctl->ticket, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      __hip_atomic_store(&a.ctl->done, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      __hip_atomic_store(&a.ctl->epoch, e == 0u || e == 0xFFFFFFFFu ? 1u : e, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+  }
 }
 
 // ------------------------------------------------------------------------------------------

@@ -19,9 +19,10 @@
 // "Last" is told by a counter; it says whose sums have been sent, and (1) marks them all as missing, so the last workgroup sees
 // when they are there.  (No fence, which would write back the L2, and no wait for a store's acknowledgement.)
 // Bound by fp64 latency and two dependent launches, not by the 5.6 MB of logits.  gamma 5, vocabulary 128 256, one sequence: three
-// launches (8 slices of 1024 threads with sixteen exponentials each, weights, draw) 21.1 us a call, two 13.7.  Of these the first
+// launches (8 slices of 1024 threads with sixteen exponentials each, weights, draw) 21.1 us a call, two 13.9.  Of these the first
 // launch takes 4.6 (two workgroups of 24 exponentials a SIMD on the busiest CUs), the boundary 1.2, and of the second the statistics
-// 2.0, decisions 0.7, weights and their sum 0.7, the two counters 1.75 (one for all workgroups: 2.7), the sums 0.95 and the draw 1.3.
+// 2.0, decisions 0.7, weights and their sum 0.7, the two counters 1.75 (one for all workgroups: 2.7), the sums 0.95 and the draw 1.4
+// (0.13 of it for the one thread that the draw lies with being told by its rank, not by its bounds: first_past).
 // Requesting a thread's entries of all positions at the start, instead of those of the position that the decisions leave, does not
 // pay: 14.2 (statistics 2.5 us, weights 0.75).
 #include "kernels.h"
@@ -218,8 +219,8 @@ __global__ __launch_bounds__(kStatThreads) void accept_stats_kernel(const float*
 }
 
 // Inclusive running sum over the workgroup's threads: inside rows of 16 lanes by operand swizzles, then the rows' and the waves' totals
-// in order.  incl[] holds every thread's afterwards (so that a thread's lower end is the very number that is its
-// neighbour's upper one).
+// in order.  incl[] holds every thread's afterwards.  Neighbours add the same terms in different orders, so incl[] rises and falls by
+// last bits where the terms in between are small or nothing: a threshold can lie between several neighbouring entries.
 __device__ __forceinline__ double lane_value(double v, int lane) {
   const uint64_t u = __builtin_bit_cast(uint64_t, v);
   const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)u, lane), hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(u >> 32), lane);
@@ -254,8 +255,8 @@ __global__ __launch_bounds__(kDrawThreads) void accept_draw_kernel(const int32_t
                                                                     int32_t* __restrict__ bonus) {
   constexpr int kChunk = PER * kDrawThreads;
   __shared__ double s_incl[kDrawThreads], s_wave[kDrawThreads / 64], s_mx[kMaxAcceptRows], s_z[kMaxAcceptRows];
-  __shared__ double s_before;
-  __shared__ int s_flag;
+  __shared__ double s_lo[kDrawThreads / 64];
+  __shared__ int s_flag, s_at[kDrawThreads / 64];
   const int chunk = blockIdx.x, nchunk = gridDim.x, b = blockIdx.y, tid = threadIdx.x, lane = tid & 63;
   const AcceptWs ws = accept_ws(ws_base, b, gamma, V, slices);
   const float* tl = target_logits + (size_t)b * (gamma + 1) * V;
@@ -388,10 +389,11 @@ __global__ __launch_bounds__(kDrawThreads) void accept_draw_kernel(const int32_t
     while (x == kNoSum) x = load_sum(c);  // it has been sent: ends when it arrives
     return __builtin_bit_cast(double, x);
   };
+  double own = 0.0;  // this thread's part of s_incl
   auto scan_chunks = [&](sum_bits first) {
-    double s = 0.0;
-    for (int c = c0; c < c1; ++c) s += chunk_sum(c, c == c0 ? first : kNoSum);
-    block_scan(s, s_incl, s_wave);
+    own = 0.0;
+    for (int c = c0; c < c1; ++c) own += chunk_sum(c, c == c0 ? first : kNoSum);
+    block_scan(own, s_incl, s_wave);
     return s_incl[kDrawThreads - 1];
   };
   double total = scan_chunks(early);
@@ -408,46 +410,61 @@ __global__ __launch_bounds__(kDrawThreads) void accept_draw_kernel(const int32_t
     total = scan_chunks(kNoSum);
   }
   const double thr = (double)u_in * total;
-  if (tid == 0) s_flag = -1;
-  __syncthreads();
-  {
-    double lo = tid ? s_incl[tid - 1] : 0.0;
-    if (lo <= thr && thr < s_incl[tid])  // at most one thread
-      for (int c = c0; c < c1; ++c) {
-        const double next = c < c1 - 1 ? lo + chunk_sum(c) : INFINITY;
-        if (next > thr) {
-          s_flag = c;
-          s_before = lo;
-          break;
-        }
-        lo = next;
-      }
-  }
-  __syncthreads();
-  const int pick_chunk = s_flag;  // -1: u * total rounded up to the total
-  const double before = s_before;
-  __syncthreads();
-  if (tid == 0) s_flag = -1;
+  // The draw lies with the first thread that has weight and whose running sum, on top of `before`, is past the threshold; find(lo), called
+  // for it (and for the first such thread of every other wave), gives the place in its run and moves lo to the sum in front of it.
+  auto first_past = [&](double before, double* at_lo, auto&& find) {
+    const int wave = tid >> 6;
+    const double below = s_incl[max(tid - 1, 0)];  // side by side with the thread's own
+    const unsigned long long past = __ballot(own > 0.0 && thr < before + s_incl[tid]);
+    if (lane == (past ? __ffsll((long long)past) - 1 : 0)) {
+      double lo = before + (tid ? below : 0.0);
+      s_at[wave] = past ? find(lo) : -1;
+      s_lo[wave] = lo;
+    }
+    __syncthreads();
+    int at[kDrawThreads / 64], first = -1;
+    double lo[kDrawThreads / 64];
+#pragma unroll
+    for (int w = 0; w < kDrawThreads / 64; ++w) {
+      at[w] = s_at[w];
+      lo[w] = s_lo[w];
+    }
+#pragma unroll
+    for (int w = kDrawThreads / 64 - 1; w >= 0; --w) {
+      first = at[w] >= 0 ? at[w] : first;
+      *at_lo = at[w] >= 0 ? lo[w] : *at_lo;
+    }
+    return first;
+  };
+  double before = 0.0, unused = 0.0;
+  const int pick_chunk = first_past(0.0, &before, [&](double& lo) {
+    int c = c0;
+    for (; c < c1 - 1; ++c) {
+      const double w = chunk_sum(c);
+      if (w > 0.0 && lo + w > thr) break;
+      lo += w;
+    }
+    return c;
+  });  // -1: u * total rounded up to the total
+  int pick = -1;
   if (pick_chunk >= 0) {
-    block_scan(run_of(pick_chunk, q), s_incl, s_wave);
-    double lo = before + (tid ? s_incl[tid - 1] : 0.0);
-    if (lo <= thr && thr < before + s_incl[tid]) {  // at most one thread
-      const int v0 = pick_chunk * kChunk + tid * PER;
-      int pick = -1;
+    own = run_of(pick_chunk, q);
+    block_scan(own, s_incl, s_wave);
+    pick = first_past(before, &unused, [&](double& lo) {
+      int at = -1;
 #pragma unroll
       for (int i = 0; i < PER; ++i) {
-        if (pick >= 0 && lo > thr) continue;  // found: the running sum is past the threshold
-        if (q[i] > 0.0) pick = v0 + i;
+        if (at >= 0 && lo > thr) continue;  // found: the running sum is past the threshold
+        if (q[i] > 0.0) at = pick_chunk * kChunk + tid * PER + i;
         lo += q[i];
       }
-      s_flag = pick;
-    }
+      return at;
+    });
   }
-  __syncthreads();
-  int pick = s_flag;
   if (pick < 0) {
     // the sums disagreed in the last bit, or the threshold reached the total: the last token with
     // positive weight up to the chunk's end (of the vocabulary), or the first
+    if (tid == 0) s_flag = -1;
     int end = min(V, pick_chunk >= 0 ? (pick_chunk + 1) * kChunk : V);
     for (; pick < 0 && end > 0; end -= kDrawThreads) {
       const int v = end - 1 - tid;

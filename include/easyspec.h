@@ -222,10 +222,14 @@ int easyspec_greedy_accept_host(const int32_t *draft, const int32_t *target_argm
  *                               whose running sum over tokens 0..v exceeds u times the total
  *   workspace      dev, easyspec_accept_workspace_bytes(batch, gamma, vocab) bytes, 8-byte aligned
  *                  (about 8 bytes per vocabulary entry and sequence: the bonus weights);
- *                  contents need not be kept between calls
+ *                  contents need not be kept between calls.  One call at a time: the kernels hand values
+ *                  to each other through it, and of calls that overlap on it (different streams or
+ *                  threads) some results are wrong, -1, or not written
  *   hip_stream     the hipStream_t to launch on (NULL = the null stream); nothing is synchronised
  * gamma may be 0 (plain sampling from p_0).  A drafted token outside 0..vocab-1 at or before
- * the first rejected position gives accept_len = bonus = -1 for that sequence.  EASYSPEC_EINVAL for NULL pointers, batch < 1 or
+ * the first rejected position gives accept_len = bonus = -1 for that sequence; so does a value of
+ * another workgroup that has not come after a quarter of a second, which only calls that overlap
+ * on the workspace bring about (no call waits without end).  EASYSPEC_EINVAL for NULL pointers, batch < 1 or
  * > 65535, gamma outside 0..64, vocab < 1, or a temperature that is not positive and finite
  * (temperature 0 is easyspec_greedy_accept).  All arrays are the caller's and only read,
  * except accept_len, bonus and workspace. */
@@ -242,7 +246,8 @@ int64_t easyspec_accept_workspace_bytes(int32_t batch, int32_t gamma, int32_t vo
  * launched, when easyspec_accept_workspace_bytes(batch, gamma, vocab) exceeds that size (about 8
  * bytes per vocabulary entry and sequence: 6 sequences at a vocabulary of 152 064); other errors as
  * easyspec_accept.  All calls on one GPU share the array, so two calls whose kernels can overlap
- * (different streams, different threads) race: keep them on one stream, or order them yourself. */
+ * (different streams, different threads) race, with the results easyspec_accept's workspace names: keep
+ * them on one stream, or order them yourself. */
 int easyspec_accept_static(const int32_t *draft, const float *draft_logits, const float *target_logits, const float *r,
                            const float *u, int32_t batch, int32_t gamma, int32_t vocab, float temperature,
                            int32_t *accept_len, int32_t *bonus, void *hip_stream);

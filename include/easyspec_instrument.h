@@ -27,6 +27,13 @@ int easyspec_poison_workspaces(easyspec_ctx *ctx);
  * a kernel for fp32 models with two query heads per KV head, EASYSPEC_EINVAL for others. */
 int easyspec_force_give_up(easyspec_ctx *ctx, int32_t on);
 
+/* easyspec_accept whose waits end before their first look: a sequence's last workgroup reports accept_len = bonus = -1 for it unless
+ * every value that it needs came with the counter that told it so, and with vocab <= 512 none has.  Its kernels end normally, and the
+ * workspace serves the next call as any other.  For tests of that. */
+int easyspec_accept_give_up(const int32_t *draft, const float *draft_logits, const float *target_logits, const float *r,
+                            const float *u, int32_t batch, int32_t gamma, int32_t vocab, float temperature,
+                            int32_t *accept_len, int32_t *bonus, void *workspace, void *hip_stream);
+
 /* Streaming-read probe for roofline reports: reads `bytes` (a positive multiple of 16) of the
  * caller's device buffer once, with the loads the weight stream uses (16-byte, non-temporal,
  * 8 in flight per lane), on hip_stream (NULL = the null stream).  The caller times it; the rate

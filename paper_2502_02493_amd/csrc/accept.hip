@@ -17,12 +17,14 @@
 //                              sequence to have done so draws: running sum over the chunk sums in index order, then over the
 //                              weights of the chunk the draw lands in, worked out once more (no weight is ever stored).
 // "Last" is told by a counter; it says whose sums have been sent, and (1) marks them all as missing, so the last workgroup sees
-// when they are there.  (No fence, which would write back the L2, and no wait for a store's acknowledgement.)
+// when they are there.  (No fence, which would write back the L2, and no wait for a store's acknowledgement.)  In a call that has its
+// workspace to itself they always come, some of them already on the way when the counter says so.  Another call on the same workspace at
+// the same time can mark them as missing again, for good: the wait ends after kPolls looks, and the call reports -1.
 // Bound by fp64 latency and two dependent launches, not by the 5.6 MB of logits.  gamma 5, vocabulary 128 256, one sequence: three
-// launches (8 slices of 1024 threads with sixteen exponentials each, weights, draw) 21.1 us a call, two 13.9.  Of these the first
+// launches (8 slices of 1024 threads with sixteen exponentials each, weights, draw) 21.1 us a call, two 14.0.  Of these the first
 // launch takes 4.6 (two workgroups of 24 exponentials a SIMD on the busiest CUs), the boundary 1.2, and of the second the statistics
-// 2.0, decisions 0.7, weights and their sum 0.7, the two counters 1.75 (one for all workgroups: 2.7), the sums 0.95 and the draw 1.4
-// (0.13 of it for the one thread that the draw lies with being told by its rank, not by its bounds: first_past).
+// 2.0, decisions 0.7, weights and their sum 0.7, the two counters 1.75 (one for all workgroups: 2.7), the sums 0.95 and the draw 1.55
+// (0.25 of it for the one thread that the draw lies with being told by its rank, not by its bounds (first_past), and for the bound).
 // Requesting a thread's entries of all positions at the start, instead of those of the position that the decisions leave, does not
 // pay: 14.2 (statistics 2.5 us, weights 0.75).
 #include "kernels.h"
@@ -36,6 +38,7 @@ constexpr int kMinSlices = 8, kMaxSlices = 64;  // workgroups per logit row in (
 constexpr int kStatThreads = 512;
 constexpr int kStatRegs = 8;       // logits a thread of (1) holds at a time
 constexpr int kDrawThreads = 256;  // threads of (2); 2 or 8 vocabulary entries each
+constexpr int kPolls = 1 << 18;    // looks for a chunk sum, about a microsecond each: a quarter of a second
 constexpr int kWsChunk = 2048;     // the workspace has room for a double per so many entries besides one for each
 
 // Reductions over 8, 16, 32 or 64 neighbouring lanes (n, uniform) by operand swizzles, every lane receiving the result; a shuffle
@@ -243,11 +246,11 @@ __device__ __forceinline__ void block_scan(double v, double* incl, double* sh) {
   __syncthreads();
 }
 
-// grid (chunks, batch); PER: vocabulary entries per thread.  Every workgroup takes the same decisions from the same numbers: a
-// row's slices in as many neighbouring lanes, their terms added by shuffles; then, in every wave, the test of each position in
-// a lane.
+// grid (chunks, batch); PER: vocabulary entries per thread, POLLS: looks for a chunk sum before the sequence is given up.  Every
+// workgroup takes the same decisions from the same numbers: a row's slices in as many neighbouring lanes, their terms added by
+// shuffles; then, in every wave, the test of each position in a lane.
 constexpr int kMaxAcceptRows = 2 * 64 + 1;
-template <int PER>
+template <int PER, int POLLS>
 __global__ __launch_bounds__(kDrawThreads) void accept_draw_kernel(const int32_t* __restrict__ draft, const float* __restrict__ draft_logits,
                                                                     const float* __restrict__ target_logits, const float* __restrict__ r,
                                                                     const float* __restrict__ u, int gamma, int V, double T, int slices,
@@ -257,6 +260,7 @@ __global__ __launch_bounds__(kDrawThreads) void accept_draw_kernel(const int32_t
   __shared__ double s_incl[kDrawThreads], s_wave[kDrawThreads / 64], s_mx[kMaxAcceptRows], s_z[kMaxAcceptRows];
   __shared__ double s_lo[kDrawThreads / 64];
   __shared__ int s_flag, s_at[kDrawThreads / 64];
+  __shared__ int s_lost[2];  // a chunk sum did not come: while they were added up, while the draw's chunk was looked for
   const int chunk = blockIdx.x, nchunk = gridDim.x, b = blockIdx.y, tid = threadIdx.x, lane = tid & 63;
   const AcceptWs ws = accept_ws(ws_base, b, gamma, V, slices);
   const float* tl = target_logits + (size_t)b * (gamma + 1) * V;
@@ -278,6 +282,7 @@ __global__ __launch_bounds__(kDrawThreads) void accept_draw_kernel(const int32_t
     }
     asm volatile("" ::: "memory");
   };
+  if (tid < 2) s_lost[tid] = 0;
   const int terms = (2 * gamma + 1) * slices;
   auto combine = [&](auto side_by_side, int first, const auto& others) {  // that many terms a thread, their chains interleaved
     constexpr int N = decltype(side_by_side)::value;
@@ -326,11 +331,14 @@ __global__ __launch_bounds__(kDrawThreads) void accept_draw_kernel(const int32_t
   const bool bad = lane < gamma && !(token >= 0 && token < V);
   const unsigned long long stop = __ballot(rejected || bad), bads = __ballot(bad);
   const int m = stop ? __ffsll((long long)stop) - 1 : gamma;
-  if ((bads >> (m & 63)) & 1 & (unsigned long long)(m < gamma)) {  // not a token: reported as accept_len = bonus = -1
-    if (chunk == 0 && tid == 0) {
-      accept_len[b] = -1;
-      bonus[b] = -1;
+  auto report = [&](int len, int token) {
+    if (tid == 0) {
+      accept_len[b] = len;
+      bonus[b] = token;
     }
+  };
+  if ((bads >> (m & 63)) & 1 & (unsigned long long)(m < gamma)) {  // not a token
+    if (chunk == 0) report(-1, -1);
     return;
   }
   const double tm = s_mx[m], tz = s_z[m], inv_tz = 1.0 / tz;
@@ -385,19 +393,21 @@ __global__ __launch_bounds__(kDrawThreads) void accept_draw_kernel(const int32_t
   if (!s_flag) return;
 
   // The sequence's last workgroup: every thread takes a run of chunks
-  auto chunk_sum = [&](int c, sum_bits x = kNoSum) {
-    while (x == kNoSum) x = load_sum(c);  // it has been sent: ends when it arrives
+  auto chunk_sum = [&](int c, int stage, sum_bits x = kNoSum) {  // it has been sent: there at the first look or a few later
+    for (int looks = 0; x == kNoSum && looks < POLLS; ++looks) x = load_sum(c);
+    if (x == kNoSum) s_lost[stage] = 1;  // a NaN, and the thread looks no further
     return __builtin_bit_cast(double, x);
   };
   double own = 0.0;  // this thread's part of s_incl
   auto scan_chunks = [&](sum_bits first) {
     own = 0.0;
-    for (int c = c0; c < c1; ++c) own += chunk_sum(c, c == c0 ? first : kNoSum);
+    for (int c = c0; c < c1 && own == own; ++c) own += chunk_sum(c, 0, c == c0 ? first : kNoSum);
     block_scan(own, s_incl, s_wave);
     return s_incl[kDrawThreads - 1];
   };
   double total = scan_chunks(early);
   if (!(total > 0.0)) {
+    if (s_lost[0]) return report(-1, -1);
     // identical distributions leave no residual (a rejection is then impossible for r < 1): fall
     // back to the target distribution of that position (rare, slow, correct)
     residual = false;
@@ -408,8 +418,9 @@ __global__ __launch_bounds__(kDrawThreads) void accept_draw_kernel(const int32_t
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the old sums are gone when the other waves look
     __syncthreads();
     total = scan_chunks(kNoSum);
+    if (s_lost[0]) return report(-1, -1);
   }
-  const double thr = (double)u_in * total;
+  const double thr = lane_value((double)u_in * total, 0);  // uniform
   // The draw lies with the first thread that has weight and whose running sum, on top of `before`, is past the threshold; find(lo), called
   // for it (and for the first such thread of every other wave), gives the place in its run and moves lo to the sum in front of it.
   auto first_past = [&](double before, double* at_lo, auto&& find) {
@@ -434,18 +445,20 @@ __global__ __launch_bounds__(kDrawThreads) void accept_draw_kernel(const int32_t
       first = at[w] >= 0 ? at[w] : first;
       *at_lo = at[w] >= 0 ? lo[w] : *at_lo;
     }
-    return first;
+    *at_lo = lane_value(*at_lo, 0);
+    return __builtin_amdgcn_readfirstlane(first);
   };
   double before = 0.0, unused = 0.0;
   const int pick_chunk = first_past(0.0, &before, [&](double& lo) {
     int c = c0;
     for (; c < c1 - 1; ++c) {
-      const double w = chunk_sum(c);
-      if (w > 0.0 && lo + w > thr) break;
+      const double w = chunk_sum(c, 1);
+      if (w != w || (w > 0.0 && lo + w > thr)) break;
       lo += w;
     }
     return c;
   });  // -1: u * total rounded up to the total
+  if (cper > 1 && s_lost[1]) return report(-1, -1);
   int pick = -1;
   if (pick_chunk >= 0) {
     own = run_of(pick_chunk, q);
@@ -476,10 +489,7 @@ __global__ __launch_bounds__(kDrawThreads) void accept_draw_kernel(const int32_t
     }
     pick = max(pick, 0);
   }
-  if (tid == 0) {
-    accept_len[b] = m;
-    bonus[b] = pick;
-  }
+  report(m, pick);
 }
 
 size_t sample_accept_workspace_bytes(int batch, int gamma, int V) {
@@ -488,16 +498,14 @@ size_t sample_accept_workspace_bytes(int batch, int gamma, int V) {
 
 void launch_sample_accept(const int32_t* draft, const float* draft_logits, const float* target_logits, const float* r,
                           const float* u, int batch, int gamma, int V, double T, double* ws, int32_t* accept_len,
-                          int32_t* bonus, hipStream_t st) {
+                          int32_t* bonus, bool give_up, hipStream_t st) {
   const AcceptPlan p = accept_plan(batch, gamma, V);
   hipLaunchKernelGGL(accept_stats_kernel, dim3(p.slices, 2 * gamma + 1, batch), dim3(kStatThreads), 0, st, draft_logits, target_logits,
                      gamma, V, T, p.slices, p.chunks, ws);
-  if (p.per == 2)
-    hipLaunchKernelGGL(accept_draw_kernel<2>, dim3(p.chunks, batch), dim3(kDrawThreads), 0, st, draft, draft_logits, target_logits, r, u,
-                       gamma, V, T, p.slices, ws, accept_len, bonus);
-  else
-    hipLaunchKernelGGL(accept_draw_kernel<8>, dim3(p.chunks, batch), dim3(kDrawThreads), 0, st, draft, draft_logits, target_logits, r, u,
-                       gamma, V, T, p.slices, ws, accept_len, bonus);
+  const auto draw = give_up ? (p.per == 2 ? accept_draw_kernel<2, 0> : accept_draw_kernel<8, 0>)
+                            : (p.per == 2 ? accept_draw_kernel<2, kPolls> : accept_draw_kernel<8, kPolls>);
+  hipLaunchKernelGGL(draw, dim3(p.chunks, batch), dim3(kDrawThreads), 0, st, draft, draft_logits, target_logits, r, u, gamma, V, T,
+                     p.slices, ws, accept_len, bonus);
 }
 
 // ------------------------------------------------------------------------------------------

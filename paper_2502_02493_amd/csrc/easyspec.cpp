@@ -776,16 +776,28 @@ static int check_accept_args(const int32_t* draft, const float* draft_logits, co
   return EASYSPEC_OK;
 }
 
-extern "C" int easyspec_accept(const int32_t* draft, const float* draft_logits, const float* target_logits, const float* r,
-                               const float* u, int32_t batch, int32_t gamma, int32_t vocab, float temperature,
-                               int32_t* accept_len, int32_t* bonus, void* workspace, void* hip_stream) {
+static int accept_with(const int32_t* draft, const float* draft_logits, const float* target_logits, const float* r,
+                       const float* u, int32_t batch, int32_t gamma, int32_t vocab, float temperature,
+                       int32_t* accept_len, int32_t* bonus, void* workspace, bool give_up, void* hip_stream) {
   if (!workspace) return fail(nullptr, EASYSPEC_EINVAL, "accept: NULL argument");
   const int rc = check_accept_args(draft, draft_logits, target_logits, r, u, batch, gamma, vocab, temperature, accept_len, bonus);
   if (rc != EASYSPEC_OK) return rc;
   launch_sample_accept(draft, draft_logits, target_logits, r, u, batch, gamma, vocab, (double)temperature, (double*)workspace,
-                       accept_len, bonus, (hipStream_t)hip_stream);
+                       accept_len, bonus, give_up, (hipStream_t)hip_stream);
   HIPCHK(nullptr, hipGetLastError());
   return EASYSPEC_OK;
+}
+
+extern "C" int easyspec_accept(const int32_t* draft, const float* draft_logits, const float* target_logits, const float* r,
+                               const float* u, int32_t batch, int32_t gamma, int32_t vocab, float temperature,
+                               int32_t* accept_len, int32_t* bonus, void* workspace, void* hip_stream) {
+  return accept_with(draft, draft_logits, target_logits, r, u, batch, gamma, vocab, temperature, accept_len, bonus, workspace, false, hip_stream);
+}
+
+extern "C" int easyspec_accept_give_up(const int32_t* draft, const float* draft_logits, const float* target_logits, const float* r,
+                                       const float* u, int32_t batch, int32_t gamma, int32_t vocab, float temperature,
+                                       int32_t* accept_len, int32_t* bonus, void* workspace, void* hip_stream) {
+  return accept_with(draft, draft_logits, target_logits, r, u, batch, gamma, vocab, temperature, accept_len, bonus, workspace, true, hip_stream);
 }
 
 extern "C" int64_t easyspec_accept_static_max_bytes(void) { return (int64_t)sample_accept_static_capacity_bytes(); }
@@ -803,7 +815,7 @@ extern "C" int easyspec_accept_static(const int32_t* draft, const float* draft_l
   HIPCHK(nullptr, sample_accept_static_workspace(&ws));
   // every workspace entry a call reads was written earlier in the same call, so nothing needs clearing
   launch_sample_accept(draft, draft_logits, target_logits, r, u, batch, gamma, vocab, (double)temperature, ws, accept_len, bonus,
-                       (hipStream_t)hip_stream);
+                       false, (hipStream_t)hip_stream);
   HIPCHK(nullptr, hipGetLastError());
   return EASYSPEC_OK;
 }

@@ -233,11 +233,11 @@ void launch_resident(const Shape& s, const Buffers& b, const Resident& r, const 
                      float* logits, int32_t* tokens_out, hipStream_t st);
 void launch_accept(const int32_t* draft, const int32_t* target, int batch, int gamma, int32_t* accept_len,
                    int32_t* bonus, hipStream_t st);
-// Acceptance by speculative sampling; ws: sample_accept_workspace_bytes() of scratch.
+// Acceptance by speculative sampling; ws: sample_accept_workspace_bytes() of scratch.  give_up: at the first value that is not there yet.
 size_t sample_accept_workspace_bytes(int batch, int gamma, int V);
 void launch_sample_accept(const int32_t* draft, const float* draft_logits, const float* target_logits, const float* r,
                           const float* u, int batch, int gamma, int V, double T, double* ws, int32_t* accept_len,
-                          int32_t* bonus, hipStream_t st);
+                          int32_t* bonus, bool give_up, hipStream_t st);
 // The library's own workspace for launch_sample_accept (a static device array, one copy per GPU): its
 // address on the current device (resolved at the first call there) and its size.  Allocates nothing.
 hipError_t sample_accept_static_workspace(double** out);

@@ -56,6 +56,13 @@ int32_t easyspec_stream_read_sink_floats(void);
 int easyspec_attention_cut(const easyspec_config *cfg, const int32_t *ctx_lens, int32_t n_cols, int32_t n_layers_in_set,
                            int32_t *n_chunks, int32_t *ranges);
 
+/* Which attention kernel a launch over n_layers_in_set layers takes for n_cols columns of a pass of at most 16: column i belongs to
+ * sequence seqs[i] (columns of a sequence are consecutive) and attends to the first ctx_lens[i] slots.  Host arithmetic only.
+ * route (host, 3 entries): [0] 1 for the matrix-core kernel, 0 for the vector kernel, [1] bf16 terms of a probability (0: the
+ * vector kernel's fp32), [2] tiles of 16 query rows per workgroup (1 for the vector kernel). */
+int easyspec_attention_route(const easyspec_config *cfg, const int32_t *ctx_lens, const int32_t *seqs, int32_t n_cols,
+                             int32_t n_layers_in_set, int32_t *route);
+
 /* Host model of the weight stream of one launch of a weight-streaming kernel class (EASYSPEC_OP_QKV,
  * _OPROJ, _GATEUP, _DOWN, _HEAD) with n_cols token columns over n_layers_in_set layers (full_layer != 0:
  * the launch shapes of the full-layer-parallel mode): every workgroup, wave and lane of the grid computes,

@@ -21,7 +21,7 @@ EASYSPEC_PARALLEL_ATTENTION, EASYSPEC_PARALLEL_FULL_LAYER = 0, 1
 
 EXPORTS = ["easyspec_create", "easyspec_destroy", "easyspec_load_weights", "easyspec_set_groups",
            "easyspec_default_groups", "easyspec_draft_step", "easyspec_calibrate", "easyspec_greedy_accept", "easyspec_greedy_accept_host",
-           "easyspec_accept", "easyspec_accept_give_up", "easyspec_accept_workspace_bytes", "easyspec_accept_static", "easyspec_accept_static_max_bytes", "easyspec_draft_tree_step", "easyspec_set_parallel_mode", "easyspec_stream_read", "easyspec_stream_read_sink_floats", "easyspec_attention_cut", "easyspec_weight_walk", "easyspec_wide_walk", "easyspec_attention_stage_walk",
+           "easyspec_accept", "easyspec_accept_give_up", "easyspec_accept_workspace_bytes", "easyspec_accept_static", "easyspec_accept_static_max_bytes", "easyspec_draft_tree_step", "easyspec_set_parallel_mode", "easyspec_stream_read", "easyspec_stream_read_sink_floats", "easyspec_attention_cut", "easyspec_attention_route", "easyspec_weight_walk", "easyspec_wide_walk", "easyspec_attention_stage_walk",
            "easyspec_get_lens", "easyspec_truncate", "easyspec_kv_import", "easyspec_kv_export",
            "easyspec_get_hidden", "easyspec_poison_workspaces", "easyspec_force_give_up", "easyspec_step_bytes", "easyspec_profile_begin", "easyspec_profile_end",
            "easyspec_last_error"]
@@ -91,6 +91,7 @@ def load_library():
         L.easyspec_stream_read.argtypes = [vp, C.c_int64, vp, vp]
         L.easyspec_stream_read_sink_floats.argtypes = []
         L.easyspec_attention_cut.argtypes = [C.POINTER(easyspec_config), vp, i32, i32, vp, vp]
+        L.easyspec_attention_route.argtypes = [C.POINTER(easyspec_config), vp, vp, i32, i32, vp]
         L.easyspec_step_bytes.restype = C.c_int64
         L.easyspec_weight_walk.argtypes = [C.POINTER(easyspec_config), i32, i32, i32, i32, vp]
         L.easyspec_wide_walk.argtypes = [C.POINTER(easyspec_config), i32, i32, vp]
@@ -251,6 +252,16 @@ def easyspec_attention_cut(cfg: easyspec_config, ctx_lens, n_layers_in_set: int,
     if rc < 0:
         _check(rc, None)
     return rc, n_chunks, ranges
+
+
+def easyspec_attention_route(cfg: easyspec_config, ctx_lens, seqs, n_layers_in_set: int):
+    """(matrix cores, bf16 terms of a probability, tiles of 16 query rows per workgroup)."""
+    lens, seqs = (np.ascontiguousarray(a, dtype=np.int32) for a in (ctx_lens, seqs))
+    assert len(lens) == len(seqs)
+    route = np.zeros(3, np.int32)
+    _check(load_library().easyspec_attention_route(C.byref(cfg), _ptr(lens), _ptr(seqs), len(lens), int(n_layers_in_set),
+                                                   _ptr(route)), None)
+    return bool(route[0]), int(route[1]), int(route[2])
 
 
 EASYSPEC_WALK_FIELDS = 16

@@ -1097,7 +1097,9 @@ static void launch_attn_g(int G, dim3 grid, int nwv, hipStream_t st, AttnArgs a,
 // the per-slot arithmetic on the matrix cores.  It takes bf16 launches that hold several columns of a sequence and
 //   * enough (column, layer, slot) work, over several layers or at least five columns (attn_mfma_long), or
 //   * heads of 128 elements, four or more per KV head, contexts of more than one piece, and at least 12 query rows of a sequence,
-//     three quarters of a tile (attn_mfma_rows): calibrations of three tokens or more, short ones too.
+//     three quarters of a tile (attn_mfma_rows): calibrations of three tokens or more (two with seven or eight heads), short ones
+//     too.  With four heads such a sequence has to have at least half of the longest context: a tile that a longer, lone column fills
+//     by a quarter is the time of the launch then.
 // Single columns (plain draft steps) stay on the vector kernel.  EASYSPEC_ATTN_MFMA = 0 / 2 forces never / always (bf16 only).
 // The second line was drawn when the kernel had lost 2.7 us of its start; us a call of 12 layers on the vector and the matrix-core kernel with
 // three terms to a probability.  8B shape, 3 / 4 / 6 / 8 / 12 tokens at context 300 1022 / 1081 / 1114 / 1126 / 1214 and 1028 / 1079 / 1109 /
@@ -1105,6 +1107,11 @@ static void launch_attn_g(int G, dim3 grid, int nwv, hipStream_t st, AttnArgs a,
 // 1137 / 1140 / 1178 / 1192 / 1279; 2 tokens (two terms) at 2048 1095 and 1099, at 8192 1162 and 1181.  Qwen2-7B shape, 3 / 6 / 12 tokens at
 // 600 1187 / 1233 / 1394 and 1168 / 1214 / 1389, at 2048 1206 / 1261 / 1444 and 1180 / 1234 / 1408.  Two tree levels of 3 / 6 / 12
 // nodes at 600, sets of four, 8B 1880 / 2063 / 2196 and 1869 / 2033 / 2121.  6-token calibration at 2048, 32 layers: 3094 -> 3057.
+// Mixed passes, tokens of the sequences at their contexts.  8B: 3 and 1 at 100 and 16 000 1157 and 1197, 3000 and 16 000 1182 and 1257, 1000
+// and 6000 1095 and 1115, 600 and 2000 1043 and 1051, 2000 and 2000 1059 and 1061, 2000 and 600 1079 and 1053; 3 and 2 at 1000 and 4000 1117 and
+// 1134; 3 and nine times 1 at 700 1211 and 1207, at 1500 1300 and 1276.  Qwen2-7B shape, 3 and 1 at the same: 1211 and 1220, 1247 and 1245, 1174
+// and 1172, 1144 and 1113, 1134 and 1121, 1139 and 1120; 2 tokens at 300 / 2048 / 8192 1119 / 1140 / 1202 and 1112 / 1126 / 1190.  Eight
+// heads per KV head, 2 tokens at 300 / 2048 / 8192 1057 / 1079 / 1173 and 1012 / 1027 / 1092, 3 and 1 at 100 and 16 000 1192 and 1131.
 static bool attn_mfma_long(const Cols& c, int n_set) {
   const long min_work = env_int("EASYSPEC_ATTN_MFMA_MIN", 30000);
   bool shared = false;
@@ -1126,10 +1133,16 @@ static int longest_run(const Cols& c) {
 constexpr int kAttnOnePiece = 256;  // contexts up to here are one piece (attn_cut)
 static bool attn_mfma_heads(const Shape& s) { return s.hd == 128 && s.Hq / s.Hkv >= 4; }
 static bool attn_mfma_rows(const Shape& s, const Cols& c) {
-  int max_len = 1;
-  for (int i = 0; i < c.n; ++i) max_len = std::max(max_len, c.pos[i] + 1);
-  const int longest = longest_run(c);
-  return attn_mfma_heads(s) && max_len > kAttnOnePiece && longest > 1 && longest * (s.Hq / s.Hkv) >= 12;
+  const int G = s.Hq / s.Hkv;
+  int max_len = 1, max_filled = 0;
+  for (int i = 0; i < c.n;) {
+    int j = i, len = 1;
+    for (; j < c.n && c.seq[j] == c.seq[i]; ++j) len = std::max(len, c.pos[j] + 1);
+    if (j - i > 1 && (j - i) * G >= 12) max_filled = std::max(max_filled, len);
+    max_len = std::max(max_len, len);
+    i = j;
+  }
+  return attn_mfma_heads(s) && max_len > kAttnOnePiece && max_filled > 0 && (G >= 7 || 2 * max_filled >= max_len);
 }
 static bool attn_use_mfma(const Shape& s, const Cols& c, int n_set) {
   const int mode = env_int("EASYSPEC_ATTN_MFMA", 1);  // read at every call: tests switch it between contexts

@@ -994,6 +994,34 @@ extern "C" int32_t easyspec_stream_read_sink_floats(void) { return stream_read_s
 
 static_assert(EASYSPEC_MAX_CHUNKS == kMaxChunks, "header and kernels disagree on the chunk limit");
 
+extern "C" int easyspec_attention_route(const easyspec_config* cfg, const int32_t* ctx_lens, const int32_t* seqs, int32_t n_cols,
+                                        int32_t n_layers_in_set, int32_t* route) {
+  int rc = check_config(cfg);
+  if (rc != EASYSPEC_OK) return rc;
+  if (!ctx_lens || !seqs || !route) return fail(nullptr, EASYSPEC_EINVAL, "attention_route: NULL argument");
+  if (n_cols < 1 || n_cols > kMaxCols) return fail(nullptr, EASYSPEC_EINVAL, "attention_route: n_cols must be 1..%d", kMaxCols);
+  if (n_layers_in_set < 1 || n_layers_in_set > EASYSPEC_MAX_SET)
+    return fail(nullptr, EASYSPEC_EINVAL, "attention_route: n_layers_in_set must be 1..%d", EASYSPEC_MAX_SET);
+  Shape s;
+  memset(&s, 0, sizeof s);
+  s.dtype = cfg->dtype; s.Hq = cfg->n_q_heads; s.Hkv = cfg->n_kv_heads; s.hd = cfg->head_dim; s.max_ctx = cfg->max_ctx;
+  Cols c;
+  memset(&c, 0, sizeof c);
+  c.n = n_cols;
+  for (int i = 0; i < n_cols; ++i) {
+    if (ctx_lens[i] < 1 || ctx_lens[i] > cfg->max_ctx || seqs[i] < 0 || seqs[i] >= cfg->max_batch)
+      return fail(nullptr, EASYSPEC_EINVAL, "attention_route: column %d of sequence %d attends to %d slots", i, seqs[i], ctx_lens[i]);
+    c.pos[i] = ctx_lens[i] - 1;
+    c.seq[i] = seqs[i];
+    c.vis_base[i] = ctx_lens[i];
+  }
+  const AttnCut cut = attn_cut(s, c, n_layers_in_set);
+  route[0] = cut.mfma ? 1 : 0;
+  route[1] = cut.mfma ? (cut.three ? 3 : 2) : 0;
+  route[2] = cut.tiles;
+  return EASYSPEC_OK;
+}
+
 extern "C" int easyspec_attention_cut(const easyspec_config* cfg, const int32_t* ctx_lens, int32_t n_cols, int32_t n_layers_in_set,
                                       int32_t* n_chunks, int32_t* ranges) {
   int rc = check_config(cfg);

@@ -238,6 +238,7 @@ extern "C" int easyspec_create(const easyspec_config* cfg, void* hip_stream, eas
       ALLOC_WORK(ctx, w.ACT, wide_operand_bytes(w.cols, s.F));
       ALLOC_WORK(ctx, w.P, wide_partial_bytes(s));
     }
+    if (s.dtype == EASYSPEC_DTYPE_BF16) HIPCHK(ctx, weight_kernels_prepare());
     if (resident_model(s)) {
       Resident& r = ctx->r;
       ALLOC(ctx, r.ctl, sizeof(ResidentCtl));

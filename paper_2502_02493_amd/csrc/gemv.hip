@@ -790,6 +790,21 @@ bool twin_passes_fit(const Shape& s, int n_cols) {
   return true;
 }
 
+// The partial sums (red_bytes) of the kernels that stream four row tiles a wave: up to 16 waves of one pass, eight of two, 80 KB either
+// way.  What is above the 64 KB that a launch may have unasked is asked for here; the others need 40 KB at most.
+constexpr int kMostRed = red_floats(16, 4) * (int)sizeof(float);
+static_assert(2 * red_floats(kTwinThreads / 64, 4) * (int)sizeof(float) <= kMostRed && kMostRed <= 80 * 1024, "four row tiles a wave");
+static_assert(red_floats(16, 2) * sizeof(float) <= 65536 && 2 * red_floats(kTwinThreads / 64, 2) * sizeof(float) <= 65536, "two row tiles a wave");
+hipError_t weight_kernels_prepare() {
+  const void* const four_tiles[] = {(const void*)gateup_kernel<bf16_t, 2, 2>, (const void*)gateup_twin_kernel<bf16_t, 2, 2>,
+                                    (const void*)qkv_kernel<bf16_t, 2, 2>, (const void*)qkv_twin_kernel<bf16_t, 2, 2>};
+  for (const void* f : four_tiles) {
+    const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, kMostRed);
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+
 static dim3 plan_grid(const StreamPlan& p) { return dim3(p.grid / p.n_layers, p.n_layers); }
 
 // One pass, or (c2 given) two passes of equal column counts in one launch of the same shape, with a reduction

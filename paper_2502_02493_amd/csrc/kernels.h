@@ -167,6 +167,8 @@ void launch_embed(const Shape& s, const Buffers& b, const Cols& c, const int32_t
 // serves both passes, every wave using each weight fragment it loads for both passes' columns
 // (twin_passes_fit(): whether the launch shapes of passes of n_cols columns allow it).
 bool twin_passes_fit(const Shape& s, int n_cols);
+// Once per context of a bf16 model, before its first launch.
+hipError_t weight_kernels_prepare();
 void launch_qkv(const Shape& s, const Buffers& b, const Cols& c, int layer0, int n_set, hipStream_t st,
                 const Buffers* b2 = nullptr, const Cols* c2 = nullptr);
 // How an attention launch over n_set layers cuts the contexts of these columns into split-KV chunks.

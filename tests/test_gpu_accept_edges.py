@@ -18,7 +18,7 @@ def compare(oracle, es, case, T):
         if margin > 1e-9:
             assert (int(acc[b]), int(bon[b])) == (m, bonus), (b, margin)
             checked += 1
-    assert checked >= draft.shape[0] - 1
+    assert checked >= max(1, draft.shape[0] - 1)
 
 
 @pytest.mark.parametrize("batch,gamma,V,noise", [(2, 3, 131073, 0.5), (2, 2, 152064, 0.4), (3, 64, 257, 0.05), (2, 1, 8, 1.0), (1, 1, 2100001, 0.3)])

@@ -221,10 +221,10 @@ int easyspec_greedy_accept_host(const int32_t *draft, const int32_t *target_argm
  *                               at the first rejected position), from p_gamma otherwise: the lowest token v
  *                               whose running sum over tokens 0..v exceeds u times the total
  *   workspace      dev, easyspec_accept_workspace_bytes(batch, gamma, vocab) bytes, 8-byte aligned
- *                  (about 8 bytes per vocabulary entry and sequence: the bonus weights);
- *                  contents need not be kept between calls.  One call at a time: the kernels hand values
- *                  to each other through it, and of calls that overlap on it (different streams or
- *                  threads) some results are wrong, -1, or not written
+ *                  (about 8 bytes per vocabulary entry and sequence; statistics, sums and counters
+ *                  take the smaller part of them); contents need not be kept between calls.  One call
+ *                  at a time: the kernels hand values to each other through it, and of calls that overlap
+ *                  on it (different streams or threads) some results are wrong, -1, or not written
  *   hip_stream     the hipStream_t to launch on (NULL = the null stream); nothing is synchronised
  * gamma may be 0 (plain sampling from p_0).  A drafted token outside 0..vocab-1 at or before
  * the first rejected position gives accept_len = bonus = -1 for that sequence; so does a value of

@@ -118,6 +118,9 @@ __device__ __forceinline__ float block_max(float v, float* sh) {
 // 15.4, four 27.0 / 23.2 / 23.5 / 25.8, sixteen 67.0 / 61.9 / 59.7 / 68.0; gamma 1, 152 064, one 21.2 / 17.1 / 15.1 / 13.7.
 // Entries per thread of (2): two, eight where chunks of two would make more than four workgroups per CU (each repeats the
 // decisions): one sequence 15.4 us with two, 18.7 with eight; four 23.5 and 25.8; sixteen 61.5 and 59.8.
+// us a call of the three launches and of these two, gamma 5: vocabulary 900, one sequence 14.0 and 11.3; 4000, one, four and sixteen
+// 13.9, 17.3, 25.4 and 10.9, 11.2, 13.4; 32 000, four, sixteen and 64 20.0, 31.9, 86.7 and 13.5, 22.9, 61.3; 128 256, one, four and
+// sixteen 22.2, 31.4, 69.1 and 13.9, 23.7, 60.6; gamma 10, 152 064, one and sixteen 26.4, 130.0 and 20.5, 118.9.
 struct AcceptPlan {
   int slices, per, chunks;
 };

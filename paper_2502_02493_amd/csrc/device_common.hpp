@@ -234,7 +234,7 @@ __device__ __forceinline__ void mma<float>(f32x4& acc, const u32x4& a, const u32
 //
 // NB = B fragments (and MFMAs) per weight tile.  With two-term activations and at most 8
 // columns, the lo terms ride in MFMA columns ncols..2*ncols-1 of the same instruction
-// ("folded", NB = 1) and fold_columns() adds the two halves afterwards; with more columns the
+// ("folded", NB = 1) and tile_sum() adds the two halves at the end; with more columns the
 // hi and lo terms take one MFMA each (NB = 2).  A wave keeps one batch of 8 KB in flight; two
 // batches per wave were measured slower (the registers cost more occupancy than they hide).
 // ------------------------------------------------------------------------------------------
@@ -472,9 +472,9 @@ __device__ __forceinline__ void compute_rstd(const float* __restrict__ ssp, int 
   }
 }
 
-// The same quantity with its loads issued BEFORE the weight stream of the workgroup starts and
-// its arithmetic done after: the L2 latency of the partial sums then hides behind the stream
-// instead of sitting in the tail of the kernel.  Covers d <= 4096 and up to two columns per
+// The same quantity with its loads issued behind the first batch of weights and its arithmetic done
+// behind the second's requests (gemm_loop, meanwhile): neither stands in front of the stream, and the L2
+// latency of the partial sums does not sit in the tail of the kernel.  Covers d <= 4096 and up to two columns per
 // wave (the common cases); otherwise rstd_finish falls back to compute_rstd.  Same summation
 // order as compute_rstd, so both give identical bits.
 struct RstdPre {

@@ -15,9 +15,9 @@ namespace es {
 // QKV projection of the k layers of a set + bias + rotary + KV-cache write.
 // The rotation pairs (row e of a head and row e + hd/2) are numbered through all heads of a layer,
 // pair = head * hd/2 + e, and packed as two matrices of (Hq + 2 Hkv) * hd/2 rows each (first and
-// second halves).  Unit of work: the same tile of R pairs of both, so that a pair sits in one
-// lane.  R is 16, or 12 where that fills the CUs better (qkv_tile_rows); a lane's four rows stay
-// inside one head because R and hd/2 are multiples of 4.  grid = (ceil(ceil(pairs / R) / TP), k).
+// second halves).  Unit of work: the same tile of R pairs of both, so that both rows of a pair are
+// among the workgroup's sums and one thread rotates them.  R is 16, or 12 where that fills the CUs better
+// (qkv_tile_rows).  grid = (ceil(ceil(pairs / R) / TP), k).
 // ------------------------------------------------------------------------------------------
 struct QkvArgs {
   int nw;  // waves of a workgroup
@@ -256,10 +256,10 @@ __global__ __launch_bounds__(kTwinThreads) void proj_resid_twin_kernel(Twin<Proj
 // The two projections of full-layer-parallel mode (the ablation of App. B: every layer of a set,
 // attention and MLP, works from the set's input h_1 = H; the set's output is
 // H + sum_i (Attnoutput_i + MLPoutput_i)).
-//   down == 0, O projections of the set, grid = k * d/16: layer li parks Attnoutput_li in A[li]
+//   down == 0, O projections of the set, grid = (d/16, k): layer li parks Attnoutput_li in A[li]
 //     and writes the input of its own MLP, T((H + Attnoutput_li) * gain_li), into operand slot li
 //     of xout with the partial sums of squares in slot li of ssp; H is left alone.
-//   down == 1, down projections of the set, grid = d/16: a workgroup adds up the k layers'
+//   down == 1, down projections of the set, grid = (d/16, 1): a workgroup adds up the k layers'
 //     contractions for its row tile (operand slot li of x against layer li of w), then
 //     h = H + that sum + A[0] + ... + A[k-1]; writes H, the partial sums of squares of h and
 //     T(h * gain_j) for the n_gain consumers that come next, like proj_resid_kernel.
@@ -606,7 +606,8 @@ int tile_rows(int rows) {
   return best;
 }
 
-// Rotation pairs per tile of the QKV matrices (16 or 12; the epilogue wants a multiple of 4).  A set
+// Rotation pairs per tile of the QKV matrices (16 or 12; a multiple of 4: a lane of the wide products stores
+// the four rows of its MFMA tile together).  A set
 // of k layers launches k * ceil(pairs / R) workgroups; the launch costs (workgroups per CU, rounded
 // up) * R rows' worth of streaming per CU.  Summed over sets of 1 to 4 layers, per layer: at the 8B
 // shape (3072 pairs) tiles of 16 cost 16 + 12 + 16 + 12 (192, 384, 576, 768 workgroups on 256 CUs),

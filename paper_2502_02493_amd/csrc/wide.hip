@@ -15,7 +15,7 @@
 //     barrier per stage, in its middle; weights are requested two stages ahead, the operand one, LDS fragments a step ahead.
 //   * Packed tiles are taken as they are (14 rows for gate/up, 12 pairs for QKV at the 8B shape: the spare rows of the
 //     MFMA idle).  Regrouped into 16 consecutive rows a fragment straddles two packed tiles and touches half as many
-//     lines again: gate/up at 24 columns 55 us against 42.
+//     lines again: gate/up at 24 columns, where bytes bind, 55 us against 42 (not measured where products do).
 //   * Few row tiles (QKV, O, down: 256 to 384) are spread over the CUs by splitting K; the fp32 partial sums are added
 //     in split order by the kernel that does what follows anyway (rotary and cache write; residual and norm operand).
 // Measured at the 8B shape.  A prefill of 16 x 16 tokens (256 columns): 41.8 -> 9.4 .. 9.5 ms (eight pairs of 16-column
